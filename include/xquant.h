@@ -138,6 +138,8 @@ xq_status_t xq_prepare_weights(const xq_attn_t *a, int32_t d, int32_t group, int
  * sequence b and query head h (KV head h / (n_q_heads/n_kv_heads)):
  *   K = X^[0:len[b]] Wk_h,  V = X^[0:len[b]] Wv_h,
  *   out[b][h] = softmax(q[b][h] K^T * softmax_scale) V.
+ * The products are formed in the cheaper order, S = (q Wk_h^T) X^^T and out = (softmax(S) X^) Wv_h, except on
+ * small steps; the same result to fp32 accuracy.
  * Exactly one source of X^ is given:
  *   xcache != NULL   an X cache (XQuant), x^ = code*scale + zero;
  *   acc_bf16 != NULL the cross-layer accumulator [B][cap][d] (XQuant-CL); one sequence's rows must stay
@@ -146,8 +148,10 @@ xq_status_t xq_prepare_weights(const xq_attn_t *a, int32_t d, int32_t group, int
  *   wprep    dev, from xq_prepare_weights with matching d / group / src_bits
  *   len      host [B], 1 <= len[b] <= cap
  *   out      dev [B][n_q_heads][head_dim] fp32
- *   workspace dev, >= xq_remat_attn_workspace_bytes(...) bytes, 16-byte aligned; holds the
- *            per-chunk softmax partials and a tile-ordered copy of the scales; contents are scratch
+ *   workspace dev, >= xq_remat_attn_workspace_bytes(...) bytes, 16-byte aligned; holds the folded
+ *            queries, softmax weights and partial sums; contents are scratch.  (On short contexts of wide
+ *            layers less is accepted too, down to 130 floats per query head and 32 tokens plus the scales: it
+ *            costs speed.)
  * B is taken from xcache->B, or passed in `B` when acc_bf16 is the source.
  * xq_remat_attn_workspace_bytes: max_len = max_b len[b]; d and group are those of the X cache,
  * group = 0 when the accumulator is the source.  Returns 0 for an invalid combination.
@@ -168,8 +172,8 @@ xq_status_t xq_remat_attn_decode(const xq_attn_t *a, const uint16_t *q_bf16,
  * xq_remat_attn_decode for callers that cannot allocate device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid it): same arguments, same kernels and same result, but
  * the workspace is a buffer built into the library, XQ_STATIC_SCRATCH_BYTES per GPU, instead of a
- * caller buffer.  The call allocates and frees nothing.  A problem whose
- * xq_remat_attn_workspace_bytes(...) exceeds XQ_STATIC_SCRATCH_BYTES is refused with
+ * caller buffer.  The call allocates and frees nothing.  A problem for which xq_remat_attn_decode would
+ * not accept XQ_STATIC_SCRATCH_BYTES of workspace is refused with
  * XQ_ERR_WORKSPACE before anything is launched (the 32 MiB cover e.g. B=8, 32 query heads, context
  * 4096, d=4096, group 128: 19.5 MB).  The buffer belongs to the device that is current at the call
  * (which must be the stream's device); its address is looked up on the first call on each device.

@@ -22,8 +22,9 @@ hipError_t run_latent_project(const uint16_t* x, const uint16_t* ut, int M, int 
                               hipStream_t s);
 hipError_t run_remat_attn_decode(const xq_attn_t* a, const uint16_t* q, const xq_cache_t* xc,
                                  const uint16_t* acc, int B, int cap, int d, const void* wprep,
-                                 const BatchI32& len, int max_len, float* out, void* ws,
+                                 const BatchI32& len, int max_len, float* out, void* ws, size_t ws_bytes,
                                  const float* rope, const BatchI32* pos0, hipStream_t s);
+size_t remat_decode_query_bytes(const xq_attn_t* a, int B, int max_len, int d, int group);
 hipError_t run_remat_attn_decode_latent(const xq_attn_t* a, const uint16_t* q, const xq_cache_t* xc,
                                         const void* wprep, const BatchI32& len, int max_len, float* out, void* ws,
                                         hipStream_t s);
@@ -245,7 +246,7 @@ size_t xq_remat_attn_workspace_bytes(const xq_attn_t* a, int32_t B, int32_t max_
 {
     if (check_attn(a) != XQ_OK || B < 1 || max_len < 1 || d <= 0 || d % 128 != 0) return 0;
     if (group != 0 && group != 64 && group != 128) return 0;
-    return remat_workspace_bytes(B, a->n_q_heads, max_len, d, group ? group : 128, group != 0);
+    return remat_decode_query_bytes(a, B, max_len, d, group);
 }
 
 size_t xq_remat_attn_prefill_workspace_bytes(const xq_attn_t* a, int32_t B, int32_t T, int32_t max_len, int32_t d,
@@ -291,7 +292,7 @@ static xq_status_t remat_attn_common(const xq_attn_t* a, const uint16_t* q_bf16,
     const bool nib = xcache && xcache->fmt.bits == 8;
     const int wd = nib ? 2 * d : d, wg = nib ? 128 : xcache ? xcache->fmt.group : 0;
     const size_t need = T > 0 ? xq_remat_attn_prefill_workspace_bytes(a, B, T, max_len, wd, wg)
-                              : xq_remat_attn_workspace_bytes(a, B, max_len, wd, wg);
+                              : remat_workspace_bytes(B, a->n_q_heads, max_len, wd, wg ? wg : 128, wg != 0);
     if (need == 0) return XQ_ERR_UNSUPPORTED;
     if (workspace_bytes < need) return XQ_ERR_WORKSPACE;
     BatchI32 pv{};
@@ -305,7 +306,7 @@ static xq_status_t remat_attn_common(const xq_attn_t* a, const uint16_t* q_bf16,
     hipError_t e = T > 0 ? run_remat_attn_prefill(a, q_bf16, T, xcache, acc_bf16, B, cap, d, wprep, lv, max_len, out,
                                                   workspace, rope, &pv, static_cast<hipStream_t>(stream))
                          : run_remat_attn_decode(a, q_bf16, xcache, acc_bf16, B, cap, d, wprep, lv, max_len, out,
-                                                 workspace, rope, &pv, static_cast<hipStream_t>(stream));
+                                                 workspace, workspace_bytes, rope, &pv, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? XQ_OK : XQ_ERR_HIP;
 }
 
@@ -707,8 +708,9 @@ xq_status_t xq_remat_attn_decode_static(const xq_attn_t* a, const uint16_t* q_bf
         if (len[b] > max_len) max_len = len[b];
     }
     const bool nib = xcache && xcache->fmt.bits == 8;
-    const size_t need = xq_remat_attn_workspace_bytes(a, B, max_len, nib ? 2 * d : d, nib ? 128 : xcache ? xcache->fmt.group : 0);
-    if (need == 0) return XQ_ERR_UNSUPPORTED;
+    if (d <= 0 || d % 128 != 0) return XQ_ERR_UNSUPPORTED;
+    const size_t need = remat_workspace_bytes(B, a->n_q_heads, max_len, nib ? 2 * d : d,
+                                              nib || !xcache ? 128 : xcache->fmt.group, xcache != nullptr);
     if (need > (size_t)XQ_STATIC_SCRATCH_BYTES) return XQ_ERR_WORKSPACE;     // beyond the built-in buffer
     void* ws = nullptr;
     st = static_scratch_of_current_device(&ws);

@@ -1,0 +1,1703 @@
+// Decode attention without rematerialised keys and values (see folded_common.hpp for the algebra and the precision):
+//   fold_query_kernel    u = q Wk_h^T for every query row, split and laid out as operand fragments of the score kernel
+//   fold_scores_kernel   S = u X^T for 128 tokens a workgroup; softmax weights against the tile's maximum
+//   fold_values_kernel   y = sum over tokens of softmax weight times cached row, for a slab range and a token range
+//   fold_output_kernel   o = y Wv_h, split over the channels
+//   fold_finish_kernel   sum of these splits, divided by the softmax denominator
+// Against rematerialising K and V tile by tile (MI355X, us per step with the append, before / after): 8 x 4096 tokens, 3 bits,
+// 32 KV heads of a d = 4096 layer 1664 / 110; 16 x up to 8191, 2 bits in groups of 64, 32 on 8 heads 1512 / 300; 4 x 32768,
+// 2 bits 6330 / 255; bf16 accumulator, 4 x up to 6000 1080 / 125.  The operations no longer bound it: what is left is the
+// latency of the codes, the unpacking, and 12 us each for reading the two halves of the weight stream.
+#include <algorithm>
+#include <mutex>
+#include <vector>
+
+#include "folded_common.hpp"
+#include "folded_attn.hpp"
+
+namespace xq {
+
+// What a launch sees of the problem: nb sequences starting at sequence b0 of the call.
+struct FoldShape {
+    int b0, nb, T, Hq, Hkv, R, nrb;      // query rows R = T Hq per sequence, nrb row blocks of 16 RT rows
+    int tiles;                           // score tiles (128 tokens) per sequence in the arrays, even
+    int splits;                          // token splits of the value kernel
+    BatchI32 len;                        // of the call's sequences
+};
+
+// element positions inside a fragment block of the softmax weights: [tile32][rt][part 2][lane 64][4 fp32], token
+// 4 i + q of the 32 is slot i of quarter q (rows of four adjacent tokens are read by one load of the value kernel)
+template <int RT>
+constexpr int FOLD_P_TILE32 = RT * 2 * 256;      // floats per 32 tokens
+
+// =====================================================================================================================
+// Folded queries.  A wave owns one slab (128 channels) of one KV head and 32 query columns (sequence, query token, query
+// head of the KV head).  The prepared stream holds the weights with 32 output columns along the lanes, contraction index
+// inside the lane -- right for x W, but here the contraction runs over the output columns.  The matrix cores transpose:
+// a product with a selection matrix gives every fragment's 16 channels as fp32 accumulator columns (exactly: one product
+// with 1 each), whose registers, cut to bf16 (exactly: the weights are bf16 numbers times a power of two), are the
+// operand of the product with the query rows.  The slab of u goes through LDS in natural channel order and leaves as
+// operand fragments of the score kernel.  Bound by reading the key half of the stream once.
+// =====================================================================================================================
+struct FoldQueryArgs {
+    FoldWeights w;
+    FoldShape s;
+    const uint16_t* q;                   // [B][T][Hq][128]
+    uint8_t* u;                          // [nb][nrb][n_slabs][u_slab]
+    float* rowfac;                       // [nb][nrb 16 RT]
+    float scale_log2e;
+    int u_slab, n_slabs, rt;
+    UnpackTable tab;                     // coded streams: channel of every slot of the stream
+};
+
+// channel inside its slab of slot (half, i) of k-step ks of the slab, in the first prepared stream
+__device__ __forceinline__ int stream_channel(const UnpackTable& tab, int group, int ks, int half, int i, int* code)
+{
+    const int ksg_n = group >> 4, gi = ks / ksg_n, ksg = ks % ksg_n;
+    const int p = tab.code_of_slot[ksg & 3][i];
+    *code = p;
+    return gi * group + half * (group >> 1) + (ksg >> 2) * 32 + p;
+}
+
+constexpr int FQ_STRIDE = 132;           // floats per query column in LDS: 16-byte pieces of different columns on different banks
+
+template <bool DENSE, int G>
+__global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
+{
+    __shared__ __attribute__((aligned(16))) float ul[2][32 * FQ_STRIDE];
+    __shared__ float nrm[2][32];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int half = lane >> 5, c32 = lane & 31;
+    const int slab = blockIdx.x * 2 + wave, h = blockIdx.y, cb = blockIdx.z;
+    if (slab >= a.n_slabs) return;                                  // (no workgroup barrier below: a wave's LDS is its own)
+    const FoldShape& s = a.s;
+    const int gq = s.Hq / s.Hkv, per_seq = s.T * gq, ncol = s.nb * per_seq;
+    float* mine = ul[wave];
+    // column -> (sequence of the launch, row of the sequence)
+    auto row_of = [&](int col, int& b) -> int {
+        b = col / per_seq;
+        const int rem = col - b * per_seq, t = rem / gq;
+        return t * s.Hq + h * gq + (rem - t * gq);
+    };
+
+    // the 32 query rows as an operand: lane = column, k-slots in the order the accumulator rows below come in
+    uint4 qa[4][2];
+    float l1 = 0.0f;
+    {
+        int b;
+        const int row = row_of(min(cb * 32 + c32, ncol - 1), b);
+        const uint16_t* qv = a.q + ((long long)(s.b0 + b) * s.R + row) * 128 + 4 * half;
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const uint2 x = *reinterpret_cast<const uint2*>(qv + 32 * nb + 16 * k);
+                const uint2 y = *reinterpret_cast<const uint2*>(qv + 32 * nb + 16 * k + 8);
+                qa[nb][k] = make_uint4(x.x, x.y, y.x, y.y);
+                const uint32_t w4[4] = {x.x, x.y, y.x, y.y};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) l1 += fabsf(bf16_lo_to_f32(w4[i])) + fabsf(bf16_hi_to_f32(w4[i]));
+            }
+        l1 += __shfl_xor(l1, 32);
+    }
+    const int sh = a.w.pair ? h >> 1 : h, nb0 = a.w.pair ? 4 * (h & 1) : 0;
+    const uint8_t* wsrc = a.w.stream + (long long)sh * a.w.head_bytes + lane * 16;
+    // A coded stream's weights are at most 2^12 (times the slot's factor): |u| <= 2^12 |q|_1, which a power of two brings
+    // below 2^15 for the fp16 parts of u.  The score kernel takes it (and the stream's own factor) out again.
+    int e = 0;
+    if constexpr (!DENSE) {
+        const uint32_t bits = __float_as_uint(l1);
+        if (bits) e = min(129 - (int)(bits >> 23), 100);
+        if (half == 0) nrm[wave][c32] = ldexpf(1.0f, e);
+    }
+    if (slab == 0 && half == 0 && cb * 32 + c32 < ncol) {
+        int b;
+        const int row = row_of(cb * 32 + c32, b);
+        const float f = DENSE ? a.scale_log2e : ldexpf(a.scale_log2e * FOLD_CODE_UNIT, -e - a.w.shift[sh]);
+        a.rowfac[(long long)b * s.nrb * 16 * a.rt + row] = f;
+    }
+
+    // selection matrices: columns 0-15 take the 16 slots of one k-step, columns 16-31 those of the next
+    uint4 sel[2];
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+        uint32_t d[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool lo = (c32 >> 4) == w && (c32 & 15) == 8 * half + 2 * i, hi = (c32 >> 4) == w && (c32 & 15) == 8 * half + 2 * i + 1;
+            const uint32_t one = DENSE ? 0x3F80u : 0x3C00u;
+            d[i] = (lo ? one : 0u) | (hi ? one << 16 : 0u);
+        }
+        sel[w] = make_uint4(d[0], d[1], d[2], d[3]);
+    }
+    f32x16 zero16;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) zero16[i] = 0.0f;
+#pragma unroll
+    for (int pr = 0; pr < 4; ++pr) {
+        uint4 wf[4][2];
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                // coded streams: column block nb runs 7 - nb k-steps late, cyclically
+                int pos = slab * 8 + 2 * pr + k + (DENSE ? 0 : COL_BLOCK_LAG_MAX - (nb0 + nb));
+                if (pos >= a.w.n16) pos -= a.w.n16;
+                wf[nb][k] = *reinterpret_cast<const uint4*>(wsrc + (long long)pos * 8192 + (nb0 + nb) * 1024);
+            }
+        f32x16 uacc = zero16;
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) {
+            f32x16 t;
+            if constexpr (DENSE) {
+                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[nb][0]), __builtin_bit_cast(bf16x8, sel[0]), zero16, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[nb][1]), __builtin_bit_cast(bf16x8, sel[1]), t, 0, 0, 0);
+            } else {
+                t = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, wf[nb][0]), __builtin_bit_cast(f16x8, sel[0]), zero16, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, wf[nb][1]), __builtin_bit_cast(f16x8, sel[1]), t, 0, 0, 0);
+            }
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                uint32_t d[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) d[i] = pack_hi16(__float_as_uint(t[8 * k + 2 * i]), __float_as_uint(t[8 * k + 2 * i + 1]));
+                uacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, qa[nb][k]),
+                                                               __builtin_bit_cast(bf16x8, make_uint4(d[0], d[1], d[2], d[3])), uacc, 0, 0, 0);
+            }
+        }
+        // lane = channel slot c32, registers = 16 of the 32 query columns: to LDS in natural channel order
+        int ch;
+        float f = 1.0f;
+        {
+            const int ks = 2 * pr + (c32 >> 4), hs = (c32 >> 3) & 1, i = c32 & 7;
+            if constexpr (DENSE) {
+                ch = ks * 16 + hs * 8 + i;
+            } else {
+                int p;
+                ch = stream_channel(a.tab, a.w.group, ks, hs, i, &p);
+                f = ldexpf(1.0f, -a.tab.wexp_of_code[p]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int col = 8 * (i >> 2) + 4 * half + (i & 3);
+            mine[col * FQ_STRIDE + ch] = DENSE ? uacc[i] : uacc[i] * f * nrm[wave][col];
+        }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+
+    // out: 16-byte pieces (column, tick, quarter); a fragment is read lane by lane, lane = 16 quarter + row
+    const int rpb = 16 * a.rt;
+#pragma unroll 1
+    for (int it = 0; it < 8; ++it) {
+        const int idx = it * 64 + lane, qd = idx & 3, tick = (idx >> 2) & 3, col = idx >> 4;
+        if (cb * 32 + col >= ncol) continue;
+        int b;
+        const int row = row_of(cb * 32 + col, b), rb = row / rpb, rr = row - rb * rpb;
+        uint8_t* dst = a.u + (((long long)b * s.nrb + rb) * a.n_slabs + slab) * a.u_slab + (qd * 16 + (rr & 15)) * 16;
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int ch = DENSE ? 32 * tick + 8 * qd + i : fold_channel<G>(tick, qd, i);
+            v[i] = mine[col * FQ_STRIDE + ch];
+        }
+        if constexpr (DENSE) {
+            uint32_t p[3][4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                uint32_t h0, m0, l0, h1, m1, l1_;
+                split_bf16x3(v[2 * i], h0, m0, l0);
+                split_bf16x3(v[2 * i + 1], h1, m1, l1_);
+                p[0][i] = pack_hi16(h0, h1); p[1][i] = pack_hi16(m0, m1); p[2][i] = pack_hi16(l0, l1_);
+            }
+            dst += ((rr >> 4) * 4 + tick) * 3 * 1024;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) *reinterpret_cast<uint4*>(dst + k * 1024) = make_uint4(p[k][0], p[k][1], p[k][2], p[k][3]);
+        } else {
+            uint32_t hi[4], lo[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const xq_f16x2 hh = {(_Float16)v[2 * i], (_Float16)v[2 * i + 1]};
+                const xq_f16x2 ll = {(_Float16)(v[2 * i] - (float)hh.x), (_Float16)(v[2 * i + 1] - (float)hh.y)};
+                hi[i] = __builtin_bit_cast(uint32_t, hh);
+                lo[i] = __builtin_bit_cast(uint32_t, ll);
+                // (the zero-point sums below are taken over the numbers the codes will meet)
+                mine[col * FQ_STRIDE + fold_channel<G>(tick, qd, 2 * i)] = (float)hh.x + (float)ll.x;
+                mine[col * FQ_STRIDE + fold_channel<G>(tick, qd, 2 * i + 1)] = (float)hh.y + (float)ll.y;
+            }
+            dst += ((rr >> 4) * 4 + tick) * 2 * 1024;
+            *reinterpret_cast<uint4*>(dst) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+            *reinterpret_cast<uint4*>(dst + 1024) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        }
+    }
+    if constexpr (!DENSE) {
+        // Zero-point term: every group adds (z + zi s) sum_c u[c].  The sums of the slab's groups, split into three bf16
+        // parts, are one more operand fragment against the three bf16 parts of z + zi s: quarter = part of the sum (the
+        // fourth is zero), slots = [group 0 three times, 0, group 1 three times, 0].
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+        float se = 0.0f, so = 0.0f;                                 // even and odd channels of this lane's half slab
+        const float* src = mine + c32 * FQ_STRIDE + half * 64;
+#pragma unroll 4
+        for (int k = 0; k < 64; k += 4) {
+            const float4 v = *reinterpret_cast<const float4*>(src + k);
+            se += v.x + v.z;
+            so += v.y + v.w;
+        }
+        float sz = (a.w.nibbles ? se : se + so) * (1.0f / FOLD_CODE_UNIT);   // (8-bit caches: a code's zero-point multiplies its weight row once)
+        float sz1 = __shfl_xor(sz, 32);
+        if constexpr (G == 128) { sz += sz1; sz1 = 0.0f; }
+        if (half == 0 && cb * 32 + c32 < ncol) {
+            int b;
+            const int row = row_of(cb * 32 + c32, b), rb = row / rpb, rr = row - rb * rpb;
+            uint8_t* dst = a.u + (((long long)b * s.nrb + rb) * a.n_slabs + slab) * a.u_slab + a.rt * 8192 + (rr >> 4) * 1024 + (rr & 15) * 16;
+            uint32_t z[3], z1[3];
+            split_bf16x3(sz, z[0], z[1], z[2]);
+            split_bf16x3(sz1, z1[0], z1[1], z1[2]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                *reinterpret_cast<uint4*>(dst + k * 256) = make_uint4(pack_hi16(z[k], z[k]), z[k] >> 16, pack_hi16(z1[k], z1[k]), z1[k] >> 16);
+            *reinterpret_cast<uint4*>(dst + 768) = make_uint4(0u, 0u, 0u, 0u);
+        }
+    }
+}
+
+// =====================================================================================================================
+// Scores.  A wave owns 128 tokens of a sequence, one block of 16 RT query rows and a run of adjacent slabs (so that a
+// token's scales share cache lines); a workgroup's 8 waves are slab ways and token ways.  A wave walks half slabs (64
+// channels) and keeps a half's folded queries in registers while its 128 tokens stream past, the next half's on their way,
+// so that neither LDS nor L2 is asked for them once per token.  A slab's codes are loaded row by row while the slab before
+// is worked on and go through the wave's own LDS image into operand order; a lane unpacks its token's codes.  A half's
+// products are summed by the matrix cores, scaled by the lane's own scale and added to the scores, which stay in
+// registers; the rests of the zero-points enter through one more matrix instruction per slab and row tile.  At the end
+// the slab ways' partial scores meet in LDS, and the softmax weights against the tile's maximum are stored as the value
+// kernel reads them.
+// Bound by the latency of the loads behind a run of few slabs and by issue: 1024 tiles of 2 bits take 114 us, 100 without
+// the meta loads, 89 without the codes' loads, 75 with nothing loaded; codes read in operand order straight into registers
+// (64 cache lines touched by every load) took 173 us.
+// =====================================================================================================================
+struct FoldScoreArgs {
+    FoldSource x;
+    FoldShape s;
+    const uint8_t* u;
+    const float* rowfac;
+    float* p;                            // [nb][nrb][tiles][4][FOLD_P_TILE32]
+    float* mtile;                        // [nb][nrb][tiles][16 RT]
+    int u_slab, sw_log2;
+};
+
+// which tokens and slabs a wave of a score workgroup has: 8 / SW token ways of one tile each, SW = 1 << sw_log2 slab ways
+struct FoldScorePlace { int b, rb, tile, len, sw, SW, tw, slab0, slab1, nw; };   // nw = slab ways that hold any slab
+__device__ __forceinline__ bool fold_score_place(const FoldShape& s, int sw_log2, int n_slabs, int wave, FoldScorePlace& o)
+{
+    const int ways = 8 >> sw_log2, tiles = (s.tiles + ways - 1) / ways, n = s.nb * s.nrb * tiles;
+    const int item = xcd_contiguous(n);
+    if (item >= n) return false;
+    o.rb = (item / tiles) % s.nrb;
+    o.b = item / (tiles * s.nrb);
+    o.len = s.len.v[s.b0 + o.b];
+    o.SW = 1 << sw_log2;
+    o.sw = wave & (o.SW - 1);
+    o.tw = wave >> sw_log2;
+    o.tile = (item % tiles) * ways + o.tw;
+    const int per = (n_slabs + o.SW - 1) >> sw_log2;                 // a run of adjacent slabs
+    o.slab0 = o.sw * per;
+    o.slab1 = o.tile * FOLD_TILE < o.len ? min(o.slab0 + per, n_slabs) : o.slab0;
+    o.nw = (n_slabs + per - 1) / per;
+    return (item % tiles) * ways * FOLD_TILE < o.len;
+}
+
+// what happens to the waves' partial scores: the end of every score kernel
+template <int RT>
+__device__ __forceinline__ void fold_scores_finish(const FoldShape& s, const float* rowfac_all, float* p_all, float* mtile_all,
+                                                   f32x4 (&S)[RT][8], float* lds, const FoldScorePlace& o, int lane, int wave)
+{
+    // partial scores [wave][rt][tile16][lane] x 4 rows, lane = (token c16, rows 4 q + [0, 4))
+    float4* part = reinterpret_cast<float4*>(lds);
+    __syncthreads();
+    if (o.slab0 < o.slab1)
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                part[((wave * RT + rt) * 8 + i) * 64 + lane] = make_float4(S[rt][i][0], S[rt][i][1], S[rt][i][2], S[rt][i][3]);
+    __syncthreads();
+    const bool live = o.tile * FOLD_TILE < o.len;
+    const int c16 = lane & 15, q = lane >> 4, share = 8 / o.SW;      // tile16s a wave of the token way sums up
+    const float* rowfac = rowfac_all + ((long long)o.b * s.nrb + o.rb) * 16 * RT;
+    float* mx = lds + 8 * RT * 8 * 256 + o.tw * 8 * 16 * RT;         // [token way][tile16][16 RT], behind the partial scores
+    // (the sums replace the first way's partial scores: what a wave reads there it has itself replaced)
+    if (live)
+        for (int j = 0; j < share; ++j) {
+            const int i16 = o.sw * share + j, tok = o.tile * FOLD_TILE + i16 * 16 + c16;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                float4* first = &part[((o.tw * o.SW * RT + rt) * 8 + i16) * 64 + lane];
+                float4 t = *first;
+                for (int k = 1; k < o.nw; ++k) {
+                    const float4 u = first[k * RT * 8 * 64];
+                    t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
+                }
+                float v[4] = {t.x, t.y, t.z, t.w}, m[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = o.rb * 16 * RT + rt * 16 + 4 * q + r;
+                    const int limit = o.len - s.T + (s.T > 1 ? min(row / s.Hq, s.T - 1) : 0);   // causal: the row's own token
+                    v[r] = tok <= limit ? v[r] * rowfac[rt * 16 + 4 * q + r] : -INFINITY;
+                    m[r] = v[r];
+                    m[r] = fmaxf(m[r], dpp_f32<DPP_QUAD_XOR1>(m[r]));
+                    m[r] = fmaxf(m[r], dpp_f32<DPP_QUAD_XOR2>(m[r]));
+                    m[r] = fmaxf(m[r], dpp_f32<DPP_ROW_HALF_MIRROR>(m[r]));
+                    m[r] = fmaxf(m[r], dpp_f32<DPP_ROW_MIRROR>(m[r]));
+                }
+                *first = make_float4(v[0], v[1], v[2], v[3]);
+                if (c16 == 0)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) mx[i16 * 16 * RT + rt * 16 + 4 * q + r] = m[r];
+            }
+        }
+    __syncthreads();
+    if (!live) return;
+    float Mu[RT][4];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = rt * 16 + 4 * q + r;
+            float M = mx[row];
+#pragma unroll
+            for (int k = 1; k < 8; ++k) M = fmaxf(M, mx[k * 16 * RT + row]);
+            Mu[rt][r] = M == -INFINITY ? 0.0f : M;                  // nothing visible: all weights 0
+            if (o.sw == 0 && c16 == 0) mtile_all[(((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile) * 16 * RT + row] = M;
+        }
+    for (int j = 0; j < share; ++j) {
+        const int i16 = o.sw * share + j, t32 = (i16 & 1) * 16 + c16, slot = t32 >> 2, qd = t32 & 3;
+        float* pt = p_all + ((((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile) * 4 + (i16 >> 1)) * FOLD_P_TILE32<RT>;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            const float4 t = part[((o.tw * o.SW * RT + rt) * 8 + i16) * 64 + lane];
+            const float v[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                pt[(rt * 2 + (slot >> 2)) * 256 + (4 * q + r + 16 * qd) * 4 + (slot & 3)] = __builtin_amdgcn_exp2f(v[r] - Mu[rt][r]);
+        }
+    }
+}
+
+template <int RT>
+constexpr int FOLD_SCORE_RED = 8 * RT * 8 * 1024 + 8 * 8 * 16 * RT * 4;
+// a wave's codes of one slab, and its records (8 bytes per token and group, 16 for nibble streams)
+template <int BITS, int G, bool NIB>
+constexpr int FOLD_SCORE_WAVE = FOLD_TILE * 16 * BITS + (128 / G) * FOLD_TILE * (NIB ? 16 : 8);
+template <int BITS, int G, int RT, bool NIB>
+constexpr int FOLD_SCORE_LDS = 8 * FOLD_SCORE_WAVE<BITS, G, NIB> > FOLD_SCORE_RED<RT> ? 8 * FOLD_SCORE_WAVE<BITS, G, NIB> : FOLD_SCORE_RED<RT>;
+
+template <int BITS, int G, int RT, bool NIB>
+__global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
+{
+    constexpr int GPS = 128 / G, ROWB = 16 * BITS;                  // groups and bytes of a slab's row
+    constexpr int NL = 2 * BITS;                                    // 1 KiB loads of a slab's codes per wave
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const FoldShape& s = a.s;
+    const FoldSource& x = a.x;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    FoldScorePlace o;
+    if (!fold_score_place(s, a.sw_log2, x.n_slabs, wave, o)) return;
+    const int b = o.b, rb = o.rb, len = o.len, tok0 = o.tile * FOLD_TILE;
+    const int c16 = lane & 15, q = lane >> 4;
+    const uint8_t* cbase = x.codes + (long long)(s.b0 + b) * x.cap * x.row_bytes;
+    const uint16_t* sbase = x.scale + (long long)(s.b0 + b) * x.cap * x.ng_row;
+    const uint16_t* zbase = x.zero + (long long)(s.b0 + b) * x.cap * x.ng_row;
+    const uint8_t* ubase = a.u + ((long long)b * s.nrb + rb) * x.n_slabs * a.u_slab;
+    const uint32_t uoff = lane * 16;
+    const int slab0 = o.slab0, slab1 = o.slab1;
+    uint8_t* image = lds + wave * FOLD_SCORE_WAVE<BITS, G, NIB>;     // [token 128][ROWB]
+    uint32_t* records = reinterpret_cast<uint32_t*>(image + FOLD_TILE * ROWB);
+
+    // Codes go through the wave's LDS image: loaded row by row (a load then touches 64 / BITS rows once; in operand order
+    // every row would be touched by four quarter waves, and L1 look-ups bound the kernel), written once the slab before has
+    // been read, read back in operand order.
+    uint32_t voff[NL];
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+        const int pc = k * 64 + lane;
+        voff[k] = (uint32_t)min(tok0 + pc / BITS, len - 1) * (uint32_t)x.row_bytes + (uint32_t)(pc % BITS) * 16u;
+    }
+    // stored zero-points and scales of the slab's groups for the tokens lane and lane + 64
+    const uint32_t moff[2] = {(uint32_t)min(tok0 + lane, len - 1) * (uint32_t)x.ng_row, (uint32_t)min(tok0 + 64 + lane, len - 1) * (uint32_t)x.ng_row};
+    uint32_t zs[2][2];
+    auto load_meta = [&](int slab) XQ_INLINE_LAMBDA {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            if constexpr (GPS == 2) {
+                zs[t][0] = *reinterpret_cast<const uint32_t*>(zbase + 2 * slab + moff[t]);
+                zs[t][1] = *reinterpret_cast<const uint32_t*>(sbase + 2 * slab + moff[t]);
+            } else {
+                zs[t][0] = (zbase + (slab >> x.meta_shift))[moff[t]];
+                zs[t][1] = (sbase + (slab >> x.meta_shift))[moff[t]];
+            }
+        }
+    };
+    // -> records: -zi (fp16) | scale (bf16), rest of the zero-point (fp32); nibble streams: -zi of either nibble, scale, rest
+    auto write_meta = [&]() XQ_INLINE_LAMBDA {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int g = 0; g < GPS; ++g) {
+                const float z = g ? bf16_hi_to_f32(zs[t][0]) : bf16_lo_to_f32(zs[t][0]);
+                const float sc = g ? bf16_hi_to_f32(zs[t][1]) : bf16_lo_to_f32(zs[t][1]);
+                float rest;
+                const float zi = fold_integer_zero(sc, z, NIB ? 255.0f : (float)((1 << BITS) - 1), rest);
+                const int at = g * FOLD_TILE + t * 64 + lane;
+                if constexpr (NIB) {
+                    const float zh = floorf(zi * (1.0f / 16.0f));
+                    reinterpret_cast<uint4*>(records)[at] =
+                        make_uint4(f16_bits((zi - 16.0f * zh) * (-1.0f / FOLD_CODE_UNIT)) | (f16_bits(zh * (-1.0f / FOLD_CODE_UNIT)) << 16),
+                                   __float_as_uint(sc), __float_as_uint(rest), 0u);
+                } else {
+                    reinterpret_cast<uint2*>(records)[at] =
+                        make_uint2(f16_bits(zi * (-1.0f / FOLD_CODE_UNIT)) | (__float_as_uint(sc) & 0xFFFF0000u), __float_as_uint(rest));
+                }
+            }
+    };
+
+    f32x4 S[RT][8];
+    const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) S[rt][i] = zero4;
+    // A slab is 16 units: half slab t / 8 against token tile t % 8.  While the 4 RT matrix instructions of unit t run, the
+    // vector ALU unpacks unit t + 1 and adds unit t - 1 to the scores, a little of each behind every matrix instruction
+    // (scheduling fences keep it there).
+    if (slab0 < slab1) {
+        uint4 u[2][RT][2][2], uz[RT];                                // folded queries of the two halves: [rt][tick][hi, lo]
+        uint32_t rec[4][3];                                          // records of units t - 1 .. t + 2: -zi, scale, rest
+        float rest0[4];                                              // (groups of 64: the first group's rest, for the second half's units)
+        uint32_t cw[4][2];                                           // code dwords of units t .. t + 2
+        uint32_t F[2][8];                                            // token operands of units t, t + 1
+        f32x4 P[2][RT];
+        auto load_u = [&](int slab, auto HF, auto I) XQ_INLINE_LAMBDA {                  // piece I of half HF
+            constexpr int h = decltype(HF)::value, i = decltype(I)::value, rt = i >> 2, t = (i >> 1) & 1, k = i & 1;
+            u[h][rt][t][k] = *reinterpret_cast<const uint4*>(ubase + (long long)slab * a.u_slab + rt * 8192 + h * 4096 + t * 2048 + k * 1024 + uoff);
+        };
+        auto read_unit = [&](auto T) XQ_INLINE_LAMBDA {               // record and codes of unit T (16, 17: the next slab's first two)
+            constexpr int t = decltype(T)::value, h = (t >> 3) & 1, i = t & 7, n = t & 3;
+            const int at = (GPS == 2 ? h : 0) * FOLD_TILE + i * 16 + c16;
+            if constexpr (NIB) {
+                const uint4 r = reinterpret_cast<const uint4*>(records)[at];
+                rec[n][0] = r.x; rec[n][1] = r.y; rec[n][2] = r.z;
+            } else {
+                const uint2 r = reinterpret_cast<const uint2*>(records)[at];
+                rec[n][0] = r.x; rec[n][1] = r.x & 0xFFFF0000u; rec[n][2] = r.y;
+                if constexpr (GPS == 2 && h == 1) rest0[n] = __uint_as_float(records[(i * 16 + c16) * 2 + 1]);
+            }
+            const uint32_t* src = reinterpret_cast<const uint32_t*>(image + (i * 16 + c16) * ROWB);
+            if constexpr (G == 128) {                                // dwords of the lane's unit of 32 codes: those of half h
+                const uint32_t* w = src + q * BITS;
+                if constexpr (BITS == 2) { cw[n][0] = w[h]; cw[n][1] = 0u; }
+                else if constexpr (BITS == 3) { cw[n][0] = w[h]; cw[n][1] = w[h + 1]; }
+                else { cw[n][0] = w[2 * h]; cw[n][1] = w[2 * h + 1]; }
+            } else {                                                 // 16 codes of group h
+                if constexpr (BITS == 2) { cw[n][0] = src[4 * h + q]; cw[n][1] = 0u; }
+                else if constexpr (BITS == 3) { const uint32_t* w = src + 6 * h + ((6 * q) >> 2); cw[n][0] = w[0]; cw[n][1] = w[1]; }
+                else { cw[n][0] = src[8 * h + 2 * q]; cw[n][1] = src[8 * h + 2 * q + 1]; }
+            }
+        };
+        uint32_t m0, m1;
+        auto unpack = [&](auto T, auto K) XQ_INLINE_LAMBDA {          // operand dword K of unit T
+            constexpr int t = decltype(T)::value, h = (t >> 3) & 1, n = t & 3, k = decltype(K)::value;
+            if constexpr (k == 0) {                                  // merged octet pair
+                m1 = 0u;
+                if constexpr (BITS == 2) {
+                    m0 = cw[n][0];
+                } else if constexpr (BITS == 3 && G == 128) {        // 48 bits at bit 0 / 16 of the two dwords
+                    m0 = perm_bytes(cw[n][1], cw[n][0], h == 0 ? 0x04030100u : 0x06050302u);
+                    m1 = perm_bytes(cw[n][1], cw[n][0], h == 0 ? 0x05040201u : 0x07060403u);
+                } else if constexpr (BITS == 3) {                    // ... at bit 0 (even quarters) or 16
+                    const uint32_t lo = __builtin_amdgcn_alignbit(cw[n][1], cw[n][0], (q & 1) * 16), hi = cw[n][1] >> ((q & 1) * 16);
+                    m0 = perm_bytes(hi, lo, 0x04030100u);
+                    m1 = perm_bytes(hi, lo, 0x05040201u);
+                } else {
+                    m0 = perm_bytes(cw[n][1], cw[n][0], 0x05040100u);
+                    m1 = perm_bytes(cw[n][1], cw[n][0], 0x07060302u);
+                }
+                if constexpr (!NIB) rec[n][0] = perm_bytes(rec[n][0], rec[n][0], 0x01000100u);
+            }
+            uint32_t add = rec[n][0];
+            if constexpr (NIB) add = perm_bytes(add, add, (k & 1) ? 0x03020302u : 0x01000100u);      // -zi of the even / odd codes
+            F[t & 1][k] = fold_code<BITS, k>(m0, m1, add);
+        };
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        u32x4 cn[NL];
+        auto load_codes = [&](int slab, auto K) XQ_INLINE_LAMBDA {
+            constexpr int k = decltype(K)::value;
+            cn[k] = *reinterpret_cast<const u32x4*>(cbase + slab * ROWB + voff[k]);
+        };
+        auto write_codes = [&]() XQ_INLINE_LAMBDA {
+            static_for<0, NL>([&](auto K) XQ_INLINE_LAMBDA {
+                constexpr int k = decltype(K)::value;
+                *reinterpret_cast<u32x4*>(image + (k * 64 + lane) * 16) = cn[k];
+            });
+        };
+        load_meta(slab0);
+        static_for<0, NL>([&](auto K) XQ_INLINE_LAMBDA { load_codes(slab0, K); });
+        static_for<0, 4 * RT>([&](auto I) XQ_INLINE_LAMBDA { load_u(slab0, std::integral_constant<int, 0>{}, I); });
+        write_meta();
+        write_codes();
+        read_unit(std::integral_constant<int, 0>{});
+        read_unit(std::integral_constant<int, 1>{});
+        static_for<0, 8>([&](auto K) XQ_INLINE_LAMBDA { unpack(std::integral_constant<int, 0>{}, K); });
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) P[1][rt] = zero4;
+        rec[3][1] = 0u;                                              // (unit -1 adds nothing)
+        for (int slab = slab0; slab < slab1; ++slab) {
+            const int snext = slab + 1 < slab1 ? slab + 1 : slab;    // (the last iteration prepares itself again)
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<0, 16>([&](auto T) XQ_INLINE_LAMBDA {
+                constexpr int t = decltype(T)::value, h = t >> 3, i = t & 7;
+                if constexpr (t == 1) load_meta(snext);
+                if constexpr (t >= 2 && t < 2 + NL) load_codes(snext, std::integral_constant<int, t - 2>{});
+                // (units 14 and 15 of this slab have been read: the next slab's records and codes may take their place)
+                if constexpr (t == 14) { write_meta(); write_codes(); }
+                read_unit(std::integral_constant<int, t + 2>{});
+                // the next half's folded queries, ahead of the codes in the first half: loads return in order, and the queries
+                // come out of L2, the codes from farther away
+                if constexpr (i == 0)
+                    static_for<0, 4 * RT>([&](auto I) XQ_INLINE_LAMBDA { load_u(h == 0 ? slab : snext, std::integral_constant<int, h ^ 1>{}, I); });
+                if constexpr (t == 0)
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+                        uz[rt] = *reinterpret_cast<const uint4*>(ubase + (long long)slab * a.u_slab + RT * 8192 + rt * 1024 + uoff);
+                __builtin_amdgcn_sched_barrier(0);
+                static_for<0, 4 * RT>([&](auto M) XQ_INLINE_LAMBDA {
+                    constexpr int m = decltype(M)::value, rt = m % RT, k = 1 - (m / RT) % 2, tick = m / (2 * RT);
+                    const uint32_t* f = &F[t & 1][4 * tick];
+                    P[t & 1][rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, u[h][rt][tick][k]), as_frag(f[0], f[1], f[2], f[3]),
+                                                                          m < RT ? zero4 : P[t & 1][rt], 0, 0, 0);
+                    static_for<0, 2 / RT>([&](auto E) XQ_INLINE_LAMBDA {
+                        unpack(std::integral_constant<int, t + 1>{}, std::integral_constant<int, m * (2 / RT) + decltype(E)::value>{});
+                    });
+                    // the unit before: rows r of row tile q2
+                    constexpr int q2 = m / 4, r = m & 3, ip = (t + 7) & 7;
+                    S[q2][ip][r] = __builtin_fmaf(P[(t + 1) & 1][q2][r], __uint_as_float(rec[(t + 3) & 3][1]), S[q2][ip][r]);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                if constexpr (h == 1) {
+                    uint32_t a3[3], b3[3];
+                    uint4 mz;
+                    split_bf16x3(__uint_as_float(rec[t & 3][2]), a3[0], a3[1], a3[2]);
+                    if constexpr (GPS == 2) {
+                        split_bf16x3(rest0[t & 3], b3[0], b3[1], b3[2]);
+                        mz = make_uint4(pack_hi16(b3[0], b3[1]), b3[2] >> 16, pack_hi16(a3[0], a3[1]), a3[2] >> 16);
+                    } else {
+                        mz = make_uint4(pack_hi16(a3[0], a3[1]), a3[2] >> 16, 0u, 0u);
+                    }
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+                        S[rt][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, uz[rt]), __builtin_bit_cast(bf16x8, mz), S[rt][i], 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        }
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)                              // the last unit
+#pragma unroll
+            for (int r = 0; r < 4; ++r) S[rt][7][r] = __builtin_fmaf(P[1][rt][r], __uint_as_float(rec[3][1]), S[rt][7][r]);
+    }
+    fold_scores_finish<RT>(s, a.rowfac, a.p, a.mtile, S, reinterpret_cast<float*>(lds), o, lane, wave);
+}
+
+// the same over bf16 rows (the cross-layer accumulator, a residual window): no codes and no groups, u in three bf16 parts.
+// The rows of a half slab (128 bytes each) go through the wave's LDS image as the codes do, 16 token rows at a time; their
+// 16-byte pieces are swizzled by the row, so that neither the row-wise write nor the fragment read meets bank conflicts.
+template <int RT>
+__global__ __launch_bounds__(512) void fold_scores_dense_kernel(const FoldScoreArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const FoldShape& s = a.s;
+    const FoldSource& x = a.x;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    FoldScorePlace o;
+    if (!fold_score_place(s, a.sw_log2, x.n_slabs, wave, o)) return;
+    const int b = o.b, rb = o.rb, len = o.len, tok0 = o.tile * FOLD_TILE;
+    const int c16 = lane & 15, q = lane >> 4;
+    const uint8_t* xbase = reinterpret_cast<const uint8_t*>(x.rows) + (long long)(s.b0 + b) * x.cap * x.row_bytes;
+    const uint8_t* ubase = a.u + ((long long)b * s.nrb + rb) * x.n_slabs * a.u_slab;
+    const uint32_t uoff = lane * 16;
+    uint8_t* image = lds + wave * 2 * 2048;                          // two images of 16 rows x 128 bytes
+    f32x4 S[RT][8];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) S[rt][i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    // load side: lane = (row lane / 8, piece lane % 8) of 8 rows; fragment side: row c16, pieces 4 tick + q
+    const int r8 = lane >> 3, pc = lane & 7;
+    uint32_t voff[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) voff[k] = (uint32_t)min(tok0 + k * 8 + r8, len - 1) * (uint32_t)x.row_bytes + pc * 16;
+    const int wpos = r8 * 128 + ((pc ^ r8) * 16), rpos = c16 * 128;
+    if (o.slab0 < o.slab1) {
+        uint4 u[2][RT][2][3];
+        u32x4 xr[16];                                                // the half slab's rows on their way: [token tile 8][8-row part 2]
+        auto load_x = [&](int half_idx, auto I) XQ_INLINE_LAMBDA {
+            constexpr int i = decltype(I)::value;
+            const uint8_t* base = xbase + half_idx * 128;
+            xr[2 * i] = *reinterpret_cast<const u32x4*>(base + voff[2 * i]);
+            xr[2 * i + 1] = *reinterpret_cast<const u32x4*>(base + voff[2 * i + 1]);
+        };
+        auto load_u = [&](int half_idx, auto HF) XQ_INLINE_LAMBDA {
+            constexpr int h = decltype(HF)::value;
+            const uint8_t* us = ubase + (long long)(half_idx >> 1) * a.u_slab + (half_idx & 1) * 6144;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) u[h][rt][t][k] = *reinterpret_cast<const uint4*>(us + (rt * 4 + t) * 3072 + k * 1024 + uoff);
+        };
+        load_u(2 * o.slab0, std::integral_constant<int, 0>{});
+        static_for<0, 8>([&](auto I) XQ_INLINE_LAMBDA { load_x(2 * o.slab0, I); });
+        for (int slab = o.slab0; slab < o.slab1; ++slab) {
+            const int snext = slab + 1 < o.slab1 ? slab + 1 : slab;
+            static_for<0, 2>([&](auto HF) XQ_INLINE_LAMBDA {
+                constexpr int h = decltype(HF)::value;
+                const int hn = h == 0 ? 2 * slab + 1 : 2 * snext;
+                load_u(hn, std::integral_constant<int, h ^ 1>{});
+                static_for<0, 8>([&](auto I) XQ_INLINE_LAMBDA {
+                    constexpr int i = decltype(I)::value;
+                    uint8_t* img = image + (i & 1) * 2048;
+                    *reinterpret_cast<u32x4*>(img + wpos) = xr[2 * i];
+                    *reinterpret_cast<u32x4*>(img + 1024 + wpos) = xr[2 * i + 1];
+                    load_x(hn, I);
+                    const u32x4 x0 = *reinterpret_cast<const u32x4*>(img + rpos + ((q ^ (c16 & 7)) * 16));
+                    const u32x4 x1 = *reinterpret_cast<const u32x4*>(img + rpos + (((4 + q) ^ (c16 & 7)) * 16));
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        const bf16x8 xf = __builtin_bit_cast(bf16x8, t ? x1 : x0);
+#pragma unroll
+                        for (int k = 2; k >= 0; --k)
+#pragma unroll
+                            for (int rt = 0; rt < RT; ++rt)
+                                S[rt][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, u[h][rt][t][k]), xf, S[rt][i], 0, 0, 0);
+                    }
+                });
+            });
+        }
+    }
+    fold_scores_finish<RT>(s, a.rowfac, a.p, a.mtile, S, reinterpret_cast<float*>(lds), o, lane, wave);
+}
+
+// =====================================================================================================================
+// Values.  A workgroup owns two slabs (256 channels) of a sequence, one row block and a range of tokens: two slab ways,
+// four token ways.  Per 256 tokens all eight waves bring the stored softmax weights to the sequence's maximum and stage
+// them in LDS with the tokens' scales, integer zero-points and rests; a wave then takes 32 tokens at a time: the weights
+// times its group's scale, split into fp16 hi + lo, against the codes.  The contraction runs over tokens, so an operand
+// dword pairs the codes of two tokens: a lane takes octet n = lane % 16 of the slab (8 channels) for eight tokens, merges
+// token pairs, and column tile k of the product is code k of every lane's octet -- no transposition.  (Groups of 64:
+// lanes n and n + 8 exchange half octets, so that a column tile lies in one group.)  The rests are summed on the vector
+// ALU.  At the end the four token ways meet in LDS.
+// =====================================================================================================================
+struct FoldValueArgs {
+    FoldSource x;
+    FoldShape s;
+    const float* p;
+    const float* mtile;
+    float* y;                            // [splits][nb][R][n_slabs 128]
+    float* yz;                           // [splits][nb][R][ng]: sum of weight times rest of the zero-point, per group
+    float* lsum;                         // [splits][nb][nrb 16 RT]
+    int cblocks;                         // workgroups per row of slabs
+};
+
+template <int RT, int GROUPS, bool NIB>
+struct FoldValueLds {
+    static constexpr int P_BYTES = 8 * FOLD_P_TILE32<RT> * 4;                   // 256 tokens of softmax weights
+    static constexpr int STRIDE = FOLD_VTILE + 4;                               // floats: scales, then rests, of a group's tokens
+    static constexpr int ZI_STRIDE = FOLD_VTILE + 8;                            // halfs: -zi (of even, then of odd codes)
+    static constexpr int GROUP_BYTES = 2 * STRIDE * 4 + (NIB ? 2 : 1) * ZI_STRIDE * 2;
+    static constexpr int SZ_BYTES = GROUPS * GROUP_BYTES;
+    static constexpr int P_OFF = 0, SZ_OFF = 2 * P_BYTES, M_OFF = SZ_OFF + 2 * SZ_BYTES;
+    static constexpr int N_OFF = M_OFF + 16 * RT * 4 * 17;                      // row maxima (one column per partial reader + result)
+    static constexpr int L_OFF = N_OFF + GROUPS * 4 * 17;
+    static constexpr int LOOP = L_OFF + 8 * 16 * RT * 4;
+    static constexpr int RED = 8 * RT * 8 * 1024;                               // every wave's accumulators, at the end
+    static constexpr int TOTAL = LOOP > RED ? LOOP : RED;
+};
+
+// tile and range of a value workgroup
+struct FoldValuePlace { int b, rb, cblk, split, len, t0, t1; };      // [t0, t1): 256-token tiles
+__device__ __forceinline__ bool fold_value_place(const FoldShape& s, int cblocks, FoldValuePlace& o)
+{
+    const int n = s.nb * s.nrb * s.splits * cblocks;
+    const int item = xcd_contiguous(n);
+    if (item >= n) return false;
+    o.cblk = item % cblocks;                                        // (neighbours share the softmax weights)
+    o.split = (item / cblocks) % s.splits;
+    o.rb = (item / (cblocks * s.splits)) % s.nrb;
+    o.b = item / (cblocks * s.splits * s.nrb);
+    o.len = s.len.v[s.b0 + o.b];
+    const int nt = (o.len + FOLD_VTILE - 1) / FOLD_VTILE, per = (nt + s.splits - 1) / s.splits;
+    o.t0 = o.split * per;
+    o.t1 = min(nt, o.t0 + per);
+    return o.t0 < o.t1;
+}
+
+// maximum of every row over the sequence's score tiles -> mrow[16 RT] (a workgroup barrier ends it)
+template <int RT>
+__device__ __forceinline__ void fold_row_maxima(const FoldShape& s, const float* mtile, int b, int rb, int len, float* scratch, float* mrow)
+{
+    constexpr int ROWS = 16 * RT, PARTS = 512 / ROWS > 16 ? 16 : 512 / ROWS;
+    const int tid = threadIdx.x, row = tid % ROWS, pt = tid / ROWS;
+    const int nt = (len + FOLD_TILE - 1) / FOLD_TILE;
+    if (pt < PARTS) {
+        float m = -INFINITY;
+        const float* src = mtile + ((long long)b * s.nrb + rb) * s.tiles * ROWS + row;
+        for (int t = pt; t < nt; t += PARTS) m = fmaxf(m, src[(long long)t * ROWS]);
+        scratch[pt * ROWS + row] = m;
+    }
+    __syncthreads();
+    if (tid < ROWS) {
+        float m = scratch[tid];
+#pragma unroll
+        for (int k = 1; k < PARTS; ++k) m = fmaxf(m, scratch[k * ROWS + tid]);
+        mrow[tid] = m;
+    }
+    __syncthreads();
+}
+
+template <int BITS, int G, int RT, bool NIB>
+__global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
+{
+    constexpr int GPS = 128 / G, NG = 2 * GPS;                      // groups of a workgroup's two slabs
+    typedef FoldValueLds<RT, NG, NIB> L;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const FoldShape& s = a.s;
+    FoldValuePlace o;
+    if (!fold_value_place(s, a.cblocks, o)) return;
+    const FoldSource& x = a.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c16 = lane & 15, q = lane >> 4;
+    const int sw = wave & 1, tw = wave >> 1;                        // two slab ways, four token ways
+    const int slab = o.cblk * 2 + sw;
+    const bool live = slab < x.n_slabs;
+    const int g0 = o.cblk * NG;                                     // first group of the workgroup
+    const long long seq = s.b0 + o.b;
+    const uint16_t* sbase = x.scale + seq * x.cap * x.ng_row;
+    const uint16_t* zbase = x.zero + seq * x.cap * x.ng_row;
+
+    float* mrow = reinterpret_cast<float*>(lds + L::M_OFF) + 16 * 16 * RT;
+    float* ginv = reinterpret_cast<float*>(lds + L::N_OFF) + 16 * NG;
+    // power of two per group that brings the range's largest scale below 2^15 (the fp16 parts of weight times scale)
+    {
+        uint32_t mx[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) mx[g] = 0u;
+        const int tend = min(o.len, o.t1 * FOLD_VTILE);
+        for (int t = o.t0 * FOLD_VTILE + tid; t < tend; t += 512) {
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+                if (g0 + g < x.ng) mx[g] = max(mx[g], (uint32_t)sbase[(long long)t * x.ng_row + ((g0 + g) >> x.meta_shift)]);
+        }
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            uint32_t m = mx[g];
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
+            if (lane == 0) reinterpret_cast<uint32_t*>(lds + L::N_OFF)[wave * NG + g] = m;
+        }
+    }
+    fold_row_maxima<RT>(s, a.mtile, o.b, o.rb, o.len, reinterpret_cast<float*>(lds + L::M_OFF), mrow);
+    if (tid < NG) {
+        const uint32_t* src = reinterpret_cast<const uint32_t*>(lds + L::N_OFF);
+        uint32_t m = 0u;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) m = max(m, src[w * NG + tid]);
+        // largest scale < 2^(e - 126): times 2^(141 - e) it is below 2^15
+        ginv[tid] = m ? ldexpf(1.0f, min(141 - (int)(m >> 7), 120)) : 1.0f;
+    }
+    __syncthreads();
+
+    // ---- staging: thread -> softmax weights (always of the same row) and (token, group) pairs
+    constexpr int NP = 2 * RT;                                      // 16-byte pieces per thread and 256 tokens
+    const int prow = RT == 2 ? ((wave >> 1) & 1) * 16 + c16 : c16;
+    const float M = mrow[prow];
+    const float* psrc = a.p + ((long long)o.b * s.nrb + o.rb) * s.tiles * 4 * FOLD_P_TILE32<RT>;
+    const float* msrc = a.mtile + ((long long)o.b * s.nrb + o.rb) * s.tiles * 16 * RT + prow;
+    float4 pv[NP];
+    float fm[2];
+    constexpr int NE = FOLD_VTILE * NG / 512;                       // (token, group) pairs per thread: 1 or 2
+    const int eg = tid % NG, et = tid / NG;                         // group and first token of this thread's pairs
+    uint32_t sv[NE], zv[NE];
+    const uint16_t* sgrp = sbase + (min(g0 + eg, x.ng - 1) >> x.meta_shift);
+    const uint16_t* zgrp = zbase + (min(g0 + eg, x.ng - 1) >> x.meta_shift);
+    const float my_ginv = ginv[eg];
+    auto load_stage = [&](int t) XQ_INLINE_LAMBDA {
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+            const int t128 = 2 * t + hf;
+            const bool ok = t128 * FOLD_TILE < o.len;
+            fm[hf] = ok ? msrc[(long long)t128 * 16 * RT] : -INFINITY;
+#pragma unroll
+            for (int k = 0; k < RT; ++k) {
+                const int e = hf * RT + k;
+                pv[e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (ok) pv[e] = *reinterpret_cast<const float4*>(psrc + (long long)t * 8 * FOLD_P_TILE32<RT> + (e * 512 + tid) * 4);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const uint32_t at = (uint32_t)min(t * FOLD_VTILE + et + e * (512 / NG), o.len - 1) * (uint32_t)x.ng_row;
+            sv[e] = sgrp[at];
+            zv[e] = zgrp[at];
+        }
+    };
+    float lacc = 0.0f;
+    auto write_stage = [&](int buf) XQ_INLINE_LAMBDA {
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+            const float f = fm[hf] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(fm[hf] - M);
+#pragma unroll
+            for (int k = 0; k < RT; ++k) {
+                const int e = hf * RT + k;
+                float4 v = pv[e];
+                v.x *= f; v.y *= f; v.z *= f; v.w *= f;
+                if (o.cblk == 0) lacc += (v.x + v.y) + (v.z + v.w);
+                *reinterpret_cast<float4*>(lds + L::P_OFF + buf * L::P_BYTES + (e * 512 + tid) * 16) = v;
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const int tok = et + e * (512 / NG), t32 = tok & 31, at = (tok & ~31) + (t32 & 3) * 8 + (t32 >> 2);
+            uint8_t* grp = lds + L::SZ_OFF + buf * L::SZ_BYTES + eg * L::GROUP_BYTES;
+            const float sf = bf16_bits_to_f32(sv[e]);
+            float rest;
+            const float zi = fold_integer_zero(sf, bf16_bits_to_f32(zv[e]), NIB ? 255.0f : (float)((1 << BITS) - 1), rest);
+            reinterpret_cast<float*>(grp)[at] = sf * my_ginv;
+            reinterpret_cast<float*>(grp)[L::STRIDE + at] = rest;
+            uint16_t* zo = reinterpret_cast<uint16_t*>(grp + 2 * L::STRIDE * 4);
+            if constexpr (NIB) {
+                const float zh = floorf(zi * (1.0f / 16.0f));
+                zo[at] = (uint16_t)f16_bits((zi - 16.0f * zh) * (-1.0f / FOLD_CODE_UNIT));
+                zo[L::ZI_STRIDE + at] = (uint16_t)f16_bits(zh * (-1.0f / FOLD_CODE_UNIT));
+            } else {
+                zo[at] = (uint16_t)f16_bits(zi * (-1.0f / FOLD_CODE_UNIT));
+            }
+        }
+    };
+
+    // ---- codes: octet n = c16 of the wave's slab for tokens 4 i + q of its 32
+    const uint8_t* cbase = x.codes + seq * x.cap * x.row_bytes + (live ? slab : 0) * (16 * BITS);
+    const uint32_t oct = BITS == 3 ? 3 * c16 - (c16 > 0) : BITS * c16;
+    uint32_t voff[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) voff[i] = (uint32_t)(4 * i + q) * (uint32_t)x.row_bytes + oct;
+    auto load_codes = [&](int k32, uint32_t (&r)[8]) XQ_INLINE_LAMBDA {
+        const uint8_t* base = cbase + (long long)k32 * 32 * x.row_bytes;
+        uint32_t off[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) off[i] = voff[i];
+        if (k32 * 32 + 32 > o.len) {                                // past the length: the last row again (32-bit offsets from the sequence's start)
+            base = cbase;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) off[i] = (uint32_t)min(k32 * 32 + 4 * i + q, o.len - 1) * (uint32_t)x.row_bytes + oct;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if constexpr (BITS == 2) r[i] = *reinterpret_cast<const uint16_t*>(base + off[i]);
+            else if constexpr (BITS == 4) r[i] = *reinterpret_cast<const uint32_t*>(base + off[i]);
+            else __builtin_memcpy(&r[i], base + off[i], 4);         // three of these four bytes (lane 0: the first three)
+        }
+    };
+    const uint32_t sel0 = c16 ? 0x06050201u : 0x05040100u, sel1 = c16 ? 0x07060302u : 0x06050201u;
+    const bool lower = c16 < 8;
+
+    f32x4 acc[RT][8];
+    float az[RT][GPS];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc[rt][k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int g = 0; g < GPS; ++g) az[rt][g] = 0.0f;
+    }
+    // A wave's tile is two steps of 32 tokens, a step one phase per group: 8 / GPS column tiles times 2 RT matrix
+    // instructions.  While a phase's matrix instructions run, the vector ALU unpacks the next column tile and forms the
+    // next phase's weights, a little behind every matrix instruction (fences keep it there).
+    constexpr int KPP = 8 / GPS, NSLOT = KPP * 2 * RT, NSUB = RT * 8, START = NSLOT / 4;
+    uint32_t raw[2][8], m0[4], m1[4], F[2][4];
+    uint4 wh[2][RT], wl[2][RT], zi[2][NIB ? 2 : 1];                 // of the running and the next phase
+    float pr[RT][8], sc[8], of[8];                                  // of the next phase
+    auto merge_pairs = [&](const uint32_t (&r)[8]) XQ_INLINE_LAMBDA {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if constexpr (BITS == 2) { m0[j] = r[2 * j] | (r[2 * j + 1] << 16); m1[j] = 0u; }
+            else if constexpr (BITS == 3) { m0[j] = perm_bytes(r[2 * j + 1], r[2 * j], sel0); m1[j] = perm_bytes(r[2 * j + 1], r[2 * j], sel1); }
+            else { m0[j] = perm_bytes(r[2 * j + 1], r[2 * j], 0x05040100u); m1[j] = perm_bytes(r[2 * j + 1], r[2 * j], 0x07060302u); }
+            if constexpr (G == 64) {
+                // lanes n and n + 8 exchange half octets: codes 0-3 then belong to the first group, 4-7 to the second
+                if constexpr (BITS == 2) {
+                    const uint32_t ot = dpp_u32<0x128 /* row_ror:8 */>(m0[j]);
+                    m0[j] = perm_bytes(ot, m0[j], lower ? 0x06020400u : 0x03070105u);
+                } else {
+                    uint32_t lo, hi;
+                    if constexpr (BITS == 3) { lo = m0[j] & 0x0FFF0FFFu; hi = (m1[j] >> 4) & 0x0FFF0FFFu; }
+                    else { lo = m0[j]; hi = m1[j]; }
+                    const uint32_t keep = lower ? lo : hi, got = dpp_u32<0x128>(lower ? hi : lo);
+                    const uint32_t n0 = lower ? keep : got, n1 = lower ? got : keep;
+                    if constexpr (BITS == 3) { m0[j] = n0 | (n1 << 12 & 0xF000F000u); m1[j] = (n0 >> 8 & 0x000F000Fu) | (n1 << 4); }
+                    else { m0[j] = n0; m1[j] = n1; }
+                }
+            }
+        }
+    };
+    // the next phase's data out of LDS: PH = step GPS + group
+    auto read_phase = [&](auto PH, int buf) XQ_INLINE_LAMBDA {
+        constexpr int st = decltype(PH)::value / GPS, g = decltype(PH)::value % GPS, n = decltype(PH)::value & 1;
+        const int k32 = tw * 2 + st;
+        if constexpr (g == 0)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const float4 v = *reinterpret_cast<const float4*>(lds + L::P_OFF + buf * L::P_BYTES + ((k32 * RT + rt) * 2 + h) * 1024 + lane * 16);
+                    pr[rt][4 * h] = v.x; pr[rt][4 * h + 1] = v.y; pr[rt][4 * h + 2] = v.z; pr[rt][4 * h + 3] = v.w;
+                }
+        const uint8_t* grp = lds + L::SZ_OFF + buf * L::SZ_BYTES + (sw * GPS + g) * L::GROUP_BYTES;
+        const float* sp = reinterpret_cast<const float*>(grp) + k32 * 32 + q * 8;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float4 a4 = *reinterpret_cast<const float4*>(sp + 4 * h), b4 = *reinterpret_cast<const float4*>(sp + L::STRIDE + 4 * h);
+            sc[4 * h] = a4.x; sc[4 * h + 1] = a4.y; sc[4 * h + 2] = a4.z; sc[4 * h + 3] = a4.w;
+            of[4 * h] = b4.x; of[4 * h + 1] = b4.y; of[4 * h + 2] = b4.z; of[4 * h + 3] = b4.w;
+        }
+#pragma unroll
+        for (int k = 0; k < (NIB ? 2 : 1); ++k)
+            zi[n][k] = *reinterpret_cast<const uint4*>(grp + 2 * L::STRIDE * 4 + (k * L::ZI_STRIDE + k32 * 32 + q * 8) * 2);
+    };
+    // weights of the next phase, piece SUB: (row tile, token pair) products and top parts, then low parts and rests
+    auto set_dword = [](uint4& v, auto J, uint32_t x) XQ_INLINE_LAMBDA {
+        constexpr int j = decltype(J)::value;
+        if constexpr (j == 0) v.x = x; else if constexpr (j == 1) v.y = x; else if constexpr (j == 2) v.z = x; else v.w = x;
+    };
+    auto weight_piece = [&](auto PH, auto SUB) XQ_INLINE_LAMBDA {
+        constexpr int g = decltype(PH)::value % GPS, n = decltype(PH)::value & 1;
+        constexpr int sub = decltype(SUB)::value, rt = sub / 8, j = (sub / 2) & 3;
+        const float p0 = pr[rt][2 * j], p1 = pr[rt][2 * j + 1], s0 = sc[2 * j], s1 = sc[2 * j + 1];
+        if constexpr ((sub & 1) == 0) {
+            const xq_f32x2 w = {p0 * s0, p1 * s1};
+            set_dword(wh[n][rt], std::integral_constant<int, j>{}, __builtin_bit_cast(uint32_t, __builtin_convertvector(w, xq_f16x2)));
+        } else {
+            const uint32_t hb = j == 0 ? wh[n][rt].x : j == 1 ? wh[n][rt].y : j == 2 ? wh[n][rt].z : wh[n][rt].w;
+            const xq_f16x2 top = __builtin_bit_cast(xq_f16x2, hb);
+            const xq_f16x2 low = {(_Float16)__builtin_fmaf(p0, s0, -(float)top.x), (_Float16)__builtin_fmaf(p1, s1, -(float)top.y)};
+            set_dword(wl[n][rt], std::integral_constant<int, j>{}, __builtin_bit_cast(uint32_t, low));
+            az[rt][g] = __builtin_fmaf(p0, of[2 * j], az[rt][g]);
+            az[rt][g] = __builtin_fmaf(p1, of[2 * j + 1], az[rt][g]);
+        }
+    };
+    // operand dword J of column tile K (its codes in m0, m1), with the integer zero-points of phase parity N
+    auto unpack = [&](auto K, auto J, auto N) XQ_INLINE_LAMBDA {
+        constexpr int k = decltype(K)::value, j = decltype(J)::value, n = decltype(N)::value;
+        const uint4 z = zi[n][NIB ? k & 1 : 0];
+        const uint32_t zj = j == 0 ? z.x : j == 1 ? z.y : j == 2 ? z.z : z.w;
+        F[k & 1][j] = fold_code<BITS, k>(m0[j], m1[j], zj);
+    };
+    auto phase = [&](auto PH, int nbuf) XQ_INLINE_LAMBDA {
+        constexpr int ph = decltype(PH)::value, st = ph / GPS, g = ph % GPS, n = ph & 1, nph = (ph + 1) % (2 * GPS);
+        read_phase(std::integral_constant<int, nph>{}, nbuf);
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<0, NSLOT>([&](auto M) XQ_INLINE_LAMBDA {
+            constexpr int m = decltype(M)::value, kk = m / (2 * RT), k = g * KPP + kk, in = m % (2 * RT), rt = in % RT;
+            const uint32_t* f = F[k & 1];
+            acc[rt][k] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, in < RT ? wl[n][rt] : wh[n][rt]), as_frag(f[0], f[1], f[2], f[3]),
+                                                                acc[rt][k], 0, 0, 0);
+            // the next column tile; the first one of the next step waits for its codes here
+            if constexpr (k == 7 && in == 0) merge_pairs(raw[st ^ 1]);
+            static_for<0, 2 / RT>([&](auto E) XQ_INLINE_LAMBDA {
+                unpack(std::integral_constant<int, (k + 1) & 7>{}, std::integral_constant<int, in * (2 / RT) + decltype(E)::value>{},
+                       std::integral_constant<int, kk == KPP - 1 ? n ^ 1 : n>{});
+            });
+            constexpr int b0 = m < START ? 0 : (m - START) * NSUB / (NSLOT - START), b1 = m < START ? 0 : (m + 1 - START) * NSUB / (NSLOT - START);
+            static_for<b0, b1>([&](auto SUB) XQ_INLINE_LAMBDA { weight_piece(std::integral_constant<int, nph>{}, SUB); });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+
+    load_stage(o.t0);
+    load_codes(o.t0 * 8 + tw * 2, raw[0]);
+    load_codes(o.t0 * 8 + tw * 2 + 1, raw[1]);
+    write_stage(0);
+    __syncthreads();
+    if (o.t0 + 1 < o.t1) load_stage(o.t0 + 1);
+    read_phase(std::integral_constant<int, 0>{}, 0);
+    static_for<0, NSUB>([&](auto SUB) XQ_INLINE_LAMBDA { weight_piece(std::integral_constant<int, 0>{}, SUB); });
+    merge_pairs(raw[0]);
+    static_for<0, 4>([&](auto J) XQ_INLINE_LAMBDA { unpack(std::integral_constant<int, 0>{}, J, std::integral_constant<int, 0>{}); });
+    // One barrier per tile, before its last phase: by then every wave has read all of the tile out of LDS (a phase reads
+    // the next one's data), so the tile after the next may overwrite it, and the next tile, written since the barrier
+    // before, may be read by the last phase.
+    for (int t = o.t0; t < o.t1; ++t) {
+        const int buf = (t - o.t0) & 1;
+        if (live) {
+            // (a step's codes are merged before it starts: their registers take those of the step after the next)
+            load_codes(min(t + 1, o.t1 - 1) * 8 + tw * 2, raw[0]);
+            static_for<0, GPS>([&](auto PH) XQ_INLINE_LAMBDA { phase(PH, buf); });
+            load_codes(min(t + 1, o.t1 - 1) * 8 + tw * 2 + 1, raw[1]);
+            static_for<GPS, 2 * GPS - 1>([&](auto PH) XQ_INLINE_LAMBDA { phase(PH, buf); });
+        }
+        if (t + 1 < o.t1) write_stage(buf ^ 1);
+        __syncthreads();
+        if (t + 2 < o.t1) load_stage(t + 2);
+        if (live) {
+            float keep[RT][GPS];                                     // (behind the last tile a phase prepares weights of nothing)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int g = 0; g < GPS; ++g) keep[rt][g] = az[rt][g];
+            phase(std::integral_constant<int, 2 * GPS - 1>{}, buf ^ 1);
+            if (t + 1 == o.t1)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int g = 0; g < GPS; ++g) az[rt][g] = keep[rt][g];
+        }
+    }
+    __syncthreads();
+
+    // softmax denominators: once per row block and split
+    if (o.cblk == 0) {
+        float l = lacc;
+        l += __shfl_xor(l, 16);
+        l += __shfl_xor(l, 32);
+        float* lp = reinterpret_cast<float*>(lds + L::L_OFF);
+        if (q == 0) lp[wave * 16 + c16] = l;
+        __syncthreads();
+        if (tid < 16 * RT) {
+            float t = 0.0f;
+#pragma unroll
+            for (int w = 0; w < 8; ++w)
+                if (RT == 1 || ((w >> 1) & 1) == (tid >> 4)) t += lp[w * 16 + (tid & 15)];
+            a.lsum[(((long long)o.split * s.nb + o.b) * s.nrb + o.rb) * 16 * RT + tid] = t;
+        }
+    }
+    // the four token ways meet in LDS: rests first, then the accumulators
+    const float inv_g[2] = {ginv[sw * GPS], ginv[sw * GPS + GPS - 1]};
+    __syncthreads();
+    float* red = reinterpret_cast<float*>(lds);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int g = 0; g < GPS; ++g) {
+            float z = az[rt][g];
+            z += __shfl_xor(z, 16);
+            z += __shfl_xor(z, 32);
+            if (q == 0) red[((wave * RT + rt) * GPS + g) * 16 + c16] = z;
+        }
+    __syncthreads();
+    const long long yrow0 = ((long long)o.split * s.nb + o.b) * s.R;
+    for (int idx = tid; idx < 2 * RT * GPS * 16; idx += 512) {
+        const int r16 = idx & 15, g = (idx >> 4) % GPS, rt = (idx / (16 * GPS)) % RT, w = idx / (16 * GPS * RT);
+        const int row = o.rb * 16 * RT + rt * 16 + r16, gg = g0 + w * GPS + g;
+        float z = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) z += red[(((2 * k + w) * RT + rt) * GPS + g) * 16 + r16];
+        if (row < s.R && gg < x.ng) a.yz[(yrow0 + row) * x.ng + gg] = z;
+    }
+    __syncthreads();
+    float4* acc_lds = reinterpret_cast<float4*>(lds);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            acc_lds[((wave * RT + rt) * 8 + k) * 64 + lane] = make_float4(acc[rt][k][0], acc[rt][k][1], acc[rt][k][2], acc[rt][k][3]);
+    __syncthreads();
+    // token way tw sums half an accumulator row tile (rt, four column tiles) of its slab over the token ways
+    if (live && tw < 2 * RT) {
+        const int rt = tw >> 1, kg = tw & 1;
+        f32x4 t[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            float4 v = acc_lds[((sw * RT + rt) * 8 + 4 * kg + k) * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < 4; ++w) {
+                const float4 u = acc_lds[(((2 * w + sw) * RT + rt) * 8 + 4 * kg + k) * 64 + lane];
+                v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+            }
+            t[k] = f32x4{v.x, v.y, v.z, v.w};
+        }
+        const int ch = G == 128 ? 8 * c16 + 4 * kg : 64 * kg + 8 * (c16 & 7) + 4 * (c16 >> 3);
+        const float f = FOLD_CODE_UNIT / (GPS == 2 && kg ? inv_g[1] : inv_g[0]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = o.rb * 16 * RT + rt * 16 + 4 * q + r;
+            if (row < s.R)
+                *reinterpret_cast<float4*>(a.y + (yrow0 + row) * (x.n_slabs * 128) + slab * 128 + ch) =
+                    make_float4(t[0][r] * f, t[1][r] * f, t[2][r] * f, t[3][r] * f);
+        }
+    }
+}
+
+// the same over bf16 rows: no scales and no offsets, the softmax weights in three bf16 parts (made once per workgroup)
+template <int RT>
+struct FoldValueDenseLds {
+    static constexpr int W_BYTES = 8 * RT * 3 * 1024;                           // [tile32][rt][part][lane 64][16 B]
+    static constexpr int M_OFF = 2 * W_BYTES;
+    static constexpr int L_OFF = M_OFF + 16 * RT * 4 * 17;
+    static constexpr int LOOP = L_OFF + 8 * 16 * RT * 4;
+    static constexpr int RED = 8 * RT * 8 * 1024;
+    static constexpr int TOTAL = LOOP > RED ? LOOP : RED;
+};
+template <int RT>
+__global__ __launch_bounds__(512) void fold_values_dense_kernel(const FoldValueArgs a)
+{
+    typedef FoldValueDenseLds<RT> L;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const FoldShape& s = a.s;
+    FoldValuePlace o;
+    if (!fold_value_place(s, a.cblocks, o)) return;
+    const FoldSource& x = a.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c16 = lane & 15, q = lane >> 4;
+    const int sw = wave & 1, tw = wave >> 1;
+    const int slab = o.cblk * 2 + sw;
+    const bool live = slab < x.n_slabs;
+    float* mrow = reinterpret_cast<float*>(lds + L::M_OFF) + 16 * 16 * RT;
+    fold_row_maxima<RT>(s, a.mtile, o.b, o.rb, o.len, reinterpret_cast<float*>(lds + L::M_OFF), mrow);
+
+    constexpr int NP = 2 * RT;
+    const int prow = RT == 2 ? ((wave >> 1) & 1) * 16 + c16 : c16;
+    const float M = mrow[prow];
+    const float* psrc = a.p + ((long long)o.b * s.nrb + o.rb) * s.tiles * 4 * FOLD_P_TILE32<RT>;
+    const float* msrc = a.mtile + ((long long)o.b * s.nrb + o.rb) * s.tiles * 16 * RT + prow;
+    float4 pv[NP];
+    float fm[2];
+    auto load_stage = [&](int t) XQ_INLINE_LAMBDA {
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+            const int t128 = 2 * t + hf;
+            const bool ok = t128 * FOLD_TILE < o.len;
+            fm[hf] = ok ? msrc[(long long)t128 * 16 * RT] : -INFINITY;
+#pragma unroll
+            for (int k = 0; k < RT; ++k) {
+                const int e = hf * RT + k;
+                pv[e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (ok) pv[e] = *reinterpret_cast<const float4*>(psrc + (long long)t * 8 * FOLD_P_TILE32<RT> + (e * 512 + tid) * 4);
+            }
+        }
+    };
+    float lacc = 0.0f;
+    auto write_stage = [&](int buf) XQ_INLINE_LAMBDA {
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+            const float f = fm[hf] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(fm[hf] - M);
+#pragma unroll
+            for (int k = 0; k < RT; ++k) {
+                const int e = hf * RT + k;
+                const float v[4] = {pv[e].x * f, pv[e].y * f, pv[e].z * f, pv[e].w * f};
+                lacc += (v[0] + v[1]) + (v[2] + v[3]);
+                uint32_t h[4], m[4], l[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) split_bf16x3(v[i], h[i], m[i], l[i]);
+                // piece e 512 + tid of [tile32][rt][half of the slots][lane]
+                const int idx = e * 512 + tid, hs = (idx >> 6) & 1, blk = idx >> 7;
+                uint8_t* dst = lds + buf * L::W_BYTES + blk * 3072 + lane * 16 + hs * 8;
+                *reinterpret_cast<uint2*>(dst) = make_uint2(pack_hi16(h[0], h[1]), pack_hi16(h[2], h[3]));
+                *reinterpret_cast<uint2*>(dst + 1024) = make_uint2(pack_hi16(m[0], m[1]), pack_hi16(m[2], m[3]));
+                *reinterpret_cast<uint2*>(dst + 2048) = make_uint2(pack_hi16(l[0], l[1]), pack_hi16(l[2], l[3]));
+            }
+        }
+    };
+    const uint8_t* xbase = reinterpret_cast<const uint8_t*>(x.rows) + (long long)(s.b0 + o.b) * x.cap * x.row_bytes + (live ? slab : 0) * 256;
+    uint4 raw[2][8];
+    uint32_t voff[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) voff[i] = (uint32_t)(4 * i + q) * (uint32_t)x.row_bytes + c16 * 16;
+    auto load_rows = [&](int k32, uint4 (&r)[8]) XQ_INLINE_LAMBDA {
+        const uint8_t* base = xbase + (long long)k32 * 32 * x.row_bytes;
+        uint32_t off[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) off[i] = voff[i];
+        if (k32 * 32 + 32 > o.len) {                                // past the length: the last row again
+            base = xbase;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) off[i] = (uint32_t)min(k32 * 32 + 4 * i + q, o.len - 1) * (uint32_t)x.row_bytes + c16 * 16;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) r[i] = *reinterpret_cast<const uint4*>(base + off[i]);
+    };
+    f32x4 acc[RT][8];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc[rt][k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto step = [&](const uint8_t* wb, int k32, const uint4 (&r)[8]) XQ_INLINE_LAMBDA {
+        uint4 w[RT][3];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) w[rt][k] = *reinterpret_cast<const uint4*>(wb + ((k32 * RT + rt) * 3 + k) * 1024 + lane * 16);
+        static_for<0, 8>([&](auto K) XQ_INLINE_LAMBDA {
+            constexpr int k = decltype(K)::value;
+            uint32_t d[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t x0[4] = {r[2 * j].x, r[2 * j].y, r[2 * j].z, r[2 * j].w};
+                const uint32_t x1[4] = {r[2 * j + 1].x, r[2 * j + 1].y, r[2 * j + 1].z, r[2 * j + 1].w};
+                d[j] = perm_bytes(x1[k >> 1], x0[k >> 1], (k & 1) ? 0x07060302u : 0x05040100u);
+            }
+            const bf16x8 xf = __builtin_bit_cast(bf16x8, make_uint4(d[0], d[1], d[2], d[3]));
+#pragma unroll
+            for (int p = 2; p >= 0; --p)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+                    acc[rt][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[rt][p]), xf, acc[rt][k], 0, 0, 0);
+        });
+    };
+    load_stage(o.t0);
+    load_rows(o.t0 * 8 + tw * 2, raw[0]);
+    load_rows(o.t0 * 8 + tw * 2 + 1, raw[1]);
+    write_stage(0);
+    __syncthreads();
+    for (int t = o.t0; t < o.t1; ++t) {
+        const int buf = (t - o.t0) & 1;
+        const bool more = t + 1 < o.t1;
+        if (more) load_stage(t + 1);
+        const uint8_t* wb = lds + buf * L::W_BYTES;
+        if (live) step(wb, tw * 2, raw[0]);
+        if (more) load_rows((t + 1) * 8 + tw * 2, raw[0]);
+        if (live) step(wb, tw * 2 + 1, raw[1]);
+        if (more) load_rows((t + 1) * 8 + tw * 2 + 1, raw[1]);
+        if (more) write_stage(buf ^ 1);
+        __syncthreads();
+    }
+    if (o.cblk == 0) {
+        float l = lacc;
+        l += __shfl_xor(l, 16);
+        l += __shfl_xor(l, 32);
+        float* lp = reinterpret_cast<float*>(lds + L::L_OFF);
+        if (q == 0) lp[wave * 16 + c16] = l;
+        __syncthreads();
+        if (tid < 16 * RT) {
+            float t = 0.0f;
+#pragma unroll
+            for (int w = 0; w < 8; ++w)
+                if (RT == 1 || ((w >> 1) & 1) == (tid >> 4)) t += lp[w * 16 + (tid & 15)];
+            a.lsum[(((long long)o.split * s.nb + o.b) * s.nrb + o.rb) * 16 * RT + tid] = t;
+        }
+        __syncthreads();
+    }
+    float4* acc_lds = reinterpret_cast<float4*>(lds);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            acc_lds[((wave * RT + rt) * 8 + k) * 64 + lane] = make_float4(acc[rt][k][0], acc[rt][k][1], acc[rt][k][2], acc[rt][k][3]);
+    __syncthreads();
+    if (live && tw < 2 * RT) {
+        const int rt = tw >> 1, kg = tw & 1;
+        f32x4 t[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            float4 v = acc_lds[((sw * RT + rt) * 8 + 4 * kg + k) * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < 4; ++w) {
+                const float4 u = acc_lds[(((2 * w + sw) * RT + rt) * 8 + 4 * kg + k) * 64 + lane];
+                v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+            }
+            t[k] = f32x4{v.x, v.y, v.z, v.w};
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = o.rb * 16 * RT + rt * 16 + 4 * q + r;
+            if (row < s.R)
+                *reinterpret_cast<float4*>(a.y + (((long long)o.split * s.nb + o.b) * s.R + row) * (x.n_slabs * 128) + slab * 128 + 8 * c16 + 4 * kg) =
+                    make_float4(t[0][r], t[1][r], t[2][r], t[3][r]);
+        }
+    }
+}
+
+// =====================================================================================================================
+// Output projection.  A workgroup takes one KV head, 32 query columns and a few slabs: it sums y over the token splits,
+// adds the offsets of the groups, and multiplies by the slabs' share of Wv_h, the prepared stream's fragments as they
+// are (fp16 ones are cut to bf16, exactly) against y in three bf16 parts.  Bound by reading the value half of the
+// stream once.
+// =====================================================================================================================
+struct FoldOutArgs {
+    FoldWeights w;
+    FoldShape s;
+    const float* y;
+    const float* yz;
+    float* part;                         // [chunks][nb][R][128]
+    int n_slabs, ng, group, chunk_slabs, rt;
+    UnpackTable tab;
+};
+
+constexpr int FO_MAX_SLABS = 4;
+constexpr int FO_STRIDE = FO_MAX_SLABS * 128 + 4;
+constexpr int FO_LDS = 32 * FO_STRIDE * 4;               // 66 KiB, reused for the waves' partial sums (64 KiB)
+
+template <bool DENSE>
+__global__ __launch_bounds__(512) void fold_output_kernel(const FoldOutArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    float* yl = reinterpret_cast<float*>(lds);
+    const FoldShape& s = a.s;
+    const int chunk = blockIdx.x, h = blockIdx.y, cb = blockIdx.z;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, c32 = lane & 31;
+    const int gq = s.Hq / s.Hkv, per_seq = s.T * gq, ncol = s.nb * per_seq;
+    const int slab0 = chunk * a.chunk_slabs, ns = min(a.chunk_slabs, a.n_slabs - slab0);
+    const int d = a.n_slabs * 128;
+    const long long split_stride = (long long)s.nb * s.R;
+    auto row_of = [&](int col, int& b) -> int {
+        b = col / per_seq;
+        const int rem = col - b * per_seq, t = rem / gq;
+        return t * s.Hq + h * gq + (rem - t * gq);
+    };
+    for (int idx = tid; idx < 32 * ns * 32; idx += 512) {            // 16-byte pieces: [column][channel / 4]
+        const int col = idx / (ns * 32), c4 = idx - col * (ns * 32);
+        float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (cb * 32 + col < ncol) {
+            int b;
+            const int row = row_of(cb * 32 + col, b);
+            const int len = s.len.v[s.b0 + b], nt = (len + FOLD_VTILE - 1) / FOLD_VTILE, per = (nt + s.splits - 1) / s.splits;
+            const int used = (nt + per - 1) / per;                   // splits that hold tokens of this sequence
+            const long long r0 = (long long)b * s.R + row;
+            const int ch = slab0 * 128 + 4 * c4;
+            for (int k = 0; k < used; ++k) {
+                const long long rk = k * split_stride + r0;
+                const float4 t = *reinterpret_cast<const float4*>(a.y + rk * d + ch);
+                v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
+                if constexpr (!DENSE) {
+                    // (8-bit caches: a code's zero-point multiplies its weight row once, that of the low nibble)
+                    const float z = a.yz[rk * a.ng + ch / a.group], zo = a.w.nibbles ? 0.0f : z;
+                    v.x += z; v.y += zo; v.z += z; v.w += zo;
+                }
+            }
+        }
+        *reinterpret_cast<float4*>(yl + col * FO_STRIDE + 4 * c4) = v;
+    }
+    __syncthreads();
+    const int sh = a.w.pair ? h >> 1 : h, nb0 = a.w.pair ? 4 * (h & 1) : 4;
+    const uint8_t* wsrc = a.w.stream + (long long)sh * a.w.head_bytes + lane * 16;
+    f32x16 acc[4];
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[nb][i] = 0.0f;
+    for (int k = wave; k < ns * 8; k += 8) {                         // a wave's k-step: the same place in every slab
+        const int sl = k >> 3, ks = k & 7;
+        uint4 wf[4];
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) {
+            int pos = (slab0 + sl) * 8 + ks + (DENSE ? 0 : COL_BLOCK_LAG_MAX - (nb0 + nb));
+            if (pos >= a.w.n16) pos -= a.w.n16;
+            wf[nb] = *reinterpret_cast<const uint4*>(wsrc + (long long)pos * 8192 + (nb0 + nb) * 1024);
+        }
+        uint32_t yp[3][4];
+        {
+            float v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                int ch;
+                float f = 1.0f;
+                if constexpr (DENSE) {
+                    ch = ks * 16 + half * 8 + i;
+                } else {
+                    int p;
+                    ch = stream_channel(a.tab, a.w.group, ks, half, i, &p);
+                    f = __uint_as_float((uint32_t)(127 - a.tab.wexp_of_code[p]) << 23);
+                }
+                v[i] = yl[c32 * FO_STRIDE + sl * 128 + ch] * f;
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                uint32_t h0, m0, l0, h1, m1, l1;
+                split_bf16x3(v[2 * i], h0, m0, l0);
+                split_bf16x3(v[2 * i + 1], h1, m1, l1);
+                yp[0][i] = pack_hi16(h0, h1); yp[1][i] = pack_hi16(m0, m1); yp[2][i] = pack_hi16(l0, l1);
+            }
+        }
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) {
+            uint4 wb = wf[nb];
+            if constexpr (!DENSE) {                                  // fp16 -> bf16: at most 8 significant bits, exact
+                const uint32_t w4[4] = {wb.x, wb.y, wb.z, wb.w};
+                uint32_t d4[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const xq_f16x2 hv = __builtin_bit_cast(xq_f16x2, w4[i]);
+                    d4[i] = pack_hi16(__float_as_uint((float)hv.x), __float_as_uint((float)hv.y));
+                }
+                wb = make_uint4(d4[0], d4[1], d4[2], d4[3]);
+            }
+#pragma unroll
+            for (int p = 2; p >= 0; --p)
+                acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wb),
+                                                                  __builtin_bit_cast(bf16x8, make_uint4(yp[p][0], yp[p][1], yp[p][2], yp[p][3])),
+                                                                  acc[nb], 0, 0, 0);
+        }
+    }
+    // the waves' sums, two column blocks at a time: [wave][block][register quad][lane] x 4
+    const float f = DENSE ? 1.0f : ldexpf(1.0f, -a.w.shift[sh]);
+    float4* red = reinterpret_cast<float4*>(lds);
+    int b = 0, row = 0;
+    const bool ok = cb * 32 + c32 < ncol;
+    if (ok) row = row_of(cb * 32 + c32, b);
+    float* dst = a.part + (((long long)chunk * s.nb + b) * s.R + row) * 128 + 4 * half;
+#pragma unroll
+    for (int rd = 0; rd < 2; ++rd) {
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4) {
+                const f32x16& v = acc[2 * rd + n];
+                red[((wave * 2 + n) * 4 + i4) * 64 + lane] = make_float4(v[4 * i4], v[4 * i4 + 1], v[4 * i4 + 2], v[4 * i4 + 3]);
+            }
+        __syncthreads();
+        // wave w sums (block w / 4, register quad w % 4): columns 32 nb + 8 i4 + 4 half + [0, 4)
+        float4 t = red[wave * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < 8; ++w) {
+            const float4 u = red[(w * 8 + wave) * 64 + lane];
+            t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
+        }
+        if (ok) *reinterpret_cast<float4*>(dst + 32 * (2 * rd + (wave >> 2)) + 8 * (wave & 3)) = make_float4(t.x * f, t.y * f, t.z * f, t.w * f);
+    }
+}
+
+// out = (sum over the channel splits) / (softmax denominator, summed over the token splits)
+__global__ __launch_bounds__(256) void fold_finish_kernel(const float* __restrict__ part, const float* __restrict__ lsum, float* __restrict__ out,
+                                                          FoldShape s, int chunks, int rt)
+{
+    const int idx = blockIdx.x * 256 + threadIdx.x;                  // (sequence, row, four columns)
+    if (idx >= s.nb * s.R * 32) return;
+    const int c4 = idx & 31, row = (idx >> 5) % s.R, b = (idx >> 5) / s.R;
+    const int nt = (s.len.v[s.b0 + b] + FOLD_VTILE - 1) / FOLD_VTILE, per = (nt + s.splits - 1) / s.splits, used = (nt + per - 1) / per;
+    float L = 0.0f;
+    for (int k = 0; k < used; ++k) L += lsum[((long long)k * s.nb + b) * s.nrb * 16 * rt + row];
+    float4 t = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int k = 0; k < chunks; ++k) {
+        const float4 u = *reinterpret_cast<const float4*>(part + (((long long)k * s.nb + b) * s.R + row) * 128 + 4 * c4);
+        t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
+    }
+    *reinterpret_cast<float4*>(out + ((long long)(s.b0 + b) * s.R + row) * 128 + 4 * c4) = make_float4(t.x / L, t.y / L, t.z / L, t.w / L);
+}
+
+// =====================================================================================================================
+// Host side
+// =====================================================================================================================
+static hipError_t allow_lds(const void* kernel, int bytes)
+{
+    struct Done { const void* kernel; int device; };
+    static std::mutex mu;
+    static std::vector<Done> done;
+    if (bytes <= 65536) return hipSuccess;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lock(mu);
+    for (const Done& d : done)
+        if (d.kernel == kernel && d.device == dev) return hipSuccess;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess) done.push_back({kernel, dev});
+    return e;
+}
+
+template <typename Args>
+static hipError_t launch(void (*kernel)(const Args), int grid, int lds_bytes, const Args& a, hipStream_t s)
+{
+    hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), lds_bytes);
+    if (e != hipSuccess) return e;
+    kernel<<<dim3(grid), dim3(512), lds_bytes, s>>>(a);
+    return hipGetLastError();
+}
+
+static size_t align256(size_t n) { return (n + 255) / 256 * 256; }
+
+// Workspace of one launch group: what depends on the number of sequences in it.
+struct FoldPlan {
+    int rt, nrb, tiles, splits, chunks, chunk_slabs, u_slab;
+    size_t p, mtile, rowfac, lsum, uy, yz, total;      // bytes; u and y share a region (u is dead when y is written),
+                                                           // the output splits lie over p (dead by then)
+};
+
+// Token splits of the value kernel: enough workgroups for the 256 CUs, but no more than leave a tile each.
+static int fold_splits(int nb, int nrb, int n_slabs_v, int max_len)
+{
+    const int per = nb * nrb * ((n_slabs_v + 1) / 2), nt = (max_len + FOLD_VTILE - 1) / FOLD_VTILE;
+    return std::max(1, std::min({nt, (256 + per - 1) / per, 16}));
+}
+
+static FoldPlan fold_plan(const FoldProblem& f, int nb, int max_len, int splits)
+{
+    FoldPlan L{};
+    const int R = f.T * f.Hq;
+    L.rt = R <= 16 ? 1 : 2;
+    const int rpb = 16 * L.rt;
+    L.nrb = (R + rpb - 1) / rpb;
+    L.tiles = (max_len + FOLD_VTILE - 1) / FOLD_VTILE * 2;
+    L.splits = splits;
+    L.u_slab = f.dense ? FOLD_U_DENSE(L.rt) : FOLD_U_CODED(L.rt);
+    const int colblocks = (nb * f.T * (f.Hq / f.Hkv) + 31) / 32;
+    L.chunk_slabs = std::max(1, std::min(FO_MAX_SLABS, f.n_slabs_v * f.Hkv * colblocks / 256));
+    L.chunks = (f.n_slabs_v + L.chunk_slabs - 1) / L.chunk_slabs;
+    L.p = align256(std::max((size_t)nb * L.nrb * L.tiles * 4 * (L.rt * 512) * 4, (size_t)L.chunks * nb * R * 512));
+    L.mtile = align256((size_t)nb * L.nrb * L.tiles * rpb * 4);
+    L.rowfac = align256((size_t)nb * L.nrb * rpb * 4);
+    L.lsum = align256((size_t)splits * nb * L.nrb * rpb * 4);
+    L.uy = align256(std::max((size_t)nb * L.nrb * f.n_slabs_k * L.u_slab, (size_t)splits * nb * R * f.n_slabs_v * 512));
+    L.yz = f.dense ? 0 : align256((size_t)splits * nb * R * f.ng_v * 4);
+    L.total = L.p + L.mtile + L.rowfac + L.lsum + L.uy + L.yz;
+    return L;
+}
+
+size_t fold_workspace_bytes(const FoldProblem& f, int B, int max_len)
+{
+    const int R = f.T * f.Hq, nrb = (R + (R <= 16 ? 15 : 31)) / (R <= 16 ? 16 : 32);
+    return fold_plan(f, B, max_len, fold_splits(B, nrb, f.n_slabs_v, max_len)).total;
+}
+
+// The largest launch group and split that fit the workspace, for B sequences; false if not even one sequence does.
+// `bytes` is cut to what the query asks for, so that results do not depend on how much more a caller brings.
+static bool fold_fit(const FoldProblem& f, int B, int max_len, size_t bytes, int* nb, FoldPlan* plan)
+{
+    const int R = f.T * f.Hq, nrb = (R + (R <= 16 ? 15 : 31)) / (R <= 16 ? 16 : 32);
+    bytes = std::min(bytes, std::max(f.query_bytes, fold_workspace_bytes(f, B, max_len)));
+    for (int groups = 1; groups <= B; ++groups) {
+        const int n = (B + groups - 1) / groups;
+        for (int sp = fold_splits(n, nrb, f.n_slabs_v, max_len); sp >= 1; --sp) {
+            const FoldPlan p = fold_plan(f, n, max_len, sp);
+            if (p.total <= bytes) { *nb = n; *plan = p; return true; }
+            if (groups < B && sp == 1) break;
+        }
+    }
+    return false;
+}
+
+bool fold_fits(const FoldProblem& f, int B, int max_len, size_t bytes)
+{
+    int nb;
+    FoldPlan p;
+    return fold_fit(f, B, max_len, bytes, &nb, &p);
+}
+
+template <int BITS, int G, int RT>
+static hipError_t run_scores(const FoldScoreArgs& a, bool nibbles, int grid, hipStream_t s)
+{
+    if constexpr (BITS == 4 && G == 128) {
+        if (nibbles) return launch(fold_scores_kernel<4, 128, RT, true>, grid, FOLD_SCORE_LDS<4, 128, RT, true>, a, s);
+    }
+    return launch(fold_scores_kernel<BITS, G, RT, false>, grid, FOLD_SCORE_LDS<BITS, G, RT, false>, a, s);
+}
+template <int BITS, int G, int RT>
+static hipError_t run_values(const FoldValueArgs& a, bool nibbles, int grid, hipStream_t s)
+{
+    if constexpr (BITS == 4 && G == 128) {
+        if (nibbles) return launch(fold_values_kernel<4, 128, RT, true>, grid, FoldValueLds<RT, 2, true>::TOTAL, a, s);
+    }
+    return launch(fold_values_kernel<BITS, G, RT, false>, grid, FoldValueLds<RT, 2 * (128 / G), false>::TOTAL, a, s);
+}
+template <int RT>
+static hipError_t scores_for(int bits, int G, bool nibbles, const FoldScoreArgs& a, int grid, hipStream_t s)
+{
+    switch (bits * 1000 + G) {
+        case 2064: return run_scores<2, 64, RT>(a, nibbles, grid, s);
+        case 2128: return run_scores<2, 128, RT>(a, nibbles, grid, s);
+        case 3064: return run_scores<3, 64, RT>(a, nibbles, grid, s);
+        case 3128: return run_scores<3, 128, RT>(a, nibbles, grid, s);
+        case 4064: return run_scores<4, 64, RT>(a, nibbles, grid, s);
+        case 4128: return run_scores<4, 128, RT>(a, nibbles, grid, s);
+    }
+    return launch(fold_scores_dense_kernel<RT>, grid, FOLD_SCORE_RED<RT>, a, s);
+}
+template <int RT>
+static hipError_t values_for(int bits, int G, bool nibbles, const FoldValueArgs& a, int grid, hipStream_t s)
+{
+    switch (bits * 1000 + G) {
+        case 2064: return run_values<2, 64, RT>(a, nibbles, grid, s);
+        case 2128: return run_values<2, 128, RT>(a, nibbles, grid, s);
+        case 3064: return run_values<3, 64, RT>(a, nibbles, grid, s);
+        case 3128: return run_values<3, 128, RT>(a, nibbles, grid, s);
+        case 4064: return run_values<4, 64, RT>(a, nibbles, grid, s);
+        case 4128: return run_values<4, 128, RT>(a, nibbles, grid, s);
+    }
+    return launch(fold_values_dense_kernel<RT>, grid, FoldValueDenseLds<RT>::TOTAL, a, s);
+}
+
+hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSource& kx, const FoldSource& vx, const FoldWeights& kw,
+                           const FoldWeights& vw, int B, const BatchI32& len, int max_len, float softmax_scale, float* out, void* ws,
+                           size_t ws_bytes, hipStream_t s)
+{
+    int nb;
+    FoldPlan L;
+    if (!fold_fit(f, B, max_len, ws_bytes, &nb, &L)) return hipErrorInvalidValue;
+    const int bits = f.dense ? 16 : f.bits;
+    UnpackTable tab{};
+    if (!f.dense && !unpack_table_for(bits, &tab)) return hipErrorInvalidValue;
+    uint8_t* w = static_cast<uint8_t*>(ws);
+    float* p = reinterpret_cast<float*>(w); w += L.p;
+    float* mtile = reinterpret_cast<float*>(w); w += L.mtile;
+    float* rowfac = reinterpret_cast<float*>(w); w += L.rowfac;
+    float* lsum = reinterpret_cast<float*>(w); w += L.lsum;
+    uint8_t* u = w;
+    float* y = reinterpret_cast<float*>(w); w += L.uy;
+    float* yz = reinterpret_cast<float*>(w);
+    float* part = p;
+    const int gq = f.Hq / f.Hkv;
+    for (int b0 = 0; b0 < B; b0 += nb) {
+        FoldShape sh{};
+        sh.b0 = b0; sh.nb = std::min(nb, B - b0); sh.T = f.T; sh.Hq = f.Hq; sh.Hkv = f.Hkv; sh.R = f.T * f.Hq; sh.nrb = L.nrb;
+        sh.tiles = L.tiles; sh.splits = L.splits; sh.len = len;
+        const int colblocks = (sh.nb * f.T * gq + 31) / 32;
+        {
+            FoldQueryArgs a{kw, sh, q, u, rowfac, softmax_scale * 1.44269504088896340736f, L.u_slab, f.n_slabs_k, L.rt, tab};
+            const dim3 grid((f.n_slabs_k + 1) / 2, f.Hkv, colblocks);
+            if (f.dense) fold_query_kernel<true, 128><<<grid, dim3(128), 0, s>>>(a);
+            else if (f.group == 64) fold_query_kernel<false, 64><<<grid, dim3(128), 0, s>>>(a);
+            else fold_query_kernel<false, 128><<<grid, dim3(128), 0, s>>>(a);
+        }
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        {
+            // Slab ways of a workgroup: eight, or four with two token tiles where that still leaves two rounds of workgroups
+            // (a wave's set-up and the meeting of the slab ways then weigh less).  Measured, 8 / 4 / 2 slab ways: 1024 tiles
+            // of 2 bits 122 / 114 / 113 us (group 128), 133 / 124 / 134 us (group 64); 256 tiles of 3 bits 38 / 51 / 84 us.
+            const int swl = sh.nb * sh.nrb * sh.tiles >= 4 * 256 ? 2 : 3, ways = 8 >> swl;
+            FoldScoreArgs a{kx, sh, u, rowfac, p, mtile, L.u_slab, swl};
+            const int grid = xcd_grid(sh.nb * sh.nrb * ((sh.tiles + ways - 1) / ways));
+            e = L.rt == 1 ? scores_for<1>(bits, f.group, f.nibbles, a, grid, s) : scores_for<2>(bits, f.group, f.nibbles, a, grid, s);
+            if (e != hipSuccess) return e;
+        }
+        {
+            FoldValueArgs a{vx, sh, p, mtile, y, yz, lsum, (f.n_slabs_v + 1) / 2};
+            const int grid = xcd_grid(sh.nb * sh.nrb * sh.splits * a.cblocks);
+            e = L.rt == 1 ? values_for<1>(bits, f.group, f.nibbles, a, grid, s) : values_for<2>(bits, f.group, f.nibbles, a, grid, s);
+            if (e != hipSuccess) return e;
+        }
+        {
+            FoldOutArgs a{vw, sh, y, yz, part, f.n_slabs_v, f.ng_v, f.group, L.chunk_slabs, L.rt, tab};
+            const dim3 grid(L.chunks, f.Hkv, colblocks);
+            if (f.dense) {
+                e = allow_lds(reinterpret_cast<const void*>(fold_output_kernel<true>), FO_LDS);
+                if (e != hipSuccess) return e;
+                fold_output_kernel<true><<<grid, dim3(512), FO_LDS, s>>>(a);
+            } else {
+                e = allow_lds(reinterpret_cast<const void*>(fold_output_kernel<false>), FO_LDS);
+                if (e != hipSuccess) return e;
+                fold_output_kernel<false><<<grid, dim3(512), FO_LDS, s>>>(a);
+            }
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        fold_finish_kernel<<<dim3((sh.nb * sh.R * 32 + 255) / 256), dim3(256), 0, s>>>(part, lsum, out, sh, L.chunks, L.rt);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace xq

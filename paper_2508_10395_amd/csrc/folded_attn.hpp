@@ -1,0 +1,23 @@
+// Host interface of the folded attention kernels (folded_attn.hip).
+#pragma once
+#include "folded_common.hpp"
+
+namespace xq {
+
+struct FoldProblem {
+    int T, Hq, Hkv;                      // query tokens per sequence, heads
+    int dense;                           // bf16 rows
+    int bits, group, nibbles;            // of the walk (8-bit caches: 4, 128, 1)
+    int n_slabs_k, n_slabs_v, ng_v;      // slabs of 128 walked channels on either side, groups of the values' side
+    size_t query_bytes;                  // what the entry point's workspace query says for this call
+};
+
+bool unpack_table_for(int bits, UnpackTable* t);
+
+size_t fold_workspace_bytes(const FoldProblem& f, int B, int max_len);
+bool fold_fits(const FoldProblem& f, int B, int max_len, size_t bytes);
+hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSource& kx, const FoldSource& vx, const FoldWeights& kw,
+                           const FoldWeights& vw, int B, const BatchI32& len, int max_len, float softmax_scale, float* out, void* ws,
+                           size_t ws_bytes, hipStream_t s);
+
+}  // namespace xq

@@ -1,8 +1,11 @@
 // Host side of the rematerialisation kernels: workspace sizes, kernel parameters, launches.  Included at the
 // end of remat_attn.hip (the kernels are templates of that translation unit).
 #pragma once
+#include <algorithm>
 #include <mutex>
 #include <vector>
+
+#include "folded_attn.hpp"
 
 namespace xq {
 
@@ -110,11 +113,64 @@ hipError_t launch_tile16_per_channel(int bits, const RematParams& p, int grid, h
 // per-query-head vector epilogue runs that many times per tile; measured break-even is about 4)
 constexpr int DECODE_MFMA_EPILOGUE_MIN_GROUP = 4;
 
+// ---- the folded kernels' view of a decode call: d, group of the walk, group 0 for the accumulator source
+static FoldProblem fold_problem(const xq_attn_t* a, int T, int d, int group, int bits, int nibbles, size_t query_bytes)
+{
+    FoldProblem f{};
+    f.T = T; f.Hq = a->n_q_heads; f.Hkv = a->n_kv_heads;
+    f.dense = group == 0; f.bits = bits; f.group = group ? group : 128; f.nibbles = nibbles;
+    f.n_slabs_k = f.n_slabs_v = d / 128;
+    f.ng_v = group ? d / group : 0;
+    f.query_bytes = query_bytes;
+    return f;
+}
+
+// Where the folded order pays.  It does 128 / (query heads per KV head) times fewer operations, but in five dependent
+// launches instead of three, so a step that the remat kernels finish in about one wave of workgroups over a narrow layer
+// stays with them: their time goes with waves x (d + 512).  Measured (us, remat / folded), one wave: d = 256 25 / 34,
+// d = 512 26 / 36, d = 1024 34 / 38, d = 2048 54 / 44, d = 4096 94 / 65; two waves of d = 512 36 / 54, four 52 / 45; two
+// waves of d = 256 28 / 44, eight 79 / 59.
+static bool folding_pays(const xq_attn_t* a, int B, int max_len, int d)
+{
+    const long long tiles = (max_len + TILE_TOKENS - 1) / TILE_TOKENS, waves = (tiles * a->n_kv_heads * B + 255) / 256;
+    return waves * (d + 512) >= 2560;
+}
+
+// What a decode call asks for: the remat kernels' partials, or the folded kernels' buffers where they need more (short
+// contexts on wide layers).  A call with less than the latter still runs, on the remat kernels.
+size_t remat_decode_query_bytes(const xq_attn_t* a, int B, int max_len, int d, int group)
+{
+    const size_t remat = remat_workspace_bytes(B, a->n_q_heads, max_len, d, group ? group : 128, group != 0);
+    return !folding_pays(a, B, max_len, d) ? remat : std::max(remat, fold_workspace_bytes(fold_problem(a, 1, d, group, 4, 0, 0), B, max_len));
+}
+
 hipError_t run_remat_attn_decode(const xq_attn_t* a, const uint16_t* q, const xq_cache_t* xc,
                                  const uint16_t* acc, int B, int cap, int d, const void* wprep,
-                                 const BatchI32& len, int max_len, float* out, void* ws,
+                                 const BatchI32& len, int max_len, float* out, void* ws, size_t ws_bytes,
                                  const float* rope, const BatchI32* pos0, hipStream_t s)
 {
+    if (!rope) {
+        const int cb = xc ? xc->fmt.bits : 16, nib = cb == 8;
+        const WPrepLayout L = make_wprep_layout_for_cache(d, xc ? xc->fmt.group : 128, cb, a->n_kv_heads);
+        const FoldProblem f = fold_problem(a, 1, L.d, xc ? L.G : 0, nib ? 4 : cb, nib,
+                                           remat_decode_query_bytes(a, B, max_len, L.d, xc ? L.G : 0));
+        if (folding_pays(a, B, max_len, L.d) && fold_fits(f, B, max_len, ws_bytes)) {
+            FoldSource x{};
+            FoldWeights w{};
+            if (xc) {
+                x.codes = xc->codes; x.scale = xc->scale; x.zero = xc->zero;
+                x.ng_row = d / xc->fmt.group;
+                x.meta_shift = (nib && xc->fmt.group == 128) ? 1 : 0;
+                w.shift = stream_shifts(wprep, L);
+            }
+            x.rows = acc;
+            x.row_bytes = xc ? (long long)d * cb / 8 : (long long)d * 2;
+            x.cap = cap; x.n_slabs = L.n_main_slabs; x.ng = L.ng;
+            w.stream = static_cast<const uint8_t*>(wprep);
+            w.head_bytes = (long long)L.head_bytes; w.n16 = L.d / 16; w.group = L.G; w.nibbles = nib;
+            return run_folded_attn(f, q, x, x, w, w, B, len, max_len, a->softmax_scale, out, ws, ws_bytes, s);
+        }
+    }
     if (a->n_q_heads / a->n_kv_heads >= DECODE_MFMA_EPILOGUE_MIN_GROUP)     // same layouts and workspace at T = 1
         return run_remat_attn_prefill(a, q, 1, xc, acc, B, cap, d, wprep, len, max_len, out, ws, rope, pos0, s);
     const int cache_bits = xc ? xc->fmt.bits : 16;

@@ -1,0 +1,90 @@
+"""GPU parity of the folded decode kernels (the query times Wk, then scores and weighted sums over the codes) against the
+CPU oracle, at the sizes where their tiles and splits end: 128-token score tiles, 256-token value tiles, pairs of 128-channel
+slabs, 16- and 32-row query blocks, launch groups of a small workspace."""
+import numpy as np
+import pytest
+import torch
+
+import xq_inputs as xi
+from oracle import xq_oracle as xo
+from tests.util import bits_to_torch, oracle_cache, rel_errors
+
+pytestmark = pytest.mark.gpu
+
+# The folded operands keep 22 bits and the sums are fp32, so a score of magnitude <= 2^4 is off by at most 2^4 (2^-21 plus a
+# random walk of 2^-24 over 2^12 terms) < 2^-15 in log2 units: weights and outputs within 2^-15; 4 times that here.
+TOL = 2.0 ** -13
+
+
+@pytest.fixture(scope="module")
+def xq():
+    import paper_2508_10395_amd as m
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    m.load_library()
+    return m
+
+
+def _run(xq, w, bits, G, lens, x_bits=None, workspaces=(None,), pairs=None):
+    x = xi.gen_x(w) if x_bits is None else x_bits
+    wk, wv = xi.gen_weights(w)
+    q = xi.gen_q(w)
+    attn = xq.XQAttn(w.Hq, w.Hkv, w.hd, w.hd ** -0.5)
+    pairs = pairs or [(b, h) for b in range(w.B) for h in sorted({0, 1, w.Hq // 2, w.Hq - 1})]
+    kw = dict(q_bf16=q, Wk=wk, Wv=wv, Hq=w.Hq, Hkv=w.Hkv, hd=w.hd, softmax_scale=w.hd ** -0.5, lens=lens, pairs=pairs)
+    if bits == 16:
+        src = dict(acc_bf16=bits_to_torch(x))
+        ref = xo.remat_attn_pairs(acc_bf16=x, **kw)
+    else:
+        cache = xq.alloc_cache(w.B, w.L + 3, w.d, G, bits)
+        cache.codes.fill_(0xFF)                              # rows past the data must not be read
+        cache.scale.view(torch.int16).fill_(0x7FC0)
+        cache.zero.view(torch.int16).fill_(0x7FC0)
+        xq.xq_quantize_append(cache, bits_to_torch(x), [0] * w.B)
+        src = dict(xcache=cache)
+        packed, scale, zero = oracle_cache(x, G, bits, seqs=[b for b, _ in pairs])
+        ref = xo.remat_attn_pairs(packed=packed, scale=scale, zero=zero, G=G, bits=bits, **kw)
+    wprep = xq.xq_prepare_weights(attn, w.d, G, bits, bits_to_torch(wk), bits_to_torch(wv))
+    for n in workspaces:
+        ws = None if n is None else torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")
+        out = xq.xq_remat_attn_decode(attn, bits_to_torch(q), wprep, lens, workspace=ws, **src).cpu().numpy()
+        assert np.all(np.isfinite(out))
+        rows, worst = rel_errors(np.array([out[b, h] for b, h in pairs]), ref)
+        assert rows.max() <= TOL and worst <= TOL, (n, float(rows.max()), float(worst))
+
+
+@pytest.mark.parametrize("bits,G", [(2, 64), (2, 128), (3, 64), (3, 128), (4, 64), (4, 128), (8, 64), (8, 128), (16, 128)])
+@pytest.mark.parametrize("Hq,Hkv,d,lens", [(16, 16, 2048, [300, 1, 129]), (32, 8, 2176, [257, 33]), (40, 40, 2048, [511])])
+def test_formats_rows_and_tile_edges(xq, bits, G, Hq, Hkv, d, lens):
+    w = xi.C2.scaled(B=len(lens), L=max(lens), d=d, Hq=Hq, Hkv=Hkv, n_outlier=d // 100)
+    _run(xq, w, bits, G, lens)
+
+
+@pytest.mark.parametrize("bits,G", [(2, 64), (3, 128), (16, 128)])
+def test_token_ways_of_a_score_workgroup(xq, bits, G):
+    """Enough tiles that a score workgroup takes two of them, on a narrow layer, with a dead second tile."""
+    w = xi.C2.scaled(B=16, L=4000, d=256, Hq=64, Hkv=4, n_outlier=2)
+    lens = [4000, 3969, 129, 128, 1, 2049] + [100] * 10
+    _run(xq, w, bits, G, lens, pairs=[(0, 0), (0, 63), (1, 17), (2, 5), (3, 40), (4, 33), (5, 62), (15, 8)])
+
+
+@pytest.mark.parametrize("bits", [3, 16])
+def test_smaller_workspaces(xq, bits):
+    """Between the smallest workspace that is accepted and the one that is asked for, the launch goes in groups of sequences,
+    or through the kernels that rematerialise keys and values."""
+    B, L, d, Hq = 3, 130, 2048, 32
+    w = xi.C2.scaled(B=B, L=L, d=d, Hq=Hq, Hkv=8, n_outlier=20)
+    asked = xq.xq_remat_attn_workspace_bytes(xq.XQAttn(Hq, 8, 128, 1.0), B, L, d, 128 if bits < 16 else 0)
+    least = B * Hq * 2 * 4 * 130 * 4 + (B * 2 * (d // 128 + 1) * 128 * 2 if bits < 16 else 0)
+    assert least < asked
+    _run(xq, w, bits, 128, [130, 128, 7], workspaces=(asked, asked // 2 + 16, asked // 3 + 16, least))
+
+
+def test_scales_of_every_magnitude(xq):
+    """Constant groups (scale 0) and groups 1000 times larger than their neighbours, large offsets."""
+    w = xi.C2.scaled(B=1, L=300, d=2048, Hq=16, Hkv=16, n_outlier=0)
+    x = xi.from_bf16_bits(xi.gen_x(w)).copy()
+    x[0, :, 128:256] = 0.5
+    x[0, ::2, 256:384] *= 30.0
+    x[0, 1::3, 512:640] += 100.0
+    x[0, :, 640:768] *= 1e-3
+    _run(xq, w, 3, 128, [300], x_bits=xi.to_bf16_bits(x))
