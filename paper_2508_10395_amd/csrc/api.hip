@@ -27,7 +27,8 @@ hipError_t run_remat_attn_decode(const xq_attn_t* a, const uint16_t* q, const xq
 size_t remat_decode_query_bytes(const xq_attn_t* a, int B, int max_len, int d, int group);
 hipError_t run_remat_attn_decode_latent(const xq_attn_t* a, const uint16_t* q, const xq_cache_t* xc,
                                         const void* wprep, const BatchI32& len, int max_len, float* out, void* ws,
-                                        hipStream_t s);
+                                        size_t ws_bytes, hipStream_t s);
+size_t remat_latent_query_bytes(const xq_attn_t* a, int B, int max_len, int r, int group);
 size_t remat_latent_workspace_bytes(int B, int Hq, int max_len, int r, int group);
 hipError_t run_latent_delta_project(const uint16_t* x, const uint16_t* acc, const uint16_t* ut, int B, int T, int cap,
                                     const BatchI32& start, int d, int n_lat, uint16_t* out, hipStream_t s);
@@ -334,7 +335,7 @@ size_t xq_remat_attn_latent_workspace_bytes(const xq_attn_t* a, int32_t B, int32
 {
     if (check_attn(a) != XQ_OK || B < 1 || max_len < 1 || r <= 0 || r % 128 != 0) return 0;
     if (group != 64 && group != 128) return 0;
-    return remat_latent_workspace_bytes(B, a->n_q_heads, max_len, r, group);
+    return remat_latent_query_bytes(a, B, max_len, r, group);
 }
 
 xq_status_t xq_remat_attn_decode_latent(const xq_attn_t* a, const uint16_t* q_bf16, const xq_cache_t* latent,
@@ -356,9 +357,9 @@ xq_status_t xq_remat_attn_decode_latent(const xq_attn_t* a, const uint16_t* q_bf
         lv.v[b] = len[b];
         if (len[b] > max_len) max_len = len[b];
     }
-    if (workspace_bytes < xq_remat_attn_latent_workspace_bytes(a, latent->B, max_len, latent->fmt.d / 2, latent->fmt.group))
+    if (workspace_bytes < remat_latent_workspace_bytes(latent->B, a->n_q_heads, max_len, latent->fmt.d / 2, latent->fmt.group))
         return XQ_ERR_WORKSPACE;
-    hipError_t e = run_remat_attn_decode_latent(a, q_bf16, latent, wprep, lv, max_len, out, workspace,
+    hipError_t e = run_remat_attn_decode_latent(a, q_bf16, latent, wprep, lv, max_len, out, workspace, workspace_bytes,
                                                 static_cast<hipStream_t>(stream));
     return e == hipSuccess ? XQ_OK : XQ_ERR_HIP;
 }

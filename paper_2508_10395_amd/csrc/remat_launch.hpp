@@ -136,6 +136,14 @@ static bool folding_pays(const xq_attn_t* a, int B, int max_len, int d)
     return waves * (d + 512) >= 2560;
 }
 
+// The same for a latent cache, whose two rematerialising passes are five launches too.  Measured (us with projection and
+// append, remat / folded), one wave: r = 256 46 / 41 to 51 / 59, r = 512 57 / 44, r = 1024 81 / 57.
+static bool latent_folding_pays(const xq_attn_t* a, int B, int max_len, int r)
+{
+    const long long tiles = (max_len + TILE_TOKENS - 1) / TILE_TOKENS, waves = (tiles * (a->n_kv_heads / 2) * B + 255) / 256;
+    return waves * (r + 128) >= 512;
+}
+
 // What a decode call asks for: the remat kernels' partials, or the folded kernels' buffers where they need more (short
 // contexts on wide layers).  A call with less than the latter still runs, on the remat kernels.
 size_t remat_decode_query_bytes(const xq_attn_t* a, int B, int max_len, int d, int group)
@@ -149,12 +157,12 @@ hipError_t run_remat_attn_decode(const xq_attn_t* a, const uint16_t* q, const xq
                                  const BatchI32& len, int max_len, float* out, void* ws, size_t ws_bytes,
                                  const float* rope, const BatchI32* pos0, hipStream_t s)
 {
-    if (!rope) {
+    if (!rope && folding_pays(a, B, max_len, xc && xc->fmt.bits == 8 ? 2 * d : d)) {
         const int cb = xc ? xc->fmt.bits : 16, nib = cb == 8;
         const WPrepLayout L = make_wprep_layout_for_cache(d, xc ? xc->fmt.group : 128, cb, a->n_kv_heads);
         const FoldProblem f = fold_problem(a, 1, L.d, xc ? L.G : 0, nib ? 4 : cb, nib,
                                            remat_decode_query_bytes(a, B, max_len, L.d, xc ? L.G : 0));
-        if (folding_pays(a, B, max_len, L.d) && fold_fits(f, B, max_len, ws_bytes)) {
+        if (fold_fits(f, B, max_len, ws_bytes)) {
             FoldSource x{};
             FoldWeights w{};
             if (xc) {
@@ -302,17 +310,47 @@ hipError_t run_remat_attn_prefill(const xq_attn_t* a, const uint16_t* q, int T, 
     return hipGetLastError();
 }
 
-// Latent cache [X Uk | X Uv] of rank r (Sec. 3.3.1): two passes of the same contraction kernel over
+static FoldProblem fold_problem_latent(const xq_attn_t* a, int r, int group, int bits, size_t query_bytes)
+{
+    return fold_problem(a, 1, r, group, bits, 0, query_bytes);
+}
+
+// as remat_decode_query_bytes
+size_t remat_latent_query_bytes(const xq_attn_t* a, int B, int max_len, int r, int group)
+{
+    const size_t remat = remat_latent_workspace_bytes(B, a->n_q_heads, max_len, r, group);
+    return !latent_folding_pays(a, B, max_len, r) ? remat : std::max(remat, fold_workspace_bytes(fold_problem_latent(a, r, group, 4, 0), B, max_len));
+}
+
+// Latent cache [X Uk | X Uv] of rank r (Sec. 3.3.1).  In the folded order the two halves of a row are the sources of the
+// scores and of the weighted sums.  On small steps: two passes of the same contraction kernel over
 // the two halves of the cache rows, each with all 256 columns in use -- pass 1 rematerialises the
 // keys of a pair of KV heads from the first r channels and stores the scaled scores, pass 2 the
 // values of the pair from the last r channels and turns scores into softmax partials.
 hipError_t run_remat_attn_decode_latent(const xq_attn_t* a, const uint16_t* q, const xq_cache_t* xc,
                                         const void* wprep, const BatchI32& len, int max_len, float* out, void* ws,
-                                        hipStream_t s)
+                                        size_t ws_bytes, hipStream_t s)
 {
     const int bits = xc->fmt.bits, G = xc->fmt.group, r = xc->fmt.d / 2, B = xc->B, cap = xc->cap;
     const int pairs = a->n_kv_heads / 2;
     const WPrepLayout L = make_wprep_layout_for_cache(r, G, bits, pairs);          // one stream per half, "head" = pair
+    const FoldProblem f = fold_problem_latent(a, r, G, bits, remat_latent_query_bytes(a, B, max_len, r, G));
+    if (latent_folding_pays(a, B, max_len, r) && fold_fits(f, B, max_len, ws_bytes)) {
+        FoldSource kx{}, vx{};
+        kx.codes = xc->codes; kx.scale = xc->scale; kx.zero = xc->zero;
+        kx.row_bytes = (long long)2 * r * bits / 8;
+        kx.cap = cap; kx.n_slabs = L.n_main_slabs; kx.ng = L.ng; kx.ng_row = 2 * L.ng;
+        vx = kx;
+        vx.codes += (size_t)r * bits / 8; vx.scale += L.ng; vx.zero += L.ng;
+        FoldWeights kw{}, vw{};
+        kw.stream = static_cast<const uint8_t*>(wprep);
+        kw.shift = stream_shifts(wprep, L);
+        kw.head_bytes = (long long)L.head_bytes; kw.n16 = L.d / 16; kw.group = G; kw.pair = 1;
+        vw = kw;
+        vw.stream += L.total_bytes;
+        vw.shift = stream_shifts(vw.stream, L);
+        return run_folded_attn(f, q, kx, vx, kw, vw, B, len, max_len, a->softmax_scale, out, ws, ws_bytes, s);
+    }
     // pass 2 runs on the 16-column fragments where the format has them (that epilogue takes 16 query rows per KV head,
     // which is the most an attention descriptor may ask for)
     const bool t16 = L.t16_bytes != 0 && a->n_q_heads / a->n_kv_heads <= 16;

@@ -88,3 +88,31 @@ def test_scales_of_every_magnitude(xq):
     x[0, 1::3, 512:640] += 100.0
     x[0, :, 640:768] *= 1e-3
     _run(xq, w, 3, 128, [300], x_bits=xi.to_bf16_bits(x))
+
+
+@pytest.mark.parametrize("bits,G", [(2, 64), (3, 128), (4, 64)])
+@pytest.mark.parametrize("small", [False, True])
+def test_latent_halves(xq, bits, G, small):
+    """Scores from the first r channels of a row, weighted sums from the last r, weights in streams of head pairs; also with
+    the smallest workspace that is accepted."""
+    r, B, L, lens = 640, 3, 290, [290, 1, 129]
+    w = xi.C4.scaled(B=B, L=L, d=2 * r, Hq=12, Hkv=4, n_outlier=12)
+    x, q = xi.gen_x(w), xi.gen_q(w)
+    wk, wv = xi.gen_weights(w)
+    wfk, wfv = np.ascontiguousarray(wk[:r]), np.ascontiguousarray(wv[r:])
+    attn = xq.XQAttn(w.Hq, w.Hkv, w.hd, w.hd ** -0.5)
+    cache = xq.alloc_cache(B, L, 2 * r, G, bits)
+    xq.xq_quantize_append(cache, bits_to_torch(x), [0] * B)
+    wprep = xq.xq_prepare_weights_latent(attn, r, G, bits, bits_to_torch(wfk), bits_to_torch(wfv))
+    tiles = 2                                               # of 256 tokens; 8 partials, a score and two scales per token each
+    least = 4 * B * w.Hq * tiles * (8 * 130 + 256) + 4 * B * tiles * (r // G + 1) * 256
+    assert least <= xq.xq_remat_attn_latent_workspace_bytes(attn, B, L, r, G)
+    ws = torch.full((least,), 0xFF, dtype=torch.uint8, device="cuda") if small else None
+    out = xq.xq_remat_attn_decode_latent(attn, bits_to_torch(q), wprep, lens, cache, workspace=ws).cpu().numpy()
+    packed, scale, zero = oracle_cache(x, G, bits)
+    wk0, wv0 = wk.copy(), wv.copy()
+    wk0[r:], wv0[:r] = 0, 0
+    ref = xo.remat_attn_pairs(q_bf16=q, Wk=wk0, Wv=wv0, Hq=w.Hq, Hkv=w.Hkv, hd=w.hd, softmax_scale=w.hd ** -0.5, lens=lens,
+                              pairs=[(b, h) for b in range(B) for h in range(w.Hq)], packed=packed, scale=scale, zero=zero, G=G, bits=bits)
+    rows, worst = rel_errors(out.reshape(-1, w.hd), ref)
+    assert np.all(np.isfinite(out)) and rows.max() <= TOL and worst <= TOL, (float(rows.max()), float(worst))
