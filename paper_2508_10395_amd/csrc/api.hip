@@ -29,6 +29,7 @@ hipError_t run_remat_attn_decode_latent(const xq_attn_t* a, const uint16_t* q, c
                                         const void* wprep, const BatchI32& len, int max_len, float* out, void* ws,
                                         size_t ws_bytes, hipStream_t s);
 size_t remat_latent_query_bytes(const xq_attn_t* a, int B, int max_len, int r, int group);
+size_t remat_pc_query_bytes(const xq_attn_t* a, int B, int max_len, int d, int block);
 size_t remat_latent_workspace_bytes(int B, int Hq, int max_len, int r, int group);
 hipError_t run_latent_delta_project(const uint16_t* x, const uint16_t* acc, const uint16_t* ut, int B, int T, int cap,
                                     const BatchI32& start, int d, int n_lat, uint16_t* out, hipStream_t s);
@@ -37,7 +38,7 @@ hipError_t run_quantize_blocks_per_channel(const xq_cache_t* c, const uint16_t* 
 size_t remat_pc_workspace_bytes(int B, int Hq, int Hkv, int max_len, int d, int block);
 hipError_t run_remat_attn_decode_pc(const xq_attn_t* a, const uint16_t* q, const xq_cache_t* xc, const uint16_t* tail,
                                     const void* wprep_coded, const void* wprep_dense, const BatchI32& len, int max_len,
-                                    void* terms, bool terms_valid, float* out, void* ws, hipStream_t s);
+                                    void* terms, bool terms_valid, float* out, void* ws, size_t ws_bytes, hipStream_t s);
 size_t pc_terms_bytes(int B, int cap, int d, int block, int col_blocks);
 size_t remat_latent_pc_workspace_bytes(int B, int Hq, int Hkv, int max_len, int r, int block, int v_group);
 hipError_t run_remat_attn_decode_latent_pc(const xq_attn_t* a, const uint16_t* q, const xq_cache_t* kc,
@@ -412,7 +413,7 @@ size_t xq_remat_attn_per_channel_workspace_bytes(const xq_attn_t* a, int32_t B, 
 {
     if (check_attn(a) != XQ_OK || B < 1 || max_len < 1 || d <= 0 || d % 128 != 0) return 0;
     if (group != 64 && group != 128) return 0;
-    return remat_pc_workspace_bytes(B, a->n_q_heads, a->n_kv_heads, max_len, d, group);
+    return remat_pc_query_bytes(a, B, max_len, d, group);
 }
 
 size_t xq_per_channel_terms_bytes(int32_t B, int32_t cap, int32_t d, int32_t group, int32_t col_blocks)
@@ -445,14 +446,14 @@ xq_status_t xq_remat_attn_decode_per_channel(const xq_attn_t* a, const uint16_t*
         lv.v[b] = len[b];
         if (len[b] > max_len) max_len = len[b];
     }
-    if (workspace_bytes < xq_remat_attn_per_channel_workspace_bytes(a, cache->B, max_len, cache->fmt.d, cache->fmt.group))
+    if (workspace_bytes < remat_pc_workspace_bytes(cache->B, a->n_q_heads, a->n_kv_heads, max_len, cache->fmt.d, cache->fmt.group))
         return XQ_ERR_WORKSPACE;
     if (terms) {
         if (!aligned16(terms)) return XQ_ERR_INVALID_ARG;
         if (terms_bytes < pc_terms_bytes(cache->B, cache->cap, cache->fmt.d, cache->fmt.group, a->n_kv_heads)) return XQ_ERR_WORKSPACE;
     }
     hipError_t e = run_remat_attn_decode_pc(a, q_bf16, cache, tail_bf16, wprep_coded, wprep_dense, lv, max_len, terms,
-                                            terms_valid != 0, out, workspace, static_cast<hipStream_t>(stream));
+                                            terms_valid != 0, out, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? XQ_OK : XQ_ERR_HIP;
 }
 

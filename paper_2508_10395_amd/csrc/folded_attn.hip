@@ -21,9 +21,30 @@ namespace xq {
 struct FoldShape {
     int b0, nb, T, Hq, Hkv, R, nrb;      // query rows R = T Hq per sequence, nrb row blocks of 16 RT rows
     int tiles;                           // score tiles (128 tokens) per sequence in the arrays, even
-    int splits;                          // token splits of the value kernel
+    int splits;                          // token splits in the arrays of the value kernel
+    int gtiles, gsplits, split0;         // tiles and splits of this launch, index of the first split
+    int block, part;                     // per-channel caches: tokens per block; launch over the coded tokens (1) or the window (2)
     BatchI32 len;                        // of the call's sequences
 };
+
+// The tokens of a launch and where their tiles lie.  A per-channel cache's complete blocks come first, its window has the
+// tiles behind them (from an even one on) and the last split.
+struct FoldSpan { int len, tile0; };
+__device__ __forceinline__ FoldSpan fold_span(const FoldShape& s, int b)
+{
+    const int len = s.len.v[s.b0 + b];
+    if (s.block == 0) return {len, 0};
+    const int coded = len / s.block * s.block;
+    return s.part == 2 ? FoldSpan{len - coded, (coded + FOLD_VTILE - 1) / FOLD_VTILE * 2} : FoldSpan{coded, 0};
+}
+// splits of a sequence that hold tokens: the first `used` ones, and the last one if `window`
+__device__ __forceinline__ void fold_used_splits(const FoldShape& s, int b, int& used, bool& window)
+{
+    const int len = s.len.v[s.b0 + b], coded = s.block ? len / s.block * s.block : len, splits = s.block ? s.splits - 1 : s.splits;
+    const int nt = (coded + FOLD_VTILE - 1) / FOLD_VTILE, per = max(1, (nt + splits - 1) / splits);
+    used = (nt + per - 1) / per;
+    window = len > coded;
+}
 
 // element positions inside a fragment block of the softmax weights: [tile32][rt][part 2][lane 64][4 fp32], token
 // 4 i + q of the 32 is slot i of quarter q (rows of four adjacent tokens are read by one load of the value kernel)
@@ -48,6 +69,7 @@ struct FoldQueryArgs {
     float scale_log2e;
     int u_slab, n_slabs, rt;
     UnpackTable tab;                     // coded streams: channel of every slot of the stream
+    uint8_t* u_dense;                    // per-channel caches: the same u for the window's bf16 rows, or null
 };
 
 // channel inside its slab of slot (half, i) of k-step ks of the slab, in the first prepared stream
@@ -189,6 +211,30 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
 
     // out: 16-byte pieces (column, tick, quarter); a fragment is read lane by lane, lane = 16 quarter + row
     const int rpb = 16 * a.rt;
+    if (!DENSE && a.u_dense) {                                       // (a code's unit is part of the row factor)
+#pragma unroll 1
+        for (int it = 0; it < 8; ++it) {
+            const int idx = it * 64 + lane, qd = idx & 3, tick = (idx >> 2) & 3, col = idx >> 4;
+            if (cb * 32 + col >= ncol) continue;
+            int b;
+            const int row = row_of(cb * 32 + col, b), rb = row / rpb, rr = row - rb * rpb;
+            uint8_t* dst = a.u_dense + (((long long)b * s.nrb + rb) * a.n_slabs + slab) * FOLD_U_DENSE(a.rt) + ((rr >> 4) * 4 + tick) * 3 * 1024 +
+                           (qd * 16 + (rr & 15)) * 16;
+            const float* src = mine + col * FQ_STRIDE + 32 * tick + 8 * qd;
+            uint32_t p[3][4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                uint32_t h0, m0, l0, h1, m1, l1_;
+                split_bf16x3(src[2 * i] * (1.0f / FOLD_CODE_UNIT), h0, m0, l0);
+                split_bf16x3(src[2 * i + 1] * (1.0f / FOLD_CODE_UNIT), h1, m1, l1_);
+                p[0][i] = pack_hi16(h0, h1); p[1][i] = pack_hi16(m0, m1); p[2][i] = pack_hi16(l0, l1_);
+            }
+#pragma unroll
+            for (int k = 0; k < 3; ++k) *reinterpret_cast<uint4*>(dst + k * 1024) = make_uint4(p[k][0], p[k][1], p[k][2], p[k][3]);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // (read before the coded pieces write their sums back)
+        __builtin_amdgcn_wave_barrier();
+    }
 #pragma unroll 1
     for (int it = 0; it < 8; ++it) {
         const int idx = it * 64 + lane, qd = idx & 3, tick = (idx >> 2) & 3, col = idx >> 4;
@@ -288,15 +334,17 @@ struct FoldScoreArgs {
 };
 
 // which tokens and slabs a wave of a score workgroup has: 8 / SW token ways of one tile each, SW = 1 << sw_log2 slab ways
-struct FoldScorePlace { int b, rb, tile, len, sw, SW, tw, slab0, slab1, nw; };   // nw = slab ways that hold any slab
+struct FoldScorePlace { int b, rb, tile, tile0, len, sw, SW, tw, slab0, slab1, nw; };   // nw = slab ways that hold any slab
 __device__ __forceinline__ bool fold_score_place(const FoldShape& s, int sw_log2, int n_slabs, int wave, FoldScorePlace& o)
 {
-    const int ways = 8 >> sw_log2, tiles = (s.tiles + ways - 1) / ways, n = s.nb * s.nrb * tiles;
+    const int ways = 8 >> sw_log2, tiles = (s.gtiles + ways - 1) / ways, n = s.nb * s.nrb * tiles;
     const int item = xcd_contiguous(n);
     if (item >= n) return false;
     o.rb = (item / tiles) % s.nrb;
     o.b = item / (tiles * s.nrb);
-    o.len = s.len.v[s.b0 + o.b];
+    const FoldSpan span = fold_span(s, o.b);
+    o.len = span.len;
+    o.tile0 = span.tile0;
     o.SW = 1 << sw_log2;
     o.sw = wave & (o.SW - 1);
     o.tw = wave >> sw_log2;
@@ -369,11 +417,11 @@ __device__ __forceinline__ void fold_scores_finish(const FoldShape& s, const flo
 #pragma unroll
             for (int k = 1; k < 8; ++k) M = fmaxf(M, mx[k * 16 * RT + row]);
             Mu[rt][r] = M == -INFINITY ? 0.0f : M;                  // nothing visible: all weights 0
-            if (o.sw == 0 && c16 == 0) mtile_all[(((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile) * 16 * RT + row] = M;
+            if (o.sw == 0 && c16 == 0) mtile_all[(((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0 + o.tile) * 16 * RT + row] = M;
         }
     for (int j = 0; j < share; ++j) {
         const int i16 = o.sw * share + j, t32 = (i16 & 1) * 16 + c16, slot = t32 >> 2, qd = t32 & 3;
-        float* pt = p_all + ((((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile) * 4 + (i16 >> 1)) * FOLD_P_TILE32<RT>;
+        float* pt = p_all + ((((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0 + o.tile) * 4 + (i16 >> 1)) * FOLD_P_TILE32<RT>;
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             const float4 t = part[((o.tw * o.SW * RT + rt) * 8 + i16) * 64 + lane];
@@ -727,34 +775,40 @@ struct FoldValueLds {
 };
 
 // tile and range of a value workgroup
-struct FoldValuePlace { int b, rb, cblk, split, len, t0, t1; };      // [t0, t1): 256-token tiles
+struct FoldValuePlace { int b, rb, cblk, split, len, tile0, t0, t1; };      // [t0, t1): 256-token tiles
 __device__ __forceinline__ bool fold_value_place(const FoldShape& s, int cblocks, FoldValuePlace& o)
 {
-    const int n = s.nb * s.nrb * s.splits * cblocks;
+    const int n = s.nb * s.nrb * s.gsplits * cblocks;
     const int item = xcd_contiguous(n);
     if (item >= n) return false;
     o.cblk = item % cblocks;                                        // (neighbours share the softmax weights)
-    o.split = (item / cblocks) % s.splits;
-    o.rb = (item / (cblocks * s.splits)) % s.nrb;
-    o.b = item / (cblocks * s.splits * s.nrb);
-    o.len = s.len.v[s.b0 + o.b];
-    const int nt = (o.len + FOLD_VTILE - 1) / FOLD_VTILE, per = (nt + s.splits - 1) / s.splits;
-    o.t0 = o.split * per;
+    const int k = (item / cblocks) % s.gsplits;
+    o.split = s.split0 + k;
+    o.rb = (item / (cblocks * s.gsplits)) % s.nrb;
+    o.b = item / (cblocks * s.gsplits * s.nrb);
+    const FoldSpan span = fold_span(s, o.b);
+    o.len = span.len;
+    o.tile0 = span.tile0;
+    const int nt = (o.len + FOLD_VTILE - 1) / FOLD_VTILE, per = (nt + s.gsplits - 1) / s.gsplits;
+    o.t0 = k * per;
     o.t1 = min(nt, o.t0 + per);
     return o.t0 < o.t1;
 }
 
 // maximum of every row over the sequence's score tiles -> mrow[16 RT] (a workgroup barrier ends it)
 template <int RT>
-__device__ __forceinline__ void fold_row_maxima(const FoldShape& s, const float* mtile, int b, int rb, int len, float* scratch, float* mrow)
+__device__ __forceinline__ void fold_row_maxima(const FoldShape& s, const float* mtile, int b, int rb, float* scratch, float* mrow)
 {
     constexpr int ROWS = 16 * RT, PARTS = 512 / ROWS > 16 ? 16 : 512 / ROWS;
     const int tid = threadIdx.x, row = tid % ROWS, pt = tid / ROWS;
-    const int nt = (len + FOLD_TILE - 1) / FOLD_TILE;
+    const int len = s.len.v[s.b0 + b], coded = s.block ? len / s.block * s.block : len;
+    const int window0 = (coded + FOLD_VTILE - 1) / FOLD_VTILE * 2;  // tiles of the window, if it holds anything
+    const int n_coded = (coded + FOLD_TILE - 1) / FOLD_TILE, nt = len > coded ? window0 + (len - coded + FOLD_TILE - 1) / FOLD_TILE : n_coded;
     if (pt < PARTS) {
         float m = -INFINITY;
         const float* src = mtile + ((long long)b * s.nrb + rb) * s.tiles * ROWS + row;
-        for (int t = pt; t < nt; t += PARTS) m = fmaxf(m, src[(long long)t * ROWS]);
+        for (int t = pt; t < nt; t += PARTS)
+            if (t < n_coded || t >= window0) m = fmaxf(m, src[(long long)t * ROWS]);
         scratch[pt * ROWS + row] = m;
     }
     __syncthreads();
@@ -808,7 +862,7 @@ __global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
             if (lane == 0) reinterpret_cast<uint32_t*>(lds + L::N_OFF)[wave * NG + g] = m;
         }
     }
-    fold_row_maxima<RT>(s, a.mtile, o.b, o.rb, o.len, reinterpret_cast<float*>(lds + L::M_OFF), mrow);
+    fold_row_maxima<RT>(s, a.mtile, o.b, o.rb, reinterpret_cast<float*>(lds + L::M_OFF), mrow);
     if (tid < NG) {
         const uint32_t* src = reinterpret_cast<const uint32_t*>(lds + L::N_OFF);
         uint32_t m = 0u;
@@ -823,8 +877,8 @@ __global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
     constexpr int NP = 2 * RT;                                      // 16-byte pieces per thread and 256 tokens
     const int prow = RT == 2 ? ((wave >> 1) & 1) * 16 + c16 : c16;
     const float M = mrow[prow];
-    const float* psrc = a.p + ((long long)o.b * s.nrb + o.rb) * s.tiles * 4 * FOLD_P_TILE32<RT>;
-    const float* msrc = a.mtile + ((long long)o.b * s.nrb + o.rb) * s.tiles * 16 * RT + prow;
+    const float* psrc = a.p + (((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) * 4 * FOLD_P_TILE32<RT>;
+    const float* msrc = a.mtile + (((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) * 16 * RT + prow;
     float4 pv[NP];
     float fm[2];
     constexpr int NE = FOLD_VTILE * NG / 512;                       // (token, group) pairs per thread: 1 or 2
@@ -1164,13 +1218,13 @@ __global__ __launch_bounds__(512) void fold_values_dense_kernel(const FoldValueA
     const int slab = o.cblk * 2 + sw;
     const bool live = slab < x.n_slabs;
     float* mrow = reinterpret_cast<float*>(lds + L::M_OFF) + 16 * 16 * RT;
-    fold_row_maxima<RT>(s, a.mtile, o.b, o.rb, o.len, reinterpret_cast<float*>(lds + L::M_OFF), mrow);
+    fold_row_maxima<RT>(s, a.mtile, o.b, o.rb, reinterpret_cast<float*>(lds + L::M_OFF), mrow);
 
     constexpr int NP = 2 * RT;
     const int prow = RT == 2 ? ((wave >> 1) & 1) * 16 + c16 : c16;
     const float M = mrow[prow];
-    const float* psrc = a.p + ((long long)o.b * s.nrb + o.rb) * s.tiles * 4 * FOLD_P_TILE32<RT>;
-    const float* msrc = a.mtile + ((long long)o.b * s.nrb + o.rb) * s.tiles * 16 * RT + prow;
+    const float* psrc = a.p + (((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) * 4 * FOLD_P_TILE32<RT>;
+    const float* msrc = a.mtile + (((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) * 16 * RT + prow;
     float4 pv[NP];
     float fm[2];
     auto load_stage = [&](int t) XQ_INLINE_LAMBDA {
@@ -1318,6 +1372,8 @@ __global__ __launch_bounds__(512) void fold_values_dense_kernel(const FoldValueA
     }
 }
 
+#include "folded_per_channel.hpp"
+
 // =====================================================================================================================
 // Output projection.  A workgroup takes one KV head, 32 query columns and a few slabs: it sums y over the token splits,
 // adds the offsets of the groups, and multiplies by the slabs' share of Wv_h, the prepared stream's fragments as they
@@ -1362,15 +1418,16 @@ __global__ __launch_bounds__(512) void fold_output_kernel(const FoldOutArgs a)
         if (cb * 32 + col < ncol) {
             int b;
             const int row = row_of(cb * 32 + col, b);
-            const int len = s.len.v[s.b0 + b], nt = (len + FOLD_VTILE - 1) / FOLD_VTILE, per = (nt + s.splits - 1) / s.splits;
-            const int used = (nt + per - 1) / per;                   // splits that hold tokens of this sequence
+            int used;
+            bool window;
+            fold_used_splits(s, b, used, window);
             const long long r0 = (long long)b * s.R + row;
             const int ch = slab0 * 128 + 4 * c4;
-            for (int k = 0; k < used; ++k) {
-                const long long rk = k * split_stride + r0;
+            for (int k = 0; k < used + (window ? 1 : 0); ++k) {
+                const long long rk = (k < used ? k : s.splits - 1) * split_stride + r0;
                 const float4 t = *reinterpret_cast<const float4*>(a.y + rk * d + ch);
                 v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
-                if constexpr (!DENSE) {
+                if (!DENSE && a.ng) {
                     // (8-bit caches: a code's zero-point multiplies its weight row once, that of the low nibble)
                     const float z = a.yz[rk * a.ng + ch / a.group], zo = a.w.nibbles ? 0.0f : z;
                     v.x += z; v.y += zo; v.z += z; v.w += zo;
@@ -1476,9 +1533,12 @@ __global__ __launch_bounds__(256) void fold_finish_kernel(const float* __restric
     const int idx = blockIdx.x * 256 + threadIdx.x;                  // (sequence, row, four columns)
     if (idx >= s.nb * s.R * 32) return;
     const int c4 = idx & 31, row = (idx >> 5) % s.R, b = (idx >> 5) / s.R;
-    const int nt = (s.len.v[s.b0 + b] + FOLD_VTILE - 1) / FOLD_VTILE, per = (nt + s.splits - 1) / s.splits, used = (nt + per - 1) / per;
+    int used;
+    bool window;
+    fold_used_splits(s, b, used, window);
     float L = 0.0f;
     for (int k = 0; k < used; ++k) L += lsum[((long long)k * s.nb + b) * s.nrb * 16 * rt + row];
+    if (window) L += lsum[((long long)(s.splits - 1) * s.nb + b) * s.nrb * 16 * rt + row];
     float4 t = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     for (int k = 0; k < chunks; ++k) {
         const float4 u = *reinterpret_cast<const float4*>(part + (((long long)k * s.nb + b) * s.R + row) * 128 + 4 * c4);
@@ -1521,7 +1581,7 @@ static size_t align256(size_t n) { return (n + 255) / 256 * 256; }
 // Workspace of one launch group: what depends on the number of sequences in it.
 struct FoldPlan {
     int rt, nrb, tiles, splits, chunks, chunk_slabs, u_slab;
-    size_t p, mtile, rowfac, lsum, uy, yz, total;      // bytes; u and y share a region (u is dead when y is written),
+    size_t p, mtile, rowfac, lsum, uy, yz, ud, total;      // bytes; u and y share a region (u is dead when y is written),
                                                            // the output splits lie over p (dead by then)
 };
 
@@ -1539,8 +1599,8 @@ static FoldPlan fold_plan(const FoldProblem& f, int nb, int max_len, int splits)
     L.rt = R <= 16 ? 1 : 2;
     const int rpb = 16 * L.rt;
     L.nrb = (R + rpb - 1) / rpb;
-    L.tiles = (max_len + FOLD_VTILE - 1) / FOLD_VTILE * 2;
-    L.splits = splits;
+    L.tiles = (max_len + FOLD_VTILE - 1) / FOLD_VTILE * 2 + (f.block ? 2 : 0);
+    L.splits = splits = splits + (f.block ? 1 : 0);
     L.u_slab = f.dense ? FOLD_U_DENSE(L.rt) : FOLD_U_CODED(L.rt);
     const int colblocks = (nb * f.T * (f.Hq / f.Hkv) + 31) / 32;
     L.chunk_slabs = std::max(1, std::min(FO_MAX_SLABS, f.n_slabs_v * f.Hkv * colblocks / 256));
@@ -1550,8 +1610,9 @@ static FoldPlan fold_plan(const FoldProblem& f, int nb, int max_len, int splits)
     L.rowfac = align256((size_t)nb * L.nrb * rpb * 4);
     L.lsum = align256((size_t)splits * nb * L.nrb * rpb * 4);
     L.uy = align256(std::max((size_t)nb * L.nrb * f.n_slabs_k * L.u_slab, (size_t)splits * nb * R * f.n_slabs_v * 512));
-    L.yz = f.dense ? 0 : align256((size_t)splits * nb * R * f.ng_v * 4);
-    L.total = L.p + L.mtile + L.rowfac + L.lsum + L.uy + L.yz;
+    L.yz = f.dense || f.block ? 0 : align256((size_t)splits * nb * R * f.ng_v * 4);
+    L.ud = f.block ? align256((size_t)nb * L.nrb * f.n_slabs_k * FOLD_U_DENSE(L.rt)) : 0;
+    L.total = L.p + L.mtile + L.rowfac + L.lsum + L.uy + L.yz + L.ud;
     return L;
 }
 
@@ -1628,9 +1689,28 @@ static hipError_t values_for(int bits, int G, bool nibbles, const FoldValueArgs&
     return launch(fold_values_dense_kernel<RT>, grid, FoldValueDenseLds<RT>::TOTAL, a, s);
 }
 
+template <int BITS, int RT>
+static hipError_t scores_pc(const FoldScoreArgs& a, int grid, hipStream_t s)
+{
+    return a.s.block == 64 ? launch(fold_scores_pc_kernel<BITS, 2, RT>, grid, FOLD_SCORE_PC_LDS<BITS, RT>, a, s)
+                           : launch(fold_scores_pc_kernel<BITS, 1, RT>, grid, FOLD_SCORE_PC_LDS<BITS, RT>, a, s);
+}
+template <int RT>
+static hipError_t scores_pc_for(int bits, const FoldScoreArgs& a, int grid, hipStream_t s)
+{
+    return bits == 2 ? scores_pc<2, RT>(a, grid, s) : bits == 3 ? scores_pc<3, RT>(a, grid, s) : scores_pc<4, RT>(a, grid, s);
+}
+template <int RT>
+static hipError_t values_pc_for(int bits, const FoldValueArgs& a, int grid, hipStream_t s)
+{
+    typedef FoldValuePcLds<RT> L;
+    return bits == 2 ? launch(fold_values_pc_kernel<2, RT>, grid, L::TOTAL, a, s)
+         : bits == 3 ? launch(fold_values_pc_kernel<3, RT>, grid, L::TOTAL, a, s) : launch(fold_values_pc_kernel<4, RT>, grid, L::TOTAL, a, s);
+}
+
 hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSource& kx, const FoldSource& vx, const FoldWeights& kw,
                            const FoldWeights& vw, int B, const BatchI32& len, int max_len, float softmax_scale, float* out, void* ws,
-                           size_t ws_bytes, hipStream_t s)
+                           size_t ws_bytes, hipStream_t s, const FoldSource* window)
 {
     int nb;
     FoldPlan L;
@@ -1645,16 +1725,23 @@ hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSo
     float* lsum = reinterpret_cast<float*>(w); w += L.lsum;
     uint8_t* u = w;
     float* y = reinterpret_cast<float*>(w); w += L.uy;
-    float* yz = reinterpret_cast<float*>(w);
+    float* yz = reinterpret_cast<float*>(w); w += L.yz;
+    uint8_t* u_dense = f.block ? w : nullptr;
     float* part = p;
+    bool any_window = false, any_coded = !f.block;
+    for (int b = 0; b < B; ++b) { any_window |= f.block && len.v[b] % f.block; any_coded |= f.block && len.v[b] >= f.block; }
     const int gq = f.Hq / f.Hkv;
     for (int b0 = 0; b0 < B; b0 += nb) {
         FoldShape sh{};
         sh.b0 = b0; sh.nb = std::min(nb, B - b0); sh.T = f.T; sh.Hq = f.Hq; sh.Hkv = f.Hkv; sh.R = f.T * f.Hq; sh.nrb = L.nrb;
         sh.tiles = L.tiles; sh.splits = L.splits; sh.len = len;
+        sh.gtiles = L.tiles - (f.block ? 2 : 0); sh.gsplits = L.splits - (f.block ? 1 : 0);
+        sh.block = f.block; sh.part = f.block ? 1 : 0;
+        FoldShape shw = sh;                                          // the window's launches
+        shw.gtiles = shw.gsplits = 1; shw.split0 = L.splits - 1; shw.part = 2;
         const int colblocks = (sh.nb * f.T * gq + 31) / 32;
         {
-            FoldQueryArgs a{kw, sh, q, u, rowfac, softmax_scale * 1.44269504088896340736f, L.u_slab, f.n_slabs_k, L.rt, tab};
+            FoldQueryArgs a{kw, sh, q, u, rowfac, softmax_scale * 1.44269504088896340736f, L.u_slab, f.n_slabs_k, L.rt, tab, u_dense};
             const dim3 grid((f.n_slabs_k + 1) / 2, f.Hkv, colblocks);
             if (f.dense) fold_query_kernel<true, 128><<<grid, dim3(128), 0, s>>>(a);
             else if (f.group == 64) fold_query_kernel<false, 64><<<grid, dim3(128), 0, s>>>(a);
@@ -1662,24 +1749,38 @@ hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSo
         }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        {
+        if (any_coded) {
             // Slab ways of a workgroup: eight, or four with two token tiles where that still leaves two rounds of workgroups
             // (a wave's set-up and the meeting of the slab ways then weigh less).  Measured, 8 / 4 / 2 slab ways: 1024 tiles
             // of 2 bits 122 / 114 / 113 us (group 128), 133 / 124 / 134 us (group 64); 256 tiles of 3 bits 38 / 51 / 84 us.
-            const int swl = sh.nb * sh.nrb * sh.tiles >= 4 * 256 ? 2 : 3, ways = 8 >> swl;
+            const int swl = sh.nb * sh.nrb * sh.gtiles >= 4 * 256 && !f.block ? 2 : 3, ways = 8 >> swl;
             FoldScoreArgs a{kx, sh, u, rowfac, p, mtile, L.u_slab, swl};
-            const int grid = xcd_grid(sh.nb * sh.nrb * ((sh.tiles + ways - 1) / ways));
-            e = L.rt == 1 ? scores_for<1>(bits, f.group, f.nibbles, a, grid, s) : scores_for<2>(bits, f.group, f.nibbles, a, grid, s);
+            const int grid = xcd_grid(sh.nb * sh.nrb * ((sh.gtiles + ways - 1) / ways));
+            e = f.block ? (L.rt == 1 ? scores_pc_for<1>(bits, a, grid, s) : scores_pc_for<2>(bits, a, grid, s))
+                        : (L.rt == 1 ? scores_for<1>(bits, f.group, f.nibbles, a, grid, s) : scores_for<2>(bits, f.group, f.nibbles, a, grid, s));
             if (e != hipSuccess) return e;
         }
-        {
+        if (any_window) {
+            FoldScoreArgs a{*window, shw, u_dense, rowfac, p, mtile, FOLD_U_DENSE(L.rt), 3};
+            const int grid = xcd_grid(sh.nb * sh.nrb);
+            e = L.rt == 1 ? scores_for<1>(16, 128, false, a, grid, s) : scores_for<2>(16, 128, false, a, grid, s);
+            if (e != hipSuccess) return e;
+        }
+        if (any_coded) {
             FoldValueArgs a{vx, sh, p, mtile, y, yz, lsum, (f.n_slabs_v + 1) / 2};
-            const int grid = xcd_grid(sh.nb * sh.nrb * sh.splits * a.cblocks);
-            e = L.rt == 1 ? values_for<1>(bits, f.group, f.nibbles, a, grid, s) : values_for<2>(bits, f.group, f.nibbles, a, grid, s);
+            const int grid = xcd_grid(sh.nb * sh.nrb * sh.gsplits * a.cblocks);
+            e = f.block ? (L.rt == 1 ? values_pc_for<1>(bits, a, grid, s) : values_pc_for<2>(bits, a, grid, s))
+                        : (L.rt == 1 ? values_for<1>(bits, f.group, f.nibbles, a, grid, s) : values_for<2>(bits, f.group, f.nibbles, a, grid, s));
+            if (e != hipSuccess) return e;
+        }
+        if (any_window) {
+            FoldValueArgs a{*window, shw, p, mtile, y, yz, lsum, (f.n_slabs_v + 1) / 2};
+            const int grid = xcd_grid(sh.nb * sh.nrb * a.cblocks);
+            e = L.rt == 1 ? values_for<1>(16, 128, false, a, grid, s) : values_for<2>(16, 128, false, a, grid, s);
             if (e != hipSuccess) return e;
         }
         {
-            FoldOutArgs a{vw, sh, y, yz, part, f.n_slabs_v, f.ng_v, f.group, L.chunk_slabs, L.rt, tab};
+            FoldOutArgs a{vw, sh, y, yz, part, f.n_slabs_v, f.block ? 0 : f.ng_v, f.group, L.chunk_slabs, L.rt, tab};
             const dim3 grid(L.chunks, f.Hkv, colblocks);
             if (f.dense) {
                 e = allow_lds(reinterpret_cast<const void*>(fold_output_kernel<true>), FO_LDS);

@@ -9,6 +9,7 @@ struct FoldProblem {
     int dense;                           // bf16 rows
     int bits, group, nibbles;            // of the walk (8-bit caches: 4, 128, 1)
     int n_slabs_k, n_slabs_v, ng_v;      // slabs of 128 walked channels on either side, groups of the values' side
+    int block;                           // per-channel cache: tokens per block (else 0); its walk has groups of 128
     size_t query_bytes;                  // what the entry point's workspace query says for this call
 };
 
@@ -18,6 +19,6 @@ size_t fold_workspace_bytes(const FoldProblem& f, int B, int max_len);
 bool fold_fits(const FoldProblem& f, int B, int max_len, size_t bytes);
 hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSource& kx, const FoldSource& vx, const FoldWeights& kw,
                            const FoldWeights& vw, int B, const BatchI32& len, int max_len, float softmax_scale, float* out, void* ws,
-                           size_t ws_bytes, hipStream_t s);
+                           size_t ws_bytes, hipStream_t s, const FoldSource* window = nullptr);   // window: of a per-channel cache
 
 }  // namespace xq

@@ -539,10 +539,26 @@ size_t remat_pc_workspace_bytes(int B, int Hq, int Hkv, int max_len, int d, int 
          + (size_t)B * blocks * 2 * sizeof(float) + 256;                          // block factors and exponents
 }
 
-// Decode attention from a per-channel cache plus the bf16 residual window of the newest len % block tokens.
+static FoldProblem fold_problem_pc(const xq_attn_t* a, int d, int block, int bits, size_t query_bytes)
+{
+    FoldProblem f = fold_problem(a, 1, d, 128, bits, 0, query_bytes);
+    f.block = block;
+    return f;
+}
+
+// as remat_decode_query_bytes
+size_t remat_pc_query_bytes(const xq_attn_t* a, int B, int max_len, int d, int block)
+{
+    const size_t remat = remat_pc_workspace_bytes(B, a->n_q_heads, a->n_kv_heads, max_len, d, block);
+    return !folding_pays(a, B, max_len, d) ? remat : std::max(remat, fold_workspace_bytes(fold_problem_pc(a, d, block, 4, 0), B, max_len));
+}
+
+// Decode attention from a per-channel cache plus the bf16 residual window of the newest len % block tokens.  In the folded
+// order the block terms are not needed; a caller's buffer is filled all the same when it is to be, so that a later step of
+// either order finds it valid.
 hipError_t run_remat_attn_decode_pc(const xq_attn_t* a, const uint16_t* q, const xq_cache_t* xc, const uint16_t* tail,
                                     const void* wprep_coded, const void* wprep_dense, const BatchI32& len, int max_len,
-                                    void* terms, bool terms_valid, float* out, void* ws, hipStream_t s)
+                                    void* terms, bool terms_valid, float* out, void* ws, size_t ws_bytes, hipStream_t s)
 {
     const int bits = xc->fmt.bits, blockT = xc->fmt.group, d = xc->fmt.d, B = xc->B, cap = xc->cap;
     const int blocks_cap = cap / blockT;
@@ -561,6 +577,8 @@ hipError_t run_remat_attn_decode_pc(const xq_attn_t* a, const uint16_t* q, const
         max_nblk = nblk.v[b] > max_nblk ? nblk.v[b] : max_nblk;
         any_tail |= len_tail.v[b];
     }
+    const FoldProblem f = fold_problem_pc(a, d, blockT, bits, remat_pc_query_bytes(a, B, max_len, d, blockT));
+    const bool folded = folding_pays(a, B, max_len, d) && fold_fits(f, B, max_len, ws_bytes);
     const int tiles_all = (max_len + TILE_TOKENS - 1) / TILE_TOKENS;
     const int tiles_coded = (max_coded + TILE_TOKENS - 1) / TILE_TOKENS;
     const int chunks_stride = (tiles_all + 1) * (TILE_TOKENS / CHUNK_TOKENS);
@@ -576,7 +594,7 @@ hipError_t run_remat_attn_decode_pc(const xq_attn_t* a, const uint16_t* q, const
         const PcTerms t = carve_pc_terms(terms, B, cap, d, blockT, a->n_kv_heads);
         img = t.img; zw = t.zw; fscale = t.fscale; eblk = t.eblk; blocks_ws = t.blocks_ws;
     }
-    const bool compute_terms = !(terms && terms_valid);
+    const bool compute_terms = folded ? terms && !terms_valid : !(terms && terms_valid);
 
     RematParams p{};
     p.q = q;
@@ -607,6 +625,20 @@ hipError_t run_remat_attn_decode_pc(const xq_attn_t* a, const uint16_t* q, const
             e = launch_with_lds(remat_attn_dense_kernel<DENSE_STORE>, LDS_DENSE_TOTAL, z, p.Hkv * B * z.tiles_per_seq, s);
         }
         if (e != hipSuccess) return e;
+    }
+    if (folded) {
+        FoldSource x{}, window{};
+        x.codes = xc->codes; x.scale = xc->scale; x.zero = xc->zero;
+        x.row_bytes = (long long)d * bits / 8;
+        x.cap = cap; x.n_slabs = Lc.n_main_slabs; x.ng = Lc.ng;
+        window.rows = tail;
+        window.row_bytes = (long long)d * 2;
+        window.cap = blockT; window.n_slabs = Lc.n_main_slabs; window.ng = Lc.ng;
+        FoldWeights w{};
+        w.stream = static_cast<const uint8_t*>(wprep_coded);
+        w.shift = stream_shifts(wprep_coded, Lc);
+        w.head_bytes = (long long)Lc.head_bytes; w.n16 = Lc.d / 16; w.group = 128;
+        return run_folded_attn(f, q, x, x, w, w, B, len, max_len, a->softmax_scale, out, ws, ws_bytes, s, &window);
     }
     if (max_nblk > 0) {
         // the coded blocks

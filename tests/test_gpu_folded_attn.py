@@ -7,6 +7,7 @@ import torch
 
 import xq_inputs as xi
 from oracle import xq_oracle as xo
+from tests.test_gpu_per_channel import _attend
 from tests.util import bits_to_torch, oracle_cache, rel_errors
 
 pytestmark = pytest.mark.gpu
@@ -116,3 +117,35 @@ def test_latent_halves(xq, bits, G, small):
                               pairs=[(b, h) for b in range(B) for h in range(w.Hq)], packed=packed, scale=scale, zero=zero, G=G, bits=bits)
     rows, worst = rel_errors(out.reshape(-1, w.hd), ref)
     assert np.all(np.isfinite(out)) and rows.max() <= TOL and worst <= TOL, (float(rows.max()), float(worst))
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("G", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,d,lens", [(16, 16, 2048, [330, 1, 256, 320]), (32, 8, 2176, [257, 63]), (40, 40, 2048, [512]), (16, 16, 2048, [50])])
+def test_per_channel_blocks_and_window(xq, bits, G, Hq, Hkv, d, lens):
+    """Blocks that end inside a 128- or 256-token tile, no window, a window alone, nothing but windows."""
+    w = xi.C2.scaled(B=len(lens), L=max(lens), d=d, Hq=Hq, Hkv=Hkv, n_outlier=d // 100)
+    assert _attend(xq, w, bits, G, lens, pairs=[(b, h) for b in range(len(lens)) for h in (0, Hq - 1)]) <= TOL
+
+
+def test_per_channel_scales_of_every_magnitude(xq):
+    w = xi.C2.scaled(B=1, L=300, d=2048, Hq=16, Hkv=16, n_outlier=0)
+    assert _attend(xq, w, 3, 128, [300], pairs=[(0, 0), (0, 9)], scale_spread=64.0) <= TOL
+
+
+def test_per_channel_terms_serve_both_orders(xq):
+    """Block terms kept by the caller, computed by a step of the folded order, used by one that rematerialises."""
+    B, G, d, Hkv = 64, 128, 1792, 2
+    x = torch.randn((B, 512, d), device="cuda", generator=torch.Generator("cuda").manual_seed(1)).bfloat16()
+    cache = xq.alloc_cache_per_channel(B, 512, d, G, 4)
+    xq.xq_quantize_blocks_per_channel(cache, x, [0] * B)
+    tail = x[:, :G].contiguous()
+    attn = xq.XQAttn(Hkv, Hkv, 128, 128 ** -0.5)
+    wk, wv = (torch.randn((d, Hkv * 128), device="cuda").mul(d ** -0.5).bfloat16() for _ in range(2))
+    wc, wd = xq.xq_prepare_weights(attn, d, G, 4, wk, wv), xq.xq_prepare_weights(attn, d, 0, 16, wk, wv)
+    q = torch.randn((B, Hkv, 128), device="cuda").bfloat16()
+    terms = xq.alloc_per_channel_terms(cache, Hkv)
+    xq.xq_remat_attn_decode_per_channel(attn, q, cache, tail, [513] * B, wc, wd, terms=terms, terms_valid=False)
+    kept = xq.xq_remat_attn_decode_per_channel(attn, q, cache, tail, [512] * B, wc, wd, terms=terms, terms_valid=True)
+    fresh = xq.xq_remat_attn_decode_per_channel(attn, q, cache, tail, [512] * B, wc, wd)
+    assert torch.equal(kept, fresh)
