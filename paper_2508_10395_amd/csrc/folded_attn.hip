@@ -88,6 +88,7 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
 {
     __shared__ __attribute__((aligned(16))) float ul[2][32 * FQ_STRIDE];
     __shared__ float nrm[2][32];
+    __shared__ int place[2][32];             // row block of the launch 16 RT + row inside it, per column (-1: none)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int half = lane >> 5, c32 = lane & 31;
     const int slab = blockIdx.x * 2 + wave, h = blockIdx.y, cb = blockIdx.z;
@@ -101,6 +102,13 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
         const int rem = col - b * per_seq, t = rem / gq;
         return t * s.Hq + h * gq + (rem - t * gq);
     };
+
+    const int rpb = 16 * a.rt;
+    if (half == 0) {
+        int b;
+        const int row = row_of(min(cb * 32 + c32, ncol - 1), b), rb = row / rpb;
+        place[wave][c32] = cb * 32 + c32 < ncol ? (b * s.nrb + rb) * rpb + (row - rb * rpb) : -1;
+    }
 
     // the 32 query rows as an operand: lane = column, k-slots in the order the accumulator rows below come in
     uint4 qa[4][2];
@@ -210,15 +218,14 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
     __builtin_amdgcn_wave_barrier();
 
     // out: 16-byte pieces (column, tick, quarter); a fragment is read lane by lane, lane = 16 quarter + row
-    const int rpb = 16 * a.rt;
+    const int rt_log2 = a.rt - 1 + 4;
     if (!DENSE && a.u_dense) {                                       // (a code's unit is part of the row factor)
 #pragma unroll 1
         for (int it = 0; it < 8; ++it) {
             const int idx = it * 64 + lane, qd = idx & 3, tick = (idx >> 2) & 3, col = idx >> 4;
-            if (cb * 32 + col >= ncol) continue;
-            int b;
-            const int row = row_of(cb * 32 + col, b), rb = row / rpb, rr = row - rb * rpb;
-            uint8_t* dst = a.u_dense + (((long long)b * s.nrb + rb) * a.n_slabs + slab) * FOLD_U_DENSE(a.rt) + ((rr >> 4) * 4 + tick) * 3 * 1024 +
+            const int at = place[wave][col], rr = at & (rpb - 1);
+            if (at < 0) continue;
+            uint8_t* dst = a.u_dense + ((long long)(at >> rt_log2) * a.n_slabs + slab) * FOLD_U_DENSE(a.rt) + ((rr >> 4) * 4 + tick) * 3 * 1024 +
                            (qd * 16 + (rr & 15)) * 16;
             const float* src = mine + col * FQ_STRIDE + 32 * tick + 8 * qd;
             uint32_t p[3][4];
@@ -238,10 +245,9 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
 #pragma unroll 1
     for (int it = 0; it < 8; ++it) {
         const int idx = it * 64 + lane, qd = idx & 3, tick = (idx >> 2) & 3, col = idx >> 4;
-        if (cb * 32 + col >= ncol) continue;
-        int b;
-        const int row = row_of(cb * 32 + col, b), rb = row / rpb, rr = row - rb * rpb;
-        uint8_t* dst = a.u + (((long long)b * s.nrb + rb) * a.n_slabs + slab) * a.u_slab + (qd * 16 + (rr & 15)) * 16;
+        const int at = place[wave][col], rr = at & (rpb - 1);
+        if (at < 0) continue;
+        uint8_t* dst = a.u + ((long long)(at >> rt_log2) * a.n_slabs + slab) * a.u_slab + (qd * 16 + (rr & 15)) * 16;
         float v[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -295,9 +301,8 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
         float sz1 = __shfl_xor(sz, 32);
         if constexpr (G == 128) { sz += sz1; sz1 = 0.0f; }
         if (half == 0 && cb * 32 + c32 < ncol) {
-            int b;
-            const int row = row_of(cb * 32 + c32, b), rb = row / rpb, rr = row - rb * rpb;
-            uint8_t* dst = a.u + (((long long)b * s.nrb + rb) * a.n_slabs + slab) * a.u_slab + a.rt * 8192 + (rr >> 4) * 1024 + (rr & 15) * 16;
+            const int at = place[wave][c32], rr = at & (rpb - 1);
+            uint8_t* dst = a.u + ((long long)(at >> rt_log2) * a.n_slabs + slab) * a.u_slab + a.rt * 8192 + (rr >> 4) * 1024 + (rr & 15) * 16;
             uint32_t z[3], z1[3];
             split_bf16x3(sz, z[0], z[1], z[2]);
             split_bf16x3(sz1, z1[0], z1[1], z1[2]);
@@ -1412,26 +1417,30 @@ __global__ __launch_bounds__(512) void fold_output_kernel(const FoldOutArgs a)
         const int rem = col - b * per_seq, t = rem / gq;
         return t * s.Hq + h * gq + (rem - t * gq);
     };
-    for (int idx = tid; idx < 32 * ns * 32; idx += 512) {            // 16-byte pieces: [column][channel / 4]
-        const int col = idx / (ns * 32), c4 = idx - col * (ns * 32);
-        float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (cb * 32 + col < ncol) {
-            int b;
-            const int row = row_of(cb * 32 + col, b);
-            int used;
-            bool window;
+    __shared__ int crow[32], cused[32];                              // per column: row of y, splits (and 256: the window's)
+    if (tid < 32) {
+        int b = 0, used = 0, row = 0;
+        bool window = false;
+        if (cb * 32 + tid < ncol) {
+            row = row_of(cb * 32 + tid, b);
             fold_used_splits(s, b, used, window);
-            const long long r0 = (long long)b * s.R + row;
-            const int ch = slab0 * 128 + 4 * c4;
-            for (int k = 0; k < used + (window ? 1 : 0); ++k) {
-                const long long rk = (k < used ? k : s.splits - 1) * split_stride + r0;
-                const float4 t = *reinterpret_cast<const float4*>(a.y + rk * d + ch);
-                v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
-                if (!DENSE && a.ng) {
-                    // (8-bit caches: a code's zero-point multiplies its weight row once, that of the low nibble)
-                    const float z = a.yz[rk * a.ng + ch / a.group], zo = a.w.nibbles ? 0.0f : z;
-                    v.x += z; v.y += zo; v.z += z; v.w += zo;
-                }
+        }
+        crow[tid] = b * s.R + row;
+        cused[tid] = used + (window ? 256 : 0);
+    }
+    __syncthreads();
+    for (int idx = tid; idx < 32 * ns * 32; idx += 512) {            // 16-byte pieces: [column][channel / 4]
+        const int col = idx / (ns * 32), c4 = idx - col * (ns * 32), used = cused[col] & 255, n = used + (cused[col] >> 8);
+        float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        const int ch = slab0 * 128 + 4 * c4;
+        for (int k = 0; k < n; ++k) {
+            const long long rk = (k < used ? k : s.splits - 1) * split_stride + crow[col];
+            const float4 t = *reinterpret_cast<const float4*>(a.y + rk * d + ch);
+            v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
+            if (!DENSE && a.ng) {
+                // (8-bit caches: a code's zero-point multiplies its weight row once, that of the low nibble)
+                const float z = a.yz[rk * a.ng + ch / a.group], zo = a.w.nibbles ? 0.0f : z;
+                v.x += z; v.y += zo; v.z += z; v.w += zo;
             }
         }
         *reinterpret_cast<float4*>(yl + col * FO_STRIDE + 4 * c4) = v;
@@ -1540,6 +1549,7 @@ __global__ __launch_bounds__(256) void fold_finish_kernel(const float* __restric
     for (int k = 0; k < used; ++k) L += lsum[((long long)k * s.nb + b) * s.nrb * 16 * rt + row];
     if (window) L += lsum[((long long)(s.splits - 1) * s.nb + b) * s.nrb * 16 * rt + row];
     float4 t = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll 4
     for (int k = 0; k < chunks; ++k) {
         const float4 u = *reinterpret_cast<const float4*>(part + (((long long)k * s.nb + b) * s.R + row) * 128 + 4 * c4);
         t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
