@@ -22,20 +22,19 @@ struct FoldShape {
     int b0, nb, T, Hq, Hkv, R, nrb;      // query rows R = T Hq per sequence, nrb row blocks of 16 RT rows
     int tiles;                           // score tiles (128 tokens) per sequence in the arrays, even
     int splits;                          // token splits in the arrays of the value kernel
-    int gtiles, gsplits, split0;         // tiles and splits of this launch, index of the first split
-    int block, part;                     // per-channel caches: tokens per block; launch over the coded tokens (1) or the window (2)
+    int block;                           // per-channel caches: tokens per block (else 0)
     BatchI32 len;                        // of the call's sequences
 };
 
-// The tokens of a launch and where their tiles lie.  A per-channel cache's complete blocks come first, its window has the
-// tiles behind them (from an even one on) and the last split.
+// The tokens a workgroup may take and where their tiles lie.  A per-channel cache's complete blocks come first, its window
+// has the tiles behind them (from an even one on) and the last split; it is the work of the first workgroups of a launch.
 struct FoldSpan { int len, tile0; };
-__device__ __forceinline__ FoldSpan fold_span(const FoldShape& s, int b)
+__device__ __forceinline__ FoldSpan fold_span(const FoldShape& s, int b, bool window)
 {
     const int len = s.len.v[s.b0 + b];
     if (s.block == 0) return {len, 0};
     const int coded = len / s.block * s.block;
-    return s.part == 2 ? FoldSpan{len - coded, (coded + FOLD_VTILE - 1) / FOLD_VTILE * 2} : FoldSpan{coded, 0};
+    return window ? FoldSpan{len - coded, (coded + FOLD_VTILE - 1) / FOLD_VTILE * 2} : FoldSpan{coded, 0};
 }
 // splits of a sequence that hold tokens: the first `used` ones, and the last one if `window`
 __device__ __forceinline__ void fold_used_splits(const FoldShape& s, int b, int& used, bool& window)
@@ -336,18 +335,21 @@ struct FoldScoreArgs {
     float* p;                            // [nb][nrb][tiles][4][FOLD_P_TILE32]
     float* mtile;                        // [nb][nrb][tiles][16 RT]
     int u_slab, sw_log2;
+    FoldSource window;                   // per-channel caches: the window's rows, its folded queries and workgroups
+    const uint8_t* u_window;
+    int n_window;
 };
 
 // which tokens and slabs a wave of a score workgroup has: 8 / SW token ways of one tile each, SW = 1 << sw_log2 slab ways
 struct FoldScorePlace { int b, rb, tile, tile0, len, sw, SW, tw, slab0, slab1, nw; };   // nw = slab ways that hold any slab
-__device__ __forceinline__ bool fold_score_place(const FoldShape& s, int sw_log2, int n_slabs, int wave, FoldScorePlace& o)
+__device__ __forceinline__ bool fold_score_place(const FoldShape& s, bool window, int sw_log2, int n_slabs, int wg, int wave, FoldScorePlace& o)
 {
-    const int ways = 8 >> sw_log2, tiles = (s.gtiles + ways - 1) / ways, n = s.nb * s.nrb * tiles;
-    const int item = xcd_contiguous(n);
+    const int ways = 8 >> sw_log2, tiles = window ? 1 : (s.tiles + ways - 1) / ways, n = s.nb * s.nrb * tiles;
+    const int item = xcd_contiguous(n, wg);
     if (item >= n) return false;
     o.rb = (item / tiles) % s.nrb;
     o.b = item / (tiles * s.nrb);
-    const FoldSpan span = fold_span(s, o.b);
+    const FoldSpan span = fold_span(s, o.b, window);
     o.len = span.len;
     o.tile0 = span.tile0;
     o.SW = 1 << sw_log2;
@@ -456,7 +458,7 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
     const FoldSource& x = a.x;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     FoldScorePlace o;
-    if (!fold_score_place(s, a.sw_log2, x.n_slabs, wave, o)) return;
+    if (!fold_score_place(s, false, a.sw_log2, x.n_slabs, blockIdx.x, wave, o)) return;
     const int b = o.b, rb = o.rb, len = o.len, tok0 = o.tile * FOLD_TILE;
     const int c16 = lane & 15, q = lane >> 4;
     const uint8_t* cbase = x.codes + (long long)(s.b0 + b) * x.cap * x.row_bytes;
@@ -666,19 +668,18 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
 // The rows of a half slab (128 bytes each) go through the wave's LDS image as the codes do, 16 token rows at a time; their
 // 16-byte pieces are swizzled by the row, so that neither the row-wise write nor the fragment read meets bank conflicts.
 template <int RT>
-__global__ __launch_bounds__(512) void fold_scores_dense_kernel(const FoldScoreArgs a)
+__device__ __forceinline__ void fold_scores_dense(const FoldScoreArgs& a, const FoldSource& x, const uint8_t* u_all, bool window, int sw_log2, uint8_t* lds)
 {
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int u_slab = FOLD_U_DENSE(RT);
     const FoldShape& s = a.s;
-    const FoldSource& x = a.x;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     FoldScorePlace o;
-    if (!fold_score_place(s, a.sw_log2, x.n_slabs, wave, o)) return;
+    if (!fold_score_place(s, window, sw_log2, x.n_slabs, blockIdx.x, wave, o)) return;
     const int b = o.b, rb = o.rb, len = o.len, tok0 = o.tile * FOLD_TILE;
     const int c16 = lane & 15, q = lane >> 4;
     const uint8_t* xbase = reinterpret_cast<const uint8_t*>(x.rows) + (long long)(s.b0 + b) * x.cap * x.row_bytes;
-    const uint8_t* ubase = a.u + ((long long)b * s.nrb + rb) * x.n_slabs * a.u_slab;
+    const uint8_t* ubase = u_all + ((long long)b * s.nrb + rb) * x.n_slabs * u_slab;
     const uint32_t uoff = lane * 16;
     uint8_t* image = lds + wave * 2 * 2048;                          // two images of 16 rows x 128 bytes
     f32x4 S[RT][8];
@@ -703,7 +704,7 @@ __global__ __launch_bounds__(512) void fold_scores_dense_kernel(const FoldScoreA
         };
         auto load_u = [&](int half_idx, auto HF) XQ_INLINE_LAMBDA {
             constexpr int h = decltype(HF)::value;
-            const uint8_t* us = ubase + (long long)(half_idx >> 1) * a.u_slab + (half_idx & 1) * 6144;
+            const uint8_t* us = ubase + (long long)(half_idx >> 1) * u_slab + (half_idx & 1) * 6144;
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
@@ -743,6 +744,13 @@ __global__ __launch_bounds__(512) void fold_scores_dense_kernel(const FoldScoreA
     fold_scores_finish<RT>(s, a.rowfac, a.p, a.mtile, S, reinterpret_cast<float*>(lds), o, lane, wave);
 }
 
+template <int RT>
+__global__ __launch_bounds__(512) void fold_scores_dense_kernel(const FoldScoreArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    fold_scores_dense<RT>(a, a.x, a.u, false, a.sw_log2, lds);
+}
+
 // =====================================================================================================================
 // Values.  A workgroup owns two slabs (256 channels) of a sequence, one row block and a range of tokens: two slab ways,
 // four token ways.  Per 256 tokens all eight waves bring the stored softmax weights to the sequence's maximum and stage
@@ -762,6 +770,8 @@ struct FoldValueArgs {
     float* yz;                           // [splits][nb][R][ng]: sum of weight times rest of the zero-point, per group
     float* lsum;                         // [splits][nb][nrb 16 RT]
     int cblocks;                         // workgroups per row of slabs
+    FoldSource window;                   // as in FoldScoreArgs
+    int n_window;
 };
 
 template <int RT, int GROUPS, bool NIB>
@@ -781,20 +791,21 @@ struct FoldValueLds {
 
 // tile and range of a value workgroup
 struct FoldValuePlace { int b, rb, cblk, split, len, tile0, t0, t1; };      // [t0, t1): 256-token tiles
-__device__ __forceinline__ bool fold_value_place(const FoldShape& s, int cblocks, FoldValuePlace& o)
+__device__ __forceinline__ bool fold_value_place(const FoldShape& s, bool window, int cblocks, int wg, FoldValuePlace& o)
 {
-    const int n = s.nb * s.nrb * s.gsplits * cblocks;
-    const int item = xcd_contiguous(n);
+    const int splits = window ? 1 : s.block ? s.splits - 1 : s.splits;
+    const int n = s.nb * s.nrb * splits * cblocks;
+    const int item = xcd_contiguous(n, wg);
     if (item >= n) return false;
     o.cblk = item % cblocks;                                        // (neighbours share the softmax weights)
-    const int k = (item / cblocks) % s.gsplits;
-    o.split = s.split0 + k;
-    o.rb = (item / (cblocks * s.gsplits)) % s.nrb;
-    o.b = item / (cblocks * s.gsplits * s.nrb);
-    const FoldSpan span = fold_span(s, o.b);
+    const int k = (item / cblocks) % splits;
+    o.split = window ? s.splits - 1 : k;
+    o.rb = (item / (cblocks * splits)) % s.nrb;
+    o.b = item / (cblocks * splits * s.nrb);
+    const FoldSpan span = fold_span(s, o.b, window);
     o.len = span.len;
     o.tile0 = span.tile0;
-    const int nt = (o.len + FOLD_VTILE - 1) / FOLD_VTILE, per = (nt + s.gsplits - 1) / s.gsplits;
+    const int nt = (o.len + FOLD_VTILE - 1) / FOLD_VTILE, per = (nt + splits - 1) / splits;
     o.t0 = k * per;
     o.t1 = min(nt, o.t0 + per);
     return o.t0 < o.t1;
@@ -834,7 +845,7 @@ __global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const FoldShape& s = a.s;
     FoldValuePlace o;
-    if (!fold_value_place(s, a.cblocks, o)) return;
+    if (!fold_value_place(s, false, a.cblocks, blockIdx.x, o)) return;
     const FoldSource& x = a.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c16 = lane & 15, q = lane >> 4;
@@ -1209,14 +1220,12 @@ struct FoldValueDenseLds {
     static constexpr int TOTAL = LOOP > RED ? LOOP : RED;
 };
 template <int RT>
-__global__ __launch_bounds__(512) void fold_values_dense_kernel(const FoldValueArgs a)
+__device__ __forceinline__ void fold_values_dense(const FoldValueArgs& a, const FoldSource& x, bool window, uint8_t* lds)
 {
     typedef FoldValueDenseLds<RT> L;
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const FoldShape& s = a.s;
     FoldValuePlace o;
-    if (!fold_value_place(s, a.cblocks, o)) return;
-    const FoldSource& x = a.x;
+    if (!fold_value_place(s, window, a.cblocks, blockIdx.x, o)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c16 = lane & 15, q = lane >> 4;
     const int sw = wave & 1, tw = wave >> 1;
@@ -1375,6 +1384,13 @@ __global__ __launch_bounds__(512) void fold_values_dense_kernel(const FoldValueA
                     make_float4(t[0][r], t[1][r], t[2][r], t[3][r]);
         }
     }
+}
+
+template <int RT>
+__global__ __launch_bounds__(512) void fold_values_dense_kernel(const FoldValueArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    fold_values_dense<RT>(a, a.x, false, lds);
 }
 
 #include "folded_per_channel.hpp"
@@ -1738,17 +1754,15 @@ hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSo
     float* yz = reinterpret_cast<float*>(w); w += L.yz;
     uint8_t* u_dense = f.block ? w : nullptr;
     float* part = p;
-    bool any_window = false, any_coded = !f.block;
-    for (int b = 0; b < B; ++b) { any_window |= f.block && len.v[b] % f.block; any_coded |= f.block && len.v[b] >= f.block; }
+    bool any_window = false;
+    for (int b = 0; b < B; ++b) any_window |= f.block && len.v[b] % f.block;
     const int gq = f.Hq / f.Hkv;
     for (int b0 = 0; b0 < B; b0 += nb) {
         FoldShape sh{};
         sh.b0 = b0; sh.nb = std::min(nb, B - b0); sh.T = f.T; sh.Hq = f.Hq; sh.Hkv = f.Hkv; sh.R = f.T * f.Hq; sh.nrb = L.nrb;
         sh.tiles = L.tiles; sh.splits = L.splits; sh.len = len;
-        sh.gtiles = L.tiles - (f.block ? 2 : 0); sh.gsplits = L.splits - (f.block ? 1 : 0);
-        sh.block = f.block; sh.part = f.block ? 1 : 0;
-        FoldShape shw = sh;                                          // the window's launches
-        shw.gtiles = shw.gsplits = 1; shw.split0 = L.splits - 1; shw.part = 2;
+        sh.block = f.block;
+        const int coded_splits = L.splits - (f.block ? 1 : 0);
         const int colblocks = (sh.nb * f.T * gq + 31) / 32;
         {
             FoldQueryArgs a{kw, sh, q, u, rowfac, softmax_scale * 1.44269504088896340736f, L.u_slab, f.n_slabs_k, L.rt, tab, u_dense};
@@ -1759,34 +1773,24 @@ hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSo
         }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        if (any_coded) {
+        {
             // Slab ways of a workgroup: eight, or four with two token tiles where that still leaves two rounds of workgroups
             // (a wave's set-up and the meeting of the slab ways then weigh less).  Measured, 8 / 4 / 2 slab ways: 1024 tiles
             // of 2 bits 122 / 114 / 113 us (group 128), 133 / 124 / 134 us (group 64); 256 tiles of 3 bits 38 / 51 / 84 us.
-            const int swl = sh.nb * sh.nrb * sh.gtiles >= 4 * 256 && !f.block ? 2 : 3, ways = 8 >> swl;
-            FoldScoreArgs a{kx, sh, u, rowfac, p, mtile, L.u_slab, swl};
-            const int grid = xcd_grid(sh.nb * sh.nrb * ((sh.gtiles + ways - 1) / ways));
+            const int swl = sh.nb * sh.nrb * sh.tiles >= 4 * 256 && !f.block ? 2 : 3, ways = 8 >> swl;
+            FoldScoreArgs a{kx, sh, u, rowfac, p, mtile, L.u_slab, swl, FoldSource{}, u_dense, 0};
+            if (any_window) { a.window = *window; a.n_window = xcd_grid(sh.nb * sh.nrb); }
+            const int grid = a.n_window + xcd_grid(sh.nb * sh.nrb * ((sh.tiles + ways - 1) / ways));
             e = f.block ? (L.rt == 1 ? scores_pc_for<1>(bits, a, grid, s) : scores_pc_for<2>(bits, a, grid, s))
                         : (L.rt == 1 ? scores_for<1>(bits, f.group, f.nibbles, a, grid, s) : scores_for<2>(bits, f.group, f.nibbles, a, grid, s));
             if (e != hipSuccess) return e;
         }
-        if (any_window) {
-            FoldScoreArgs a{*window, shw, u_dense, rowfac, p, mtile, FOLD_U_DENSE(L.rt), 3};
-            const int grid = xcd_grid(sh.nb * sh.nrb);
-            e = L.rt == 1 ? scores_for<1>(16, 128, false, a, grid, s) : scores_for<2>(16, 128, false, a, grid, s);
-            if (e != hipSuccess) return e;
-        }
-        if (any_coded) {
-            FoldValueArgs a{vx, sh, p, mtile, y, yz, lsum, (f.n_slabs_v + 1) / 2};
-            const int grid = xcd_grid(sh.nb * sh.nrb * sh.gsplits * a.cblocks);
+        {
+            FoldValueArgs a{vx, sh, p, mtile, y, yz, lsum, (f.n_slabs_v + 1) / 2, FoldSource{}, 0};
+            if (any_window) { a.window = *window; a.n_window = xcd_grid(sh.nb * sh.nrb * a.cblocks); }
+            const int grid = a.n_window + xcd_grid(sh.nb * sh.nrb * coded_splits * a.cblocks);
             e = f.block ? (L.rt == 1 ? values_pc_for<1>(bits, a, grid, s) : values_pc_for<2>(bits, a, grid, s))
                         : (L.rt == 1 ? values_for<1>(bits, f.group, f.nibbles, a, grid, s) : values_for<2>(bits, f.group, f.nibbles, a, grid, s));
-            if (e != hipSuccess) return e;
-        }
-        if (any_window) {
-            FoldValueArgs a{*window, shw, p, mtile, y, yz, lsum, (f.n_slabs_v + 1) / 2};
-            const int grid = xcd_grid(sh.nb * sh.nrb * a.cblocks);
-            e = L.rt == 1 ? values_for<1>(16, 128, false, a, grid, s) : values_for<2>(16, 128, false, a, grid, s);
             if (e != hipSuccess) return e;
         }
         {

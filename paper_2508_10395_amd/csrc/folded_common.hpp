@@ -135,10 +135,10 @@ __device__ __forceinline__ uint32_t pack_hi16(uint32_t a, uint32_t b) { return p
 
 // workgroup order: the workgroups of one XCD (blockIdx % 8) get a contiguous range of the work, so that what neighbours
 // share (a sequence's folded queries, its softmax weights) is fetched into one L2
-__device__ __forceinline__ int xcd_contiguous(int n)
+__device__ __forceinline__ int xcd_contiguous(int n, int wg)
 {
     const int per = (n + 7) >> 3;
-    return ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
+    return (wg & 7) * per + (wg >> 3);
 }
 inline int xcd_grid(int n) { return (n + 7) / 8 * 8; }
 

@@ -8,7 +8,8 @@
 // Values: the codes are summed with the softmax weights alone, and every 64 tokens the sums are taken times the block's scales
 // into y, z + c0 s times the sum of the weights (one more column tile, of ones) along with them.
 // Bound by issue and by the latency of the loads, as the per-token kernels.  8 sequences of up to 4077 tokens, 3 bits, 32 KV
-// heads, d = 4096: scores 37 us, values 36 us, window 31 + 11 us; the step 1432 us when K and V were rematerialised, 160 now.
+// heads, d = 4096: scores 40 us, values 43 us with the windows (36 + 32 and 34 + 11 in launches of their own); the step 1432 us
+// when K and V were rematerialised, 124 now.
 #pragma once
 
 template <int BITS>
@@ -27,7 +28,9 @@ constexpr int FOLD_SCORE_PC_IMAGES = 8 * FOLD_TILE * 16 * BITS > FOLD_SCORE_RED<
 template <int BITS, int RT>
 constexpr int FOLD_SCORE_PC_LDS = FOLD_SCORE_PC_IMAGES<BITS, RT> + 256;         // behind them: the blocks' largest numbers
 
-// Workgroup and waves as in fold_scores_kernel (one tile, eight slab ways); NB blocks per tile of 128 tokens.
+// Workgroup and waves as in fold_scores_kernel (one tile, eight slab ways); NB blocks per tile of 128 tokens.  The first
+// n_window workgroups (a multiple of 8) take the windows: few, and each slow at its one tile, they run beside the coded
+// tiles' workgroups.
 template <int BITS, int NB, int RT>
 __global__ __launch_bounds__(512) void fold_scores_pc_kernel(const FoldScoreArgs a)
 {
@@ -37,8 +40,12 @@ __global__ __launch_bounds__(512) void fold_scores_pc_kernel(const FoldScoreArgs
     const FoldShape& s = a.s;
     const FoldSource& x = a.x;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if ((int)blockIdx.x < a.n_window) {
+        fold_scores_dense<RT>(a, a.window, a.u_window, true, 3, lds);
+        return;
+    }
     FoldScorePlace o;
-    if (!fold_score_place(s, 3, x.n_slabs, wave, o)) return;
+    if (!fold_score_place(s, false, 3, x.n_slabs, (int)blockIdx.x - a.n_window, wave, o)) return;
     const int b = o.b, rb = o.rb, len = o.len, tok0 = o.tile * FOLD_TILE;
     const int c16 = lane & 15, q = lane >> 4, d = x.n_slabs * 128;
     const int nblk = len / s.block, blk0 = tok0 / s.block;
@@ -261,8 +268,12 @@ __global__ __launch_bounds__(512) void fold_values_pc_kernel(const FoldValueArgs
     typedef FoldValuePcLds<RT> L;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const FoldShape& s = a.s;
+    if ((int)blockIdx.x < a.n_window) {
+        fold_values_dense<RT>(a, a.window, true, lds);
+        return;
+    }
     FoldValuePlace o;
-    if (!fold_value_place(s, a.cblocks, o)) return;
+    if (!fold_value_place(s, false, a.cblocks, (int)blockIdx.x - a.n_window, o)) return;
     const FoldSource& x = a.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c16 = lane & 15, q = lane >> 4;
