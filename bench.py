@@ -4,7 +4,8 @@
 One step = one decode step of one layer of the Llama-2-7B-shaped workload (config 2:
 d=4096, 32x128 MHA, batch 8, context 4096, X cached 3-bit asym, group 128): quantise and
 append the new token's X row (xq_quantize_append, T=1), then rematerialise K,V from the
-packed cache and attend (xq_remat_attn_decode).  Inputs are seeded synthetic tensors that
+packed cache and attend (xq_remat_attn_decode; the products taken in the order that
+needs no K and V in memory or registers: (q Wk^T) X^T, then (p X) Wv).  Inputs are seeded synthetic tensors that
 are resident in HBM before the timed region.  Prints ONE JSON line.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W]
@@ -20,13 +21,11 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA, published
 PEAK_HBM_GBS = 8000.0         # MI355X HBM3E, published
-# HBM-side bytes of one launch of the fused kernel on this workload: rocprofv3 FETCH_SIZE + WRITE_SIZE,
+# HBM-side bytes of one xq_remat_attn_decode on this workload, its five kernels together: rocprofv3 FETCH_SIZE + WRITE_SIZE,
 # each scaled by the factor that makes the counter read 256 MiB for a plain 256 MiB device copy
-# (profiles/remat_attn_hbm_traffic.txt; counters cannot be read from inside this process, so this is a
-# recorded constant: measured with the library built from the commit named here; remat_attn16.hip's tiling,
-# which fixes the figure, has not changed since)
-K3_HBM_BYTES_PER_LAUNCH = 2.18e9
-K3_HBM_BYTES_MEASURED_AT = "d65b3cd"
+# (profiles/remat_attn_hbm_traffic.txt; counters cannot be read from inside this process, so this is a recorded constant)
+DECODE_HBM_BYTES = 3.143e8
+DECODE_HBM_BYTES_MEASURED_AT = "8e4dc45"
 
 
 def parse():
@@ -109,13 +108,13 @@ def main():
     torch.cuda.synchronize()
     t1 = time.perf_counter()
     ms_per_step = (t1 - t0) * 1e3 / args.steps
-    remat_ms = sum(a.elapsed_time(b) for a, b in evs) / args.steps   # fused kernel + combine, on the launch stream
+    remat_ms = sum(a.elapsed_time(b) for a, b in evs) / args.steps   # the decode call's kernels, on the launch stream
 
     from paper_2508_10395_amd import cost_model as cm
     tokens = B * L
     value = tokens / (ms_per_step * 1e-3)
-    flops = cm.remat_attn_flops(tokens, d, Hq, Hkv, hd)                    # remat (Sec. 3.4) + attention
-    achieved_tflops = flops / (remat_ms * 1e-3) / 1e12
+    decode_bytes = cm.remat_attn_algorithmic_bytes(tokens, d, bits, G, Hkv, hd)    # codes, metadata, weights, once each
+    flops = 4.0 * tokens * d * Hq + 4.0 * B * Hq * d * hd       # scores and weighted sums over X, products with Wk and Wv
 
     if args.profile_copy:
         y = torch.empty_like(x)
@@ -229,8 +228,8 @@ def main():
                                        "frac_hbm_peak": dq_bytes / t_dq / 1e6 / PEAK_HBM_GBS},
             "remat_attn_with_rope_ms": t_rope,
             "remat_attn_dense_acc": {"workload": "XQuant-CL source (bf16 accumulator), c2 shape", "ms": t_dense,
-                                     "TFLOP/s": flops / t_dense / 1e9,
-                                     "frac_mfma_peak": flops / t_dense / 1e9 / PEAK_BF16_TFLOPS},
+                                     "GB/s": (tokens * d * 2.0 + 4.0 * d * Hkv * hd) / t_dense / 1e6,
+                                     "frac_hbm_peak": (tokens * d * 2.0 + 4.0 * d * Hkv * hd) / t_dense / 1e6 / PEAK_HBM_GBS},
         }
 
     if extra is not None:
@@ -255,9 +254,10 @@ def main():
                 xq.xq_quantize_append(sub, device_x(ow, ow.L), [0])
             return c_
 
-        def remat_entry(ms, ow, fl):
-            return {"ms": ms, "tokens/s/layer": ow.B * ow.L / (ms * 1e-3), "TFLOP/s": fl / ms / 1e9,
-                    "frac_mfma_peak": fl / ms / 1e9 / PEAK_BF16_TFLOPS}
+        def decode_entry(ms, ow):
+            nbytes = cm.remat_attn_algorithmic_bytes(ow.B * ow.L, ow.d, ow.bits, ow.G, ow.Hkv, ow.hd)
+            return {"ms": ms, "tokens/s/layer": ow.B * ow.L / (ms * 1e-3), "GB/s": nbytes / ms / 1e6,
+                    "frac_hbm_peak": nbytes / ms / 1e6 / PEAK_HBM_GBS}
 
         # config 2 again, cycling through 8 distinct layers (8 X caches + 8 weight streams = 1.0 GB, four times the
         # 256 MB Infinity Cache), so that no layer finds its cache or weights where its last visit left them
@@ -276,27 +276,11 @@ def main():
 
         t_rot = timed(rotate, n=5, warm=2) / n_rot
         extra["remat_attn_c2_rotating_8_layers"] = dict(
-            remat_entry(t_rot, w, flops),
+            decode_entry(t_rot, w),
             workload="c2, xq_remat_attn_decode over 8 distinct layers in turn (caches + weight streams 1.0 GB); ms per layer",
             ratio_to_single_layer=t_rot / remat_ms)
         del rot_caches, rot_streams
         torch.cuda.empty_cache()
-
-        # The same launch (same cache, same instruction stream) with other weight VALUES: all weights zero, and all
-        # weights one constant.  The matrix pipe's power draw depends on the bits that toggle in its operands and the
-        # GPU lowers its clock under it, so this separates what the kernel's structure allows from what the data costs.
-        dep = {}
-        for tag, fillv in (("all_zero", 0.0), ("all_equal", 2.0 ** -6)):
-            wc = torch.full((d, Hkv * hd), fillv, dtype=torch.bfloat16, device=dev)
-            wpc = xq.xq_prepare_weights(attn, d, G, bits, wc, wc)
-            t_w = timed(lambda: xq.xq_remat_attn_decode(attn, q, wpc, lens, xcache=cache, out=out, workspace=ws), n=20, warm=10)
-            dep[tag + "_ms"] = t_w
-            dep[tag + "_frac_mfma_peak"] = flops / t_w / 1e9 / PEAK_BF16_TFLOPS
-            del wc, wpc
-        dep["workload_weights_ms"] = remat_ms
-        dep["note"] = ("xq_remat_attn_decode on c2 with the workload's N(0, 1/d) weights against the same call with constant "
-                       "weights: identical work and instruction stream, the time follows the operand data (clock under load)")
-        extra["remat_attn_c2_weight_data_dependence"] = dep
 
         # config 4 (GQA, B=16, L=8192, 2-bit, group 64): the naive X cache, and the latent cache of Sec. 3.3.1
         w4 = xi.C4
@@ -309,7 +293,7 @@ def main():
         c4 = filled_cache(w4, w4.G, w4.bits)
         ws4 = torch.empty(xq.xq_remat_attn_workspace_bytes(a4, w4.B, w4.L, w4.d, w4.G), dtype=torch.uint8, device=dev)
         t_c4 = timed(lambda: xq.xq_remat_attn_decode(a4, q4, wp4, lens4, xcache=c4, out=out4, workspace=ws4), n=10, warm=5)
-        extra["remat_attn_c4_gqa_naive"] = dict(remat_entry(t_c4, w4, cm.remat_attn_flops(w4.B * w4.L, w4.d, w4.Hq, w4.Hkv, w4.hd)),
+        extra["remat_attn_c4_gqa_naive"] = dict(decode_entry(t_c4, w4),
                                                 workload="c4: B=16, L=8192, d=4096, 32 query / 8 KV heads, X cache 2-bit group 64")
         del c4, wp4, ws4
         r4 = w4.Hkv * w4.hd
@@ -322,11 +306,10 @@ def main():
         lwp4 = xq.xq_prepare_weights_latent(a4, r4, w4.G, w4.bits, wfk4, wfv4)
         lws4 = torch.empty(xq.xq_remat_attn_latent_workspace_bytes(a4, w4.B, w4.L, r4, w4.G), dtype=torch.uint8, device=dev)
         t_l4 = timed(lambda: xq.xq_remat_attn_decode_latent(a4, q4, lwp4, lens4, lat4, out=out4, workspace=lws4), n=10, warm=5)
-        lfl4 = 2.0 * w4.B * w4.L * r4 * (2 * r4) + 4.0 * w4.B * w4.L * w4.Hq * w4.hd
         extra["remat_attn_c4_gqa_latent"] = dict(
-            remat_entry(t_l4, w4, lfl4),
+            ms=t_l4, **{"tokens/s/layer": w4.B * w4.L / (t_l4 * 1e-3)},
             workload="c4 layer served from the latent cache [X Uk | X Uv] (r=1024, width 2048, 2-bit, group 64); random latent "
-                     "rows and fused matrices; TFLOP/s counts the latent contraction 2*M*r*2r")
+                     "rows and fused matrices")
         del lat4, lwp4, lws4, wfk4, wfv4
         torch.cuda.empty_cache()
 
@@ -347,7 +330,7 @@ def main():
 
         t_5 = timed(c5_step, n=5, warm=2)
         extra["decode_step_c5_long_context"] = dict(
-            remat_entry(t_5, w5, cm.remat_attn_flops(w5.B * w5.L, w5.d, w5.Hq, w5.Hkv, w5.hd)),
+            decode_entry(t_5, w5),
             workload="c5: B=4, context 32768, d=4096 MHA, 2-bit group 128; append 1 token per sequence + attend")
         del c5, wp5, ws5
         torch.cuda.empty_cache()
@@ -382,7 +365,6 @@ def main():
                 xq.xq_remat_attn_decode(a3, q3, streams3[l], lens3, acc_bf16=acc3, out=out3, workspace=ws3)
 
         t_3 = timed(cl_layers, n=3, warm=1) / n3
-        fl3 = cm.remat_attn_flops(w3.B * w3.L, w3.d, w3.Hq, w3.Hkv, w3.hd)
         acc3_bytes = w3.B * w3.L * w3.d * cm.cl_accumulate_bytes_per_element(w3.delta_bits, w3.G)
         extra["cl_decode_c3_4_layers"] = {
             "workload": "c3: B=8, L=8192, d=4096 MHA, 2-bit deltas group 128; 4 distinct layers of one XQuant-CL decode step "
@@ -390,7 +372,8 @@ def main():
             "ms_per_layer": t_3, "tokens/s/layer": w3.B * w3.L / (t_3 * 1e-3),
             "accumulate_ms": t_a3, "accumulate_GB/s": acc3_bytes / t_a3 / 1e6,
             "accumulate_frac_hbm_peak": acc3_bytes / t_a3 / 1e6 / PEAK_HBM_GBS,
-            "remat_attn_ms": t_3 - t_a3, "remat_attn_frac_mfma_peak": fl3 / (t_3 - t_a3) / 1e9 / PEAK_BF16_TFLOPS}
+            "remat_attn_ms": t_3 - t_a3,
+            "remat_attn_frac_hbm_peak": (w3.B * w3.L * w3.d * 2.0 + 4.0 * w3.d * w3.Hkv * w3.hd) / (t_3 - t_a3) / 1e6 / PEAK_HBM_GBS}
         del deltas3, streams3, acc3, ws3
         torch.cuda.empty_cache()
 
@@ -414,10 +397,7 @@ def main():
             olens = [ow.L] * ow.B
             t_o = timed(lambda: xq.xq_remat_attn_decode(oattn, oq, owp, olens, xcache=ocache, out=oout, workspace=ows),
                         n=10, warm=12)    # (from an idle GPU the clock takes some 10 launches to settle)
-            oflops = 2.0 * ow.B * ow.L * ow.d * (2 * ow.Hkv * ow.hd) + 4.0 * ow.B * ow.L * ow.Hq * ow.hd
-            extra["remat_attn_" + ow.name] = {"ms": t_o, "tokens/s/layer": ow.B * ow.L / (t_o * 1e-3),
-                                              "TFLOP/s": oflops / t_o / 1e9,
-                                              "frac_mfma_peak": oflops / t_o / 1e9 / PEAK_BF16_TFLOPS}
+            extra["remat_attn_" + ow.name] = decode_entry(t_o, ow)
             del ocache, owp, ows
         # the same GQA layer served from the latent cache [X Uk | X Uv] (Sec. 3.3.1): r = 1024, cache width 2048
         ow = xi.C4
@@ -436,14 +416,12 @@ def main():
         olens = [ow.L] * ow.B
         t_l = timed(lambda: xq.xq_remat_attn_decode_latent(oattn, oq, lwp, olens, lcache, out=oout, workspace=lws),
                     n=10, warm=12)    # (from an idle GPU the clock takes some 10 launches to settle)
-        lflops = 2.0 * ow.B * ow.L * r * (2 * r) + 4.0 * ow.B * ow.L * ow.Hq * ow.hd
         ut = (torch.randn((2 * r, ow.d), device=dev, generator=gen) * ow.d ** -0.5).to(torch.bfloat16)
         xnew = torch.randn((ow.B, 1, ow.d), device=dev, generator=gen).to(torch.bfloat16)
         t_p = timed(lambda: xq.xq_latent_project(xnew, ut), n=20)
         extra["remat_attn_c4_latent"] = {"workload": "c4 layer from the latent cache (r=1024, width 2048, 2-bit, group 64); "
                                                      "random latent rows and fused matrices (timing only)",
                                          "ms": t_l, "tokens/s/layer": ow.B * ow.L / (t_l * 1e-3),
-                                         "useful_TFLOP/s": lflops / t_l / 1e9,
                                          "decode_projection_us": t_p * 1e3}
         # the paper's setting for this layer: X Uk per channel (blocks of 128 tokens, 100 of the newest in the bf16
         # window), X Uv per token
@@ -585,7 +563,7 @@ def main():
                                        "tokens/s/layer": w5.B * w5.L / (t_c5 / 64 * 1e-3)}
         del c5, wp5, ws5
 
-    traffic = K3_HBM_BYTES_PER_LAUNCH
+    traffic = DECODE_HBM_BYTES
 
     result = {
         "metric": "cached tokens rematerialized+attended/sec/layer",
@@ -602,13 +580,13 @@ def main():
         "data": "synthetic",
         "config": {"workload": "c2 Llama-2-7B-shaped decode step, one layer: d=4096, 32x128 MHA, batch 8, "
                                "context 4096, X cache 3-bit asym group 128; step = quantize+append 1 token/seq "
-                               "then fused dequant-remat-attention",
+                               "then attention over the dequantised cache",
                    "batch": B, "context": L, "d": d, "heads": Hq, "kv_heads": Hkv, "bits": bits, "group": G,
                    "settle_launches": args.settle},
-        "roofline": {"bound": "mfma", "kernel": "remat_attn_tile16_kernel<3,128,0> (events bracket xq_remat_attn_decode: + scale pre-pass and combine, ~1%)",
-                     "achieved": achieved_tflops, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved_tflops / PEAK_BF16_TFLOPS, "traffic": traffic,
-                     "traffic_measured_at_commit": K3_HBM_BYTES_MEASURED_AT,
+        "roofline": {"bound": "hbm", "kernel": "fold_query, fold_scores, fold_values, fold_output, fold_finish (events bracket xq_remat_attn_decode)",
+                     "achieved": decode_bytes / remat_ms / 1e6, "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                     "frac": decode_bytes / remat_ms / 1e6 / PEAK_HBM_GBS, "bytes_per_launch": decode_bytes, "traffic": traffic,
+                     "traffic_measured_at_commit": DECODE_HBM_BYTES_MEASURED_AT,
                      "avg_ms": remat_ms, "flops_per_launch": flops},
         "extra": extra,
     }
