@@ -760,6 +760,14 @@ __global__ __launch_bounds__(512) void fold_scores_dense_kernel(const FoldScoreA
 // token pairs, and column tile k of the product is code k of every lane's octet -- no transposition.  (Groups of 64:
 // lanes n and n + 8 exchange half octets, so that a column tile lies in one group.)  The rests are summed on the vector
 // ALU.  At the end the four token ways meet in LDS.
+//
+// Range of the fp16 parts.  Weights are taken against the range's own maximum of the row and scales against the range's
+// largest scale of the group, so the parts end 2^-40 below their product: a token is cut by at most 2^-41 of the largest
+// scale, whatever its weight.  Every row has a token of weight 1 in its tiles, so with scales within a factor 2^13 (12
+// exponents) that is 2^-28 of what the row sums up, and 2^12 such cuts in random directions reach the 2^-22 that
+// the parts carry.  A range with a wider group, a zero scale among others, a negative or a non-finite one is summed in plain
+// fp32 instead (fold_values_plain).  Measured, one token of 300 larger by 2^20 / 2^28 that no row attends to: error
+// 1.1e-5 / 1.7e-3 with one factor per group and no such limit, 5e-7 now.
 // =====================================================================================================================
 struct FoldValueArgs {
     FoldSource x;
@@ -782,12 +790,14 @@ struct FoldValueLds {
     static constexpr int GROUP_BYTES = 2 * STRIDE * 4 + (NIB ? 2 : 1) * ZI_STRIDE * 2;
     static constexpr int SZ_BYTES = GROUPS * GROUP_BYTES;
     static constexpr int P_OFF = 0, SZ_OFF = 2 * P_BYTES, M_OFF = SZ_OFF + 2 * SZ_BYTES;
-    static constexpr int N_OFF = M_OFF + 16 * RT * 4 * 17;                      // row maxima (one column per partial reader + result)
+    static constexpr int N_OFF = M_OFF + 16 * RT * 4 * 34;                      // row maxima (a column per partial reader, twice, and the results)
     static constexpr int L_OFF = N_OFF + GROUPS * 4 * 17;
     static constexpr int LOOP = L_OFF + 8 * 16 * RT * 4;
     static constexpr int RED = 8 * RT * 8 * 1024;                               // every wave's accumulators, at the end
     static constexpr int TOTAL = LOOP > RED ? LOOP : RED;
 };
+
+constexpr int FOLD_SCALE_SPREAD = 12;        // exponents between a range's scales of a group that the fp16 parts are used for
 
 // tile and range of a value workgroup
 struct FoldValuePlace { int b, rb, cblk, split, len, tile0, t0, t1; };      // [t0, t1): 256-token tiles
@@ -811,9 +821,10 @@ __device__ __forceinline__ bool fold_value_place(const FoldShape& s, bool window
     return o.t0 < o.t1;
 }
 
-// maximum of every row over the sequence's score tiles -> mrow[16 RT] (a workgroup barrier ends it)
-template <int RT>
-__device__ __forceinline__ void fold_row_maxima(const FoldShape& s, const float* mtile, int b, int rb, float* scratch, float* mrow)
+// maximum of every row over the sequence's score tiles -> mrow[16 RT] (a workgroup barrier ends it).  RANGE: over the score
+// tiles [r0, r1) of a per-token cache instead, and behind them the factor from that maximum to the sequence's
+template <int RT, bool RANGE = false>
+__device__ __forceinline__ void fold_row_maxima(const FoldShape& s, const float* mtile, int b, int rb, float* scratch, float* mrow, int r0 = 0, int r1 = 0)
 {
     constexpr int ROWS = 16 * RT, PARTS = 512 / ROWS > 16 ? 16 : 512 / ROWS;
     const int tid = threadIdx.x, row = tid % ROWS, pt = tid / ROWS;
@@ -821,11 +832,16 @@ __device__ __forceinline__ void fold_row_maxima(const FoldShape& s, const float*
     const int window0 = (coded + FOLD_VTILE - 1) / FOLD_VTILE * 2;  // tiles of the window, if it holds anything
     const int n_coded = (coded + FOLD_TILE - 1) / FOLD_TILE, nt = len > coded ? window0 + (len - coded + FOLD_TILE - 1) / FOLD_TILE : n_coded;
     if (pt < PARTS) {
-        float m = -INFINITY;
+        float m = -INFINITY, mr = -INFINITY;
         const float* src = mtile + ((long long)b * s.nrb + rb) * s.tiles * ROWS + row;
         for (int t = pt; t < nt; t += PARTS)
-            if (t < n_coded || t >= window0) m = fmaxf(m, src[(long long)t * ROWS]);
+            if (t < n_coded || t >= window0) {
+                const float v = src[(long long)t * ROWS];
+                m = fmaxf(m, v);
+                if (RANGE && t >= r0 && t < r1) mr = fmaxf(mr, v);
+            }
         scratch[pt * ROWS + row] = m;
+        if constexpr (RANGE) scratch[(PARTS + pt) * ROWS + row] = mr;
     }
     __syncthreads();
     if (tid < ROWS) {
@@ -833,8 +849,134 @@ __device__ __forceinline__ void fold_row_maxima(const FoldShape& s, const float*
 #pragma unroll
         for (int k = 1; k < PARTS; ++k) m = fmaxf(m, scratch[k * ROWS + tid]);
         mrow[tid] = m;
+        if constexpr (RANGE) {
+            float mr = scratch[PARTS * ROWS + tid];
+#pragma unroll
+            for (int k = 1; k < PARTS; ++k) mr = fmaxf(mr, scratch[(PARTS + k) * ROWS + tid]);
+            mrow[tid] = mr;
+            mrow[ROWS + tid] = mr == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mr - m);
+        }
     }
     __syncthreads();
+}
+
+// softmax denominators of a row block and split from every thread's share of them, times f (of row tid)
+template <int RT>
+__device__ __forceinline__ void fold_denominators(const FoldValueArgs& a, const FoldValuePlace& o, float l, float f, float* lp)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (lane < 16) lp[wave * 16 + lane] = l;
+    __syncthreads();
+    if (tid < 16 * RT) {
+        float t = 0.0f;
+#pragma unroll
+        for (int w = 0; w < 8; ++w)
+            if (RT == 1 || ((w >> 1) & 1) == (tid >> 4)) t += lp[w * 16 + (tid & 15)];
+        a.lsum[(((long long)o.split * a.s.nb + o.b) * a.s.nrb + o.rb) * 16 * RT + tid] = t * f;
+    }
+}
+
+// The sums of a range whose scales lie too far apart for fp16 parts: x^ and the sums in fp32, a thread per channel of
+// either slab and quarter of the rows.  Rare, and bound by the vector ALU and the LDS reads of the weights: with every
+// range on it a step over 8 x 4096 tokens of 3 bits (32 heads, d = 4096) takes 330 us (105 on the fp16 parts, 1650 when K and V
+// are rematerialised), 16 x 8191 of 2 bits in groups of 64 1160 us (300; 1790).
+template <int BITS, int G, int RT, bool NIB>
+__device__ __forceinline__ void fold_values_plain(const FoldValueArgs& a, const FoldValuePlace& o, const float* mrow, uint8_t* lds, float* lp)
+{
+    constexpr int ROWS = 4 * RT, GROUPS = 256 / G;
+    const FoldShape& s = a.s;
+    const FoldSource& x = a.x;
+    const int tid = threadIdx.x, part = tid >> 7, ch = tid & 127;
+    const bool second = o.cblk * 2 + 1 < x.n_slabs;                  // (else the first slab's codes again, and nothing stored)
+    // a channel's code lies in two bytes of its row's slab
+    const int byte = BITS == 3 ? min(ch * 3 >> 3, 46) : ch * BITS >> 3, shift = ch * BITS - 8 * byte;
+    const long long seq = s.b0 + o.b;
+    const uint8_t* code = x.codes + seq * x.cap * x.row_bytes + o.cblk * 32 * BITS + byte;
+    const int step = second ? 16 * BITS : 0;                         // from the first slab to the second
+    const long long meta = seq * x.cap * x.ng_row;
+    const int prow = RT == 2 ? ((tid >> 7) & 1) * 16 + (tid & 15) : tid & 15;
+    const float M = mrow[prow];
+    const float* psrc = a.p + (((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) * 4 * FOLD_P_TILE32<RT>;
+    const float* msrc = a.mtile + (((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) * 16 * RT + prow;
+    float4* p = reinterpret_cast<float4*>(lds);                      // 256 tokens' weights, as stored
+    float2* sz = reinterpret_cast<float2*>(lds + 8 * FOLD_P_TILE32<RT> * 4);   // and scales and zero-points: [group][token]
+    float y[2][ROWS], lacc = 0.0f;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) y[0][r] = y[1][r] = 0.0f;
+    for (int t = o.t0; t < o.t1; ++t) {
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 2 * RT; ++e) {
+            const int t128 = 2 * t + e / RT;
+            float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (t128 * FOLD_TILE < o.len) {
+                const float m = msrc[(long long)t128 * 16 * RT], f = m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - M);
+                v = *reinterpret_cast<const float4*>(psrc + (long long)t * 8 * FOLD_P_TILE32<RT> + (e * 512 + tid) * 4);
+                v.x *= f; v.y *= f; v.z *= f; v.w *= f;
+                lacc += (v.x + v.y) + (v.z + v.w);
+            }
+            p[e * 512 + tid] = v;
+        }
+#pragma unroll
+        for (int e = 0; e < GROUPS / 2; ++e) {
+            const int idx = e * 512 + tid, g = min(o.cblk * GROUPS + (idx >> 8), x.ng - 1) >> x.meta_shift;
+            const long long at = meta + (long long)min(t * FOLD_VTILE + (idx & 255), o.len - 1) * x.ng_row + g;
+            sz[idx] = make_float2(bf16_bits_to_f32(x.scale[at]), bf16_bits_to_f32(x.zero[at]));
+        }
+        __syncthreads();
+        const int ntok = min(o.len - t * FOLD_VTILE, FOLD_VTILE);
+        const float2* szg = sz + ch / G * 256;
+        for (int k = 0; k < (ntok + 31) / 32 * 4; ++k) {             // [tokens / 32][half of the slots][pair of quarters]: 8 tokens at a time
+            const int k32 = k >> 2, h = (k >> 1) & 1, q0 = (k & 1) * 2;
+            float xv[2][2][4];
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int at = k32 * 32 + 4 * (4 * h + i) + q0 + q;
+                    const uint8_t* c = code + (long long)min(t * FOLD_VTILE + at, o.len - 1) * x.row_bytes;
+#pragma unroll
+                    for (int n = 0; n < 2; ++n) {
+                        uint16_t v;
+                        if constexpr (BITS == 3) __builtin_memcpy(&v, c + n * step, 2);
+                        else v = c[n * step];
+                        const float num = (float)((v >> shift) & ((1u << BITS) - 1u));
+                        const float2 m = szg[n * (128 / G) * 256 + at];
+                        xv[n][q][i] = NIB && (ch & 1) ? num * m.x : __builtin_fmaf(num, m.x, m.y);   // (8-bit caches: the zero-point goes with the low nibble)
+                    }
+                }
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int r = 0; r < ROWS; ++r) {
+                    const int row = part * ROWS + r;
+                    const float4 w = p[((k32 * RT + (row >> 4)) * 2 + h) * 64 + (row & 15) + 16 * (q0 + q)];
+#pragma unroll
+                    for (int n = 0; n < 2; ++n) {
+                        y[n][r] = __builtin_fmaf(w.x, xv[n][q][0], y[n][r]);
+                        y[n][r] = __builtin_fmaf(w.y, xv[n][q][1], y[n][r]);
+                        y[n][r] = __builtin_fmaf(w.z, xv[n][q][2], y[n][r]);
+                        y[n][r] = __builtin_fmaf(w.w, xv[n][q][3], y[n][r]);
+                    }
+                }
+        }
+    }
+    if (o.cblk == 0) fold_denominators<RT>(a, o, lacc, tid < 16 * RT ? mrow[16 * RT + tid] : 0.0f, lp);
+    const long long yrow0 = ((long long)o.split * s.nb + o.b) * s.R;
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const int local = part * ROWS + r, row = o.rb * 16 * RT + local;
+            if ((n == 0 || second) && row < s.R)
+                a.y[(yrow0 + row) * (x.n_slabs * 128) + (o.cblk * 2 + n) * 128 + ch] = y[n][r] * mrow[16 * RT + local];
+        }
+    for (int idx = tid; idx < 16 * RT * GROUPS; idx += 512) {        // (the zero-points are in y)
+        const int row = o.rb * 16 * RT + idx / GROUPS, g = o.cblk * GROUPS + idx % GROUPS;
+        if (row < s.R && g < x.ng) a.yz[(yrow0 + row) * x.ng + g] = 0.0f;
+    }
 }
 
 template <int BITS, int G, int RT, bool NIB>
@@ -857,37 +999,52 @@ __global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
     const uint16_t* sbase = x.scale + seq * x.cap * x.ng_row;
     const uint16_t* zbase = x.zero + seq * x.cap * x.ng_row;
 
-    float* mrow = reinterpret_cast<float*>(lds + L::M_OFF) + 16 * 16 * RT;
+    float* mrow = reinterpret_cast<float*>(lds + L::M_OFF) + 32 * 16 * RT;
     float* ginv = reinterpret_cast<float*>(lds + L::N_OFF) + 16 * NG;
     // power of two per group that brings the range's largest scale below 2^15 (the fp16 parts of weight times scale)
     {
-        uint32_t mx[NG];
+        typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+        auto max2 = [](uint32_t u, uint32_t v) XQ_INLINE_LAMBDA {
+            return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, u), __builtin_bit_cast(u16x2, v)));
+        };
+        uint32_t mx[NG];                                            // largest scale; above it the complement of the smallest
 #pragma unroll
         for (int g = 0; g < NG; ++g) mx[g] = 0u;
         const int tend = min(o.len, o.t1 * FOLD_VTILE);
         for (int t = o.t0 * FOLD_VTILE + tid; t < tend; t += 512) {
 #pragma unroll
             for (int g = 0; g < NG; ++g)
-                if (g0 + g < x.ng) mx[g] = max(mx[g], (uint32_t)sbase[(long long)t * x.ng_row + ((g0 + g) >> x.meta_shift)]);
+                if (g0 + g < x.ng) {
+                    const uint32_t v = sbase[(long long)t * x.ng_row + ((g0 + g) >> x.meta_shift)];
+                    mx[g] = max2(mx[g], perm_bytes(v, v, 0x01000100u) ^ 0xFFFF0000u);
+                }
         }
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
             uint32_t m = mx[g];
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
+            for (int off = 32; off > 0; off >>= 1) m = max2(m, (uint32_t)__shfl_xor((int)m, off));
             if (lane == 0) reinterpret_cast<uint32_t*>(lds + L::N_OFF)[wave * NG + g] = m;
         }
-    }
-    fold_row_maxima<RT>(s, a.mtile, o.b, o.rb, reinterpret_cast<float*>(lds + L::M_OFF), mrow);
-    if (tid < NG) {
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(lds + L::N_OFF);
-        uint32_t m = 0u;
+        fold_row_maxima<RT, true>(s, a.mtile, o.b, o.rb, reinterpret_cast<float*>(lds + L::M_OFF), mrow, 2 * o.t0, 2 * o.t1);
+        if (tid < NG) {
+            const uint32_t* src = reinterpret_cast<const uint32_t*>(lds + L::N_OFF);
+            uint32_t m = 0u;
 #pragma unroll
-        for (int w = 0; w < 8; ++w) m = max(m, src[w * NG + tid]);
-        // largest scale < 2^(e - 126): times 2^(141 - e) it is below 2^15
-        ginv[tid] = m ? ldexpf(1.0f, min(141 - (int)(m >> 7), 120)) : 1.0f;
+            for (int w = 0; w < 8; ++w) m = max2(m, src[w * NG + tid]);
+            const int top = (int)(m & 0xFFFFu) >> 7, low = (int)(0xFFFFu - (m >> 16)) >> 7;
+            // largest scale < 2^(top - 126): times 2^(141 - top) it is below 2^15.  (0: for fold_values_plain.)
+            ginv[tid] = top >= 255 || top - low > FOLD_SCALE_SPREAD ? 0.0f : ldexpf(1.0f, min(141 - top, 120));
+        }
     }
     __syncthreads();
+    bool wide = false;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) wide |= ginv[g] == 0.0f;
+    if (wide) {
+        fold_values_plain<BITS, G, RT, NIB>(a, o, mrow, lds, reinterpret_cast<float*>(lds + L::L_OFF));
+        return;
+    }
 
     // ---- staging: thread -> softmax weights (always of the same row) and (token, group) pairs
     constexpr int NP = 2 * RT;                                      // 16-byte pieces per thread and 256 tokens
@@ -1137,21 +1294,12 @@ __global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
     __syncthreads();
 
     // softmax denominators: once per row block and split
-    if (o.cblk == 0) {
-        float l = lacc;
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
-        float* lp = reinterpret_cast<float*>(lds + L::L_OFF);
-        if (q == 0) lp[wave * 16 + c16] = l;
-        __syncthreads();
-        if (tid < 16 * RT) {
-            float t = 0.0f;
+    if (o.cblk == 0) fold_denominators<RT>(a, o, lacc, tid < 16 * RT ? mrow[16 * RT + tid] : 0.0f, reinterpret_cast<float*>(lds + L::L_OFF));
+    // row factors of what this thread stores below (the sums overwrite them)
+    const float zfac = mrow[16 * RT + (tid / (16 * GPS)) % RT * 16 + (tid & 15)];
+    float yfac[4];
 #pragma unroll
-            for (int w = 0; w < 8; ++w)
-                if (RT == 1 || ((w >> 1) & 1) == (tid >> 4)) t += lp[w * 16 + (tid & 15)];
-            a.lsum[(((long long)o.split * s.nb + o.b) * s.nrb + o.rb) * 16 * RT + tid] = t;
-        }
-    }
+    for (int r = 0; r < 4; ++r) yfac[r] = mrow[16 * RT + ((tw >> 1) % RT) * 16 + 4 * q + r];
     // the four token ways meet in LDS: rests first, then the accumulators
     const float inv_g[2] = {ginv[sw * GPS], ginv[sw * GPS + GPS - 1]};
     __syncthreads();
@@ -1167,13 +1315,14 @@ __global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
         }
     __syncthreads();
     const long long yrow0 = ((long long)o.split * s.nb + o.b) * s.R;
-    for (int idx = tid; idx < 2 * RT * GPS * 16; idx += 512) {
+    static_assert(2 * RT * GPS * 16 <= 512, "one rest sum per thread");
+    if (const int idx = tid; idx < 2 * RT * GPS * 16) {
         const int r16 = idx & 15, g = (idx >> 4) % GPS, rt = (idx / (16 * GPS)) % RT, w = idx / (16 * GPS * RT);
         const int row = o.rb * 16 * RT + rt * 16 + r16, gg = g0 + w * GPS + g;
         float z = 0.0f;
 #pragma unroll
         for (int k = 0; k < 4; ++k) z += red[(((2 * k + w) * RT + rt) * GPS + g) * 16 + r16];
-        if (row < s.R && gg < x.ng) a.yz[(yrow0 + row) * x.ng + gg] = z;
+        if (row < s.R && gg < x.ng) a.yz[(yrow0 + row) * x.ng + gg] = z * zfac;
     }
     __syncthreads();
     float4* acc_lds = reinterpret_cast<float4*>(lds);
@@ -1204,7 +1353,7 @@ __global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
             const int row = o.rb * 16 * RT + rt * 16 + 4 * q + r;
             if (row < s.R)
                 *reinterpret_cast<float4*>(a.y + (yrow0 + row) * (x.n_slabs * 128) + slab * 128 + ch) =
-                    make_float4(t[0][r] * f, t[1][r] * f, t[2][r] * f, t[3][r] * f);
+                    make_float4(t[0][r] * (f * yfac[r]), t[1][r] * (f * yfac[r]), t[2][r] * (f * yfac[r]), t[3][r] * (f * yfac[r]));
         }
     }
 }
@@ -1341,19 +1490,7 @@ __device__ __forceinline__ void fold_values_dense(const FoldValueArgs& a, const 
         __syncthreads();
     }
     if (o.cblk == 0) {
-        float l = lacc;
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
-        float* lp = reinterpret_cast<float*>(lds + L::L_OFF);
-        if (q == 0) lp[wave * 16 + c16] = l;
-        __syncthreads();
-        if (tid < 16 * RT) {
-            float t = 0.0f;
-#pragma unroll
-            for (int w = 0; w < 8; ++w)
-                if (RT == 1 || ((w >> 1) & 1) == (tid >> 4)) t += lp[w * 16 + (tid & 15)];
-            a.lsum[(((long long)o.split * s.nb + o.b) * s.nrb + o.rb) * 16 * RT + tid] = t;
-        }
+        fold_denominators<RT>(a, o, lacc, 1.0f, reinterpret_cast<float*>(lds + L::L_OFF));
         __syncthreads();
     }
     float4* acc_lds = reinterpret_cast<float4*>(lds);

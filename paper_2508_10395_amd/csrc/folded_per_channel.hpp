@@ -436,19 +436,7 @@ __global__ __launch_bounds__(512) void fold_values_pc_kernel(const FoldValueArgs
         __syncthreads();
     }
     if (o.cblk == 0) {
-        float l = lacc;
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
-        float* lp = reinterpret_cast<float*>(lds + L::L_OFF);
-        if (q == 0) lp[wave * 16 + c16] = l;
-        __syncthreads();
-        if (tid < 16 * RT) {
-            float t = 0.0f;
-#pragma unroll
-            for (int w = 0; w < 8; ++w)
-                if (RT == 1 || ((w >> 1) & 1) == (tid >> 4)) t += lp[w * 16 + (tid & 15)];
-            a.lsum[(((long long)o.split * s.nb + o.b) * s.nrb + o.rb) * 16 * RT + tid] = t;
-        }
+        fold_denominators<RT>(a, o, lacc, 1.0f, reinterpret_cast<float*>(lds + L::L_OFF));
         __syncthreads();
     }
     // the four token ways meet in LDS; token way tw sums half a row tile (rt, four column tiles) of its slab

@@ -25,9 +25,10 @@ def xq():
     return m
 
 
-def _run(xq, w, bits, G, lens, x_bits=None, workspaces=(None,), pairs=None):
+def _run(xq, w, bits, G, lens, x_bits=None, workspaces=(None,), pairs=None, wk=None, scale_sign=None):
     x = xi.gen_x(w) if x_bits is None else x_bits
-    wk, wv = xi.gen_weights(w)
+    wk0, wv = xi.gen_weights(w)
+    wk = wk0 if wk is None else wk
     q = xi.gen_q(w)
     attn = xq.XQAttn(w.Hq, w.Hkv, w.hd, w.hd ** -0.5)
     pairs = pairs or [(b, h) for b in range(w.B) for h in sorted({0, 1, w.Hq // 2, w.Hq - 1})]
@@ -43,6 +44,9 @@ def _run(xq, w, bits, G, lens, x_bits=None, workspaces=(None,), pairs=None):
         xq.xq_quantize_append(cache, bits_to_torch(x), [0] * w.B)
         src = dict(xcache=cache)
         packed, scale, zero = oracle_cache(x, G, bits, seqs=[b for b, _ in pairs])
+        if scale_sign is not None:                           # rows whose stored scales change their sign
+            scale[:, scale_sign] ^= 0x8000
+            cache.scale[:, scale_sign] = -cache.scale[:, scale_sign]
         ref = xo.remat_attn_pairs(packed=packed, scale=scale, zero=zero, G=G, bits=bits, **kw)
     wprep = xq.xq_prepare_weights(attn, w.d, G, bits, bits_to_torch(wk), bits_to_torch(wv))
     for n in workspaces:
@@ -89,6 +93,55 @@ def test_scales_of_every_magnitude(xq):
     x[0, 1::3, 512:640] += 100.0
     x[0, :, 640:768] *= 1e-3
     _run(xq, w, 3, 128, [300], x_bits=xi.to_bf16_bits(x))
+
+
+CODED = [(2, 64), (2, 128), (3, 64), (3, 128), (4, 64), (4, 128), (8, 64), (8, 128)]
+
+
+@pytest.mark.parametrize("bits,G", CODED)
+@pytest.mark.parametrize("Hq,Hkv", [(16, 16), (32, 8)])
+def test_a_few_rows_far_larger_than_the_others(xq, bits, G, Hq, Hkv):
+    """Rows 2^28 times larger than their neighbours: heads that attend to them see little else, the others must not lose the
+    ordinary rows' digits to them.  They lie in different token ranges of the value kernel, one range has none."""
+    w = xi.C2.scaled(B=2, L=900, d=2304, Hq=Hq, Hkv=Hkv, n_outlier=23)
+    x = xi.from_bf16_bits(xi.gen_x(w)).copy()
+    x[0, [5, 300]] *= 2.0 ** 28
+    x[1, 77] *= 2.0 ** 36
+    x[1, 79] *= 2.0 ** -40
+    _run(xq, w, bits, G, [900, 130], x_bits=xi.to_bf16_bits(x), pairs=[(b, h) for b in range(2) for h in range(Hq)])
+
+
+def _small_weight_rows(w, k, nats, rows):
+    """X and Wk for which `rows` (of sequence 0) score 0 and all others about `nats`, the former holding nothing but channels
+    128-255 (which no key sees) 2^k times larger: they count as much as the others where 2^k exp(-nats) is about 1."""
+    x = xi.from_bf16_bits(xi.gen_x(w)).copy() * 0.1
+    wk = xi.from_bf16_bits(xi.gen_weights(w)[0]).copy()
+    q = xi.from_bf16_bits(xi.gen_q(w))[0]
+    wk[128:256] = 0.0
+    for h in range(w.Hkv):
+        v = q[h * (w.Hq // w.Hkv)]
+        wk[0, h * w.hd:(h + 1) * w.hd] = v / (v @ v) * w.hd ** 0.5 * nats
+    x[0, :, 0] = 1.0
+    big = x[0, rows, 128:256] * 10.0 * 2.0 ** k
+    x[0, rows] = 0.0
+    x[0, rows, 128:256] = big
+    return xi.to_bf16_bits(x), xi.to_bf16_bits(wk)
+
+
+@pytest.mark.parametrize("bits,G", CODED)
+@pytest.mark.parametrize("rows", [[77, 690], list(range(256, 512))])
+def test_large_rows_of_small_weight(xq, bits, G, rows):
+    """The softmax weight of a row may be 2^-40 and the row still count: single rows, and a whole token range of them."""
+    w = xi.C2.scaled(B=1, L=700, d=2304, Hq=16, Hkv=16, n_outlier=0)
+    x, wk = _small_weight_rows(w, 40, 28.0, rows)
+    _run(xq, w, bits, G, [700], x_bits=x, wk=wk, pairs=[(0, h) for h in range(w.Hq)])
+
+
+@pytest.mark.parametrize("bits,G", CODED)
+def test_scales_of_either_sign(xq, bits, G):
+    """x^ = code scale + zero holds for a negative scale too."""
+    w = xi.C2.scaled(B=1, L=600, d=2304, Hq=16, Hkv=16, n_outlier=0)
+    _run(xq, w, bits, G, [600], scale_sign=[3, 299], pairs=[(0, h) for h in range(w.Hq)])
 
 
 @pytest.mark.parametrize("bits,G", [(2, 64), (3, 128), (4, 64)])
