@@ -23,6 +23,7 @@ struct FoldShape {
     int tiles;                           // score tiles (128 tokens) per sequence in the arrays, even
     int splits;                          // token splits in the arrays of the value kernel
     int block;                           // per-channel caches: tokens per block (else 0)
+    int mhalf;                           // softmax weights and maxima per 128 tokens (0) or 64 (1: per-channel blocks of 64)
     BatchI32 len;                        // of the call's sequences
 };
 
@@ -333,7 +334,7 @@ struct FoldScoreArgs {
     const uint8_t* u;
     const float* rowfac;
     float* p;                            // [nb][nrb][tiles][4][FOLD_P_TILE32]
-    float* mtile;                        // [nb][nrb][tiles][16 RT]
+    float* mtile;                        // [nb][nrb][tiles << mhalf][16 RT]
     int u_slab, sw_log2;
     FoldSource window;                   // per-channel caches: the window's rows, its folded queries and workgroups
     const uint8_t* u_window;
@@ -414,17 +415,24 @@ __device__ __forceinline__ void fold_scores_finish(const FoldShape& s, const flo
         }
     __syncthreads();
     if (!live) return;
+    // maximum of the tile, or of the wave's half of it (eight slab ways then: a wave's tile16s lie in one half)
+    const int i0 = o.sw * share, mrow0 = (o.tile0 + o.tile) << s.mhalf | (s.mhalf ? i0 >> 2 : 0);
+    const bool stores = c16 == 0 && (s.mhalf ? (i0 & 3) == 0 : i0 == 0);
     float Mu[RT][4];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int row = rt * 16 + 4 * q + r;
-            float M = mx[row];
+            float h0 = mx[row], h1 = mx[4 * 16 * RT + row];
 #pragma unroll
-            for (int k = 1; k < 8; ++k) M = fmaxf(M, mx[k * 16 * RT + row]);
+            for (int k = 1; k < 4; ++k) {
+                h0 = fmaxf(h0, mx[k * 16 * RT + row]);
+                h1 = fmaxf(h1, mx[(4 + k) * 16 * RT + row]);
+            }
+            const float M = s.mhalf ? (i0 & 4 ? h1 : h0) : fmaxf(h0, h1);
             Mu[rt][r] = M == -INFINITY ? 0.0f : M;                  // nothing visible: all weights 0
-            if (o.sw == 0 && c16 == 0) mtile_all[(((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0 + o.tile) * 16 * RT + row] = M;
+            if (stores) mtile_all[((((long long)o.b * s.nrb + o.rb) * s.tiles << s.mhalf) + mrow0) * 16 * RT + row] = M;
         }
     for (int j = 0; j < share; ++j) {
         const int i16 = o.sw * share + j, t32 = (i16 & 1) * 16 + c16, slot = t32 >> 2, qd = t32 & 3;
@@ -821,27 +829,30 @@ __device__ __forceinline__ bool fold_value_place(const FoldShape& s, bool window
     return o.t0 < o.t1;
 }
 
-// maximum of every row over the sequence's score tiles -> mrow[16 RT] (a workgroup barrier ends it).  RANGE: over the score
-// tiles [r0, r1) of a per-token cache instead, and behind them the factor from that maximum to the sequence's
-template <int RT, bool RANGE = false>
+// maximum of every row over the sequence's score tiles -> mrow[16 RT] (a workgroup barrier ends it).  FOLD_RANGE_TOP:
+// over the stored maxima [r0, r1) instead, and behind them the factor from that maximum to the sequence's.  FOLD_RANGE_LOW:
+// behind them the lowest of the stored maxima [r0, r1)
+enum { FOLD_RANGE_TOP = 1, FOLD_RANGE_LOW = 2 };
+template <int RT, int RANGE = 0>
 __device__ __forceinline__ void fold_row_maxima(const FoldShape& s, const float* mtile, int b, int rb, float* scratch, float* mrow, int r0 = 0, int r1 = 0)
 {
     constexpr int ROWS = 16 * RT, PARTS = 512 / ROWS > 16 ? 16 : 512 / ROWS;
     const int tid = threadIdx.x, row = tid % ROWS, pt = tid / ROWS;
     const int len = s.len.v[s.b0 + b], coded = s.block ? len / s.block * s.block : len;
-    const int window0 = (coded + FOLD_VTILE - 1) / FOLD_VTILE * 2;  // tiles of the window, if it holds anything
-    const int n_coded = (coded + FOLD_TILE - 1) / FOLD_TILE, nt = len > coded ? window0 + (len - coded + FOLD_TILE - 1) / FOLD_TILE : n_coded;
+    const int unit = FOLD_TILE >> s.mhalf;                          // tokens of a stored maximum
+    const int window0 = (coded + FOLD_VTILE - 1) / FOLD_VTILE * (FOLD_VTILE / unit);  // maxima of the window, if it holds anything
+    const int n_coded = (coded + unit - 1) / unit, nt = len > coded ? window0 + (len - coded + unit - 1) / unit : n_coded;
     if (pt < PARTS) {
-        float m = -INFINITY, mr = -INFINITY;
-        const float* src = mtile + ((long long)b * s.nrb + rb) * s.tiles * ROWS + row;
+        float m = -INFINITY, mr = RANGE == FOLD_RANGE_LOW ? INFINITY : -INFINITY;
+        const float* src = mtile + (((long long)b * s.nrb + rb) * s.tiles << s.mhalf) * ROWS + row;
         for (int t = pt; t < nt; t += PARTS)
             if (t < n_coded || t >= window0) {
                 const float v = src[(long long)t * ROWS];
                 m = fmaxf(m, v);
-                if (RANGE && t >= r0 && t < r1) mr = fmaxf(mr, v);
+                if (RANGE && t >= r0 && t < r1) mr = RANGE == FOLD_RANGE_LOW ? fminf(mr, v == -INFINITY ? INFINITY : v) : fmaxf(mr, v);
             }
         scratch[pt * ROWS + row] = m;
-        if constexpr (RANGE) scratch[(PARTS + pt) * ROWS + row] = mr;
+        if constexpr (RANGE != 0) scratch[(PARTS + pt) * ROWS + row] = mr;
     }
     __syncthreads();
     if (tid < ROWS) {
@@ -849,12 +860,19 @@ __device__ __forceinline__ void fold_row_maxima(const FoldShape& s, const float*
 #pragma unroll
         for (int k = 1; k < PARTS; ++k) m = fmaxf(m, scratch[k * ROWS + tid]);
         mrow[tid] = m;
-        if constexpr (RANGE) {
+        if constexpr (RANGE != 0) {
             float mr = scratch[PARTS * ROWS + tid];
 #pragma unroll
-            for (int k = 1; k < PARTS; ++k) mr = fmaxf(mr, scratch[(PARTS + k) * ROWS + tid]);
-            mrow[tid] = mr;
-            mrow[ROWS + tid] = mr == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mr - m);
+            for (int k = 1; k < PARTS; ++k) {
+                const float v = scratch[(PARTS + k) * ROWS + tid];
+                mr = RANGE == FOLD_RANGE_LOW ? fminf(mr, v) : fmaxf(mr, v);
+            }
+            if constexpr (RANGE == FOLD_RANGE_TOP) {
+                mrow[tid] = mr;
+                mrow[ROWS + tid] = mr == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mr - m);
+            } else {
+                mrow[ROWS + tid] = mr;
+            }
         }
     }
     __syncthreads();
@@ -1026,7 +1044,7 @@ __global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
             for (int off = 32; off > 0; off >>= 1) m = max2(m, (uint32_t)__shfl_xor((int)m, off));
             if (lane == 0) reinterpret_cast<uint32_t*>(lds + L::N_OFF)[wave * NG + g] = m;
         }
-        fold_row_maxima<RT, true>(s, a.mtile, o.b, o.rb, reinterpret_cast<float*>(lds + L::M_OFF), mrow, 2 * o.t0, 2 * o.t1);
+        fold_row_maxima<RT, FOLD_RANGE_TOP>(s, a.mtile, o.b, o.rb, reinterpret_cast<float*>(lds + L::M_OFF), mrow, 2 * o.t0, 2 * o.t1);
         if (tid < NG) {
             const uint32_t* src = reinterpret_cast<const uint32_t*>(lds + L::N_OFF);
             uint32_t m = 0u;
@@ -1387,7 +1405,8 @@ __device__ __forceinline__ void fold_values_dense(const FoldValueArgs& a, const 
     const int prow = RT == 2 ? ((wave >> 1) & 1) * 16 + c16 : c16;
     const float M = mrow[prow];
     const float* psrc = a.p + (((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) * 4 * FOLD_P_TILE32<RT>;
-    const float* msrc = a.mtile + (((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) * 16 * RT + prow;
+    // (maxima per 64 tokens: the window of blocks of 64 holds fewer, all in the first half of its first tile)
+    const float* msrc = a.mtile + ((((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) << s.mhalf) * 16 * RT + prow;
     float4 pv[NP];
     float fm[2];
     auto load_stage = [&](int t) XQ_INLINE_LAMBDA {
@@ -1395,7 +1414,7 @@ __device__ __forceinline__ void fold_values_dense(const FoldValueArgs& a, const 
         for (int hf = 0; hf < 2; ++hf) {
             const int t128 = 2 * t + hf;
             const bool ok = t128 * FOLD_TILE < o.len;
-            fm[hf] = ok ? msrc[(long long)t128 * 16 * RT] : -INFINITY;
+            fm[hf] = ok ? msrc[(long long)(t128 << s.mhalf) * 16 * RT] : -INFINITY;
 #pragma unroll
             for (int k = 0; k < RT; ++k) {
                 const int e = hf * RT + k;
@@ -1769,7 +1788,7 @@ static FoldPlan fold_plan(const FoldProblem& f, int nb, int max_len, int splits)
     L.chunk_slabs = std::max(1, std::min(FO_MAX_SLABS, f.n_slabs_v * f.Hkv * colblocks / 256));
     L.chunks = (f.n_slabs_v + L.chunk_slabs - 1) / L.chunk_slabs;
     L.p = align256(std::max((size_t)nb * L.nrb * L.tiles * 4 * (L.rt * 512) * 4, (size_t)L.chunks * nb * R * 512));
-    L.mtile = align256((size_t)nb * L.nrb * L.tiles * rpb * 4);
+    L.mtile = align256(((size_t)nb * L.nrb * L.tiles * rpb * 4) << (f.block == 64));
     L.rowfac = align256((size_t)nb * L.nrb * rpb * 4);
     L.lsum = align256((size_t)splits * nb * L.nrb * rpb * 4);
     L.uy = align256(std::max((size_t)nb * L.nrb * f.n_slabs_k * L.u_slab, (size_t)splits * nb * R * f.n_slabs_v * 512));
@@ -1898,7 +1917,7 @@ hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSo
         FoldShape sh{};
         sh.b0 = b0; sh.nb = std::min(nb, B - b0); sh.T = f.T; sh.Hq = f.Hq; sh.Hkv = f.Hkv; sh.R = f.T * f.Hq; sh.nrb = L.nrb;
         sh.tiles = L.tiles; sh.splits = L.splits; sh.len = len;
-        sh.block = f.block;
+        sh.block = f.block; sh.mhalf = f.block == 64;
         const int coded_splits = L.splits - (f.block ? 1 : 0);
         const int colblocks = (sh.nb * f.T * gq + 31) / 32;
         {

@@ -6,10 +6,16 @@
 // that only factors more than 2^-29 below the block's largest are rounded, at 2^-40 of it), so every product of a tile goes
 // straight into its scores; sum_c u[c] z[c] and sum_c u[c] s[c] are one more token tile, whose first columns hold z and s.
 // Values: the codes are summed with the softmax weights alone, and every 64 tokens the sums are taken times the block's scales
-// into y, z + c0 s times the sum of the weights (one more column tile, of ones) along with them.
+// into y, z + c0 s times the sum of the weights (one more column tile, of ones) along with them.  The weights are cut to fp16
+// hi + lo, with parts down to 2^-40, against the sequence's maximum of their row.  A block whose own maximum lies more than 2^16
+// below that would keep too few digits there, and it may yet count, being far larger than the others: a range that holds such
+// a block cuts the weights as they are stored, against the maximum of their own block (128 or 64 tokens, FoldShape::mhalf),
+// and multiplies the rest of the factor in with the scales, in fp32.  So a block's largest weight is cut to 2^-25 of itself or
+// better (a block 2^30 larger at weights of 2^-30 was off by 2e-4 without).  Both loops take as
+// long (a step of 8 x 4077 tokens 114 us either way); one loop that always does the latter, unrolled alone, ran 3 us slower.
 // Bound by issue and by the latency of the loads, as the per-token kernels.  8 sequences of up to 4077 tokens, 3 bits, 32 KV
-// heads, d = 4096: scores 40 us, values 43 us with the windows (36 + 32 and 34 + 11 in launches of their own); the step 1432 us
-// when K and V were rematerialised, 124 now.
+// heads, d = 4096: scores 39 us, values 43 us with the windows (36 + 32 and 34 + 11 in launches of their own); the step 1432 us
+// when K and V were rematerialised, 126 now.
 #pragma once
 
 template <int BITS>
@@ -255,7 +261,9 @@ template <int RT>
 struct FoldValuePcLds {
     static constexpr int W_BYTES = 8 * RT * 2 * 1024;                           // [tile32][rt][hi, lo][lane 64][16 B]
     static constexpr int M_OFF = 2 * W_BYTES;
-    static constexpr int L_OFF = M_OFF + 16 * RT * 4 * 17;
+    static constexpr int F_BYTES = 4 * 16 * RT * 4;                             // factors of a tile's rows, per 64 tokens
+    static constexpr int F_OFF = M_OFF + 16 * RT * 4 * 34;
+    static constexpr int L_OFF = F_OFF + 2 * F_BYTES;
     static constexpr int LOOP = L_OFF + 8 * 16 * RT * 4;
     static constexpr int RED = 8 * RT * 8 * 1024;
     static constexpr int TOTAL = LOOP > RED ? LOOP : RED;
@@ -281,56 +289,57 @@ __global__ __launch_bounds__(512) void fold_values_pc_kernel(const FoldValueArgs
     const int slab = o.cblk * 2 + sw;
     const bool live = slab < x.n_slabs;
     const long long seq = s.b0 + o.b;
-    float* mrow = reinterpret_cast<float*>(lds + L::M_OFF) + 16 * 16 * RT;
-    fold_row_maxima<RT>(s, a.mtile, o.b, o.rb, reinterpret_cast<float*>(lds + L::M_OFF), mrow);
+    float* mrow = reinterpret_cast<float*>(lds + L::M_OFF) + 32 * 16 * RT;
+    fold_row_maxima<RT, FOLD_RANGE_LOW>(s, a.mtile, o.b, o.rb, reinterpret_cast<float*>(lds + L::M_OFF), mrow, (2 * o.t0) << s.mhalf, (2 * o.t1) << s.mhalf);
+    // does the range hold a block far below its row's maximum?
+    const int any_row = lane % (16 * RT);
+    const bool apart = __ballot(mrow[16 * RT + any_row] - mrow[any_row] < -16.0f && o.rb * 16 * RT + any_row < s.R) != 0;
 
     constexpr int NP = 2 * RT;
     constexpr float UP = 32768.0f;                                  // the weights are at most 1: fp16 parts below 2^15
+    const float* psrc = a.p + (((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) * 4 * FOLD_P_TILE32<RT>;
     const int prow = RT == 2 ? ((wave >> 1) & 1) * 16 + c16 : c16;
     const float M = mrow[prow];
-    const float* psrc = a.p + (((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) * 4 * FOLD_P_TILE32<RT>;
-    const float* msrc = a.mtile + (((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) * 16 * RT + prow;
+    const float* msrc = a.mtile + ((((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) << s.mhalf) * 16 * RT + prow;
     float4 pv[NP];
-    float fm[2];
+    float fm[NP];
     auto load_stage = [&](int t) XQ_INLINE_LAMBDA {
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-            const int t128 = 2 * t + hf;
-            const bool ok = t128 * FOLD_TILE < o.len;
-            fm[hf] = ok ? msrc[(long long)t128 * 16 * RT] : -INFINITY;
-#pragma unroll
-            for (int k = 0; k < RT; ++k) {
-                const int e = hf * RT + k;
-                pv[e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                if (ok) pv[e] = *reinterpret_cast<const float4*>(psrc + (long long)t * 8 * FOLD_P_TILE32<RT> + (e * 512 + tid) * 4);
-            }
+        for (int e = 0; e < NP; ++e) {
+            const int g64 = RT == 2 ? e : 2 * e + (wave >> 2);
+            fm[e] = t * FOLD_VTILE + g64 * 64 < o.len ? msrc[(long long)((4 * t + g64) >> (1 - s.mhalf)) * 16 * RT] : -INFINITY;
+            pv[e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if ((2 * t + e / RT) * FOLD_TILE < o.len) pv[e] = *reinterpret_cast<const float4*>(psrc + (long long)t * 8 * FOLD_P_TILE32<RT> + (e * 512 + tid) * 4);
         }
     };
     float lacc = 0.0f;
-    auto write_stage = [&](int buf) XQ_INLINE_LAMBDA {
+    // (a piece belongs to one row and 64 tokens: the first lanes of four waves, RT = 1, or two hold all the factors)
+    auto write_stage = [&](auto APART, int buf) XQ_INLINE_LAMBDA {
+        constexpr bool apart = decltype(APART)::value;
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-            const float f = fm[hf] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(fm[hf] - M);
-#pragma unroll
-            for (int k = 0; k < RT; ++k) {
-                const int e = hf * RT + k;
-                const float v[4] = {pv[e].x * f, pv[e].y * f, pv[e].z * f, pv[e].w * f};
-                lacc += (v[0] + v[1]) + (v[2] + v[3]);
-                uint32_t hi[2], lo[2];
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const float w0 = v[2 * i] * UP, w1 = v[2 * i + 1] * UP;
-                    const xq_f16x2 hh = {(_Float16)w0, (_Float16)w1};
-                    const xq_f16x2 ll = {(_Float16)(w0 - (float)hh.x), (_Float16)(w1 - (float)hh.y)};
-                    hi[i] = __builtin_bit_cast(uint32_t, hh);
-                    lo[i] = __builtin_bit_cast(uint32_t, ll);
-                }
-                // piece e 512 + tid of [tile32][rt][half of the slots][lane]
-                const int idx = e * 512 + tid, hs = (idx >> 6) & 1, blk = idx >> 7;
-                uint8_t* dst = lds + buf * L::W_BYTES + blk * 2048 + lane * 16 + hs * 8;
-                *reinterpret_cast<uint2*>(dst) = make_uint2(hi[0], hi[1]);
-                *reinterpret_cast<uint2*>(dst + 1024) = make_uint2(lo[0], lo[1]);
+        for (int e = 0; e < NP; ++e) {
+            const float f = fm[e] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(fm[e] - M);
+            if constexpr (apart) {
+                if (q == 0 && (RT == 2 ? wave == 0 || wave == 2 : (wave & 3) == 0))
+                    reinterpret_cast<float*>(lds + L::F_OFF + buf * L::F_BYTES)[(RT == 2 ? e : 2 * e + (wave >> 2)) * 16 * RT + prow] = f;
+                lacc += ((pv[e].x + pv[e].y) + (pv[e].z + pv[e].w)) * f;
             }
+            const float v[4] = {apart ? pv[e].x : pv[e].x * f, apart ? pv[e].y : pv[e].y * f, apart ? pv[e].z : pv[e].z * f, apart ? pv[e].w : pv[e].w * f};
+            if constexpr (!apart) lacc += (v[0] + v[1]) + (v[2] + v[3]);
+            uint32_t hi[2], lo[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const float w0 = v[2 * i] * UP, w1 = v[2 * i + 1] * UP;
+                const xq_f16x2 hh = {(_Float16)w0, (_Float16)w1};
+                const xq_f16x2 ll = {(_Float16)(w0 - (float)hh.x), (_Float16)(w1 - (float)hh.y)};
+                hi[i] = __builtin_bit_cast(uint32_t, hh);
+                lo[i] = __builtin_bit_cast(uint32_t, ll);
+            }
+            // piece e 512 + tid of [tile32][rt][half of the slots][lane]
+            const int idx = e * 512 + tid, hs = (idx >> 6) & 1, blk = idx >> 7;
+            uint8_t* dst = lds + buf * L::W_BYTES + blk * 2048 + lane * 16 + hs * 8;
+            *reinterpret_cast<uint2*>(dst) = make_uint2(hi[0], hi[1]);
+            *reinterpret_cast<uint2*>(dst + 1024) = make_uint2(lo[0], lo[1]);
         }
     };
     // codes: octet n = c16 of the wave's slab for tokens 4 i + q of its 32
@@ -373,68 +382,85 @@ __global__ __launch_bounds__(512) void fold_values_pc_kernel(const FoldValueArgs
 #pragma unroll
         for (int k = 0; k < 8; ++k) y[rt][k] = zero4;
     uint32_t raw[2][8];
-    load_stage(o.t0);
-    load_codes(o.t0 * 8 + tw * 2, raw[0]);
-    load_codes(o.t0 * 8 + tw * 2 + 1, raw[1]);
-    load_meta(o.t0);
-    write_stage(0);
-    __syncthreads();
     const f16x8 ones = as_frag(0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0x3C003C00u);
-    for (int t = o.t0; t < o.t1; ++t) {
-        const int buf = (t - o.t0) & 1, next = min(t + 1, o.t1 - 1);
-        const bool more = t + 1 < o.t1;
-        if (more) load_stage(t + 1);
-        const uint8_t* wb = lds + buf * L::W_BYTES;
-        f32x4 acc[RT][8], psum[RT];
-        static_for<0, 2>([&](auto ST) XQ_INLINE_LAMBDA {
-            constexpr int st = decltype(ST)::value;
-            uint4 w[RT][2];
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                for (int k = 0; k < 2; ++k) w[rt][k] = *reinterpret_cast<const uint4*>(wb + (((tw * 2 + st) * RT + rt) * 2 + k) * 1024 + lane * 16);
-            uint32_t m0[4], m1[4];
-            const uint32_t (&r)[8] = raw[st];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if constexpr (BITS == 2) { m0[j] = r[2 * j] | (r[2 * j + 1] << 16); m1[j] = 0u; }
-                else if constexpr (BITS == 3) { m0[j] = perm_bytes(r[2 * j + 1], r[2 * j], sel0); m1[j] = perm_bytes(r[2 * j + 1], r[2 * j], sel1); }
-                else { m0[j] = perm_bytes(r[2 * j + 1], r[2 * j], 0x05040100u); m1[j] = perm_bytes(r[2 * j + 1], r[2 * j], 0x07060302u); }
-            }
-            load_codes(next * 8 + tw * 2 + st, raw[st]);
-            static_for<0, 9>([&](auto K) XQ_INLINE_LAMBDA {          // eight column tiles, and one of ones
-                constexpr int k = decltype(K)::value;
-                f16x8 f = ones;
-                if constexpr (k < 8) {
-                    uint32_t F[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) F[j] = fold_code<BITS, k>(m0[j], m1[j], fold_pc_add<BITS>());
-                    f = as_frag(F[0], F[1], F[2], F[3]);
-                }
-#pragma unroll
-                for (int p = 1; p >= 0; --p)
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) {
-                        f32x4& to = *(k < 8 ? &acc[rt][k & 7] : &psum[rt]);
-                        to = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w[rt][p]), f, st == 0 && p == 1 ? zero4 : to, 0, 0, 0);
-                    }
-            });
-        });
-        const uint32_t s4[4] = {sv.x, sv.y, sv.z, sv.w}, z4[4] = {zv.x, zv.y, zv.z, zv.w};
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const float sc = (k & 1) ? bf16_hi_to_f32(s4[k >> 1]) : bf16_lo_to_f32(s4[k >> 1]);
-            const float z = (k & 1) ? bf16_hi_to_f32(z4[k >> 1]) : bf16_lo_to_f32(z4[k >> 1]);
-            const float off = __builtin_fmaf(sc, (float)FOLD_PC_CENTRE<BITS>, z), f = sc * FOLD_CODE_UNIT;
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) y[rt][k][r] = __builtin_fmaf(acc[rt][k][r], f, __builtin_fmaf(psum[rt][r], off, y[rt][k][r]));
-        }
-        load_meta(next);
-        if (more) write_stage(buf ^ 1);
+    auto walk = [&](auto APART) XQ_INLINE_LAMBDA {
+        constexpr bool apart = decltype(APART)::value;
+        load_stage(o.t0);
+        load_codes(o.t0 * 8 + tw * 2, raw[0]);
+        load_codes(o.t0 * 8 + tw * 2 + 1, raw[1]);
+        load_meta(o.t0);
+        write_stage(APART, 0);
         __syncthreads();
-    }
+        for (int t = o.t0; t < o.t1; ++t) {
+            const int buf = (t - o.t0) & 1, next = min(t + 1, o.t1 - 1);
+            const bool more = t + 1 < o.t1;
+            if (more) load_stage(t + 1);
+            const uint8_t* wb = lds + buf * L::W_BYTES;
+            f32x4 acc[RT][8], psum[RT];
+            static_for<0, 2>([&](auto ST) XQ_INLINE_LAMBDA {
+                constexpr int st = decltype(ST)::value;
+                uint4 w[RT][2];
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) w[rt][k] = *reinterpret_cast<const uint4*>(wb + (((tw * 2 + st) * RT + rt) * 2 + k) * 1024 + lane * 16);
+                uint32_t m0[4], m1[4];
+                const uint32_t (&r)[8] = raw[st];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if constexpr (BITS == 2) { m0[j] = r[2 * j] | (r[2 * j + 1] << 16); m1[j] = 0u; }
+                    else if constexpr (BITS == 3) { m0[j] = perm_bytes(r[2 * j + 1], r[2 * j], sel0); m1[j] = perm_bytes(r[2 * j + 1], r[2 * j], sel1); }
+                    else { m0[j] = perm_bytes(r[2 * j + 1], r[2 * j], 0x05040100u); m1[j] = perm_bytes(r[2 * j + 1], r[2 * j], 0x07060302u); }
+                }
+                load_codes(next * 8 + tw * 2 + st, raw[st]);
+                static_for<0, 9>([&](auto K) XQ_INLINE_LAMBDA {          // eight column tiles, and one of ones
+                    constexpr int k = decltype(K)::value;
+                    f16x8 f = ones;
+                    if constexpr (k < 8) {
+                        uint32_t F[4];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) F[j] = fold_code<BITS, k>(m0[j], m1[j], fold_pc_add<BITS>());
+                        f = as_frag(F[0], F[1], F[2], F[3]);
+                    }
+#pragma unroll
+                    for (int p = 1; p >= 0; --p)
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt) {
+                            f32x4& to = *(k < 8 ? &acc[rt][k & 7] : &psum[rt]);
+                            to = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w[rt][p]), f, st == 0 && p == 1 ? zero4 : to, 0, 0, 0);
+                        }
+                });
+            });
+            if constexpr (apart)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    const float4 fv = *reinterpret_cast<const float4*>(lds + L::F_OFF + buf * L::F_BYTES + (tw * 16 * RT + rt * 16 + 4 * q) * 4);
+                    const float fac[4] = {fv.x, fv.y, fv.z, fv.w};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        psum[rt][r] *= fac[r];
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) acc[rt][k][r] *= fac[r];
+                    }
+                }
+            const uint32_t s4[4] = {sv.x, sv.y, sv.z, sv.w}, z4[4] = {zv.x, zv.y, zv.z, zv.w};
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float sc = (k & 1) ? bf16_hi_to_f32(s4[k >> 1]) : bf16_lo_to_f32(s4[k >> 1]);
+                const float z = (k & 1) ? bf16_hi_to_f32(z4[k >> 1]) : bf16_lo_to_f32(z4[k >> 1]);
+                const float off = __builtin_fmaf(sc, (float)FOLD_PC_CENTRE<BITS>, z), f = sc * FOLD_CODE_UNIT;
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) y[rt][k][r] = __builtin_fmaf(acc[rt][k][r], f, __builtin_fmaf(psum[rt][r], off, y[rt][k][r]));
+            }
+            load_meta(next);
+            if (more) write_stage(APART, buf ^ 1);
+            __syncthreads();
+        }
+    };
+    if (apart) walk(std::true_type{});
+    else walk(std::false_type{});
     if (o.cblk == 0) {
         fold_denominators<RT>(a, o, lacc, 1.0f, reinterpret_cast<float*>(lds + L::L_OFF));
         __syncthreads();

@@ -8,7 +8,7 @@ import torch
 import xq_inputs as xi
 from oracle import xq_oracle as xo
 from tests.test_gpu_per_channel import _attend
-from tests.util import bits_to_torch, oracle_cache, rel_errors
+from tests.util import bits_to_torch, oracle_cache, oracle_cache_per_channel, rel_errors
 
 pytestmark = pytest.mark.gpu
 
@@ -184,6 +184,34 @@ def test_per_channel_blocks_and_window(xq, bits, G, Hq, Hkv, d, lens):
 def test_per_channel_scales_of_every_magnitude(xq):
     w = xi.C2.scaled(B=1, L=300, d=2048, Hq=16, Hkv=16, n_outlier=0)
     assert _attend(xq, w, 3, 128, [300], pairs=[(0, 0), (0, 9)], scale_spread=64.0) <= TOL
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("G", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv", [(16, 16), (32, 8)])
+def test_per_channel_large_block_of_small_weight(xq, bits, G, Hq, Hkv):
+    """A block whose rows are 2^40 larger and whose softmax weights are 2^-40 counts as much as the others: with its neighbour
+    in one tile (blocks of 64), in a tile of its own, and as the last block before the window."""
+    L = 600
+    pairs = [(0, h) for h in (0, 1, Hq - 1)]
+    for block in sorted({1, L // G // 2, L // G - 1}):
+        w = xi.C2.scaled(B=1, L=L, d=2304, Hq=Hq, Hkv=Hkv, n_outlier=0)
+        x, wk = _small_weight_rows(w, 40, 28.0, list(range(block * G, (block + 1) * G)))
+        wv, q = xi.gen_weights(w)[1], xi.gen_q(w)
+        nblk, rem = divmod(L, G)
+        cache = xq.alloc_cache_per_channel(1, nblk * G, w.d, G, bits)
+        xt = bits_to_torch(x)
+        xq.xq_quantize_blocks_per_channel(cache, xt[:, :nblk * G].contiguous(), [0])
+        tail = torch.full((1, G, w.d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        tail[:, :rem] = xt[:, nblk * G:]
+        attn = xq.XQAttn(Hq, Hkv, w.hd, w.hd ** -0.5)
+        wc, wd = (xq.xq_prepare_weights(attn, w.d, g, b, bits_to_torch(wk), bits_to_torch(wv)) for g, b in ((128, bits), (0, 16)))
+        out = xq.xq_remat_attn_decode_per_channel(attn, bits_to_torch(q), cache, tail, [L], wc, wd).cpu().numpy()
+        packed, scale, zero, tail_o = oracle_cache_per_channel(x, G, bits, [L])
+        ref = xo.remat_attn_pairs_per_channel(q_bf16=q, Wk=wk, Wv=wv, Hq=Hq, Hkv=Hkv, hd=w.hd, softmax_scale=w.hd ** -0.5, lens=[L],
+                                              pairs=pairs, packed=packed, scale=scale, zero=zero, G=G, bits=bits, tail_bf16=tail_o)
+        rows, worst = rel_errors(np.array([out[b, h] for b, h in pairs]), ref)
+        assert np.all(np.isfinite(out)) and rows.max() <= TOL and worst <= TOL, (block, float(rows.max()), float(worst))
 
 
 def test_per_channel_terms_serve_both_orders(xq):
