@@ -170,9 +170,10 @@ xq_status_t xq_remat_attn_decode(const xq_attn_t *a, const uint16_t *q_bf16,
 
 /*
  * xq_remat_attn_decode for callers that cannot allocate device memory (code under HIP graph capture,
- * tight serving loops, harnesses that forbid it): same arguments, same kernels and same result, but
+ * tight serving loops, harnesses that forbid it): same arguments, same kernels and same result (bit for
+ * bit, up to layers of n_q_heads * d = 2^22 at the least), but
  * the workspace is a buffer built into the library, XQ_STATIC_SCRATCH_BYTES per GPU, instead of a
- * caller buffer.  The call allocates and frees nothing.  A problem for which xq_remat_attn_decode would
+ * caller buffer; a step that asks for more runs through it in several groups of sequences.  The call allocates and frees nothing.  A problem for which xq_remat_attn_decode would
  * not accept XQ_STATIC_SCRATCH_BYTES of workspace is refused with
  * XQ_ERR_WORKSPACE before anything is launched (the 32 MiB cover e.g. B=8, 32 query heads, context
  * 4096, d=4096, group 128: 19.5 MB).  The buffer belongs to the device that is current at the call

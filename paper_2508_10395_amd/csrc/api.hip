@@ -693,7 +693,7 @@ xq_status_t xq_remat_attn_decode_static(const xq_attn_t* a, const uint16_t* q_bf
                                         const uint16_t* acc_bf16, int32_t B, int32_t cap, int32_t d,
                                         const void* wprep, const int32_t* len, float* out, void* stream)
 {
-    // size check first, on the host, from the same query the caller-workspace entry point uses
+    // size check first, on the host: the least workspace that the caller-workspace entry point accepts
     xq_status_t st = check_attn(a);
     if (st != XQ_OK) return st;
     if ((xcache != nullptr) == (acc_bf16 != nullptr) || !len) return XQ_ERR_INVALID_ARG;
@@ -717,8 +717,7 @@ xq_status_t xq_remat_attn_decode_static(const xq_attn_t* a, const uint16_t* q_bf
     void* ws = nullptr;
     st = static_scratch_of_current_device(&ws);
     if (st != XQ_OK) return st;
-    // nothing in the buffer has to start at zero: the scale pre-pass and the attention kernel write every
-    // element that the combine reads for these lengths
+    // nothing in the buffer has to start at zero: every kernel reads only what one before it has written for these lengths
     return remat_attn_common(a, q_bf16, xcache, acc_bf16, B, cap, d, wprep, len, out, ws, XQ_STATIC_SCRATCH_BYTES,
                              nullptr, 0, nullptr, stream);
 }

@@ -1760,7 +1760,8 @@ static hipError_t launch(void (*kernel)(const Args), int grid, int lds_bytes, co
 
 static size_t align256(size_t n) { return (n + 255) / 256 * 256; }
 
-// Workspace of one launch group: what depends on the number of sequences in it.
+// Workspace of one launch group of nb of the call's B sequences.  What shapes the sums (token splits, slabs per output
+// workgroup, slab ways) follows from B, so that a sequence's result does not depend on the group it is launched in.
 struct FoldPlan {
     int rt, nrb, tiles, splits, chunks, chunk_slabs, u_slab;
     size_t p, mtile, rowfac, lsum, uy, yz, ud, total;      // bytes; u and y share a region (u is dead when y is written),
@@ -1774,7 +1775,7 @@ static int fold_splits(int nb, int nrb, int n_slabs_v, int max_len)
     return std::max(1, std::min({nt, (256 + per - 1) / per, 16}));
 }
 
-static FoldPlan fold_plan(const FoldProblem& f, int nb, int max_len, int splits)
+static FoldPlan fold_plan(const FoldProblem& f, int B, int nb, int max_len, int splits)
 {
     FoldPlan L{};
     const int R = f.T * f.Hq;
@@ -1784,7 +1785,7 @@ static FoldPlan fold_plan(const FoldProblem& f, int nb, int max_len, int splits)
     L.tiles = (max_len + FOLD_VTILE - 1) / FOLD_VTILE * 2 + (f.block ? 2 : 0);
     L.splits = splits = splits + (f.block ? 1 : 0);
     L.u_slab = f.dense ? FOLD_U_DENSE(L.rt) : FOLD_U_CODED(L.rt);
-    const int colblocks = (nb * f.T * (f.Hq / f.Hkv) + 31) / 32;
+    const int colblocks = (B * f.T * (f.Hq / f.Hkv) + 31) / 32;
     L.chunk_slabs = std::max(1, std::min(FO_MAX_SLABS, f.n_slabs_v * f.Hkv * colblocks / 256));
     L.chunks = (f.n_slabs_v + L.chunk_slabs - 1) / L.chunk_slabs;
     L.p = align256(std::max((size_t)nb * L.nrb * L.tiles * 4 * (L.rt * 512) * 4, (size_t)L.chunks * nb * R * 512));
@@ -1801,22 +1802,26 @@ static FoldPlan fold_plan(const FoldProblem& f, int nb, int max_len, int splits)
 size_t fold_workspace_bytes(const FoldProblem& f, int B, int max_len)
 {
     const int R = f.T * f.Hq, nrb = (R + (R <= 16 ? 15 : 31)) / (R <= 16 ? 16 : 32);
-    return fold_plan(f, B, max_len, fold_splits(B, nrb, f.n_slabs_v, max_len)).total;
+    return fold_plan(f, B, B, max_len, fold_splits(B, nrb, f.n_slabs_v, max_len)).total;
 }
 
-// The largest launch group and split that fit the workspace, for B sequences; false if not even one sequence does.
-// `bytes` is cut to what the query asks for, so that results do not depend on how much more a caller brings.
+// The largest launch group that fits the workspace, for B sequences; where not even one does, one with fewer splits; false if
+// that does not either.  `bytes` is cut to what the query asks for, so that results do not depend on how much more a caller
+// brings; they depend on less only where splits are given up.
 static bool fold_fit(const FoldProblem& f, int B, int max_len, size_t bytes, int* nb, FoldPlan* plan)
 {
     const int R = f.T * f.Hq, nrb = (R + (R <= 16 ? 15 : 31)) / (R <= 16 ? 16 : 32);
     bytes = std::min(bytes, std::max(f.query_bytes, fold_workspace_bytes(f, B, max_len)));
-    for (int groups = 1; groups <= B; ++groups) {
+    const int splits = fold_splits(B, nrb, f.n_slabs_v, max_len);
+    for (int groups = 1;; ++groups) {
         const int n = (B + groups - 1) / groups;
-        for (int sp = fold_splits(n, nrb, f.n_slabs_v, max_len); sp >= 1; --sp) {
-            const FoldPlan p = fold_plan(f, n, max_len, sp);
-            if (p.total <= bytes) { *nb = n; *plan = p; return true; }
-            if (groups < B && sp == 1) break;
-        }
+        const FoldPlan p = fold_plan(f, B, n, max_len, splits);
+        if (p.total <= bytes) { *nb = n; *plan = p; return true; }
+        if (n == 1) break;
+    }
+    for (int sp = splits - 1; sp >= 1; --sp) {
+        const FoldPlan p = fold_plan(f, B, 1, max_len, sp);
+        if (p.total <= bytes) { *nb = 1; *plan = p; return true; }
     }
     return false;
 }
@@ -1933,7 +1938,7 @@ hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSo
             // Slab ways of a workgroup: eight, or four with two token tiles where that still leaves two rounds of workgroups
             // (a wave's set-up and the meeting of the slab ways then weigh less).  Measured, 8 / 4 / 2 slab ways: 1024 tiles
             // of 2 bits 122 / 114 / 113 us (group 128), 133 / 124 / 134 us (group 64); 256 tiles of 3 bits 38 / 51 / 84 us.
-            const int swl = sh.nb * sh.nrb * sh.tiles >= 4 * 256 && !f.block ? 2 : 3, ways = 8 >> swl;
+            const int swl = B * sh.nrb * sh.tiles >= 4 * 256 && !f.block ? 2 : 3, ways = 8 >> swl;
             FoldScoreArgs a{kx, sh, u, rowfac, p, mtile, L.u_slab, swl, FoldSource{}, u_dense, 0};
             if (any_window) { a.window = *window; a.n_window = xcd_grid(sh.nb * sh.nrb); }
             const int grid = a.n_window + xcd_grid(sh.nb * sh.nrb * ((sh.tiles + ways - 1) / ways));

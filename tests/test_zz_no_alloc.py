@@ -58,6 +58,28 @@ def test_static_workspace_two_calls_second_smaller(xq):
     _pair_of_calls(xq, xi.C3.scaled(B=2, L=330, d=512, Hq=4, Hkv=4), 0, 0, lens=[330, 100], dense=True)
 
 
+def test_static_workspace_of_a_large_step(xq):
+    """Steps that ask for more than the built-in buffer run in several launch groups there; the bits must not depend on it."""
+    wide = xi.C2.scaled(B=64, L=130, d=8192, Hq=8, Hkv=8, n_outlier=80)          # slabs per output workgroup go with the batch
+    narrow = xi.C2.scaled(B=64, L=2048, d=8192, Hq=2, Hkv=2, n_outlier=80)       # slab ways of the scores go with the tiles
+    for w in (wide, narrow):
+        attn = xq.XQAttn(w.Hq, w.Hkv, w.hd, w.hd ** -0.5)
+        assert xq.xq_remat_attn_workspace_bytes(attn, w.B, w.L, w.d, 128) > xq.XQ_STATIC_SCRATCH_BYTES
+        gen = torch.Generator("cuda").manual_seed(5)
+        wk, wv = (torch.randn((w.d, w.Hkv * w.hd), generator=gen, device="cuda").mul(w.d ** -0.5).bfloat16() for _ in range(2))
+        cache = xq.alloc_cache(w.B, w.L, w.d, 128, 2)
+        for b in range(w.B):
+            one = xq.XQCache(cache.codes[b:b + 1], cache.scale[b:b + 1], cache.zero[b:b + 1], 1, w.L, w.d, 128, 2)
+            xq.xq_quantize_append(one, torch.randn((1, w.L, w.d), generator=gen, device="cuda").bfloat16(), [0])
+        wprep = xq.xq_prepare_weights(attn, w.d, 128, 2, wk, wv)
+        q = torch.randn((w.B, w.Hq, w.hd), generator=gen, device="cuda").bfloat16()
+        lens = [w.L - 3 * (b % 7) for b in range(w.B)]
+        want = xq.xq_remat_attn_decode(attn, q, wprep, lens, xcache=cache)
+        got = torch.full_like(want, float("nan"))
+        xq.xq_remat_attn_decode_static(attn, q, wprep, lens, xcache=cache, out=got)
+        assert bool(torch.isfinite(got).all()) and torch.equal(got, want)
+
+
 def test_static_workspace_refuses_what_does_not_fit(xq):
     """Config 4's batch, heads and context (B=16, 32 query heads, 8192 rows, group 64) need 69 MB of softmax
     partials alone, more than the built-in buffer: refused on the host, nothing is launched.  (Hidden size 128
