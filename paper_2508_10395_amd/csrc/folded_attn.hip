@@ -1769,7 +1769,7 @@ struct FoldPlan {
 };
 
 // Token splits of the value kernel: enough workgroups for the 256 CUs, but no more than leave a tile each.
-static int fold_splits(int nb, int nrb, int n_slabs_v, int max_len)
+int fold_splits(int nb, int nrb, int n_slabs_v, int max_len)
 {
     const int per = nb * nrb * ((n_slabs_v + 1) / 2), nt = (max_len + FOLD_VTILE - 1) / FOLD_VTILE;
     return std::max(1, std::min({nt, (256 + per - 1) / per, 16}));

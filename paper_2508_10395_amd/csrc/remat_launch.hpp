@@ -126,14 +126,65 @@ static FoldProblem fold_problem(const xq_attn_t* a, int T, int d, int group, int
 }
 
 // Where the folded order pays.  It does 128 / (query heads per KV head) times fewer operations, but in five dependent
-// launches instead of three, so a step that the remat kernels finish in about one wave of workgroups over a narrow layer
-// stays with them: their time goes with waves x (d + 512).  Measured (us, remat / folded), one wave: d = 256 25 / 34,
-// d = 512 26 / 36, d = 1024 34 / 38, d = 2048 54 / 44, d = 4096 94 / 65; two waves of d = 512 36 / 54, four 52 / 45; two
-// waves of d = 256 28 / 44, eight 79 / 59.
-static bool folding_pays(const xq_attn_t* a, int B, int max_len, int d)
+// launches instead of three, reads every row twice, and works in blocks of 16 or 32 query rows.  A step that the remat kernels
+// finish in about one wave of workgroups over a narrow layer stays with them: their time goes with waves x (d + 512).
+// Measured (us, remat / folded), one wave: d = 256 25 / 34, d = 512 26 / 36, d = 1024 34 / 38, d = 2048 54 / 44, d = 4096 94 / 65;
+// two waves of d = 512 36 / 54, three 61 / 42 (32 KV heads) to 66 / 55 (2); d = 256 two 28 / 44, four 57 / 43 to 65 / 62.
+//
+// That alone is wrong where few KV heads meet many rows or tokens, above all over bf16 rows, whose two readings cost more than
+// the matrix products of one or two KV heads: 16 x 8192 rows of d = 1024, one KV head 70 / 120, two of 16 query heads each
+// (of 2048 tokens) 64 / 83; coded, 16 x 100 tokens, 128 on 8 heads of d = 2048 59 / 80.  So the times are estimated as well.  The
+// estimates are least-squares fits (us) to 6000 steps, d 128 to 4096, 1 to 16 sequences of 100 to 32768 tokens, 1 to 32 KV heads of
+// 1 to 16 query heads, all formats, nearest where the two are within a factor of two of each other; the median step is 5 % off.
+// Of the steps that folding made slower by 3 % or more, 62 of 4120 coded ones (up to 1.35 times), 86 of 809 over bf16 rows (1.71) and
+// 56 of 1288 per-channel ones (1.58), 22 (1.12), 12 (1.20) and 24 (1.21) still fold, and 33 that folding makes faster no longer do.
+struct StepCost {
+    float base, wave_d, wave, wave_gqa, rows, len, bytes, head_bytes;                       // rematerialising
+    float f_base, f_ways, f_scores, f_values, f_len, f_sums, f_tiles, f_bytes, f_row_bytes, f_weights;
+    int more_tiles;                      // a window's score tiles
+};
+constexpr StepCost STEP_CODED  = {0.0f, 5.9f, 8.7f, 2.3f, 2.4f, 8.5f, 0.0f, 0.0f,    32.0f, 2.2f, 1.6f, 2.5f, 4.0f, 4.4f, 1.5f, 0.0f, 0.0f, 0.0f, 0};
+constexpr StepCost STEP_ACC    = {2.1f, 4.0f, 4.5f, 2.4f, 1.1f, 6.1f, 37.0f, 56.0f,  27.0f, 0.05f, 3.0f, 0.9f, 3.1f, 3.9f, 0.4f, 150.0f, 79.0f, 7.7f, 0};
+constexpr StepCost STEP_BLOCKS = {3.1f, 5.3f, 2.6f, 1.7f, 24.0f, 11.0f, 0.0f, 0.0f,  27.0f, 2.9f, 2.2f, 1.8f, 5.8f, 2.0f, 2.9f, 0.0f, 0.0f, 0.0f, 2};
+constexpr StepCost STEP_WINDOW = {0.0f, 3.8f, 8.6f, 0.0f, 78.0f, 0.0f, 0.0f, 0.0f,   25.0f, 1.9f, 2.0f, 0.3f, 0.0f, 6.5f, 5.9f, 0.0f, 0.0f, 0.0f, 2};   // a residual window alone
+
+// the first part of the rule, which also decides what the workspace queries ask for
+static bool folding_may_pay(const xq_attn_t* a, int B, int max_len, int d)
 {
-    const long long tiles = (max_len + TILE_TOKENS - 1) / TILE_TOKENS, waves = (tiles * a->n_kv_heads * B + 255) / 256;
+    const long long nt = (max_len + TILE_TOKENS - 1) / TILE_TOKENS, waves = (nt * a->n_kv_heads * B + 255) / 256;
     return waves * (d + 512) >= 2560;
+}
+
+// (extra: what the rematerialising order does besides, us)
+static bool folding_pays(const StepCost& c, const xq_attn_t* a, int B, int max_len, int d, float extra = 0.0f)
+{
+    const long long nt = (max_len + TILE_TOKENS - 1) / TILE_TOKENS, waves = (nt * a->n_kv_heads * B + 255) / 256;
+    if (!folding_may_pay(a, B, max_len, d)) return false;
+    const int Hq = a->n_q_heads, Hkv = a->n_kv_heads, rt = Hq <= 16 ? 1 : 2, slabs = d / 128;
+    const long long nbt = (long long)B * ((Hq + 16 * rt - 1) / (16 * rt)), splits = fold_splits(B, (int)(nbt / B), slabs, max_len);
+    const float kd = (float)d / 256, len = (float)max_len / 8192, gb = 2e-9f * B * max_len * d;
+    const float remat = c.base + waves * (c.wave_d * kd + c.wave + (Hq / Hkv >= 4 ? c.wave_gqa : 0.0f)) + 1e-6f * c.rows * B * Hq * max_len +
+                        c.len * len + (c.bytes + c.head_bytes * Hkv) * gb + extra;
+    const int ways = (slabs + 7) / 8;
+    const float tiles = (float)((nbt * (2 * nt + c.more_tiles) + 255) / 256 * rt);
+    const float folded = c.f_base + c.f_ways * ways + (c.f_scores * ways + c.f_tiles) * tiles +
+                         c.f_values * (float)((nbt * splits * ((slabs + 1) / 2) + 255) / 256 * ((nt + splits - 1) / splits) * rt) + c.f_len * len +
+                         1e-6f * c.f_sums * B * Hq * splits * d + (c.f_bytes + c.f_row_bytes * (float)(nbt / B)) * gb + 1e-5f * c.f_weights * Hkv * d;
+    return folded <= 1.03f * remat;
+}
+static bool decode_folding_pays(const xq_attn_t* a, int B, int max_len, int d, bool coded)
+{
+    return folding_pays(coded ? STEP_CODED : STEP_ACC, a, B, max_len, d);
+}
+// per-channel caches: the terms that the rematerialising order derives from the blocks, unless the caller keeps them, take
+// 13 + 4.2 d / 256 us, 35 us per 10^9 codes and 2.8 us per 10^6 (token, KV head) pairs.  A window alone is attended to one query
+// head of a KV head after the other, 1.6 us each
+static bool pc_folding_pays(const xq_attn_t* a, int B, int max_len, int d, int block, bool terms)
+{
+    if (max_len < block)
+        return folding_pays(STEP_WINDOW, a, B, max_len, d, (a->n_kv_heads * B + 255) / 256 * 1.6f * (a->n_q_heads / a->n_kv_heads - 1));
+    const float derive = 13.0f + 4.2f * d / 256 + 35e-9f * B * max_len * d + 2.8e-6f * B * max_len * a->n_kv_heads;
+    return folding_pays(STEP_BLOCKS, a, B, max_len, d, terms ? 0.0f : derive);
 }
 
 // The same for a latent cache, whose two rematerialising passes are five launches too.  Measured (us with projection and
@@ -149,7 +200,7 @@ static bool latent_folding_pays(const xq_attn_t* a, int B, int max_len, int r)
 size_t remat_decode_query_bytes(const xq_attn_t* a, int B, int max_len, int d, int group)
 {
     const size_t remat = remat_workspace_bytes(B, a->n_q_heads, max_len, d, group ? group : 128, group != 0);
-    return !folding_pays(a, B, max_len, d) ? remat : std::max(remat, fold_workspace_bytes(fold_problem(a, 1, d, group, 4, 0, 0), B, max_len));
+    return !folding_may_pay(a, B, max_len, d) ? remat : std::max(remat, fold_workspace_bytes(fold_problem(a, 1, d, group, 4, 0, 0), B, max_len));
 }
 
 hipError_t run_remat_attn_decode(const xq_attn_t* a, const uint16_t* q, const xq_cache_t* xc,
@@ -157,7 +208,7 @@ hipError_t run_remat_attn_decode(const xq_attn_t* a, const uint16_t* q, const xq
                                  const BatchI32& len, int max_len, float* out, void* ws, size_t ws_bytes,
                                  const float* rope, const BatchI32* pos0, hipStream_t s)
 {
-    if (!rope && folding_pays(a, B, max_len, xc && xc->fmt.bits == 8 ? 2 * d : d)) {
+    if (!rope && decode_folding_pays(a, B, max_len, xc && xc->fmt.bits == 8 ? 2 * d : d, xc != nullptr)) {
         const int cb = xc ? xc->fmt.bits : 16, nib = cb == 8;
         const WPrepLayout L = make_wprep_layout_for_cache(d, xc ? xc->fmt.group : 128, cb, a->n_kv_heads);
         const FoldProblem f = fold_problem(a, 1, L.d, xc ? L.G : 0, nib ? 4 : cb, nib,
@@ -550,7 +601,7 @@ static FoldProblem fold_problem_pc(const xq_attn_t* a, int d, int block, int bit
 size_t remat_pc_query_bytes(const xq_attn_t* a, int B, int max_len, int d, int block)
 {
     const size_t remat = remat_pc_workspace_bytes(B, a->n_q_heads, a->n_kv_heads, max_len, d, block);
-    return !folding_pays(a, B, max_len, d) ? remat : std::max(remat, fold_workspace_bytes(fold_problem_pc(a, d, block, 4, 0), B, max_len));
+    return !folding_may_pay(a, B, max_len, d) ? remat : std::max(remat, fold_workspace_bytes(fold_problem_pc(a, d, block, 4, 0), B, max_len));
 }
 
 // Decode attention from a per-channel cache plus the bf16 residual window of the newest len % block tokens.  In the folded
@@ -578,7 +629,7 @@ hipError_t run_remat_attn_decode_pc(const xq_attn_t* a, const uint16_t* q, const
         any_tail |= len_tail.v[b];
     }
     const FoldProblem f = fold_problem_pc(a, d, blockT, bits, remat_pc_query_bytes(a, B, max_len, d, blockT));
-    const bool folded = folding_pays(a, B, max_len, d) && fold_fits(f, B, max_len, ws_bytes);
+    const bool folded = pc_folding_pays(a, B, max_len, d, blockT, terms != nullptr) && fold_fits(f, B, max_len, ws_bytes);
     const int tiles_all = (max_len + TILE_TOKENS - 1) / TILE_TOKENS;
     const int tiles_coded = (max_coded + TILE_TOKENS - 1) / TILE_TOKENS;
     const int chunks_stride = (tiles_all + 1) * (TILE_TOKENS / CHUNK_TOKENS);

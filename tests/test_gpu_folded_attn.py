@@ -25,6 +25,56 @@ def xq():
     return m
 
 
+def _kernels(call):
+    """Names of the kernels that a call launches."""
+    torch.cuda.synchronize()
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    return [e.name for e in p.events()]
+
+
+def _step(xq, B, L, d, Hq, Hkv, bits, G=128, per_channel=False, terms=False):
+    """One decode step on caches of arbitrary codes, as a call without arguments."""
+    gen = torch.Generator("cuda").manual_seed(B * L + d)
+    attn = xq.XQAttn(Hq, Hkv, 128, 128 ** -0.5)
+    wk, wv = (torch.randn((d, Hkv * 128), generator=gen, device="cuda").mul(d ** -0.5).bfloat16() for _ in range(2))
+    q = torch.randn((B, Hq, 128), generator=gen, device="cuda").bfloat16()
+    lens = [L - b % 3 for b in range(B)]
+    if bits == 16:
+        x = torch.randn((B, L, d), generator=gen, device="cuda", dtype=torch.bfloat16)
+        wp = xq.xq_prepare_weights(attn, d, 0, 16, wk, wv)
+        return lambda: xq.xq_remat_attn_decode(attn, q, wp, lens, acc_bf16=x)
+    groups = (L // G, d) if per_channel else (L, d // G)
+    codes = torch.randint(0, 256, (B, L // G * G if per_channel else L, d * bits // 8), generator=gen, device="cuda", dtype=torch.uint8)
+    scale, zero = (torch.rand((B, *groups), generator=gen, device="cuda").mul(f).sub(1.0 - f).bfloat16().abs() * s for f, s in ((0.5, 1), (0.3, -1)))
+    cache = xq.XQCache(codes, scale.contiguous(), zero.contiguous(), B, codes.shape[1], d, G, bits)
+    wp = xq.xq_prepare_weights(attn, d, 128 if per_channel else G, bits, wk, wv)
+    if not per_channel:
+        return lambda: xq.xq_remat_attn_decode(attn, q, wp, lens, xcache=cache)
+    wd = xq.xq_prepare_weights(attn, d, 0, 16, wk, wv)
+    tail = torch.randn((B, G, d), generator=gen, device="cuda", dtype=torch.bfloat16)
+    t = xq.alloc_per_channel_terms(cache, Hkv) if terms else None
+    if terms:
+        xq.xq_remat_attn_decode_per_channel(attn, q, cache, tail, lens, wp, wd, terms=t, terms_valid=False)
+    return lambda: xq.xq_remat_attn_decode_per_channel(attn, q, cache, tail, lens, wp, wd, terms=t, terms_valid=terms)
+
+
+@pytest.mark.parametrize("folded,step", [
+    (False, dict(B=16, L=8192, d=1024, Hq=1, Hkv=1, bits=16)), (False, dict(B=16, L=2048, d=2048, Hq=32, Hkv=2, bits=16)),
+    (False, dict(B=16, L=100, d=2048, Hq=128, Hkv=8, bits=3)), (False, dict(B=16, L=8192, d=128, Hq=2, Hkv=2, bits=3, per_channel=True, terms=True)),
+    (False, dict(B=1, L=512, d=256, Hq=2, Hkv=2, bits=4)),
+    (True, dict(B=4, L=2048, d=1024, Hq=32, Hkv=32, bits=16)), (True, dict(B=2, L=1000, d=4096, Hq=32, Hkv=8, bits=2, G=64)),
+    (True, dict(B=2, L=1000, d=2304, Hq=16, Hkv=16, bits=8)), (True, dict(B=4, L=1000, d=4096, Hq=32, Hkv=32, bits=3, per_channel=True, terms=True)),
+    (True, dict(B=16, L=7000, d=512, Hq=2, Hkv=2, bits=3, per_channel=True))])
+def test_which_order_a_step_takes(xq, folded, step):
+    """The order that was measured to be the faster one, on either side of the rule."""
+    call = _step(xq, **step)
+    call()
+    names = _kernels(call)
+    assert any("fold_scores" in n for n in names) == folded and any("remat_attn" in n for n in names) != folded, names
+
+
 def _run(xq, w, bits, G, lens, x_bits=None, workspaces=(None,), pairs=None, wk=None, scale_sign=None):
     x = xi.gen_x(w) if x_bits is None else x_bits
     wk0, wv = xi.gen_weights(w)
