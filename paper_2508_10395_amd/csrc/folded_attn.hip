@@ -9,8 +9,6 @@
 // 2 bits 6330 / 255; bf16 accumulator, 4 x up to 6000 1080 / 125.  The operations no longer bound it: what is left is the
 // latency of the codes, the unpacking, and 12 us each for reading the two halves of the weight stream.
 #include <algorithm>
-#include <mutex>
-#include <vector>
 
 #include "folded_common.hpp"
 #include "folded_attn.hpp"
@@ -19,7 +17,7 @@ namespace xq {
 
 // What a launch sees of the problem: nb sequences starting at sequence b0 of the call.
 struct FoldShape {
-    int b0, nb, T, Hq, Hkv, R, nrb;      // query rows R = T Hq per sequence, nrb row blocks of 16 RT rows
+    int b0, nb, Hq, Hkv, R, nrb;         // query rows per sequence R = Hq, nrb row blocks of 16 RT rows
     int tiles;                           // score tiles (128 tokens) per sequence in the arrays, even
     int splits;                          // token splits in the arrays of the value kernel
     int block;                           // per-channel caches: tokens per block (else 0)
@@ -63,7 +61,7 @@ constexpr int FOLD_P_TILE32 = RT * 2 * 256;      // floats per 32 tokens
 struct FoldQueryArgs {
     FoldWeights w;
     FoldShape s;
-    const uint16_t* q;                   // [B][T][Hq][128]
+    const uint16_t* q;                   // [B][Hq][128]
     uint8_t* u;                          // [nb][nrb][n_slabs][u_slab]
     float* rowfac;                       // [nb][nrb 16 RT]
     float scale_log2e;
@@ -94,13 +92,12 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
     const int slab = blockIdx.x * 2 + wave, h = blockIdx.y, cb = blockIdx.z;
     if (slab >= a.n_slabs) return;                                  // (no workgroup barrier below: a wave's LDS is its own)
     const FoldShape& s = a.s;
-    const int gq = s.Hq / s.Hkv, per_seq = s.T * gq, ncol = s.nb * per_seq;
+    const int gq = s.Hq / s.Hkv, ncol = s.nb * gq;
     float* mine = ul[wave];
     // column -> (sequence of the launch, row of the sequence)
     auto row_of = [&](int col, int& b) -> int {
-        b = col / per_seq;
-        const int rem = col - b * per_seq, t = rem / gq;
-        return t * s.Hq + h * gq + (rem - t * gq);
+        b = col / gq;
+        return h * gq + (col - b * gq);
     };
 
     const int rpb = 16 * a.rt;
@@ -398,9 +395,7 @@ __device__ __forceinline__ void fold_scores_finish(const FoldShape& s, const flo
                 float v[4] = {t.x, t.y, t.z, t.w}, m[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int row = o.rb * 16 * RT + rt * 16 + 4 * q + r;
-                    const int limit = o.len - s.T + (s.T > 1 ? min(row / s.Hq, s.T - 1) : 0);   // causal: the row's own token
-                    v[r] = tok <= limit ? v[r] * rowfac[rt * 16 + 4 * q + r] : -INFINITY;
+                    v[r] = tok < o.len ? v[r] * rowfac[rt * 16 + 4 * q + r] : -INFINITY;
                     m[r] = v[r];
                     m[r] = fmaxf(m[r], dpp_f32<DPP_QUAD_XOR1>(m[r]));
                     m[r] = fmaxf(m[r], dpp_f32<DPP_QUAD_XOR2>(m[r]));
@@ -896,6 +891,32 @@ __device__ __forceinline__ void fold_denominators(const FoldValueArgs& a, const 
     }
 }
 
+// The four token ways of a workgroup's two slabs meet in LDS: wave (slab way, token way w < 2 RT) gets half a row tile of its
+// slab (row tile w / 2, column tiles 4 (w % 2) + [0, 4)) summed over the token ways
+template <int RT>
+__device__ __forceinline__ void fold_meet(const f32x4 (&acc)[RT][8], uint8_t* lds, int wave, int lane, f32x4 (&t)[4])
+{
+    float4* acc_lds = reinterpret_cast<float4*>(lds);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            acc_lds[((wave * RT + rt) * 8 + k) * 64 + lane] = make_float4(acc[rt][k][0], acc[rt][k][1], acc[rt][k][2], acc[rt][k][3]);
+    __syncthreads();
+    const int sw = wave & 1, tw = wave >> 1, rt = tw >> 1, kg = tw & 1;
+    if (tw >= 2 * RT) return;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        float4 v = acc_lds[((sw * RT + rt) * 8 + 4 * kg + k) * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) {
+            const float4 u = acc_lds[(((2 * w + sw) * RT + rt) * 8 + 4 * kg + k) * 64 + lane];
+            v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+        }
+        t[k] = f32x4{v.x, v.y, v.z, v.w};
+    }
+}
+
 // The sums of a range whose scales lie too far apart for fp16 parts: x^ and the sums in fp32, a thread per channel of
 // either slab and quarter of the rows.  Rare, and bound by the vector ALU and the LDS reads of the weights: with every
 // range on it a step over 8 x 4096 tokens of 3 bits (32 heads, d = 4096) takes 330 us (105 on the fp16 parts, 1650 when K and V
@@ -1343,27 +1364,11 @@ __global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
         if (row < s.R && gg < x.ng) a.yz[(yrow0 + row) * x.ng + gg] = z * zfac;
     }
     __syncthreads();
-    float4* acc_lds = reinterpret_cast<float4*>(lds);
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            acc_lds[((wave * RT + rt) * 8 + k) * 64 + lane] = make_float4(acc[rt][k][0], acc[rt][k][1], acc[rt][k][2], acc[rt][k][3]);
-    __syncthreads();
+    f32x4 t[4];
+    fold_meet<RT>(acc, lds, wave, lane, t);
     // token way tw sums half an accumulator row tile (rt, four column tiles) of its slab over the token ways
     if (live && tw < 2 * RT) {
         const int rt = tw >> 1, kg = tw & 1;
-        f32x4 t[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            float4 v = acc_lds[((sw * RT + rt) * 8 + 4 * kg + k) * 64 + lane];
-#pragma unroll
-            for (int w = 1; w < 4; ++w) {
-                const float4 u = acc_lds[(((2 * w + sw) * RT + rt) * 8 + 4 * kg + k) * 64 + lane];
-                v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
-            }
-            t[k] = f32x4{v.x, v.y, v.z, v.w};
-        }
         const int ch = G == 128 ? 8 * c16 + 4 * kg : 64 * kg + 8 * (c16 & 7) + 4 * (c16 >> 3);
         const float f = FOLD_CODE_UNIT / (GPS == 2 && kg ? inv_g[1] : inv_g[0]);
 #pragma unroll
@@ -1512,26 +1517,10 @@ __device__ __forceinline__ void fold_values_dense(const FoldValueArgs& a, const 
         fold_denominators<RT>(a, o, lacc, 1.0f, reinterpret_cast<float*>(lds + L::L_OFF));
         __syncthreads();
     }
-    float4* acc_lds = reinterpret_cast<float4*>(lds);
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            acc_lds[((wave * RT + rt) * 8 + k) * 64 + lane] = make_float4(acc[rt][k][0], acc[rt][k][1], acc[rt][k][2], acc[rt][k][3]);
-    __syncthreads();
+    f32x4 t[4];
+    fold_meet<RT>(acc, lds, wave, lane, t);
     if (live && tw < 2 * RT) {
         const int rt = tw >> 1, kg = tw & 1;
-        f32x4 t[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            float4 v = acc_lds[((sw * RT + rt) * 8 + 4 * kg + k) * 64 + lane];
-#pragma unroll
-            for (int w = 1; w < 4; ++w) {
-                const float4 u = acc_lds[(((2 * w + sw) * RT + rt) * 8 + 4 * kg + k) * 64 + lane];
-                v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
-            }
-            t[k] = f32x4{v.x, v.y, v.z, v.w};
-        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int row = o.rb * 16 * RT + rt * 16 + 4 * q + r;
@@ -1563,7 +1552,7 @@ struct FoldOutArgs {
     const float* y;
     const float* yz;
     float* part;                         // [chunks][nb][R][128]
-    int n_slabs, ng, group, chunk_slabs, rt;
+    int n_slabs, ng, group, chunk_slabs;
     UnpackTable tab;
 };
 
@@ -1580,14 +1569,13 @@ __global__ __launch_bounds__(512) void fold_output_kernel(const FoldOutArgs a)
     const int chunk = blockIdx.x, h = blockIdx.y, cb = blockIdx.z;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, c32 = lane & 31;
-    const int gq = s.Hq / s.Hkv, per_seq = s.T * gq, ncol = s.nb * per_seq;
+    const int gq = s.Hq / s.Hkv, ncol = s.nb * gq;
     const int slab0 = chunk * a.chunk_slabs, ns = min(a.chunk_slabs, a.n_slabs - slab0);
     const int d = a.n_slabs * 128;
     const long long split_stride = (long long)s.nb * s.R;
     auto row_of = [&](int col, int& b) -> int {
-        b = col / per_seq;
-        const int rem = col - b * per_seq, t = rem / gq;
-        return t * s.Hq + h * gq + (rem - t * gq);
+        b = col / gq;
+        return h * gq + (col - b * gq);
     };
     __shared__ int crow[32], cused[32];                              // per column: row of y, splits (and 256: the window's)
     if (tid < 32) {
@@ -1732,28 +1720,13 @@ __global__ __launch_bounds__(256) void fold_finish_kernel(const float* __restric
 // =====================================================================================================================
 // Host side
 // =====================================================================================================================
-static hipError_t allow_lds(const void* kernel, int bytes)
-{
-    struct Done { const void* kernel; int device; };
-    static std::mutex mu;
-    static std::vector<Done> done;
-    if (bytes <= 65536) return hipSuccess;
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    std::lock_guard<std::mutex> lock(mu);
-    for (const Done& d : done)
-        if (d.kernel == kernel && d.device == dev) return hipSuccess;
-    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess) done.push_back({kernel, dev});
-    return e;
-}
-
 template <typename Args>
 static hipError_t launch(void (*kernel)(const Args), int grid, int lds_bytes, const Args& a, hipStream_t s)
 {
-    hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), lds_bytes);
-    if (e != hipSuccess) return e;
+    if (lds_bytes > 65536) {
+        hipError_t e = allow_large_lds(reinterpret_cast<const void*>(kernel), lds_bytes);
+        if (e != hipSuccess) return e;
+    }
     kernel<<<dim3(grid), dim3(512), lds_bytes, s>>>(a);
     return hipGetLastError();
 }
@@ -1778,14 +1751,14 @@ int fold_splits(int nb, int nrb, int n_slabs_v, int max_len)
 static FoldPlan fold_plan(const FoldProblem& f, int B, int nb, int max_len, int splits)
 {
     FoldPlan L{};
-    const int R = f.T * f.Hq;
+    const int R = f.Hq;
     L.rt = R <= 16 ? 1 : 2;
     const int rpb = 16 * L.rt;
     L.nrb = (R + rpb - 1) / rpb;
     L.tiles = (max_len + FOLD_VTILE - 1) / FOLD_VTILE * 2 + (f.block ? 2 : 0);
     L.splits = splits = splits + (f.block ? 1 : 0);
     L.u_slab = f.dense ? FOLD_U_DENSE(L.rt) : FOLD_U_CODED(L.rt);
-    const int colblocks = (B * f.T * (f.Hq / f.Hkv) + 31) / 32;
+    const int colblocks = (B * (f.Hq / f.Hkv) + 31) / 32;
     L.chunk_slabs = std::max(1, std::min(FO_MAX_SLABS, f.n_slabs_v * f.Hkv * colblocks / 256));
     L.chunks = (f.n_slabs_v + L.chunk_slabs - 1) / L.chunk_slabs;
     L.p = align256(std::max((size_t)nb * L.nrb * L.tiles * 4 * (L.rt * 512) * 4, (size_t)L.chunks * nb * R * 512));
@@ -1801,7 +1774,7 @@ static FoldPlan fold_plan(const FoldProblem& f, int B, int nb, int max_len, int 
 
 size_t fold_workspace_bytes(const FoldProblem& f, int B, int max_len)
 {
-    const int R = f.T * f.Hq, nrb = (R + (R <= 16 ? 15 : 31)) / (R <= 16 ? 16 : 32);
+    const int R = f.Hq, nrb = (R + (R <= 16 ? 15 : 31)) / (R <= 16 ? 16 : 32);
     return fold_plan(f, B, B, max_len, fold_splits(B, nrb, f.n_slabs_v, max_len)).total;
 }
 
@@ -1810,7 +1783,7 @@ size_t fold_workspace_bytes(const FoldProblem& f, int B, int max_len)
 // brings; they depend on less only where splits are given up.
 static bool fold_fit(const FoldProblem& f, int B, int max_len, size_t bytes, int* nb, FoldPlan* plan)
 {
-    const int R = f.T * f.Hq, nrb = (R + (R <= 16 ? 15 : 31)) / (R <= 16 ? 16 : 32);
+    const int R = f.Hq, nrb = (R + (R <= 16 ? 15 : 31)) / (R <= 16 ? 16 : 32);
     bytes = std::min(bytes, std::max(f.query_bytes, fold_workspace_bytes(f, B, max_len)));
     const int splits = fold_splits(B, nrb, f.n_slabs_v, max_len);
     for (int groups = 1;; ++groups) {
@@ -1920,11 +1893,11 @@ hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSo
     const int gq = f.Hq / f.Hkv;
     for (int b0 = 0; b0 < B; b0 += nb) {
         FoldShape sh{};
-        sh.b0 = b0; sh.nb = std::min(nb, B - b0); sh.T = f.T; sh.Hq = f.Hq; sh.Hkv = f.Hkv; sh.R = f.T * f.Hq; sh.nrb = L.nrb;
+        sh.b0 = b0; sh.nb = std::min(nb, B - b0); sh.Hq = f.Hq; sh.Hkv = f.Hkv; sh.R = f.Hq; sh.nrb = L.nrb;
         sh.tiles = L.tiles; sh.splits = L.splits; sh.len = len;
         sh.block = f.block; sh.mhalf = f.block == 64;
         const int coded_splits = L.splits - (f.block ? 1 : 0);
-        const int colblocks = (sh.nb * f.T * gq + 31) / 32;
+        const int colblocks = (sh.nb * gq + 31) / 32;
         {
             FoldQueryArgs a{kw, sh, q, u, rowfac, softmax_scale * 1.44269504088896340736f, L.u_slab, f.n_slabs_k, L.rt, tab, u_dense};
             const dim3 grid((f.n_slabs_k + 1) / 2, f.Hkv, colblocks);
@@ -1955,14 +1928,14 @@ hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSo
             if (e != hipSuccess) return e;
         }
         {
-            FoldOutArgs a{vw, sh, y, yz, part, f.n_slabs_v, f.block ? 0 : f.ng_v, f.group, L.chunk_slabs, L.rt, tab};
+            FoldOutArgs a{vw, sh, y, yz, part, f.n_slabs_v, f.block ? 0 : f.ng_v, f.group, L.chunk_slabs, tab};
             const dim3 grid(L.chunks, f.Hkv, colblocks);
             if (f.dense) {
-                e = allow_lds(reinterpret_cast<const void*>(fold_output_kernel<true>), FO_LDS);
+                e = allow_large_lds(reinterpret_cast<const void*>(fold_output_kernel<true>), FO_LDS);
                 if (e != hipSuccess) return e;
                 fold_output_kernel<true><<<grid, dim3(512), FO_LDS, s>>>(a);
             } else {
-                e = allow_lds(reinterpret_cast<const void*>(fold_output_kernel<false>), FO_LDS);
+                e = allow_large_lds(reinterpret_cast<const void*>(fold_output_kernel<false>), FO_LDS);
                 if (e != hipSuccess) return e;
                 fold_output_kernel<false><<<grid, dim3(512), FO_LDS, s>>>(a);
             }

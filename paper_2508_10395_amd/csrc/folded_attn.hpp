@@ -5,7 +5,7 @@
 namespace xq {
 
 struct FoldProblem {
-    int T, Hq, Hkv;                      // query tokens per sequence, heads
+    int Hq, Hkv;                         // heads
     int dense;                           // bf16 rows
     int bits, group, nibbles;            // of the walk (8-bit caches: 4, 128, 1)
     int n_slabs_k, n_slabs_v, ng_v;      // slabs of 128 walked channels on either side, groups of the values' side
@@ -13,6 +13,7 @@ struct FoldProblem {
     size_t query_bytes;                  // what the entry point's workspace query says for this call
 };
 
+hipError_t allow_large_lds(const void* kernel, int lds_bytes);
 bool unpack_table_for(int bits, UnpackTable* t);
 
 int fold_splits(int nb, int nrb, int n_slabs_v, int max_len);          // token splits of the weighted sums

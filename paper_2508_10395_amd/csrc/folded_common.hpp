@@ -1,5 +1,4 @@
-// Shared pieces of the folded attention kernels (folded_query.hip, folded_scores.hip, folded_values.hip,
-// folded_output.hip): the order in which operand slots hold channels and tokens, the unpacking of packed codes to
+// Shared pieces of the folded attention kernels (folded_attn.hip, folded_per_channel.hpp): the order in which operand slots hold channels and tokens, the unpacking of packed codes to
 // normal fp16 numbers, the layout of the workspace.
 //
 // What they compute (Sec. 3.1 of arxiv 2508.10395, with the products taken in another order).  For a query row q of KV
@@ -21,8 +20,7 @@ namespace xq {
 
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
-// ---- query rows.  A sequence has R = T n_q_heads of them, row = (query token) n_q_heads + (query head); they are taken
-// in blocks of 16 RT (RT = 1 or 2 MFMA row tiles).
+// ---- query rows.  A sequence has one per query head; they are taken in blocks of 16 RT (RT = 1 or 2 MFMA row tiles).
 constexpr int FOLD_TILE = 128;           // tokens of a score workgroup: unit of the stored softmax weights
 constexpr int FOLD_VTILE = 256;          // tokens a value workgroup stages at a time
 
@@ -120,8 +118,6 @@ __device__ __forceinline__ float fold_integer_zero(float s, float z, float qmax,
 __device__ __forceinline__ uint32_t f16_bits(float v) { return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)v); }
 
 __device__ __forceinline__ uint32_t perm_bytes(uint32_t hi, uint32_t lo, uint32_t sel) { return __builtin_amdgcn_perm(hi, lo, sel); }
-
-__device__ __forceinline__ f16x8 fold_frag16(uint32_t a, uint32_t b, uint32_t c, uint32_t d) { return as_frag(a, b, c, d); }
 
 // exact split of an fp32 number into three bf16 parts (8 + 8 + 8 bits, by truncation): the upper halves of the results
 __device__ __forceinline__ void split_bf16x3(float v, uint32_t& h, uint32_t& m, uint32_t& l)

@@ -2,9 +2,9 @@
 // tokens); part of folded_attn.hip, inside its namespace.
 //
 // x^ = (code - c0) s + (z + c0 s) with c0 = 2^(BITS - 1).  Scores: the scale is a factor of the token operand, one packed fp16
-// multiplication that is exact ((code - c0) has at most 3 significant bits, s has 8; both powers of two are set per block so
-// that only factors more than 2^-29 below the block's largest are rounded, at 2^-40 of it), so every product of a tile goes
-// straight into its scores; sum_c u[c] z[c] and sum_c u[c] s[c] are one more token tile, whose first columns hold z and s.
+// multiplication ((code - c0) has at most 3 significant bits, s has 8: exact, but that the operand is a multiple of 2^-24 and
+// carries 2^-9, so that with scales more than 2^22 below the block's largest it is rounded, by at most 2^-31 of a code step of the
+// largest), so every product of a tile goes straight into its scores; sum_c u[c] z[c] and sum_c u[c] s[c] are one more token tile, whose first columns hold z and s.
 // Values: the codes are summed with the softmax weights alone, and every 64 tokens the sums are taken times the block's scales
 // into y, z + c0 s times the sum of the weights (one more column tile, of ones) along with them.  The weights are cut to fp16
 // hi + lo, with parts down to 2^-40, against the sequence's maximum of their row.  A block whose own maximum lies more than 2^16
@@ -466,27 +466,11 @@ __global__ __launch_bounds__(512) void fold_values_pc_kernel(const FoldValueArgs
         __syncthreads();
     }
     // the four token ways meet in LDS; token way tw sums half a row tile (rt, four column tiles) of its slab
-    float4* acc_lds = reinterpret_cast<float4*>(lds);
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            acc_lds[((wave * RT + rt) * 8 + k) * 64 + lane] = make_float4(y[rt][k][0], y[rt][k][1], y[rt][k][2], y[rt][k][3]);
-    __syncthreads();
+    f32x4 t[4];
+    fold_meet<RT>(y, lds, wave, lane, t);
     if (live && tw < 2 * RT) {
         const long long yrow0 = ((long long)o.split * s.nb + o.b) * s.R;
         const int rt = tw >> 1, kg = tw & 1;
-        f32x4 t[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            float4 v = acc_lds[((sw * RT + rt) * 8 + 4 * kg + k) * 64 + lane];
-#pragma unroll
-            for (int w = 1; w < 4; ++w) {
-                const float4 u = acc_lds[(((2 * w + sw) * RT + rt) * 8 + 4 * kg + k) * 64 + lane];
-                v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
-            }
-            t[k] = f32x4{v.x, v.y, v.z, v.w};
-        }
         constexpr float down = 1.0f / UP;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {

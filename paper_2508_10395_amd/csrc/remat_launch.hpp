@@ -16,7 +16,7 @@ static const int32_t* stream_shifts(const void* wprep, const WPrepLayout& L)
 }
 
 // Kernels that use more than 64 KiB of LDS must be told so once (per device); remember which have been.
-static hipError_t allow_large_lds(const void* kernel, int lds_bytes)
+hipError_t allow_large_lds(const void* kernel, int lds_bytes)
 {
     struct Done { const void* kernel; int device; int bytes; };
     static std::mutex mu;
@@ -114,10 +114,10 @@ hipError_t launch_tile16_per_channel(int bits, const RematParams& p, int grid, h
 constexpr int DECODE_MFMA_EPILOGUE_MIN_GROUP = 4;
 
 // ---- the folded kernels' view of a decode call: d, group of the walk, group 0 for the accumulator source
-static FoldProblem fold_problem(const xq_attn_t* a, int T, int d, int group, int bits, int nibbles, size_t query_bytes)
+static FoldProblem fold_problem(const xq_attn_t* a, int d, int group, int bits, int nibbles, size_t query_bytes)
 {
     FoldProblem f{};
-    f.T = T; f.Hq = a->n_q_heads; f.Hkv = a->n_kv_heads;
+    f.Hq = a->n_q_heads; f.Hkv = a->n_kv_heads;
     f.dense = group == 0; f.bits = bits; f.group = group ? group : 128; f.nibbles = nibbles;
     f.n_slabs_k = f.n_slabs_v = d / 128;
     f.ng_v = group ? d / group : 0;
@@ -200,7 +200,7 @@ static bool latent_folding_pays(const xq_attn_t* a, int B, int max_len, int r)
 size_t remat_decode_query_bytes(const xq_attn_t* a, int B, int max_len, int d, int group)
 {
     const size_t remat = remat_workspace_bytes(B, a->n_q_heads, max_len, d, group ? group : 128, group != 0);
-    return !folding_may_pay(a, B, max_len, d) ? remat : std::max(remat, fold_workspace_bytes(fold_problem(a, 1, d, group, 4, 0, 0), B, max_len));
+    return !folding_may_pay(a, B, max_len, d) ? remat : std::max(remat, fold_workspace_bytes(fold_problem(a, d, group, 4, 0, 0), B, max_len));
 }
 
 hipError_t run_remat_attn_decode(const xq_attn_t* a, const uint16_t* q, const xq_cache_t* xc,
@@ -211,7 +211,7 @@ hipError_t run_remat_attn_decode(const xq_attn_t* a, const uint16_t* q, const xq
     if (!rope && decode_folding_pays(a, B, max_len, xc && xc->fmt.bits == 8 ? 2 * d : d, xc != nullptr)) {
         const int cb = xc ? xc->fmt.bits : 16, nib = cb == 8;
         const WPrepLayout L = make_wprep_layout_for_cache(d, xc ? xc->fmt.group : 128, cb, a->n_kv_heads);
-        const FoldProblem f = fold_problem(a, 1, L.d, xc ? L.G : 0, nib ? 4 : cb, nib,
+        const FoldProblem f = fold_problem(a, L.d, xc ? L.G : 0, nib ? 4 : cb, nib,
                                            remat_decode_query_bytes(a, B, max_len, L.d, xc ? L.G : 0));
         if (fold_fits(f, B, max_len, ws_bytes)) {
             FoldSource x{};
@@ -363,7 +363,7 @@ hipError_t run_remat_attn_prefill(const xq_attn_t* a, const uint16_t* q, int T, 
 
 static FoldProblem fold_problem_latent(const xq_attn_t* a, int r, int group, int bits, size_t query_bytes)
 {
-    return fold_problem(a, 1, r, group, bits, 0, query_bytes);
+    return fold_problem(a, r, group, bits, 0, query_bytes);
 }
 
 // as remat_decode_query_bytes
@@ -592,7 +592,7 @@ size_t remat_pc_workspace_bytes(int B, int Hq, int Hkv, int max_len, int d, int 
 
 static FoldProblem fold_problem_pc(const xq_attn_t* a, int d, int block, int bits, size_t query_bytes)
 {
-    FoldProblem f = fold_problem(a, 1, d, 128, bits, 0, query_bytes);
+    FoldProblem f = fold_problem(a, d, 128, bits, 0, query_bytes);
     f.block = block;
     return f;
 }
