@@ -34,6 +34,13 @@ def _kernels(call):
     return [e.name for e in p.events()]
 
 
+def _folds(call):
+    names = _kernels(call)
+    folded = any("fold_scores" in n for n in names)
+    assert folded != any("remat_attn" in n for n in names), names
+    return folded
+
+
 def _step(xq, B, L, d, Hq, Hkv, bits, G=128, per_channel=False, terms=False):
     """One decode step on caches of arbitrary codes, as a call without arguments."""
     gen = torch.Generator("cuda").manual_seed(B * L + d)
@@ -71,8 +78,7 @@ def test_which_order_a_step_takes(xq, folded, step):
     """The order that was measured to be the faster one, on either side of the rule."""
     call = _step(xq, **step)
     call()
-    names = _kernels(call)
-    assert any("fold_scores" in n for n in names) == folded and any("remat_attn" in n for n in names) != folded, names
+    assert _folds(call) == folded
 
 
 def _run(xq, w, bits, G, lens, x_bits=None, workspaces=(None,), pairs=None, wk=None, scale_sign=None):
@@ -101,14 +107,17 @@ def _run(xq, w, bits, G, lens, x_bits=None, workspaces=(None,), pairs=None, wk=N
     wprep = xq.xq_prepare_weights(attn, w.d, G, bits, bits_to_torch(wk), bits_to_torch(wv))
     for n in workspaces:
         ws = None if n is None else torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")
-        out = xq.xq_remat_attn_decode(attn, bits_to_torch(q), wprep, lens, workspace=ws, **src).cpu().numpy()
+        call = lambda: xq.xq_remat_attn_decode(attn, bits_to_torch(q), wprep, lens, workspace=ws, **src)
+        out = call().cpu().numpy()
+        if n is None:
+            assert _folds(call)
         assert np.all(np.isfinite(out))
         rows, worst = rel_errors(np.array([out[b, h] for b, h in pairs]), ref)
         assert rows.max() <= TOL and worst <= TOL, (n, float(rows.max()), float(worst))
 
 
 @pytest.mark.parametrize("bits,G", [(2, 64), (2, 128), (3, 64), (3, 128), (4, 64), (4, 128), (8, 64), (8, 128), (16, 128)])
-@pytest.mark.parametrize("Hq,Hkv,d,lens", [(16, 16, 2048, [300, 1, 129]), (32, 8, 2176, [257, 33]), (40, 40, 2048, [511])])
+@pytest.mark.parametrize("Hq,Hkv,d,lens", [(16, 16, 4096, [300, 1, 129]), (32, 8, 4224, [257, 33]), (40, 40, 4096, [511])])
 def test_formats_rows_and_tile_edges(xq, bits, G, Hq, Hkv, d, lens):
     w = xi.C2.scaled(B=len(lens), L=max(lens), d=d, Hq=Hq, Hkv=Hkv, n_outlier=d // 100)
     _run(xq, w, bits, G, lens)
@@ -117,7 +126,7 @@ def test_formats_rows_and_tile_edges(xq, bits, G, Hq, Hkv, d, lens):
 @pytest.mark.parametrize("bits,G", [(2, 64), (3, 128), (16, 128)])
 def test_token_ways_of_a_score_workgroup(xq, bits, G):
     """Enough tiles that a score workgroup takes two of them, on a narrow layer, with a dead second tile."""
-    w = xi.C2.scaled(B=16, L=4000, d=256, Hq=64, Hkv=4, n_outlier=2)
+    w = xi.C2.scaled(B=16, L=4000, d=256, Hq=64, Hkv=8, n_outlier=2)
     lens = [4000, 3969, 129, 128, 1, 2049] + [100] * 10
     _run(xq, w, bits, G, lens, pairs=[(0, 0), (0, 63), (1, 17), (2, 5), (3, 40), (4, 33), (5, 62), (15, 8)])
 
@@ -126,7 +135,7 @@ def test_token_ways_of_a_score_workgroup(xq, bits, G):
 def test_smaller_workspaces(xq, bits):
     """Between the smallest workspace that is accepted and the one that is asked for, the launch goes in groups of sequences,
     or through the kernels that rematerialise keys and values."""
-    B, L, d, Hq = 3, 130, 2048, 32
+    B, L, d, Hq = 3, 130, 4096, 32
     w = xi.C2.scaled(B=B, L=L, d=d, Hq=Hq, Hkv=8, n_outlier=20)
     asked = xq.xq_remat_attn_workspace_bytes(xq.XQAttn(Hq, 8, 128, 1.0), B, L, d, 128 if bits < 16 else 0)
     least = B * Hq * 2 * 4 * 130 * 4 + (B * 2 * (d // 128 + 1) * 128 * 2 if bits < 16 else 0)
@@ -136,7 +145,7 @@ def test_smaller_workspaces(xq, bits):
 
 def test_scales_of_every_magnitude(xq):
     """Constant groups (scale 0) and groups 1000 times larger than their neighbours, large offsets."""
-    w = xi.C2.scaled(B=1, L=300, d=2048, Hq=16, Hkv=16, n_outlier=0)
+    w = xi.C2.scaled(B=1, L=300, d=2304, Hq=16, Hkv=16, n_outlier=0)
     x = xi.from_bf16_bits(xi.gen_x(w)).copy()
     x[0, :, 128:256] = 0.5
     x[0, ::2, 256:384] *= 30.0
@@ -224,16 +233,20 @@ def test_latent_halves(xq, bits, G, small):
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
 @pytest.mark.parametrize("G", [64, 128])
-@pytest.mark.parametrize("Hq,Hkv,d,lens", [(16, 16, 2048, [330, 1, 256, 320]), (32, 8, 2176, [257, 63]), (40, 40, 2048, [512]), (16, 16, 2048, [50])])
+@pytest.mark.parametrize("Hq,Hkv,d,lens", [(16, 16, 4096, [330, 1, 256, 320]), (32, 8, 4224, [257, 63]), (40, 40, 4096, [512]), (16, 16, 4096, [50])])
 def test_per_channel_blocks_and_window(xq, bits, G, Hq, Hkv, d, lens):
     """Blocks that end inside a 128- or 256-token tile, no window, a window alone, nothing but windows."""
+    err = []
     w = xi.C2.scaled(B=len(lens), L=max(lens), d=d, Hq=Hq, Hkv=Hkv, n_outlier=d // 100)
-    assert _attend(xq, w, bits, G, lens, pairs=[(b, h) for b in range(len(lens)) for h in (0, Hq - 1)]) <= TOL
+    assert _folds(lambda: err.append(_attend(xq, w, bits, G, lens, pairs=[(b, h) for b in range(len(lens)) for h in (0, Hq - 1)])))
+    assert err[0] <= TOL
 
 
 def test_per_channel_scales_of_every_magnitude(xq):
-    w = xi.C2.scaled(B=1, L=300, d=2048, Hq=16, Hkv=16, n_outlier=0)
-    assert _attend(xq, w, 3, 128, [300], pairs=[(0, 0), (0, 9)], scale_spread=64.0) <= TOL
+    w = xi.C2.scaled(B=1, L=300, d=2304, Hq=16, Hkv=16, n_outlier=0)
+    err = []
+    assert _folds(lambda: err.append(_attend(xq, w, 3, 128, [300], pairs=[(0, 0), (0, 9)], scale_spread=64.0)))
+    assert err[0] <= TOL
 
 
 @pytest.mark.parametrize("bits", [2, 3, 4])
@@ -277,6 +290,107 @@ def test_per_channel_terms_serve_both_orders(xq):
     q = torch.randn((B, Hkv, 128), device="cuda").bfloat16()
     terms = xq.alloc_per_channel_terms(cache, Hkv)
     xq.xq_remat_attn_decode_per_channel(attn, q, cache, tail, [513] * B, wc, wd, terms=terms, terms_valid=False)
+    assert _folds(lambda: xq.xq_remat_attn_decode_per_channel(attn, q, cache, tail, [513] * B, wc, wd, terms=terms, terms_valid=True))
+    assert not _folds(lambda: xq.xq_remat_attn_decode_per_channel(attn, q, cache, tail, [512] * B, wc, wd, terms=terms, terms_valid=True))
     kept = xq.xq_remat_attn_decode_per_channel(attn, q, cache, tail, [512] * B, wc, wd, terms=terms, terms_valid=True)
     fresh = xq.xq_remat_attn_decode_per_channel(attn, q, cache, tail, [512] * B, wc, wd)
     assert torch.equal(kept, fresh)
+
+
+def _cases(xq, kind, B=3, L=700, Hq=32, Hkv=8):
+    """A large step of every source, as call(q, lens, order, workspace): sequences in the given order (None: as they are)."""
+    take = lambda t, order: t if order is None else t[order].contiguous()
+    gen = torch.Generator("cuda").manual_seed(11)
+    attn = xq.XQAttn(Hq, Hkv, 128, 128 ** -0.5)
+    d = 1280 if kind == "latent" else 4096
+    rows = torch.randn((B, L, 2 * d if kind == "latent" else d), generator=gen, device="cuda").bfloat16()
+    wk, wv = (torch.randn((d, Hkv * 128), generator=gen, device="cuda").mul(d ** -0.5).bfloat16() for _ in range(2))
+    q = torch.randn((B, Hq, 128), generator=gen, device="cuda").bfloat16()
+    if kind == "acc":
+        wp = xq.xq_prepare_weights(attn, d, 0, 16, wk, wv)
+        return q, lambda q, lens, order, ws=None: xq.xq_remat_attn_decode(attn, take(q, order), wp, lens if order is None else [lens[i] for i in order],
+                                                                          acc_bf16=take(rows, order), workspace=ws), rows
+    if kind == "per_channel":
+        G, nblk = 64, L // 64
+        cache = xq.alloc_cache_per_channel(B, nblk * G, d, G, 3)
+        xq.xq_quantize_blocks_per_channel(cache, rows[:, :nblk * G].contiguous(), [0] * B)
+        wc, wd = xq.xq_prepare_weights(attn, d, 128, 3, wk, wv), xq.xq_prepare_weights(attn, d, 0, 16, wk, wv)
+        tail = rows[:, :G].contiguous()
+    elif kind == "latent":
+        cache = xq.alloc_cache(B, L, 2 * d, 64, 2)
+        xq.xq_quantize_append(cache, rows, [0] * B)
+        wp = xq.xq_prepare_weights_latent(attn, d, 64, 2, wk, wv)
+    else:
+        cache = xq.alloc_cache(B, L, d, 128, 3)
+        xq.xq_quantize_append(cache, rows, [0] * B)
+        wp = xq.xq_prepare_weights(attn, d, 128, 3, wk, wv)
+
+    def call(q, lens, order, ws=None):
+        c = xq.XQCache(*(take(t, order) for t in (cache.codes, cache.scale, cache.zero)), B, cache.cap, cache.d, cache.group, cache.bits)
+        qq, ll = take(q, order), lens if order is None else [lens[i] for i in order]
+        if kind == "per_channel":
+            return xq.xq_remat_attn_decode_per_channel(attn, qq, c, take(tail, order), ll, wc, wd, workspace=ws)
+        if kind == "latent":
+            return xq.xq_remat_attn_decode_latent(attn, qq, wp, ll, c, workspace=ws)
+        return xq.xq_remat_attn_decode(attn, qq, wp, ll, xcache=c, workspace=ws)
+    return q, call, cache
+
+
+KINDS = ["coded", "acc", "latent", "per_channel"]
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_same_bits_again_in_any_order_on_any_workspace(xq, kind):
+    """A batch's results do not depend on what the workspace held, nor on the order of its sequences."""
+    q, call, _ = _cases(xq, kind)
+    lens = [700, 130, 515]
+    assert _folds(lambda: call(q, lens, [0, 1, 2]))
+    want = call(q, lens, [0, 1, 2])
+    n = 64 << 20
+    for fill in (0x00, 0xFF, 0x7F):
+        got = call(q, lens, [0, 1, 2], torch.full((n,), fill, dtype=torch.uint8, device="cuda"))
+        assert torch.equal(got, want), fill
+    assert torch.equal(call(q, lens, [2, 0, 1]), want[[2, 0, 1]])
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_numbers_that_are_not_finite_stay_in_their_sequence(xq, kind):
+    """NaN or infinity in a cached row makes that sequence's outputs NaN, in a query only its own head's; all others keep their
+    bits."""
+    q, call, src = _cases(xq, kind)
+    lens, order = [700, 130, 515], None
+    want = call(q, lens, order)
+    rows, at = (src, 40) if kind == "acc" else (src.scale, 40 if kind == "per_channel" else 3)
+    for v in (float("nan"), float("inf")):
+        keep = rows[1, 0, at].clone()
+        rows[1, 0, at] = v
+        got = call(q, lens, order)
+        rows[1, 0, at] = keep
+        assert bool(got[1].isnan().all()) and torch.equal(got[[0, 2]], want[[0, 2]]), v
+    bad = q.clone()
+    bad[2, 5, 17] = float("nan")
+    got = call(bad, lens, order)
+    assert bool(got[2, 5].isnan().all())
+    got[2, 5] = want[2, 5]
+    assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_large_step_replays_from_a_graph(xq, kind):
+    """The five kernels in a graph, replayed with eager work between the replays, against the eager result."""
+    q, call, _ = _cases(xq, kind)
+    lens, order = [700, 130, 515], None
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    static_q = q.clone()
+    call(static_q, lens, order, ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = call(static_q, lens, order, ws)
+    gen = torch.Generator("cuda").manual_seed(4)
+    for _ in range(4):
+        static_q.copy_(torch.randn(q.shape, generator=gen, device="cuda").bfloat16())
+        graph.replay()
+        torch.cuda.synchronize()
+        got = out.clone()
+        assert torch.equal(got, call(static_q, lens, order))

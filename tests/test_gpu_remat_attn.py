@@ -159,7 +159,7 @@ def test_dense_accumulator_source(xq):
 
 
 def test_determinism_and_independence_of_batch_order(xq):
-    """Same inputs twice -> identical bits; a sequence's output does not depend on its neighbours."""
+    """Same inputs twice -> identical bits; a sequence's output does not depend on its place in the batch."""
     w = xi.C2.scaled(B=2, L=300, d=512, Hq=4, Hkv=4, n_outlier=5)
     x, (wk, wv), q = xi.gen_x(w), xi.gen_weights(w), xi.gen_q(w)
     attn = xq.XQAttn(w.Hq, w.Hkv, w.hd, w.hd ** -0.5)

@@ -56,6 +56,9 @@ def test_static_workspace_two_calls_second_smaller(xq):
     gqa = xi.C4.scaled(B=2, L=700, d=768, Hq=8, Hkv=2)
     _pair_of_calls(xq, gqa, 2, 64, lens=[700, 130])
     _pair_of_calls(xq, xi.C3.scaled(B=2, L=330, d=512, Hq=4, Hkv=4), 0, 0, lens=[330, 100], dense=True)
+    # layers wide enough for the kernels of large steps
+    _pair_of_calls(xq, xi.C2.scaled(B=2, L=700, d=4096, Hq=32, Hkv=8, n_outlier=40), 3, 128, lens=[700, 130])
+    _pair_of_calls(xq, xi.C3.scaled(B=2, L=600, d=4096, Hq=16, Hkv=16), 0, 0, lens=[600, 257], dense=True)
 
 
 def test_static_workspace_of_a_large_step(xq):
