@@ -3,9 +3,9 @@
 
 One step = one decode step of one layer of the Llama-2-7B-shaped workload (config 2:
 d=4096, 32x128 MHA, batch 8, context 4096, X cached 3-bit asym, group 128): quantise and
-append the new token's X row (xq_quantize_append, T=1), then rematerialise K,V from the
-packed cache and attend (xq_remat_attn_decode; the products taken in the order that
-needs no K and V in memory or registers: (q Wk^T) X^T, then (p X) Wv).  Inputs are seeded synthetic tensors that
+append the new token's X row (xq_quantize_append, T=1), then attend to the cached tokens'
+keys and values (xq_remat_attn_decode; the products taken in the order that forms no
+key and no value: (q Wk^T) X^T, then (p X) Wv).  Inputs are seeded synthetic tensors that
 are resident in HBM before the timed region.  Prints ONE JSON line.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W]
@@ -34,9 +34,9 @@ def parse():
     ap.add_argument("--steps", type=int, default=200)
     ap.add_argument("--warmup", type=int, default=40)
     ap.add_argument("--settle", type=int, default=40,
-                    help="launches of the fused kernel during set-up, before the warm-up steps: from an idle GPU the clock "
-                         "takes some 15 launches to settle (the first ones run 1.8 - 2.2 ms against 1.7), which a short "
-                         "--warmup alone would put inside the timed steps; reported as config.settle_launches")
+                    help="launches of the decode call during set-up, before the warm-up steps: from an idle GPU the first steps "
+                         "are slower (20 steps after 5 of warm-up: 0.115 - 0.117 ms with none of these, 0.111 - 0.114 with 40, "
+                         "0.111 with 400 or 4000); reported as config.settle_launches")
     ap.add_argument("--no-cpu-baseline", action="store_true", help="skip the oracle timing leg")
     ap.add_argument("--cpu-pairs", type=int, default=96, help="(sequence, head) pairs the oracle times")
     ap.add_argument("--profile-copy", action="store_true",

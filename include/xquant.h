@@ -138,8 +138,10 @@ xq_status_t xq_prepare_weights(const xq_attn_t *a, int32_t d, int32_t group, int
  * sequence b and query head h (KV head h / (n_q_heads/n_kv_heads)):
  *   K = X^[0:len[b]] Wk_h,  V = X^[0:len[b]] Wv_h,
  *   out[b][h] = softmax(q[b][h] K^T * softmax_scale) V.
- * The products are formed in the cheaper order, S = (q Wk_h^T) X^^T and out = (softmax(S) X^) Wv_h, except on
- * small steps; the same result to fp32 accuracy.
+ * The products are formed in the order S = (q Wk_h^T) X^^T and out = (softmax(S) X^) Wv_h wherever that is
+ * the faster one for the step's sizes; the same result to fp32 accuracy.  The same call gives the same bits, in
+ * whatever order the sequences come; which order is taken and how the sums are split follows from the whole
+ * batch (B, max_b len[b]), so in another batch a sequence's result may differ in its last bits.
  * Exactly one source of X^ is given:
  *   xcache != NULL   an X cache (XQuant), x^ = code*scale + zero;
  *   acc_bf16 != NULL the cross-layer accumulator [B][cap][d] (XQuant-CL); one sequence's rows must stay
@@ -170,10 +172,11 @@ xq_status_t xq_remat_attn_decode(const xq_attn_t *a, const uint16_t *q_bf16,
 
 /*
  * xq_remat_attn_decode for callers that cannot allocate device memory (code under HIP graph capture,
- * tight serving loops, harnesses that forbid it): same arguments, same kernels and same result (bit for
- * bit, up to layers of n_q_heads * d = 2^22 at the least), but
+ * tight serving loops, harnesses that forbid it): same arguments and same result (bit for bit as with the
+ * workspace asked for, up to n_q_heads * d = 2^21 and 2^18 tokens at the least; beyond, to rounding), but
  * the workspace is a buffer built into the library, XQ_STATIC_SCRATCH_BYTES per GPU, instead of a
- * caller buffer; a step that asks for more runs through it in several groups of sequences.  The call allocates and frees nothing.  A problem for which xq_remat_attn_decode would
+ * caller buffer; a step that asks for more runs through it in several groups of sequences.  The call
+ * allocates and frees nothing.  A problem for which xq_remat_attn_decode would
  * not accept XQ_STATIC_SCRATCH_BYTES of workspace is refused with
  * XQ_ERR_WORKSPACE before anything is launched (the 32 MiB cover e.g. B=8, 32 query heads, context
  * 4096, d=4096, group 128: 19.5 MB).  The buffer belongs to the device that is current at the call
@@ -365,10 +368,12 @@ xq_status_t xq_quantize_blocks_per_channel(const xq_cache_t *cache, const uint16
  *   workspace    dev, xq_remat_attn_per_channel_workspace_bytes(a, B, max len, d, group) bytes
  *   terms        dev or NULL.  The terms the call derives from the complete blocks (operand factors,
  *                zero-points times [Wk | Wv], block exponents) change only when a block is completed.
- *                NULL: they are recomputed in the workspace on every call.  Otherwise a buffer the caller
+ *                Large steps do not need them, and pass NULL best: filling a buffer takes about as long as such a
+ *                step itself.  Steps that do need them recompute them in the workspace on every call where
+ *                terms is NULL.  Otherwise a buffer the caller
  *                keeps per (cache, weights), xq_per_channel_terms_bytes(B, cap, d, group, n_kv_heads)
  *                bytes, 16-byte aligned, laid out for the cache's capacity:
- *                  terms_valid = 0  the call computes the terms into it, then uses them;
+ *                  terms_valid = 0  the call computes the terms into it (also where it does not use them);
  *                  terms_valid != 0 the call only reads it: the caller states that since the last call
  *                                   with terms_valid = 0 on this buffer no sequence of the batch has
  *                                   completed a block and the cache, the weights and B are the same.
