@@ -197,6 +197,18 @@ def test_large_rows_of_small_weight(xq, bits, G, rows):
 
 
 @pytest.mark.parametrize("bits,G", CODED)
+@pytest.mark.parametrize("rows", [[5, 300], list(range(256, 520)), [899]])
+@pytest.mark.parametrize("nats", [3.0, -28.0])
+def test_rows_of_zeros(xq, bits, G, rows, nats):
+    """Rows of zeros (every scale 0) among rows that score `nats`: with the weights of the others, or with nearly all of it, when
+    the output is what the others' small weights leave."""
+    w = xi.C2.scaled(B=1, L=900, d=2304, Hq=16, Hkv=16, n_outlier=0)
+    x, wk = _small_weight_rows(w, 0, nats, rows)
+    x[0, rows] = 0
+    _run(xq, w, bits, G, [900], x_bits=x, wk=wk, pairs=[(0, h) for h in (0, 7, 15)])
+
+
+@pytest.mark.parametrize("bits,G", CODED)
 def test_scales_of_either_sign(xq, bits, G):
     """x^ = code scale + zero holds for a negative scale too."""
     w = xi.C2.scaled(B=1, L=600, d=2304, Hq=16, Hkv=16, n_outlier=0)
