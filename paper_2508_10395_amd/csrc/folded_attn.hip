@@ -312,8 +312,10 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
 }
 
 // =====================================================================================================================
-// Scores.  A wave owns 128 tokens of a sequence, one block of 16 RT query rows and a run of adjacent slabs (so that a
-// token's scales share cache lines); a workgroup's 8 waves are slab ways and token ways.  A wave walks half slabs (64
+// Scores.  A wave owns 128 tokens of a sequence, one block of 16 RT query rows and every SW-th slab, so that the slab ways are
+// at neighbouring pieces of a token's cache lines at the same time (with runs of adjacent slabs per way a line left L2 before
+// the wave came to its next piece: 8 x 4096 tokens of 3 bits 38 us against 31, 16 x 8191 of 2 bits in groups of 64 124 against
+// 102, 4 x 32768 of 2 bits 114 against 96); a workgroup's 8 waves are slab ways and token ways.  A wave walks half slabs (64
 // channels) and keeps a half's folded queries in registers while its 128 tokens stream past, the next half's on their way,
 // so that neither LDS nor L2 is asked for them once per token.  A slab's codes are loaded row by row while the slab before
 // is worked on and go through the wave's own LDS image into operand order; a lane unpacks its token's codes.  A half's
@@ -321,9 +323,9 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
 // registers; the rests of the zero-points enter through one more matrix instruction per slab and row tile.  At the end
 // the slab ways' partial scores meet in LDS, and the softmax weights against the tile's maximum are stored as the value
 // kernel reads them.
-// Bound by the latency of the loads behind a run of few slabs and by issue: 1024 tiles of 2 bits take 114 us, 100 without
-// the meta loads, 89 without the codes' loads, 75 with nothing loaded; codes read in operand order straight into registers
-// (64 cache lines touched by every load) took 173 us.
+// Bound by issue and by the latency of the loads (with runs of adjacent slabs 1024 tiles of 2 bits took 114 us: 89 without the
+// codes' loads, 75 with nothing loaded); codes read in operand order straight into registers (64 cache lines touched by every
+// load) took 173 us.
 // =====================================================================================================================
 struct FoldScoreArgs {
     FoldSource x;
@@ -354,10 +356,9 @@ __device__ __forceinline__ bool fold_score_place(const FoldShape& s, bool window
     o.sw = wave & (o.SW - 1);
     o.tw = wave >> sw_log2;
     o.tile = (item % tiles) * ways + o.tw;
-    const int per = (n_slabs + o.SW - 1) >> sw_log2;                 // a run of adjacent slabs
-    o.slab0 = o.sw * per;
-    o.slab1 = o.tile * FOLD_TILE < o.len ? min(o.slab0 + per, n_slabs) : o.slab0;
-    o.nw = (n_slabs + per - 1) / per;
+    o.slab0 = o.sw;                                                  // every SW-th slab
+    o.slab1 = o.tile * FOLD_TILE < o.len ? max(o.sw, n_slabs) : o.sw;
+    o.nw = min(o.SW, n_slabs);
     return (item % tiles) * ways * FOLD_TILE < o.len;
 }
 
@@ -610,8 +611,8 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) P[1][rt] = zero4;
         rec[3][1] = 0u;                                              // (unit -1 adds nothing)
-        for (int slab = slab0; slab < slab1; ++slab) {
-            const int snext = slab + 1 < slab1 ? slab + 1 : slab;    // (the last iteration prepares itself again)
+        for (int slab = slab0; slab < slab1; slab += o.SW) {
+            const int snext = slab + o.SW < slab1 ? slab + o.SW : slab;    // (the last iteration prepares itself again)
             __builtin_amdgcn_sched_barrier(0);
             static_for<0, 16>([&](auto T) XQ_INLINE_LAMBDA {
                 constexpr int t = decltype(T)::value, h = t >> 3, i = t & 7;
@@ -717,8 +718,8 @@ __device__ __forceinline__ void fold_scores_dense(const FoldScoreArgs& a, const 
         };
         load_u(2 * o.slab0, std::integral_constant<int, 0>{});
         static_for<0, 8>([&](auto I) XQ_INLINE_LAMBDA { load_x(2 * o.slab0, I); });
-        for (int slab = o.slab0; slab < o.slab1; ++slab) {
-            const int snext = slab + 1 < o.slab1 ? slab + 1 : slab;
+        for (int slab = o.slab0; slab < o.slab1; slab += o.SW) {
+            const int snext = slab + o.SW < o.slab1 ? slab + o.SW : slab;
             static_for<0, 2>([&](auto HF) XQ_INLINE_LAMBDA {
                 constexpr int h = decltype(HF)::value;
                 const int hn = h == 0 ? 2 * slab + 1 : 2 * snext;
@@ -1975,8 +1976,8 @@ hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSo
         if (e != hipSuccess) return e;
         {
             // Slab ways of a workgroup: eight, or four with two token tiles where that still leaves two rounds of workgroups
-            // (a wave's set-up and the meeting of the slab ways then weigh less).  Measured, 8 / 4 / 2 slab ways: 1024 tiles
-            // of 2 bits 122 / 114 / 113 us (group 128), 133 / 124 / 134 us (group 64); 256 tiles of 3 bits 38 / 51 / 84 us.
+            // (a wave's set-up and the meeting of the slab ways then weigh less).  Measured, 8 / 4 slab ways: 1024 tiles of
+            // 2 bits 111 / 98 us (group 128), 120 / 108 us (group 64), half the width 58 / 47 us; 256 tiles of 3 bits 33 / 51.
             const int swl = B * sh.nrb * sh.tiles >= 4 * 256 && !f.block ? 2 : 3, ways = 8 >> swl;
             FoldScoreArgs a{kx, sh, u, rowfac, p, mtile, L.u_slab, swl, FoldSource{}, u_dense, 0};
             if (any_window) { a.window = *window; a.n_window = xcd_grid(sh.nb * sh.nrb); }

@@ -205,8 +205,8 @@ __global__ __launch_bounds__(512) void fold_scores_pc_kernel(const FoldScoreArgs
         read_unit(std::integral_constant<int, 0>{});
         read_unit(std::integral_constant<int, 1>{});
         static_for<0, 8>([&](auto K) XQ_INLINE_LAMBDA { unpack(std::integral_constant<int, 0>{}, K); });
-        for (int slab = slab0; slab < slab1; ++slab) {
-            const int snext = slab + 1 < slab1 ? slab + 1 : slab;
+        for (int slab = slab0; slab < slab1; slab += o.SW) {
+            const int snext = slab + o.SW < slab1 ? slab + o.SW : slab;
             __builtin_amdgcn_sched_barrier(0);
             static_for<0, 16>([&](auto T) XQ_INLINE_LAMBDA {
                 constexpr int t = decltype(T)::value, h = t >> 3, i = t & 7;
