@@ -315,7 +315,7 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
 // Scores.  A wave owns 128 tokens of a sequence, one block of 16 RT query rows and every SW-th slab, so that the slab ways are
 // at neighbouring pieces of a token's cache lines at the same time (with runs of adjacent slabs per way a line left L2 before
 // the wave came to its next piece: 8 x 4096 tokens of 3 bits 38 us against 31, 16 x 8191 of 2 bits in groups of 64 124 against
-// 102, 4 x 32768 of 2 bits 114 against 96); a workgroup's 8 waves are slab ways and token ways.  A wave walks half slabs (64
+// 102, 4 x 32768 of 2 bits 114 against 96); a workgroup's waves are the slab ways of one tile.  A wave walks half slabs (64
 // channels) and keeps a half's folded queries in registers while its 128 tokens stream past, the next half's on their way,
 // so that neither LDS nor L2 is asked for them once per token.  A slab's codes are loaded row by row while the slab before
 // is worked on and go through the wave's own LDS image into operand order; a lane unpacks its token's codes.  A half's
@@ -334,32 +334,30 @@ struct FoldScoreArgs {
     const float* rowfac;
     float* p;                            // [nb][nrb][tiles][4][FOLD_P_TILE32]
     float* mtile;                        // [nb][nrb][tiles << mhalf][16 RT]
-    int u_slab, sw_log2;
+    int u_slab, waves;                   // waves of a workgroup
     FoldSource window;                   // per-channel caches: the window's rows, its folded queries and workgroups
     const uint8_t* u_window;
     int n_window;
 };
 
-// which tokens and slabs a wave of a score workgroup has: 8 / SW token ways of one tile each, SW = 1 << sw_log2 slab ways
-struct FoldScorePlace { int b, rb, tile, tile0, len, sw, SW, tw, slab0, slab1, nw; };   // nw = slab ways that hold any slab
-__device__ __forceinline__ bool fold_score_place(const FoldShape& s, bool window, int sw_log2, int n_slabs, int wg, int wave, FoldScorePlace& o)
+// the tile of a score workgroup and the slabs of a wave: every SW-th one, SW the waves of the workgroup (4 or 8)
+struct FoldScorePlace { int b, rb, tile, tile0, len, SW, slab0, slab1, nw; };           // nw = waves that hold any slab
+__device__ __forceinline__ bool fold_score_place(const FoldShape& s, bool window, int waves, int n_slabs, int wg, int wave, FoldScorePlace& o)
 {
-    const int ways = 8 >> sw_log2, tiles = window ? 1 : (s.tiles + ways - 1) / ways, n = s.nb * s.nrb * tiles;
+    const int tiles = window ? 1 : s.tiles, n = s.nb * s.nrb * tiles;
     const int item = xcd_contiguous(n, wg);
     if (item >= n) return false;
+    o.tile = item % tiles;
     o.rb = (item / tiles) % s.nrb;
     o.b = item / (tiles * s.nrb);
     const FoldSpan span = fold_span(s, o.b, window);
     o.len = span.len;
     o.tile0 = span.tile0;
-    o.SW = 1 << sw_log2;
-    o.sw = wave & (o.SW - 1);
-    o.tw = wave >> sw_log2;
-    o.tile = (item % tiles) * ways + o.tw;
-    o.slab0 = o.sw;                                                  // every SW-th slab
-    o.slab1 = o.tile * FOLD_TILE < o.len ? max(o.sw, n_slabs) : o.sw;
-    o.nw = min(o.SW, n_slabs);
-    return (item % tiles) * ways * FOLD_TILE < o.len;
+    o.SW = waves;
+    o.slab0 = wave;
+    o.slab1 = max(wave, n_slabs);
+    o.nw = min(waves, n_slabs);
+    return o.tile * FOLD_TILE < o.len;
 }
 
 // what happens to the waves' partial scores: the end of every score kernel
@@ -377,42 +375,39 @@ __device__ __forceinline__ void fold_scores_finish(const FoldShape& s, const flo
             for (int i = 0; i < 8; ++i)
                 part[((wave * RT + rt) * 8 + i) * 64 + lane] = make_float4(S[rt][i][0], S[rt][i][1], S[rt][i][2], S[rt][i][3]);
     __syncthreads();
-    const bool live = o.tile * FOLD_TILE < o.len;
-    const int c16 = lane & 15, q = lane >> 4, share = 8 / o.SW;      // tile16s a wave of the token way sums up
+    const int c16 = lane & 15, q = lane >> 4, share = 8 / o.SW;      // tile16s a wave sums up
     const float* rowfac = rowfac_all + ((long long)o.b * s.nrb + o.rb) * 16 * RT;
-    float* mx = lds + 8 * RT * 8 * 256 + o.tw * 8 * 16 * RT;         // [token way][tile16][16 RT], behind the partial scores
-    // (the sums replace the first way's partial scores: what a wave reads there it has itself replaced)
-    if (live)
-        for (int j = 0; j < share; ++j) {
-            const int i16 = o.sw * share + j, tok = o.tile * FOLD_TILE + i16 * 16 + c16;
+    float* mx = lds + o.SW * RT * 8 * 256;                           // [tile16][16 RT], behind the partial scores
+    // (the sums replace the first wave's partial scores: what a wave reads there it has itself replaced)
+    for (int j = 0; j < share; ++j) {
+        const int i16 = wave * share + j, tok = o.tile * FOLD_TILE + i16 * 16 + c16;
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-                float4* first = &part[((o.tw * o.SW * RT + rt) * 8 + i16) * 64 + lane];
-                float4 t = *first;
-                for (int k = 1; k < o.nw; ++k) {
-                    const float4 u = first[k * RT * 8 * 64];
-                    t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
-                }
-                float v[4] = {t.x, t.y, t.z, t.w}, m[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    v[r] = tok < o.len ? v[r] * rowfac[rt * 16 + 4 * q + r] : -INFINITY;
-                    m[r] = v[r];
-                    m[r] = fmaxf(m[r], dpp_f32<DPP_QUAD_XOR1>(m[r]));
-                    m[r] = fmaxf(m[r], dpp_f32<DPP_QUAD_XOR2>(m[r]));
-                    m[r] = fmaxf(m[r], dpp_f32<DPP_ROW_HALF_MIRROR>(m[r]));
-                    m[r] = fmaxf(m[r], dpp_f32<DPP_ROW_MIRROR>(m[r]));
-                }
-                *first = make_float4(v[0], v[1], v[2], v[3]);
-                if (c16 == 0)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) mx[i16 * 16 * RT + rt * 16 + 4 * q + r] = m[r];
+        for (int rt = 0; rt < RT; ++rt) {
+            float4* first = &part[(rt * 8 + i16) * 64 + lane];
+            float4 t = *first;
+            for (int k = 1; k < o.nw; ++k) {
+                const float4 u = first[k * RT * 8 * 64];
+                t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
             }
+            float v[4] = {t.x, t.y, t.z, t.w}, m[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                v[r] = tok < o.len ? v[r] * rowfac[rt * 16 + 4 * q + r] : -INFINITY;
+                m[r] = v[r];
+                m[r] = fmaxf(m[r], dpp_f32<DPP_QUAD_XOR1>(m[r]));
+                m[r] = fmaxf(m[r], dpp_f32<DPP_QUAD_XOR2>(m[r]));
+                m[r] = fmaxf(m[r], dpp_f32<DPP_ROW_HALF_MIRROR>(m[r]));
+                m[r] = fmaxf(m[r], dpp_f32<DPP_ROW_MIRROR>(m[r]));
+            }
+            *first = make_float4(v[0], v[1], v[2], v[3]);
+            if (c16 == 0)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) mx[i16 * 16 * RT + rt * 16 + 4 * q + r] = m[r];
         }
+    }
     __syncthreads();
-    if (!live) return;
     // maximum of the tile, or of the wave's half of it (eight slab ways then: a wave's tile16s lie in one half)
-    const int i0 = o.sw * share, mrow0 = (o.tile0 + o.tile) << s.mhalf | (s.mhalf ? i0 >> 2 : 0);
+    const int i0 = wave * share, mrow0 = (o.tile0 + o.tile) << s.mhalf | (s.mhalf ? i0 >> 2 : 0);
     const bool stores = c16 == 0 && (s.mhalf ? (i0 & 3) == 0 : i0 == 0);
     float Mu[RT][4];
 #pragma unroll
@@ -431,11 +426,11 @@ __device__ __forceinline__ void fold_scores_finish(const FoldShape& s, const flo
             if (stores) mtile_all[((((long long)o.b * s.nrb + o.rb) * s.tiles << s.mhalf) + mrow0) * 16 * RT + row] = M;
         }
     for (int j = 0; j < share; ++j) {
-        const int i16 = o.sw * share + j, t32 = (i16 & 1) * 16 + c16, slot = t32 >> 2, qd = t32 & 3;
+        const int i16 = wave * share + j, t32 = (i16 & 1) * 16 + c16, slot = t32 >> 2, qd = t32 & 3;
         float* pt = p_all + ((((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0 + o.tile) * 4 + (i16 >> 1)) * FOLD_P_TILE32<RT>;
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-            const float4 t = part[((o.tw * o.SW * RT + rt) * 8 + i16) * 64 + lane];
+            const float4 t = part[(rt * 8 + i16) * 64 + lane];
             const float v[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
             for (int r = 0; r < 4; ++r)
@@ -462,7 +457,7 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
     const FoldSource& x = a.x;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     FoldScorePlace o;
-    if (!fold_score_place(s, false, a.sw_log2, x.n_slabs, blockIdx.x, wave, o)) return;
+    if (!fold_score_place(s, false, a.waves, x.n_slabs, blockIdx.x, wave, o)) return;
     const int b = o.b, rb = o.rb, len = o.len, tok0 = o.tile * FOLD_TILE;
     const int c16 = lane & 15, q = lane >> 4;
     const uint8_t* cbase = x.codes + (long long)(s.b0 + b) * x.cap * x.row_bytes;
@@ -672,14 +667,14 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
 // The rows of a half slab (128 bytes each) go through the wave's LDS image as the codes do, 16 token rows at a time; their
 // 16-byte pieces are swizzled by the row, so that neither the row-wise write nor the fragment read meets bank conflicts.
 template <int RT>
-__device__ __forceinline__ void fold_scores_dense(const FoldScoreArgs& a, const FoldSource& x, const uint8_t* u_all, bool window, int sw_log2, uint8_t* lds)
+__device__ __forceinline__ void fold_scores_dense(const FoldScoreArgs& a, const FoldSource& x, const uint8_t* u_all, bool window, int waves, uint8_t* lds)
 {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     constexpr int u_slab = FOLD_U_DENSE(RT);
     const FoldShape& s = a.s;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     FoldScorePlace o;
-    if (!fold_score_place(s, window, sw_log2, x.n_slabs, blockIdx.x, wave, o)) return;
+    if (!fold_score_place(s, window, waves, x.n_slabs, blockIdx.x, wave, o)) return;
     const int b = o.b, rb = o.rb, len = o.len, tok0 = o.tile * FOLD_TILE;
     const int c16 = lane & 15, q = lane >> 4;
     const uint8_t* xbase = reinterpret_cast<const uint8_t*>(x.rows) + (long long)(s.b0 + b) * x.cap * x.row_bytes;
@@ -752,7 +747,7 @@ template <int RT>
 __global__ __launch_bounds__(512) void fold_scores_dense_kernel(const FoldScoreArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    fold_scores_dense<RT>(a, a.x, a.u, false, a.sw_log2, lds);
+    fold_scores_dense<RT>(a, a.x, a.u, false, a.waves, lds);
 }
 
 // =====================================================================================================================
@@ -1788,13 +1783,13 @@ __global__ __launch_bounds__(256) void fold_finish_kernel(const float* __restric
 // Host side
 // =====================================================================================================================
 template <typename Args>
-static hipError_t launch(void (*kernel)(const Args), int grid, int lds_bytes, const Args& a, hipStream_t s)
+static hipError_t launch(void (*kernel)(const Args), int grid, int lds_bytes, const Args& a, hipStream_t s, int waves = 8)
 {
     if (lds_bytes > 65536) {
         hipError_t e = allow_large_lds(reinterpret_cast<const void*>(kernel), lds_bytes);
         if (e != hipSuccess) return e;
     }
-    kernel<<<dim3(grid), dim3(512), lds_bytes, s>>>(a);
+    kernel<<<dim3(grid), dim3(64 * waves), lds_bytes, s>>>(a);
     return hipGetLastError();
 }
 
@@ -1877,9 +1872,9 @@ template <int BITS, int G, int RT>
 static hipError_t run_scores(const FoldScoreArgs& a, bool nibbles, int grid, hipStream_t s)
 {
     if constexpr (BITS == 4 && G == 128) {
-        if (nibbles) return launch(fold_scores_kernel<4, 128, RT, true>, grid, FOLD_SCORE_LDS<4, 128, RT, true>, a, s);
+        if (nibbles) return launch(fold_scores_kernel<4, 128, RT, true>, grid, FOLD_SCORE_LDS<4, 128, RT, true> / 8 * a.waves, a, s, a.waves);
     }
-    return launch(fold_scores_kernel<BITS, G, RT, false>, grid, FOLD_SCORE_LDS<BITS, G, RT, false>, a, s);
+    return launch(fold_scores_kernel<BITS, G, RT, false>, grid, FOLD_SCORE_LDS<BITS, G, RT, false> / 8 * a.waves, a, s, a.waves);
 }
 template <int BITS, int G, int RT>
 static hipError_t run_values(const FoldValueArgs& a, bool nibbles, int grid, hipStream_t s)
@@ -1900,7 +1895,7 @@ static hipError_t scores_for(int bits, int G, bool nibbles, const FoldScoreArgs&
         case 4064: return run_scores<4, 64, RT>(a, nibbles, grid, s);
         case 4128: return run_scores<4, 128, RT>(a, nibbles, grid, s);
     }
-    return launch(fold_scores_dense_kernel<RT>, grid, FOLD_SCORE_RED<RT>, a, s);
+    return launch(fold_scores_dense_kernel<RT>, grid, FOLD_SCORE_RED<RT> / 8 * a.waves, a, s, a.waves);
 }
 template <int RT>
 static hipError_t values_for(int bits, int G, bool nibbles, const FoldValueArgs& a, int grid, hipStream_t s)
@@ -1975,13 +1970,15 @@ hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSo
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         {
-            // Slab ways of a workgroup: eight, or four with two token tiles where that still leaves two rounds of workgroups
-            // (a wave's set-up and the meeting of the slab ways then weigh less).  Measured, 8 / 4 slab ways: 1024 tiles of
-            // 2 bits 111 / 98 us (group 128), 120 / 108 us (group 64), half the width 58 / 47 us; 256 tiles of 3 bits 33 / 51.
-            const int swl = B * sh.nrb * sh.tiles >= 4 * 256 && !f.block ? 2 : 3, ways = 8 >> swl;
-            FoldScoreArgs a{kx, sh, u, rowfac, p, mtile, L.u_slab, swl, FoldSource{}, u_dense, 0};
+            // A workgroup is one token tile with eight slab ways, or with four where that still gives most CUs two workgroups
+            // (registers allow two waves per SIMD, so two of four waves fit): one's set-up, last loads and meeting of the slab
+            // ways then run beside the other's products, and fewer ways meet.  Whole steps, eight waves / four: 1024 tiles of 2
+            // bits 233 / 215 us (group 128), 273 / 263 (group 64), latent 136 / 127, 16 heads of 4 bits 124 / 111; 512 tiles of
+            // 3 bits 143 / 138; 384 tiles 166 / 161; 256 tiles 94.4 / 94.1.
+            const int waves = B * sh.nrb * sh.tiles >= 3 * 128 && !f.block ? 4 : 8;
+            FoldScoreArgs a{kx, sh, u, rowfac, p, mtile, L.u_slab, waves, FoldSource{}, u_dense, 0};
             if (any_window) { a.window = *window; a.n_window = xcd_grid(sh.nb * sh.nrb); }
-            const int grid = a.n_window + xcd_grid(sh.nb * sh.nrb * ((sh.tiles + ways - 1) / ways));
+            const int grid = a.n_window + xcd_grid(sh.nb * sh.nrb * sh.tiles);
             e = f.block ? (L.rt == 1 ? scores_pc_for<1>(bits, a, grid, s) : scores_pc_for<2>(bits, a, grid, s))
                         : (L.rt == 1 ? scores_for<1>(bits, f.group, f.nibbles, a, grid, s) : scores_for<2>(bits, f.group, f.nibbles, a, grid, s));
             if (e != hipSuccess) return e;

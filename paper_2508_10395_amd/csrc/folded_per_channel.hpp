@@ -47,11 +47,11 @@ __global__ __launch_bounds__(512) void fold_scores_pc_kernel(const FoldScoreArgs
     const FoldSource& x = a.x;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if ((int)blockIdx.x < a.n_window) {
-        fold_scores_dense<RT>(a, a.window, a.u_window, true, 3, lds);
+        fold_scores_dense<RT>(a, a.window, a.u_window, true, 8, lds);
         return;
     }
     FoldScorePlace o;
-    if (!fold_score_place(s, false, 3, x.n_slabs, (int)blockIdx.x - a.n_window, wave, o)) return;
+    if (!fold_score_place(s, false, 8, x.n_slabs, (int)blockIdx.x - a.n_window, wave, o)) return;
     const int b = o.b, rb = o.rb, len = o.len, tok0 = o.tile * FOLD_TILE;
     const int c16 = lane & 15, q = lane >> 4, d = x.n_slabs * 128;
     const int nblk = len / s.block, blk0 = tok0 / s.block;
