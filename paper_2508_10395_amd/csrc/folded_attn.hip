@@ -751,18 +751,25 @@ __global__ __launch_bounds__(512) void fold_scores_dense_kernel(const FoldScoreA
 }
 
 // =====================================================================================================================
-// Values.  A workgroup owns two slabs (256 channels) of a sequence, one row block and a range of tokens: two slab ways,
-// four token ways.  Per 256 tokens all eight waves bring the stored softmax weights to the sequence's maximum and stage
-// them in LDS with the tokens' scales, integer zero-points and rests; a wave then takes 32 tokens at a time: the weights
-// times its group's scale, split into fp16 hi + lo, against the codes.  The contraction runs over tokens, so an operand
-// dword pairs the codes of two tokens: a lane takes octet n = lane % 16 of the slab (8 channels) for eight tokens, merges
-// token pairs, and column tile k of the product is code k of every lane's octet -- no transposition.  (Groups of 64:
-// lanes n and n + 8 exchange half octets, so that a column tile lies in one group.)  The rests are summed on the vector
-// ALU.  At the end the four token ways meet in LDS.
+// Values.  A workgroup owns two slabs (256 channels) of a sequence, one row block and a range of tokens; its four waves are
+// two slab ways and two token ways, and two workgroups share a CU, so that one's set-up, barriers and sums run beside the
+// other's products.  Per 128 tokens all waves bring the stored softmax weights to the sequence's maximum and stage them in LDS
+// with the tokens' scales, integer zero-points and rests; a wave then takes 32 tokens at a time.  The contraction runs over
+// tokens, so an operand dword pairs the codes of two tokens: a lane takes octet n = lane % 16 of the slab (8 channels) for
+// eight tokens, merges token pairs, and column tile k of the product is code k of every lane's octet -- no transposition.
+// (Groups of 64: lanes n and n + 8 exchange half octets, so that a column tile lies in one group.)  The rests are summed on the
+// vector ALU by the threads that stage the weights.  At the end the token ways meet in LDS.
+//
+// 2 and 3 bits: (code - zi) times the scale has at most 3 + 8 bits, so it is exact in fp16 and goes into the codes' operand (one
+// packed product per dword), and the weights are cut into fp16 hi + lo once, when they are staged.  Other codes have a bit too
+// many: there weight times scale is cut per group.  Bound by issue: the vector ALU takes about 1.5 times as long as the matrix
+// instructions.  Measured, us, waves of weight times scale in workgroups of eight / this: 4 x 32768 tokens of 2 bits 118 / 106,
+// 16 x 8191 of 2 bits in groups of 64 154 / 115, half the width 43 / 37, 8 x 4096 of 3 bits 36 / 34; of these the loads of
+// scales and maxima before the loop eight at a time 10, 3, 2, 0.5.
 //
 // Range of the fp16 parts.  Weights are taken against the range's own maximum of the row and scales against the range's
-// largest scale of the group, so the parts end 2^-40 below their product: a token is cut by at most 2^-41 of the largest
-// scale, whatever its weight.  Every row has a token of weight 1 in its tiles, so with scales within a factor 2^13 (12
+// largest scale of the group, so the parts end 2^-40 below their product (or below the weight alone): a token is cut by at most
+// 2^-41 of the largest scale, whatever its weight.  Every row has a token of weight 1 in its tiles, so with scales within a factor 2^13 (12
 // exponents) that is 2^-28 of what the row sums up, and 2^12 such cuts in random directions reach the 2^-22 that
 // the parts carry.  A range with a wider group, a negative scale or a non-finite one is summed in plain
 // fp32 instead (fold_values_plain), and one with zero scales among others where their tokens may hold all the weight.  Measured, one token of 300 larger by 2^20 / 2^28 that no row attends to: error
@@ -781,19 +788,28 @@ struct FoldValueArgs {
     int n_window;
 };
 
-template <int RT, int GROUPS, bool NIB>
+// Workgroups of four waves over coded rows: two slab ways, two token ways of 64 tokens.
+constexpr int FOLD_VALUE_WAVES = 4, FOLD_VALUE_THREADS = 64 * FOLD_VALUE_WAVES;
+constexpr int FOLD_VSTEP = 32 * FOLD_VALUE_WAVES;                               // tokens staged at a time
+// the scale goes into the codes' operand: (code - zi) s has at most 8 + 3 bits (see above)
+constexpr bool fold_scaled_codes(int bits) { return bits <= 3; }
+
+template <int RT, int GROUPS, bool NIB, bool SCALED>
 struct FoldValueLds {
-    static constexpr int P_BYTES = 8 * FOLD_P_TILE32<RT> * 4;                   // 256 tokens of softmax weights
-    static constexpr int STRIDE = FOLD_VTILE + 4;                               // floats: scales, then rests, of a group's tokens
-    static constexpr int ZI_STRIDE = FOLD_VTILE + 8;                            // halfs: -zi (of even, then of odd codes)
-    static constexpr int GROUP_BYTES = 2 * STRIDE * 4 + (NIB ? 2 : 1) * ZI_STRIDE * 2;
+    static constexpr int P_BYTES = FOLD_VSTEP / 32 * FOLD_P_TILE32<RT> * 4;     // softmax weights of a step
+    static constexpr int STRIDE = FOLD_VSTEP + 4;                               // floats: rests (and scales) of a group's tokens
+    static constexpr int H_STRIDE = FOLD_VSTEP + 8;                             // halfs: -zi (of even, then of odd codes), or -zi and scales
+    static constexpr int REST = SCALED ? 0 : STRIDE * 4, HALFS = REST + STRIDE * 4;
+    static constexpr int GROUP_BYTES = HALFS + (NIB || SCALED ? 2 : 1) * H_STRIDE * 2;
     static constexpr int SZ_BYTES = GROUPS * GROUP_BYTES;
     static constexpr int P_OFF = 0, SZ_OFF = 2 * P_BYTES, M_OFF = SZ_OFF + 2 * SZ_BYTES;
     static constexpr int N_OFF = M_OFF + 16 * RT * 4 * 34;                      // row maxima (a column per partial reader, twice, and the results)
     static constexpr int L_OFF = N_OFF + GROUPS * 4 * 17;
     static constexpr int LOOP = L_OFF + 8 * 16 * RT * 4;
-    static constexpr int RED = 8 * RT * 8 * 1024;                               // every wave's accumulators, at the end
+    static constexpr int RED = FOLD_VALUE_WAVES * RT * 8 * 1024;                // every wave's accumulators, at the end
     static constexpr int TOTAL = LOOP > RED ? LOOP : RED;
+    // what fold_values_plain keeps there lies below the row maxima
+    static_assert(8 * FOLD_P_TILE32<RT> * 4 + GROUPS * FOLD_VTILE * 8 <= M_OFF, "256 tokens' weights, scales and zero-points");
 };
 
 constexpr int FOLD_SCALE_SPREAD = 12;        // exponents between a range's scales of a group that the fp16 parts are used for
@@ -824,10 +840,10 @@ __device__ __forceinline__ bool fold_value_place(const FoldShape& s, bool window
 // over the stored maxima [r0, r1) instead, and behind them the factor from that maximum to the sequence's.  FOLD_RANGE_LOW:
 // behind them the lowest of the stored maxima [r0, r1)
 enum { FOLD_RANGE_TOP = 1, FOLD_RANGE_LOW = 2 };
-template <int RT, int RANGE = 0>
+template <int RT, int RANGE = 0, int NT = 512>
 __device__ __forceinline__ void fold_row_maxima(const FoldShape& s, const float* mtile, int b, int rb, float* scratch, float* mrow, int r0 = 0, int r1 = 0)
 {
-    constexpr int ROWS = 16 * RT, PARTS = 512 / ROWS > 16 ? 16 : 512 / ROWS;
+    constexpr int ROWS = 16 * RT, PARTS = NT / ROWS > 16 ? 16 : NT / ROWS;
     const int tid = threadIdx.x, row = tid % ROWS, pt = tid / ROWS;
     const int len = s.len.v[s.b0 + b], coded = s.block ? len / s.block * s.block : len;
     const int unit = FOLD_TILE >> s.mhalf;                          // tokens of a stored maximum
@@ -836,12 +852,20 @@ __device__ __forceinline__ void fold_row_maxima(const FoldShape& s, const float*
     if (pt < PARTS) {
         float m = -INFINITY, mr = RANGE == FOLD_RANGE_LOW ? INFINITY : -INFINITY;
         const float* src = mtile + (((long long)b * s.nrb + rb) * s.tiles << s.mhalf) * ROWS + row;
-        for (int t = pt; t < nt; t += PARTS)
-            if (t < n_coded || t >= window0) {
-                const float v = src[(long long)t * ROWS];
-                m = fmaxf(m, v);
-                if (RANGE && t >= r0 && t < r1) mr = RANGE == FOLD_RANGE_LOW ? fminf(mr, v == -INFINITY ? INFINITY : v) : fmaxf(mr, v);
+        // (eight loads at a time: one latency for them all; behind the last maximum it is read again)
+        for (int t0 = pt; t0 < nt; t0 += 8 * PARTS) {
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = src[(long long)min(t0 + k * PARTS, nt - 1) * ROWS];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int t = min(t0 + k * PARTS, nt - 1);
+                if (t < n_coded || t >= window0) {
+                    m = fmaxf(m, v[k]);
+                    if (RANGE && t >= r0 && t < r1) mr = RANGE == FOLD_RANGE_LOW ? fminf(mr, v[k] == -INFINITY ? INFINITY : v[k]) : fmaxf(mr, v[k]);
+                }
             }
+        }
         scratch[pt * ROWS + row] = m;
         if constexpr (RANGE != 0) scratch[(PARTS + pt) * ROWS + row] = mr;
     }
@@ -870,7 +894,7 @@ __device__ __forceinline__ void fold_row_maxima(const FoldShape& s, const float*
 }
 
 // softmax denominators of a row block and split from every thread's share of them, times f (of row tid)
-template <int RT>
+template <int RT, int NW = 8>
 __device__ __forceinline__ void fold_denominators(const FoldValueArgs& a, const FoldValuePlace& o, float l, float f, float* lp)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -881,17 +905,20 @@ __device__ __forceinline__ void fold_denominators(const FoldValueArgs& a, const 
     if (tid < 16 * RT) {
         float t = 0.0f;
 #pragma unroll
-        for (int w = 0; w < 8; ++w)
+        for (int w = 0; w < NW; ++w)
             if (RT == 1 || ((w >> 1) & 1) == (tid >> 4)) t += lp[w * 16 + (tid & 15)];
         a.lsum[(((long long)o.split * a.s.nb + o.b) * a.s.nrb + o.rb) * 16 * RT + tid] = t * f;
     }
 }
 
-// The four token ways of a workgroup's two slabs meet in LDS: wave (slab way, token way w < 2 RT) gets half a row tile of its
-// slab (row tile w / 2, column tiles 4 (w % 2) + [0, 4)) summed over the token ways
-template <int RT>
-__device__ __forceinline__ void fold_meet(const f32x4 (&acc)[RT][8], uint8_t* lds, int wave, int lane, f32x4 (&t)[4])
+// The token ways of a workgroup's two slabs meet in LDS: half a row tile of a slab (row tile h / 2, column tiles 4 (h % 2) +
+// [0, 4)) is summed by the wave (slab way, token way h), or by the token ways in turn where there are fewer
+template <int RT, int NW>
+constexpr int FOLD_MEET = NW / 2 >= 2 * RT ? 1 : 2 * RT / (NW / 2);             // halves per wave
+template <int RT, int NW>
+__device__ __forceinline__ void fold_meet(const f32x4 (&acc)[RT][8], uint8_t* lds, int wave, int lane, f32x4 (&t)[FOLD_MEET<RT, NW>][4])
 {
+    constexpr int TW = NW / 2;
     float4* acc_lds = reinterpret_cast<float4*>(lds);
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
@@ -899,17 +926,21 @@ __device__ __forceinline__ void fold_meet(const f32x4 (&acc)[RT][8], uint8_t* ld
         for (int k = 0; k < 8; ++k)
             acc_lds[((wave * RT + rt) * 8 + k) * 64 + lane] = make_float4(acc[rt][k][0], acc[rt][k][1], acc[rt][k][2], acc[rt][k][3]);
     __syncthreads();
-    const int sw = wave & 1, tw = wave >> 1, rt = tw >> 1, kg = tw & 1;
+    const int sw = wave & 1, tw = wave >> 1;
     if (tw >= 2 * RT) return;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        float4 v = acc_lds[((sw * RT + rt) * 8 + 4 * kg + k) * 64 + lane];
+    for (int i = 0; i < FOLD_MEET<RT, NW>; ++i) {
+        const int h = tw + i * TW, rt = h >> 1, kg = h & 1;
 #pragma unroll
-        for (int w = 1; w < 4; ++w) {
-            const float4 u = acc_lds[(((2 * w + sw) * RT + rt) * 8 + 4 * kg + k) * 64 + lane];
-            v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+        for (int k = 0; k < 4; ++k) {
+            float4 v = acc_lds[((sw * RT + rt) * 8 + 4 * kg + k) * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < TW; ++w) {
+                const float4 u = acc_lds[(((2 * w + sw) * RT + rt) * 8 + 4 * kg + k) * 64 + lane];
+                v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+            }
+            t[i][k] = f32x4{v.x, v.y, v.z, v.w};
         }
-        t[k] = f32x4{v.x, v.y, v.z, v.w};
     }
 }
 
@@ -920,7 +951,7 @@ __device__ __forceinline__ void fold_meet(const f32x4 (&acc)[RT][8], uint8_t* ld
 template <int BITS, int G, int RT, bool NIB>
 __device__ __forceinline__ void fold_values_plain(const FoldValueArgs& a, const FoldValuePlace& o, const float* mrow, uint8_t* lds, float* lp)
 {
-    constexpr int ROWS = 4 * RT, GROUPS = 256 / G;
+    constexpr int NT = FOLD_VALUE_THREADS, ROWS = 16 * RT * 128 / NT, GROUPS = 256 / G, PH = 512 * RT / NT;   // PH: pieces per thread of 128 tokens' weights
     const FoldShape& s = a.s;
     const FoldSource& x = a.x;
     const int tid = threadIdx.x, part = tid >> 7, ch = tid & 127;
@@ -943,20 +974,20 @@ __device__ __forceinline__ void fold_values_plain(const FoldValueArgs& a, const 
     for (int t = o.t0; t < o.t1; ++t) {
         __syncthreads();
 #pragma unroll
-        for (int e = 0; e < 2 * RT; ++e) {
-            const int t128 = 2 * t + e / RT;
+        for (int e = 0; e < 2 * PH; ++e) {
+            const int t128 = 2 * t + e / PH;
             float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             if (t128 * FOLD_TILE < o.len) {
                 const float m = msrc[(long long)t128 * 16 * RT], f = m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - M);
-                v = *reinterpret_cast<const float4*>(psrc + (long long)t * 8 * FOLD_P_TILE32<RT> + (e * 512 + tid) * 4);
+                v = *reinterpret_cast<const float4*>(psrc + (long long)t * 8 * FOLD_P_TILE32<RT> + (e * NT + tid) * 4);
                 v.x *= f; v.y *= f; v.z *= f; v.w *= f;
                 lacc += (v.x + v.y) + (v.z + v.w);
             }
-            p[e * 512 + tid] = v;
+            p[e * NT + tid] = v;
         }
 #pragma unroll
-        for (int e = 0; e < GROUPS / 2; ++e) {
-            const int idx = e * 512 + tid, g = min(o.cblk * GROUPS + (idx >> 8), x.ng - 1) >> x.meta_shift;
+        for (int e = 0; e < GROUPS * 256 / NT; ++e) {
+            const int idx = e * NT + tid, g = min(o.cblk * GROUPS + (idx >> 8), x.ng - 1) >> x.meta_shift;
             const long long at = meta + (long long)min(t * FOLD_VTILE + (idx & 255), o.len - 1) * x.ng_row + g;
             sz[idx] = make_float2(bf16_bits_to_f32(x.scale[at]), bf16_bits_to_f32(x.zero[at]));
         }
@@ -998,7 +1029,7 @@ __device__ __forceinline__ void fold_values_plain(const FoldValueArgs& a, const 
                 }
         }
     }
-    if (o.cblk == 0) fold_denominators<RT>(a, o, lacc, tid < 16 * RT ? mrow[16 * RT + tid] : 0.0f, lp);
+    if (o.cblk == 0) fold_denominators<RT, FOLD_VALUE_WAVES>(a, o, lacc, tid < 16 * RT ? mrow[16 * RT + tid] : 0.0f, lp);
     const long long yrow0 = ((long long)o.split * s.nb + o.b) * s.R;
 #pragma unroll
     for (int n = 0; n < 2; ++n)
@@ -1008,7 +1039,7 @@ __device__ __forceinline__ void fold_values_plain(const FoldValueArgs& a, const 
             if ((n == 0 || second) && row < s.R)
                 a.y[(yrow0 + row) * (x.n_slabs * 128) + (o.cblk * 2 + n) * 128 + ch] = y[n][r] * mrow[16 * RT + local];
         }
-    for (int idx = tid; idx < 16 * RT * GROUPS; idx += 512) {        // (the zero-points are in y)
+    for (int idx = tid; idx < 16 * RT * GROUPS; idx += NT) {        // (the zero-points are in y)
         const int row = o.rb * 16 * RT + idx / GROUPS, g = o.cblk * GROUPS + idx % GROUPS;
         if (row < s.R && g < x.ng) a.yz[(yrow0 + row) * x.ng + g] = 0.0f;
     }
@@ -1022,22 +1053,22 @@ __device__ __forceinline__ void fold_values_plain(const FoldValueArgs& a, const 
 template <int NG, int RT>
 __device__ __forceinline__ bool fold_zero_scales_harmless(const FoldValueArgs& a, const FoldValuePlace& o, const float* mrow, const float* ginv, int g0, uint8_t* lds)
 {
-    constexpr int ROWS = 16 * RT, MOST_TILES = 8192;
+    constexpr int NT = FOLD_VALUE_THREADS, NW = FOLD_VALUE_WAVES, ROWS = 16 * RT, MOST_TILES = 8192;
     const FoldShape& s = a.s;
     const FoldSource& x = a.x;
     const int tid = threadIdx.x, n_tiles = 2 * (o.t1 - o.t0);
     if (n_tiles > MOST_TILES) return false;
     uint8_t* zero_in = lds;                                          // per tile; behind it the row maxima of the other tiles
-    float* clean = reinterpret_cast<float*>(lds + MOST_TILES);       // [512 / ROWS][ROWS]
+    float* clean = reinterpret_cast<float*>(lds + MOST_TILES);       // [NT / ROWS][ROWS]
     const uint16_t* sbase = x.scale + (long long)(s.b0 + o.b) * x.cap * x.ng_row;
-    for (int i = tid; i < n_tiles; i += 512) zero_in[i] = 0;
+    for (int i = tid; i < n_tiles; i += NT) zero_in[i] = 0;
     __syncthreads();
     int spread = 0;
 #pragma unroll 1
     for (int g = 0; g < NG; ++g) {
         if (!(ginv[g] < 0.0f)) continue;
         int top = 0, low = 255;
-        for (int t = o.t0 * FOLD_VTILE + tid; t < min(o.len, o.t1 * FOLD_VTILE); t += 512) {
+        for (int t = o.t0 * FOLD_VTILE + tid; t < min(o.len, o.t1 * FOLD_VTILE); t += NT) {
             const int v = sbase[(long long)t * x.ng_row + ((g0 + g) >> x.meta_shift)];
             if (v == 0) zero_in[t / FOLD_TILE - 2 * o.t0] = 1;       // (several threads, one value)
             else { top = max(top, v >> 7); low = min(low, v >> 7); }
@@ -1048,9 +1079,9 @@ __device__ __forceinline__ bool fold_zero_scales_harmless(const FoldValueArgs& a
             low = min(low, __shfl_xor(low, off));
         }
         int* red = reinterpret_cast<int*>(clean);
-        if ((tid & 63) == 0) { red[tid >> 6] = top; red[8 + (tid >> 6)] = low; }
+        if ((tid & 63) == 0) { red[tid >> 6] = top; red[NW + (tid >> 6)] = low; }
         __syncthreads();
-        for (int w = 0; w < 8; ++w) { top = max(top, red[w]); low = min(low, red[8 + w]); }
+        for (int w = 0; w < NW; ++w) { top = max(top, red[w]); low = min(low, red[NW + w]); }
         spread = max(spread, top - low);
         __syncthreads();
     }
@@ -1058,23 +1089,26 @@ __device__ __forceinline__ bool fold_zero_scales_harmless(const FoldValueArgs& a
     const int live_tiles = min(n_tiles, (o.len - o.t0 * FOLD_VTILE + FOLD_TILE - 1) / FOLD_TILE);
     const float* src = a.mtile + (((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0 + 2 * o.t0) * ROWS + row;
     float m = -INFINITY;
-    for (int i = pt; i < live_tiles; i += 512 / ROWS)
+    for (int i = pt; i < live_tiles; i += NT / ROWS)
         if (!zero_in[i]) m = fmaxf(m, src[(long long)i * ROWS]);
     clean[pt * ROWS + row] = m;
     __syncthreads();
     bool ok = true;
     if (tid < ROWS && o.rb * ROWS + tid < s.R) {
-        for (int k = 1; k < 512 / ROWS; ++k) m = fmaxf(m, clean[k * ROWS + tid]);
+        for (int k = 1; k < NT / ROWS; ++k) m = fmaxf(m, clean[k * ROWS + tid]);
         ok = m - mrow[tid] >= (float)(spread - FOLD_SCALE_SPREAD);
     }
     return __syncthreads_and(ok);
 }
 
 template <int BITS, int G, int RT, bool NIB>
-__global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
+__global__ __launch_bounds__(FOLD_VALUE_THREADS, 2) void fold_values_kernel(const FoldValueArgs a)
 {
     constexpr int GPS = 128 / G, NG = 2 * GPS;                      // groups of a workgroup's two slabs
-    typedef FoldValueLds<RT, NG, NIB> L;
+    constexpr int NT = FOLD_VALUE_THREADS, NW = FOLD_VALUE_WAVES, VT = FOLD_VSTEP;
+    constexpr bool SCALED = fold_scaled_codes(BITS);
+    constexpr int P_EXP = SCALED ? 15 : 0;                          // softmax weights are cut to fp16 parts times 2^15
+    typedef FoldValueLds<RT, NG, NIB, SCALED> L;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const FoldShape& s = a.s;
     FoldValuePlace o;
@@ -1082,13 +1116,40 @@ __global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
     const FoldSource& x = a.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c16 = lane & 15, q = lane >> 4;
-    const int sw = wave & 1, tw = wave >> 1;                        // two slab ways, four token ways
+    const int sw = wave & 1, tw = wave >> 1;                        // two slab ways, two token ways
     const int slab = o.cblk * 2 + sw;
     const bool live = slab < x.n_slabs;
     const int g0 = o.cblk * NG;                                     // first group of the workgroup
     const long long seq = s.b0 + o.b;
     const uint16_t* sbase = x.scale + seq * x.cap * x.ng_row;
     const uint16_t* zbase = x.zero + seq * x.cap * x.ng_row;
+
+    // ---- codes: octet n = c16 of the wave's slab for tokens 4 i + q of its 32
+    const uint8_t* cbase = x.codes + seq * x.cap * x.row_bytes + (live ? slab : 0) * (16 * BITS);     // (a way without a slab repeats the first)
+    const uint32_t oct = BITS == 2 ? 4 * (c16 >> 1) : BITS == 3 ? 3 * c16 - (c16 > 0) : 4 * c16;
+    uint32_t voff[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) voff[i] = (uint32_t)(4 * i + q) * (uint32_t)x.row_bytes + oct;
+    auto load_codes = [&](int k32, uint32_t (&r)[8]) XQ_INLINE_LAMBDA {
+        const uint8_t* base = cbase + (long long)k32 * 32 * x.row_bytes;
+        uint32_t off[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) off[i] = voff[i];
+        if (k32 * 32 + 32 > o.len) {                                // past the length: the last row again (32-bit offsets from the sequence's start)
+            base = cbase;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) off[i] = (uint32_t)min(k32 * 32 + 4 * i + q, o.len - 1) * (uint32_t)x.row_bytes + oct;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if constexpr (BITS == 3) __builtin_memcpy(&r[i], base + off[i], 4);     // three of these four bytes (lane 0: the first three)
+            else r[i] = *reinterpret_cast<const uint32_t*>(base + off[i]);          // (2 bits: shared by two lanes)
+        }
+    };
+    const int v0 = o.t0 * (FOLD_VTILE / VT), v1 = min(o.t1 * (FOLD_VTILE / VT), (o.len + VT - 1) / VT);     // steps of VT tokens
+    uint32_t raw[2][8];                                             // codes of the next two times 32 tokens
+    load_codes(v0 * (VT / 32) + tw * 2, raw[0]);
+    load_codes(v0 * (VT / 32) + tw * 2 + 1, raw[1]);
 
     float* mrow = reinterpret_cast<float*>(lds + L::M_OFF) + 32 * 16 * RT;
     float* ginv = reinterpret_cast<float*>(lds + L::N_OFF) + 16 * NG;
@@ -1098,32 +1159,55 @@ __global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
         auto max2 = [](uint32_t u, uint32_t v) XQ_INLINE_LAMBDA {
             return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, u), __builtin_bit_cast(u16x2, v)));
         };
-        uint32_t mx[NG];                                            // largest scale; above it the complement of the smallest
+        auto min2 = [](uint32_t u, uint32_t v) XQ_INLINE_LAMBDA {
+            return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, u), __builtin_bit_cast(u16x2, v)));
+        };
+        uint32_t mx[GPS], mn[GPS];                                  // largest and smallest scales, of pairs of groups
 #pragma unroll
-        for (int g = 0; g < NG; ++g) mx[g] = 0u;
+        for (int j = 0; j < GPS; ++j) { mx[j] = 0u; mn[j] = 0xFFFFFFFFu; }
         const int tend = min(o.len, o.t1 * FOLD_VTILE);
-        for (int t = o.t0 * FOLD_VTILE + tid; t < tend; t += 512) {
+        // A token's scales lie in a cache line of their own, so what counts is the lines a load touches: all groups in one load
+        // where the alignment allows.
+        if (x.meta_shift == 0 && g0 + NG <= x.ng && ((reinterpret_cast<uintptr_t>(sbase) | (uint32_t)x.ng_row * 2u) & (2 * NG - 1)) == 0) {
+            for (int t = o.t0 * FOLD_VTILE + tid; t < tend; t += 8 * NT) {          // (eight loads at a time, the last token's again)
+                uint32_t v[8][GPS];
 #pragma unroll
-            for (int g = 0; g < NG; ++g)
-                if (g0 + g < x.ng) {
-                    const uint32_t v = sbase[(long long)t * x.ng_row + ((g0 + g) >> x.meta_shift)];
-                    mx[g] = max2(mx[g], perm_bytes(v, v, 0x01000100u) ^ 0xFFFF0000u);
-                }
+                for (int k = 0; k < 8; ++k)
+                    __builtin_memcpy(v[k], __builtin_assume_aligned(sbase + (long long)min(t + k * NT, tend - 1) * x.ng_row + g0, 2 * NG), 2 * NG);
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+#pragma unroll
+                    for (int j = 0; j < GPS; ++j) { mx[j] = max2(mx[j], v[k][j]); mn[j] = min2(mn[j], v[k][j]); }
+            }
+        } else {
+            for (int t = o.t0 * FOLD_VTILE + tid; t < tend; t += NT)
+#pragma unroll
+                for (int g = 0; g < NG; ++g)
+                    if (g0 + g < x.ng) {
+                        const uint32_t v = (uint32_t)sbase[(long long)t * x.ng_row + ((g0 + g) >> x.meta_shift)] << (16 * (g & 1));
+                        mx[g >> 1] = max2(mx[g >> 1], v);
+                        mn[g >> 1] = min2(mn[g >> 1], v | (0xFFFFu << (16 * (~g & 1))));
+                    }
         }
 #pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            uint32_t m = mx[g];
+        for (int j = 0; j < GPS; ++j) {
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) m = max2(m, (uint32_t)__shfl_xor((int)m, off));
-            if (lane == 0) reinterpret_cast<uint32_t*>(lds + L::N_OFF)[wave * NG + g] = m;
+            for (int off = 32; off > 0; off >>= 1) {
+                mx[j] = max2(mx[j], (uint32_t)__shfl_xor((int)mx[j], off));
+                mn[j] = min2(mn[j], (uint32_t)__shfl_xor((int)mn[j], off));
+            }
+            if (lane == 0) {
+                reinterpret_cast<uint32_t*>(lds + L::N_OFF)[wave * NG + 2 * j] = mx[j];
+                reinterpret_cast<uint32_t*>(lds + L::N_OFF)[wave * NG + 2 * j + 1] = mn[j];
+            }
         }
-        fold_row_maxima<RT, FOLD_RANGE_TOP>(s, a.mtile, o.b, o.rb, reinterpret_cast<float*>(lds + L::M_OFF), mrow, 2 * o.t0, 2 * o.t1);
+        fold_row_maxima<RT, FOLD_RANGE_TOP, NT>(s, a.mtile, o.b, o.rb, reinterpret_cast<float*>(lds + L::M_OFF), mrow, 2 * o.t0, 2 * o.t1);
         if (tid < NG) {
-            const uint32_t* src = reinterpret_cast<const uint32_t*>(lds + L::N_OFF);
-            uint32_t m = 0u;
+            const uint32_t* src = reinterpret_cast<const uint32_t*>(lds + L::N_OFF) + (tid & ~1);
+            uint32_t m = 0u, n = 0xFFFFFFFFu;
 #pragma unroll
-            for (int w = 0; w < 8; ++w) m = max2(m, src[w * NG + tid]);
-            const int top = (int)(m & 0xFFFFu) >> 7, low = (int)(0xFFFFu - (m >> 16)) >> 7;
+            for (int w = 0; w < NW; ++w) { m = max2(m, src[w * NG]); n = min2(n, src[w * NG + 1]); }
+            const int hs = 16 * (tid & 1), top = (int)(m >> hs & 0xFFFFu) >> 7, low = (int)(n >> hs & 0xFFFFu) >> 7;
             // largest scale < 2^(top - 126): times 2^(141 - top) it is below 2^15.  (0: for fold_values_plain; negative: scales too
             // far apart, if zeros count.)
             const float f = ldexpf(1.0f, min(141 - top, 120));
@@ -1148,14 +1232,14 @@ __global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
     }
 
     // ---- staging: thread -> softmax weights (always of the same row) and (token, group) pairs
-    constexpr int NP = 2 * RT;                                      // 16-byte pieces per thread and 256 tokens
+    constexpr int NP = 2 * RT, PH = 512 * RT / NT;                  // 16-byte pieces per thread and VT (128) tokens
     const int prow = RT == 2 ? ((wave >> 1) & 1) * 16 + c16 : c16;
     const float M = mrow[prow];
     const float* psrc = a.p + (((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) * 4 * FOLD_P_TILE32<RT>;
     const float* msrc = a.mtile + (((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) * 16 * RT + prow;
     float4 pv[NP];
-    float fm[2];
-    constexpr int NE = FOLD_VTILE * NG / 512;                       // (token, group) pairs per thread: 1 or 2
+    float fm[VT / FOLD_TILE];
+    constexpr int NE = VT * NG / NT;                       // (token, group) pairs per thread: 1 or 2
     const int eg = tid % NG, et = tid / NG;                         // group and first token of this thread's pairs
     uint32_t sv[NE], zv[NE];
     const uint16_t* sgrp = sbase + (min(g0 + eg, x.ng - 1) >> x.meta_shift);
@@ -1163,104 +1247,115 @@ __global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
     const float my_ginv = ginv[eg];
     auto load_stage = [&](int t) XQ_INLINE_LAMBDA {
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-            const int t128 = 2 * t + hf;
-            const bool ok = t128 * FOLD_TILE < o.len;
-            fm[hf] = ok ? msrc[(long long)t128 * 16 * RT] : -INFINITY;
+        for (int hf = 0; hf < VT / FOLD_TILE; ++hf) {
+            fm[hf] = msrc[(long long)(VT / FOLD_TILE * t + hf) * 16 * RT];
 #pragma unroll
-            for (int k = 0; k < RT; ++k) {
-                const int e = hf * RT + k;
-                pv[e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                if (ok) pv[e] = *reinterpret_cast<const float4*>(psrc + (long long)t * 8 * FOLD_P_TILE32<RT> + (e * 512 + tid) * 4);
+            for (int k = 0; k < PH; ++k) {
+                const int e = hf * PH + k;
+                pv[e] = *reinterpret_cast<const float4*>(psrc + (long long)t * (VT / 32) * FOLD_P_TILE32<RT> + (e * NT + tid) * 4);
             }
         }
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
-            const uint32_t at = (uint32_t)min(t * FOLD_VTILE + et + e * (512 / NG), o.len - 1) * (uint32_t)x.ng_row;
+            const uint32_t at = (uint32_t)min(t * VT + et + e * (NT / NG), o.len - 1) * (uint32_t)x.ng_row;
             sv[e] = sgrp[at];
             zv[e] = zgrp[at];
         }
     };
-    float lacc = 0.0f;
+    // what a thread's pieces are: four adjacent slots of row prow and token quarter q of 32 tokens
+    auto piece = [&](int e, int& t32, int& rt, int& part) XQ_INLINE_LAMBDA {
+        const int k = e * NW + wave;
+        part = k & 1; rt = (k >> 1) & (RT - 1); t32 = k / (2 * RT);
+    };
+    float lacc = 0.0f, az[NG];                                      // of row prow: sums of the weights, and of weight times rest per group
+#pragma unroll
+    for (int g = 0; g < NG; ++g) az[g] = 0.0f;
     auto write_stage = [&](int buf) XQ_INLINE_LAMBDA {
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-            const float f = fm[hf] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(fm[hf] - M);
+        for (int hf = 0; hf < VT / FOLD_TILE; ++hf) {
+            const float f = fm[hf] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(fm[hf] - M + P_EXP);
 #pragma unroll
-            for (int k = 0; k < RT; ++k) {
-                const int e = hf * RT + k;
-                float4 v = pv[e];
+            for (int k = 0; k < PH; ++k) {
+                const int e = hf * PH + k;
+                float4& v = pv[e];
                 v.x *= f; v.y *= f; v.z *= f; v.w *= f;
                 if (o.cblk == 0) lacc += (v.x + v.y) + (v.z + v.w);
-                *reinterpret_cast<float4*>(lds + L::P_OFF + buf * L::P_BYTES + (e * 512 + tid) * 16) = v;
+                if constexpr (SCALED) {
+                    int t32, rt, part;
+                    piece(e, t32, rt, part);
+                    const xq_f32x2 a2 = {v.x, v.y}, b2 = {v.z, v.w};
+                    const xq_f16x2 ah = __builtin_convertvector(a2, xq_f16x2), bh = __builtin_convertvector(b2, xq_f16x2);
+                    const xq_f32x2 ar = {v.x - (float)ah.x, v.y - (float)ah.y}, br = {v.z - (float)bh.x, v.w - (float)bh.y};
+                    const xq_f16x2 al = __builtin_convertvector(ar, xq_f16x2), bl = __builtin_convertvector(br, xq_f16x2);
+                    uint8_t* dst = lds + L::P_OFF + buf * L::P_BYTES + (t32 * RT + rt) * 2048 + lane * 16 + part * 8;
+                    *reinterpret_cast<uint2*>(dst) = make_uint2(__builtin_bit_cast(uint32_t, ah), __builtin_bit_cast(uint32_t, bh));
+                    *reinterpret_cast<uint2*>(dst + 1024) = make_uint2(__builtin_bit_cast(uint32_t, al), __builtin_bit_cast(uint32_t, bl));
+                } else {
+                    *reinterpret_cast<float4*>(lds + L::P_OFF + buf * L::P_BYTES + (e * NT + tid) * 16) = v;
+                }
             }
         }
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
-            const int tok = et + e * (512 / NG), t32 = tok & 31, at = (tok & ~31) + (t32 & 3) * 8 + (t32 >> 2);
+            const int tok = et + e * (NT / NG), t32 = tok & 31, at = (tok & ~31) + (t32 & 3) * 8 + (t32 >> 2);
             uint8_t* grp = lds + L::SZ_OFF + buf * L::SZ_BYTES + eg * L::GROUP_BYTES;
             const float sf = bf16_bits_to_f32(sv[e]);
             float rest;
             const float zi = fold_integer_zero(sf, bf16_bits_to_f32(zv[e]), NIB ? 255.0f : (float)((1 << BITS) - 1), rest);
-            reinterpret_cast<float*>(grp)[at] = sf * my_ginv;
-            reinterpret_cast<float*>(grp)[L::STRIDE + at] = rest;
-            uint16_t* zo = reinterpret_cast<uint16_t*>(grp + 2 * L::STRIDE * 4);
+            reinterpret_cast<float*>(grp + L::REST)[at] = rest;
+            uint16_t* zo = reinterpret_cast<uint16_t*>(grp + L::HALFS);
+            if constexpr (SCALED) zo[L::H_STRIDE + at] = (uint16_t)f16_bits(sf * my_ginv);
+            else reinterpret_cast<float*>(grp)[at] = sf * my_ginv;
             if constexpr (NIB) {
                 const float zh = floorf(zi * (1.0f / 16.0f));
                 zo[at] = (uint16_t)f16_bits((zi - 16.0f * zh) * (-1.0f / FOLD_CODE_UNIT));
-                zo[L::ZI_STRIDE + at] = (uint16_t)f16_bits(zh * (-1.0f / FOLD_CODE_UNIT));
+                zo[L::H_STRIDE + at] = (uint16_t)f16_bits(zh * (-1.0f / FOLD_CODE_UNIT));
             } else {
                 zo[at] = (uint16_t)f16_bits(zi * (-1.0f / FOLD_CODE_UNIT));
             }
         }
     };
-
-    // ---- codes: octet n = c16 of the wave's slab for tokens 4 i + q of its 32
-    const uint8_t* cbase = x.codes + seq * x.cap * x.row_bytes + (live ? slab : 0) * (16 * BITS);
-    const uint32_t oct = BITS == 3 ? 3 * c16 - (c16 > 0) : BITS * c16;
-    uint32_t voff[8];
+    // weight times rest, from the weights that the thread still holds of the step staged last
+    auto add_rests = [&](int buf) XQ_INLINE_LAMBDA {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) voff[i] = (uint32_t)(4 * i + q) * (uint32_t)x.row_bytes + oct;
-    auto load_codes = [&](int k32, uint32_t (&r)[8]) XQ_INLINE_LAMBDA {
-        const uint8_t* base = cbase + (long long)k32 * 32 * x.row_bytes;
-        uint32_t off[8];
+        for (int e = 0; e < NP; ++e) {
+            int t32, rt, part;
+            piece(e, t32, rt, part);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) off[i] = voff[i];
-        if (k32 * 32 + 32 > o.len) {                                // past the length: the last row again (32-bit offsets from the sequence's start)
-            base = cbase;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) off[i] = (uint32_t)min(k32 * 32 + 4 * i + q, o.len - 1) * (uint32_t)x.row_bytes + oct;
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            if constexpr (BITS == 2) r[i] = *reinterpret_cast<const uint16_t*>(base + off[i]);
-            else if constexpr (BITS == 4) r[i] = *reinterpret_cast<const uint32_t*>(base + off[i]);
-            else __builtin_memcpy(&r[i], base + off[i], 4);         // three of these four bytes (lane 0: the first three)
+            for (int g = 0; g < NG; ++g) {
+                const float4 r = *reinterpret_cast<const float4*>(lds + L::SZ_OFF + buf * L::SZ_BYTES + g * L::GROUP_BYTES + L::REST +
+                                                                  (t32 * 32 + q * 8 + part * 4) * 4);
+                az[g] = __builtin_fmaf(pv[e].x, r.x, az[g]);
+                az[g] = __builtin_fmaf(pv[e].y, r.y, az[g]);
+                az[g] = __builtin_fmaf(pv[e].z, r.z, az[g]);
+                az[g] = __builtin_fmaf(pv[e].w, r.w, az[g]);
+            }
         }
     };
-    const uint32_t sel0 = c16 ? 0x06050201u : 0x05040100u, sel1 = c16 ? 0x07060302u : 0x06050201u;
+
+    const uint32_t sel0 = BITS == 2 ? (c16 & 1 ? 0x07060302u : 0x05040100u) : c16 ? 0x06050201u : 0x05040100u, sel1 = c16 ? 0x07060302u : 0x06050201u;
     const bool lower = c16 < 8;
 
     f32x4 acc[RT][8];
-    float az[RT][GPS];
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int k = 0; k < 8; ++k) acc[rt][k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    // A wave has 32 tokens twice per step, and of these one phase per group: 8 / GPS column tiles times 2 RT matrix
+    // instructions.  While a phase's matrix instructions run, the vector ALU unpacks the next column tile and, with 4-bit codes,
+    // forms the next phase's weights, a little behind every matrix instruction (fences keep it there).
+    constexpr int KPP = 8 / GPS, NSLOT = KPP * 2 * RT, NSUB = SCALED ? 0 : RT * 8, START = NSLOT / 4;
+    uint32_t m0[4], m1[4], F[2][4];
+    // weights (of the running and the next 32 tokens if SCALED, else of the running and the next phase); -zi, scales or -zi of odd codes
+    uint4 wh[2][RT], wl[2][RT], zi[2][NIB || SCALED ? 2 : 1];
+    float pr[RT][8], sc[8];                                         // of the next phase
+    auto merge_pairs = [&](uint32_t (&r)[8]) XQ_INLINE_LAMBDA {
+        // (here and not earlier: merged where they are loaded, the codes would be waited for there)
 #pragma unroll
-        for (int g = 0; g < GPS; ++g) az[rt][g] = 0.0f;
-    }
-    // A wave's tile is two steps of 32 tokens, a step one phase per group: 8 / GPS column tiles times 2 RT matrix
-    // instructions.  While a phase's matrix instructions run, the vector ALU unpacks the next column tile and forms the
-    // next phase's weights, a little behind every matrix instruction (fences keep it there).
-    constexpr int KPP = 8 / GPS, NSLOT = KPP * 2 * RT, NSUB = RT * 8, START = NSLOT / 4;
-    uint32_t raw[2][8], m0[4], m1[4], F[2][4];
-    uint4 wh[2][RT], wl[2][RT], zi[2][NIB ? 2 : 1];                 // of the running and the next phase
-    float pr[RT][8], sc[8], of[8];                                  // of the next phase
-    auto merge_pairs = [&](const uint32_t (&r)[8]) XQ_INLINE_LAMBDA {
+        for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(r[i]));
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            if constexpr (BITS == 2) { m0[j] = r[2 * j] | (r[2 * j + 1] << 16); m1[j] = 0u; }
+            if constexpr (BITS == 2) { m0[j] = perm_bytes(r[2 * j + 1], r[2 * j], sel0); m1[j] = 0u; }
             else if constexpr (BITS == 3) { m0[j] = perm_bytes(r[2 * j + 1], r[2 * j], sel0); m1[j] = perm_bytes(r[2 * j + 1], r[2 * j], sel1); }
             else { m0[j] = perm_bytes(r[2 * j + 1], r[2 * j], 0x05040100u); m1[j] = perm_bytes(r[2 * j + 1], r[2 * j], 0x07060302u); }
             if constexpr (G == 64) {
@@ -1286,31 +1381,37 @@ __global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
         const int k32 = tw * 2 + st;
         if constexpr (g == 0)
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
+            for (int rt = 0; rt < RT; ++rt) {
+                const uint8_t* src = lds + L::P_OFF + buf * L::P_BYTES + (k32 * RT + rt) * 2048 + lane * 16;
+                if constexpr (SCALED) {
+                    wh[st][rt] = *reinterpret_cast<const uint4*>(src);
+                    wl[st][rt] = *reinterpret_cast<const uint4*>(src + 1024);
+                } else {
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const float4 v = *reinterpret_cast<const float4*>(lds + L::P_OFF + buf * L::P_BYTES + ((k32 * RT + rt) * 2 + h) * 1024 + lane * 16);
-                    pr[rt][4 * h] = v.x; pr[rt][4 * h + 1] = v.y; pr[rt][4 * h + 2] = v.z; pr[rt][4 * h + 3] = v.w;
+                    for (int h = 0; h < 2; ++h) {
+                        const float4 v = *reinterpret_cast<const float4*>(src + h * 1024);
+                        pr[rt][4 * h] = v.x; pr[rt][4 * h + 1] = v.y; pr[rt][4 * h + 2] = v.z; pr[rt][4 * h + 3] = v.w;
+                    }
                 }
+            }
         const uint8_t* grp = lds + L::SZ_OFF + buf * L::SZ_BYTES + (sw * GPS + g) * L::GROUP_BYTES;
-        const float* sp = reinterpret_cast<const float*>(grp) + k32 * 32 + q * 8;
+        if constexpr (!SCALED)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const float4 a4 = *reinterpret_cast<const float4*>(sp + 4 * h), b4 = *reinterpret_cast<const float4*>(sp + L::STRIDE + 4 * h);
-            sc[4 * h] = a4.x; sc[4 * h + 1] = a4.y; sc[4 * h + 2] = a4.z; sc[4 * h + 3] = a4.w;
-            of[4 * h] = b4.x; of[4 * h + 1] = b4.y; of[4 * h + 2] = b4.z; of[4 * h + 3] = b4.w;
-        }
+            for (int h = 0; h < 2; ++h) {
+                const float4 a4 = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(grp) + k32 * 32 + q * 8 + 4 * h);
+                sc[4 * h] = a4.x; sc[4 * h + 1] = a4.y; sc[4 * h + 2] = a4.z; sc[4 * h + 3] = a4.w;
+            }
 #pragma unroll
-        for (int k = 0; k < (NIB ? 2 : 1); ++k)
-            zi[n][k] = *reinterpret_cast<const uint4*>(grp + 2 * L::STRIDE * 4 + (k * L::ZI_STRIDE + k32 * 32 + q * 8) * 2);
+        for (int k = 0; k < (NIB || SCALED ? 2 : 1); ++k)
+            zi[n][k] = *reinterpret_cast<const uint4*>(grp + L::HALFS + (k * L::H_STRIDE + k32 * 32 + q * 8) * 2);
     };
-    // weights of the next phase, piece SUB: (row tile, token pair) products and top parts, then low parts and rests
+    // weights of the next phase, piece SUB: (row tile, token pair) products and top parts, then low parts
     auto set_dword = [](uint4& v, auto J, uint32_t x) XQ_INLINE_LAMBDA {
         constexpr int j = decltype(J)::value;
         if constexpr (j == 0) v.x = x; else if constexpr (j == 1) v.y = x; else if constexpr (j == 2) v.z = x; else v.w = x;
     };
     auto weight_piece = [&](auto PH, auto SUB) XQ_INLINE_LAMBDA {
-        constexpr int g = decltype(PH)::value % GPS, n = decltype(PH)::value & 1;
+        constexpr int n = decltype(PH)::value & 1;
         constexpr int sub = decltype(SUB)::value, rt = sub / 8, j = (sub / 2) & 3;
         const float p0 = pr[rt][2 * j], p1 = pr[rt][2 * j + 1], s0 = sc[2 * j], s1 = sc[2 * j + 1];
         if constexpr ((sub & 1) == 0) {
@@ -1321,124 +1422,139 @@ __global__ __launch_bounds__(512) void fold_values_kernel(const FoldValueArgs a)
             const xq_f16x2 top = __builtin_bit_cast(xq_f16x2, hb);
             const xq_f16x2 low = {(_Float16)__builtin_fmaf(p0, s0, -(float)top.x), (_Float16)__builtin_fmaf(p1, s1, -(float)top.y)};
             set_dword(wl[n][rt], std::integral_constant<int, j>{}, __builtin_bit_cast(uint32_t, low));
-            az[rt][g] = __builtin_fmaf(p0, of[2 * j], az[rt][g]);
-            az[rt][g] = __builtin_fmaf(p1, of[2 * j + 1], az[rt][g]);
         }
     };
-    // operand dword J of column tile K (its codes in m0, m1), with the integer zero-points of phase parity N
+    auto component = [](const uint4& v, auto J) XQ_INLINE_LAMBDA {
+        constexpr int j = decltype(J)::value;
+        return j == 0 ? v.x : j == 1 ? v.y : j == 2 ? v.z : v.w;
+    };
+    // operand dword J of column tile K (its codes in m0, m1), with the integer zero-points of phase parity N, and then the scales
     auto unpack = [&](auto K, auto J, auto N) XQ_INLINE_LAMBDA {
         constexpr int k = decltype(K)::value, j = decltype(J)::value, n = decltype(N)::value;
-        const uint4 z = zi[n][NIB ? k & 1 : 0];
-        const uint32_t zj = j == 0 ? z.x : j == 1 ? z.y : j == 2 ? z.z : z.w;
-        F[k & 1][j] = fold_code<BITS, k>(m0[j], m1[j], zj);
+        F[k & 1][j] = fold_code<BITS, k>(m0[j], m1[j], component(zi[n][NIB ? k & 1 : 0], J));
+    };
+    auto scale = [&](auto K, auto J, auto N) XQ_INLINE_LAMBDA {
+        constexpr int k = decltype(K)::value, j = decltype(J)::value, n = decltype(N)::value;
+        if constexpr (SCALED)
+            F[k & 1][j] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(xq_f16x2, F[k & 1][j]) * __builtin_bit_cast(xq_f16x2, component(zi[n][1], J)));
+    };
+    // a column tile's four dwords over the slots of the one before; what a dword's scaling reads was not written right before it
+    auto unpack_slot = [&](auto K, auto IN, auto N) XQ_INLINE_LAMBDA {
+        constexpr int in = decltype(IN)::value;
+        constexpr std::integral_constant<int, 0> j0{};
+        constexpr std::integral_constant<int, 1> j1{};
+        constexpr std::integral_constant<int, 2> j2{};
+        constexpr std::integral_constant<int, 3> j3{};
+        if constexpr (RT == 2) {
+            if constexpr (in == 0) { unpack(K, j0, N); unpack(K, j1, N); }
+            else if constexpr (in == 1) { scale(K, j0, N); unpack(K, j2, N); }
+            else if constexpr (in == 2) { scale(K, j1, N); unpack(K, j3, N); }
+            else { scale(K, j2, N); scale(K, j3, N); }
+        } else {
+            if constexpr (in == 0) { unpack(K, j0, N); unpack(K, j1, N); unpack(K, j2, N); scale(K, j0, N); }
+            else { unpack(K, j3, N); scale(K, j1, N); scale(K, j2, N); scale(K, j3, N); }
+        }
     };
     auto phase = [&](auto PH, int nbuf) XQ_INLINE_LAMBDA {
-        constexpr int ph = decltype(PH)::value, st = ph / GPS, g = ph % GPS, n = ph & 1, nph = (ph + 1) % (2 * GPS);
+        constexpr int ph = decltype(PH)::value, st = ph / GPS, g = ph % GPS, n = ph & 1, nw = SCALED ? st : n, nph = (ph + 1) % (2 * GPS);
         read_phase(std::integral_constant<int, nph>{}, nbuf);
         __builtin_amdgcn_sched_barrier(0);
         static_for<0, NSLOT>([&](auto M) XQ_INLINE_LAMBDA {
             constexpr int m = decltype(M)::value, kk = m / (2 * RT), k = g * KPP + kk, in = m % (2 * RT), rt = in % RT;
             const uint32_t* f = F[k & 1];
-            acc[rt][k] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, in < RT ? wl[n][rt] : wh[n][rt]), as_frag(f[0], f[1], f[2], f[3]),
+            acc[rt][k] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, in < RT ? wl[nw][rt] : wh[nw][rt]), as_frag(f[0], f[1], f[2], f[3]),
                                                                 acc[rt][k], 0, 0, 0);
             // the next column tile; the first one of the next step waits for its codes here
             if constexpr (k == 7 && in == 0) merge_pairs(raw[st ^ 1]);
-            static_for<0, 2 / RT>([&](auto E) XQ_INLINE_LAMBDA {
-                unpack(std::integral_constant<int, (k + 1) & 7>{}, std::integral_constant<int, in * (2 / RT) + decltype(E)::value>{},
-                       std::integral_constant<int, kk == KPP - 1 ? n ^ 1 : n>{});
-            });
+            unpack_slot(std::integral_constant<int, (k + 1) & 7>{}, std::integral_constant<int, in>{}, std::integral_constant<int, kk == KPP - 1 ? n ^ 1 : n>{});
             constexpr int b0 = m < START ? 0 : (m - START) * NSUB / (NSLOT - START), b1 = m < START ? 0 : (m + 1 - START) * NSUB / (NSLOT - START);
             static_for<b0, b1>([&](auto SUB) XQ_INLINE_LAMBDA { weight_piece(std::integral_constant<int, nph>{}, SUB); });
             __builtin_amdgcn_sched_barrier(0);
         });
     };
 
-    load_stage(o.t0);
-    load_codes(o.t0 * 8 + tw * 2, raw[0]);
-    load_codes(o.t0 * 8 + tw * 2 + 1, raw[1]);
+    load_stage(v0);
     write_stage(0);
     __syncthreads();
-    if (o.t0 + 1 < o.t1) load_stage(o.t0 + 1);
+    add_rests(0);
+    load_stage(min(v0 + 1, v1 - 1));
     read_phase(std::integral_constant<int, 0>{}, 0);
     static_for<0, NSUB>([&](auto SUB) XQ_INLINE_LAMBDA { weight_piece(std::integral_constant<int, 0>{}, SUB); });
     merge_pairs(raw[0]);
-    static_for<0, 4>([&](auto J) XQ_INLINE_LAMBDA { unpack(std::integral_constant<int, 0>{}, J, std::integral_constant<int, 0>{}); });
-    // One barrier per tile, before its last phase: by then every wave has read all of the tile out of LDS (a phase reads
-    // the next one's data), so the tile after the next may overwrite it, and the next tile, written since the barrier
+    static_for<0, 2 * RT>([&](auto IN) XQ_INLINE_LAMBDA { unpack_slot(std::integral_constant<int, 0>{}, IN, std::integral_constant<int, 0>{}); });
+    // One barrier per step, before its last phase: by then every wave has read all of the step out of LDS (a phase reads
+    // the next one's data), so the step after the next may overwrite it, and the next step, written since the barrier
     // before, may be read by the last phase.
-    for (int t = o.t0; t < o.t1; ++t) {
-        const int buf = (t - o.t0) & 1;
-        if (live) {
-            // (a step's codes are merged before it starts: their registers take those of the step after the next)
-            load_codes(min(t + 1, o.t1 - 1) * 8 + tw * 2, raw[0]);
-            static_for<0, GPS>([&](auto PH) XQ_INLINE_LAMBDA { phase(PH, buf); });
-            load_codes(min(t + 1, o.t1 - 1) * 8 + tw * 2 + 1, raw[1]);
-            static_for<GPS, 2 * GPS - 1>([&](auto PH) XQ_INLINE_LAMBDA { phase(PH, buf); });
-        }
-        if (t + 1 < o.t1) write_stage(buf ^ 1);
+    // No load stands under a condition: where paths with and without one meet, the compiler waits for all that are in flight
+    // (a whole latency per step: 4 x 32768 tokens of 2 bits 118 us, 115 without).  The last loads are repeated instead.
+    for (int t = v0; t < v1 - 1; ++t) {
+        const int buf = (t - v0) & 1;
+        // (codes are merged before their phases start: their registers take those of the step after the next)
+        load_codes((t + 1) * (VT / 32) + tw * 2, raw[0]);
+        static_for<0, GPS>([&](auto PH) XQ_INLINE_LAMBDA { phase(PH, buf); });
+        load_codes((t + 1) * (VT / 32) + tw * 2 + 1, raw[1]);
+        static_for<GPS, 2 * GPS - 1>([&](auto PH) XQ_INLINE_LAMBDA { phase(PH, buf); });
+        write_stage(buf ^ 1);
         __syncthreads();
-        if (t + 2 < o.t1) load_stage(t + 2);
-        if (live) {
-            float keep[RT][GPS];                                     // (behind the last tile a phase prepares weights of nothing)
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                for (int g = 0; g < GPS; ++g) keep[rt][g] = az[rt][g];
-            phase(std::integral_constant<int, 2 * GPS - 1>{}, buf ^ 1);
-            if (t + 1 == o.t1)
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                    for (int g = 0; g < GPS; ++g) az[rt][g] = keep[rt][g];
-        }
+        add_rests(buf ^ 1);
+        load_stage(min(t + 2, v1 - 1));
+        phase(std::integral_constant<int, 2 * GPS - 1>{}, buf ^ 1);
     }
+    static_for<0, 2 * GPS>([&](auto PH) XQ_INLINE_LAMBDA { phase(PH, (v1 - 1 - v0) & 1); });     // (the last one prepares nothing that is used)
     __syncthreads();
 
     // softmax denominators: once per row block and split
-    if (o.cblk == 0) fold_denominators<RT>(a, o, lacc, tid < 16 * RT ? mrow[16 * RT + tid] : 0.0f, reinterpret_cast<float*>(lds + L::L_OFF));
+    constexpr float P_UNIT = 1.0f / (1 << P_EXP);
+    if (o.cblk == 0)
+        fold_denominators<RT, NW>(a, o, lacc, tid < 16 * RT ? mrow[16 * RT + tid] * P_UNIT : 0.0f, reinterpret_cast<float*>(lds + L::L_OFF));
     // row factors of what this thread stores below (the sums overwrite them)
-    const float zfac = mrow[16 * RT + (tid / (16 * GPS)) % RT * 16 + (tid & 15)];
-    float yfac[4];
+    static_assert(16 * RT * NG <= NT, "one rest sum per thread");
+    constexpr int MEET = FOLD_MEET<RT, NW>;
+    const float zfac = mrow[16 * RT + (tid / (16 * NG)) % RT * 16 + (tid & 15)] * P_UNIT;
+    float yfac[MEET][4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) yfac[r] = mrow[16 * RT + ((tw >> 1) % RT) * 16 + 4 * q + r];
-    // the four token ways meet in LDS: rests first, then the accumulators
+    for (int i = 0; i < MEET; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) yfac[i][r] = mrow[16 * RT + (((tw + i * (NW / 2)) >> 1) % RT) * 16 + 4 * q + r] * P_UNIT;
+    // the rests' sums meet in LDS, then the accumulators
     const float inv_g[2] = {ginv[sw * GPS], ginv[sw * GPS + GPS - 1]};
     __syncthreads();
     float* red = reinterpret_cast<float*>(lds);
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int g = 0; g < GPS; ++g) {
-            float z = az[rt][g];
-            z += __shfl_xor(z, 16);
-            z += __shfl_xor(z, 32);
-            if (q == 0) red[((wave * RT + rt) * GPS + g) * 16 + c16] = z;
-        }
-    __syncthreads();
-    const long long yrow0 = ((long long)o.split * s.nb + o.b) * s.R;
-    static_assert(2 * RT * GPS * 16 <= 512, "one rest sum per thread");
-    if (const int idx = tid; idx < 2 * RT * GPS * 16) {
-        const int r16 = idx & 15, g = (idx >> 4) % GPS, rt = (idx / (16 * GPS)) % RT, w = idx / (16 * GPS * RT);
-        const int row = o.rb * 16 * RT + rt * 16 + r16, gg = g0 + w * GPS + g;
-        float z = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) z += red[(((2 * k + w) * RT + rt) * GPS + g) * 16 + r16];
-        if (row < s.R && gg < x.ng) a.yz[(yrow0 + row) * x.ng + gg] = z * zfac;
+    for (int g = 0; g < NG; ++g) {
+        float z = az[g];
+        z += __shfl_xor(z, 16);
+        z += __shfl_xor(z, 32);
+        if (q == 0) red[(wave * NG + g) * 16 + c16] = z;
     }
     __syncthreads();
-    f32x4 t[4];
-    fold_meet<RT>(acc, lds, wave, lane, t);
-    // token way tw sums half an accumulator row tile (rt, four column tiles) of its slab over the token ways
-    if (live && tw < 2 * RT) {
-        const int rt = tw >> 1, kg = tw & 1;
-        const int ch = G == 128 ? 8 * c16 + 4 * kg : 64 * kg + 8 * (c16 & 7) + 4 * (c16 >> 3);
-        const float f = FOLD_CODE_UNIT / (GPS == 2 && kg ? inv_g[1] : inv_g[0]);
+    const long long yrow0 = ((long long)o.split * s.nb + o.b) * s.R;
+    if (tid < 16 * RT * NG) {
+        const int r16 = tid & 15, g = (tid >> 4) % NG, rt = tid / (16 * NG);
+        const int row = o.rb * 16 * RT + rt * 16 + r16;
+        float z = 0.0f;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = o.rb * 16 * RT + rt * 16 + 4 * q + r;
-            if (row < s.R)
-                *reinterpret_cast<float4*>(a.y + (yrow0 + row) * (x.n_slabs * 128) + slab * 128 + ch) =
-                    make_float4(t[0][r] * (f * yfac[r]), t[1][r] * (f * yfac[r]), t[2][r] * (f * yfac[r]), t[3][r] * (f * yfac[r]));
+        for (int w = 0; w < NW; ++w)
+            if (RT == 1 || ((w >> 1) & 1) == rt) z += red[(w * NG + g) * 16 + r16];
+        if (row < s.R && g0 + g < x.ng) a.yz[(yrow0 + row) * x.ng + g0 + g] = z * zfac;
+    }
+    __syncthreads();
+    f32x4 t[MEET][4];
+    fold_meet<RT, NW>(acc, lds, wave, lane, t);
+    if (live && tw < 2 * RT) {
+#pragma unroll
+        for (int i = 0; i < MEET; ++i) {
+            const int h = tw + i * (NW / 2), rt = h >> 1, kg = h & 1;
+            const int ch = G == 128 ? 8 * c16 + 4 * kg : 64 * kg + 8 * (c16 & 7) + 4 * (c16 >> 3);
+            const float f = FOLD_CODE_UNIT / (GPS == 2 && kg ? inv_g[1] : inv_g[0]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = o.rb * 16 * RT + rt * 16 + 4 * q + r;
+                const float fr = f * yfac[i][r];
+                if (row < s.R)
+                    *reinterpret_cast<float4*>(a.y + (yrow0 + row) * (x.n_slabs * 128) + slab * 128 + ch) =
+                        make_float4(t[i][0][r] * fr, t[i][1][r] * fr, t[i][2][r] * fr, t[i][3][r] * fr);
+            }
         }
     }
 }
@@ -1579,8 +1695,8 @@ __device__ __forceinline__ void fold_values_dense(const FoldValueArgs& a, const 
         fold_denominators<RT>(a, o, lacc, 1.0f, reinterpret_cast<float*>(lds + L::L_OFF));
         __syncthreads();
     }
-    f32x4 t[4];
-    fold_meet<RT>(acc, lds, wave, lane, t);
+    f32x4 t[1][4];
+    fold_meet<RT, 8>(acc, lds, wave, lane, t);
     if (live && tw < 2 * RT) {
         const int rt = tw >> 1, kg = tw & 1;
 #pragma unroll
@@ -1588,7 +1704,7 @@ __device__ __forceinline__ void fold_values_dense(const FoldValueArgs& a, const 
             const int row = o.rb * 16 * RT + rt * 16 + 4 * q + r;
             if (row < s.R)
                 *reinterpret_cast<float4*>(a.y + (((long long)o.split * s.nb + o.b) * s.R + row) * (x.n_slabs * 128) + slab * 128 + 8 * c16 + 4 * kg) =
-                    make_float4(t[0][r], t[1][r], t[2][r], t[3][r]);
+                    make_float4(t[0][0][r], t[0][1][r], t[0][2][r], t[0][3][r]);
         }
     }
 }
@@ -1653,9 +1769,10 @@ __global__ __launch_bounds__(512) void fold_output_kernel(const FoldOutArgs a)
     __syncthreads();
     for (int idx = tid; idx < 32 * ns * 32; idx += 512) {            // 16-byte pieces: [column][channel / 4]
         const int col = idx / (ns * 32), c4 = idx - col * (ns * 32), used = cused[col] & 255, n = used + (cused[col] >> 8);
-        float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        float4 v2[2] = {};                                           // even and odd splits: a shorter chain of roundings
         const int ch = slab0 * 128 + 4 * c4;
         for (int k = 0; k < n; ++k) {
+            float4& v = v2[k & 1];
             const long long rk = (k < used ? k : s.splits - 1) * split_stride + crow[col];
             const float4 t = *reinterpret_cast<const float4*>(a.y + rk * d + ch);
             v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
@@ -1665,7 +1782,7 @@ __global__ __launch_bounds__(512) void fold_output_kernel(const FoldOutArgs a)
                 v.x += z; v.y += zo; v.z += z; v.w += zo;
             }
         }
-        *reinterpret_cast<float4*>(yl + col * FO_STRIDE + 4 * c4) = v;
+        *reinterpret_cast<float4*>(yl + col * FO_STRIDE + 4 * c4) = make_float4(v2[0].x + v2[1].x, v2[0].y + v2[1].y, v2[0].z + v2[1].z, v2[0].w + v2[1].w);
     }
     __syncthreads();
     const int sh = a.w.pair ? h >> 1 : h, nb0 = a.w.pair ? 4 * (h & 1) : 4;
@@ -1767,8 +1884,12 @@ __global__ __launch_bounds__(256) void fold_finish_kernel(const float* __restric
     int used;
     bool window;
     fold_used_splits(s, b, used, window);
-    float L = 0.0f;
-    for (int k = 0; k < used; ++k) L += lsum[((long long)k * s.nb + b) * s.nrb * 16 * rt + row];
+    float L4[4] = {};
+    for (int k = 0; k < used; k += 4)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (k + j < used) L4[j] += lsum[((long long)(k + j) * s.nb + b) * s.nrb * 16 * rt + row];
+    float L = (L4[0] + L4[1]) + (L4[2] + L4[3]);
     if (window) L += lsum[((long long)(s.splits - 1) * s.nb + b) * s.nrb * 16 * rt + row];
     float4 t = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll 4
@@ -1803,11 +1924,16 @@ struct FoldPlan {
                                                            // the output splits lie over p (dead by then)
 };
 
-// Token splits of the value kernel: enough workgroups for the 256 CUs, but no more than leave a tile each.
-int fold_splits(int nb, int nrb, int n_slabs_v, int max_len)
+// Token splits of the value kernel: enough workgroups for the 256 CUs, two on each over coded rows (groups along the channels),
+// but no more than leave a tile each.
+int fold_splits(int nb, int nrb, int n_slabs_v, int max_len, int per_cu)
 {
     const int per = nb * nrb * ((n_slabs_v + 1) / 2), nt = (max_len + FOLD_VTILE - 1) / FOLD_VTILE;
-    return std::max(1, std::min({nt, (256 + per - 1) / per, 16}));
+    return std::max(1, std::min({nt, (256 * per_cu + per - 1) / per, 16 * per_cu}));
+}
+static int fold_splits(const FoldProblem& f, int B, int nrb, int max_len)
+{
+    return fold_splits(B, nrb, f.n_slabs_v, max_len, f.dense || f.block ? 1 : 2);
 }
 
 static FoldPlan fold_plan(const FoldProblem& f, int B, int nb, int max_len, int splits)
@@ -1837,7 +1963,7 @@ static FoldPlan fold_plan(const FoldProblem& f, int B, int nb, int max_len, int 
 size_t fold_workspace_bytes(const FoldProblem& f, int B, int max_len)
 {
     const int R = f.Hq, nrb = (R + (R <= 16 ? 15 : 31)) / (R <= 16 ? 16 : 32);
-    return fold_plan(f, B, B, max_len, fold_splits(B, nrb, f.n_slabs_v, max_len)).total;
+    return fold_plan(f, B, B, max_len, fold_splits(f, B, nrb, max_len)).total;
 }
 
 // The largest launch group that fits the workspace, for B sequences; where not even one does, one with fewer splits; false if
@@ -1847,7 +1973,7 @@ static bool fold_fit(const FoldProblem& f, int B, int max_len, size_t bytes, int
 {
     const int R = f.Hq, nrb = (R + (R <= 16 ? 15 : 31)) / (R <= 16 ? 16 : 32);
     bytes = std::min(bytes, std::max(f.query_bytes, fold_workspace_bytes(f, B, max_len)));
-    const int splits = fold_splits(B, nrb, f.n_slabs_v, max_len);
+    const int splits = fold_splits(f, B, nrb, max_len);
     for (int groups = 1;; ++groups) {
         const int n = (B + groups - 1) / groups;
         const FoldPlan p = fold_plan(f, B, n, max_len, splits);
@@ -1880,9 +2006,9 @@ template <int BITS, int G, int RT>
 static hipError_t run_values(const FoldValueArgs& a, bool nibbles, int grid, hipStream_t s)
 {
     if constexpr (BITS == 4 && G == 128) {
-        if (nibbles) return launch(fold_values_kernel<4, 128, RT, true>, grid, FoldValueLds<RT, 2, true>::TOTAL, a, s);
+        if (nibbles) return launch(fold_values_kernel<4, 128, RT, true>, grid, FoldValueLds<RT, 2, true, false>::TOTAL, a, s, FOLD_VALUE_WAVES);
     }
-    return launch(fold_values_kernel<BITS, G, RT, false>, grid, FoldValueLds<RT, 2 * (128 / G), false>::TOTAL, a, s);
+    return launch(fold_values_kernel<BITS, G, RT, false>, grid, FoldValueLds<RT, 2 * (128 / G), false, fold_scaled_codes(BITS)>::TOTAL, a, s, FOLD_VALUE_WAVES);
 }
 template <int RT>
 static hipError_t scores_for(int bits, int G, bool nibbles, const FoldScoreArgs& a, int grid, hipStream_t s)

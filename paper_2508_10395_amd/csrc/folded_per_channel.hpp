@@ -466,8 +466,8 @@ __global__ __launch_bounds__(512) void fold_values_pc_kernel(const FoldValueArgs
         __syncthreads();
     }
     // the four token ways meet in LDS; token way tw sums half a row tile (rt, four column tiles) of its slab
-    f32x4 t[4];
-    fold_meet<RT>(y, lds, wave, lane, t);
+    f32x4 t[1][4];
+    fold_meet<RT, 8>(y, lds, wave, lane, t);
     if (live && tw < 2 * RT) {
         const long long yrow0 = ((long long)o.split * s.nb + o.b) * s.R;
         const int rt = tw >> 1, kg = tw & 1;
@@ -477,7 +477,7 @@ __global__ __launch_bounds__(512) void fold_values_pc_kernel(const FoldValueArgs
             const int row = o.rb * 16 * RT + rt * 16 + 4 * q + r;
             if (row < s.R)
                 *reinterpret_cast<float4*>(a.y + (yrow0 + row) * (x.n_slabs * 128) + slab * 128 + 8 * c16 + 4 * kg) =
-                    make_float4(t[0][r] * down, t[1][r] * down, t[2][r] * down, t[3][r] * down);
+                    make_float4(t[0][0][r] * down, t[0][1][r] * down, t[0][2][r] * down, t[0][3][r] * down);
         }
     }
 }

@@ -125,10 +125,18 @@ def test_formats_rows_and_tile_edges(xq, bits, G, Hq, Hkv, d, lens):
 
 @pytest.mark.parametrize("bits,G", [(2, 64), (3, 128), (16, 128)])
 def test_token_ways_of_a_score_workgroup(xq, bits, G):
-    """Enough tiles that a score workgroup takes two of them, on a narrow layer, with a dead second tile."""
+    """Enough tiles for score workgroups of four waves, two of them without a slab on this narrow layer, and tiles past the length."""
     w = xi.C2.scaled(B=16, L=4000, d=256, Hq=64, Hkv=8, n_outlier=2)
     lens = [4000, 3969, 129, 128, 1, 2049] + [100] * 10
     _run(xq, w, bits, G, lens, pairs=[(0, 0), (0, 63), (1, 17), (2, 5), (3, 40), (4, 33), (5, 62), (15, 8)])
+
+
+@pytest.mark.parametrize("bits,G", [(2, 64), (2, 128), (3, 64), (3, 128), (4, 64), (4, 128), (8, 128)])
+def test_steps_of_a_value_workgroup(xq, bits, G):
+    """Ranges of one to four steps of 128 tokens, with a last step that is full, holds one token, or is missing."""
+    w = xi.C2.scaled(B=32, L=1100, d=1024, Hq=32, Hkv=8, n_outlier=10)
+    lens = [1100, 1025, 897, 896, 513, 512, 385, 130] + [64] * 24
+    _run(xq, w, bits, G, lens, pairs=[(b, (5 * b + 3) % 32) for b in range(9)])
 
 
 @pytest.mark.parametrize("bits", [3, 16])
