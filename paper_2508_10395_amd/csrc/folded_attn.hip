@@ -107,6 +107,23 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
         place[wave][c32] = cb * 32 + c32 < ncol ? (b * s.nrb + rb) * rpb + (row - rb * rpb) : -1;
     }
 
+    // Every weight fragment of the wave's slab is asked for before anything is waited for (2 waves in flight on a SIMD at most,
+    // 32 loads each): with eight at a time a wave met the memory's latency four times, 15 us for 16 to 34 MB.
+    const int sh = a.w.pair ? h >> 1 : h, nb0 = a.w.pair ? 4 * (h & 1) : 0;
+    const uint8_t* wsrc = a.w.stream + (long long)sh * a.w.head_bytes + lane * 16;
+    uint4 wf[4][4][2];
+#pragma unroll
+    for (int pr = 0; pr < 4; ++pr)
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                // coded streams: column block nb runs 7 - nb k-steps late, cyclically
+                int pos = slab * 8 + 2 * pr + k + (DENSE ? 0 : COL_BLOCK_LAG_MAX - (nb0 + nb));
+                if (pos >= a.w.n16) pos -= a.w.n16;
+                wf[pr][nb][k] = *reinterpret_cast<const uint4*>(wsrc + (long long)pos * 8192 + (nb0 + nb) * 1024);
+            }
+
     // the 32 query rows as an operand: lane = column, k-slots in the order the accumulator rows below come in
     uint4 qa[4][2];
     float l1 = 0.0f;
@@ -127,8 +144,6 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
             }
         l1 += __shfl_xor(l1, 32);
     }
-    const int sh = a.w.pair ? h >> 1 : h, nb0 = a.w.pair ? 4 * (h & 1) : 0;
-    const uint8_t* wsrc = a.w.stream + (long long)sh * a.w.head_bytes + lane * 16;
     // A coded stream's weights are at most 2^12 (times the slot's factor): |u| <= 2^12 |q|_1, which a power of two brings
     // below 2^15 for the fp16 parts of u.  The score kernel takes it (and the stream's own factor) out again.
     int e = 0;
@@ -162,26 +177,16 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
     for (int i = 0; i < 16; ++i) zero16[i] = 0.0f;
 #pragma unroll
     for (int pr = 0; pr < 4; ++pr) {
-        uint4 wf[4][2];
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                // coded streams: column block nb runs 7 - nb k-steps late, cyclically
-                int pos = slab * 8 + 2 * pr + k + (DENSE ? 0 : COL_BLOCK_LAG_MAX - (nb0 + nb));
-                if (pos >= a.w.n16) pos -= a.w.n16;
-                wf[nb][k] = *reinterpret_cast<const uint4*>(wsrc + (long long)pos * 8192 + (nb0 + nb) * 1024);
-            }
         f32x16 uacc = zero16;
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb) {
             f32x16 t;
             if constexpr (DENSE) {
-                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[nb][0]), __builtin_bit_cast(bf16x8, sel[0]), zero16, 0, 0, 0);
-                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[nb][1]), __builtin_bit_cast(bf16x8, sel[1]), t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[pr][nb][0]), __builtin_bit_cast(bf16x8, sel[0]), zero16, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[pr][nb][1]), __builtin_bit_cast(bf16x8, sel[1]), t, 0, 0, 0);
             } else {
-                t = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, wf[nb][0]), __builtin_bit_cast(f16x8, sel[0]), zero16, 0, 0, 0);
-                t = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, wf[nb][1]), __builtin_bit_cast(f16x8, sel[1]), t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, wf[pr][nb][0]), __builtin_bit_cast(f16x8, sel[0]), zero16, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, wf[pr][nb][1]), __builtin_bit_cast(f16x8, sel[1]), t, 0, 0, 0);
             }
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
@@ -1737,6 +1742,7 @@ struct FoldOutArgs {
 constexpr int FO_MAX_SLABS = 4;
 constexpr int FO_STRIDE = FO_MAX_SLABS * 128 + 4;
 constexpr int FO_LDS = 32 * FO_STRIDE * 4;               // 66 KiB, reused for the waves' partial sums (64 KiB)
+constexpr int FO_MAX_GROUPS = FO_MAX_SLABS * 2;
 
 template <bool DENSE>
 __global__ __launch_bounds__(512) void fold_output_kernel(const FoldOutArgs a)
@@ -1751,10 +1757,24 @@ __global__ __launch_bounds__(512) void fold_output_kernel(const FoldOutArgs a)
     const int slab0 = chunk * a.chunk_slabs, ns = min(a.chunk_slabs, a.n_slabs - slab0);
     const int d = a.n_slabs * 128;
     const long long split_stride = (long long)s.nb * s.R;
+    // the weights first: they come out of HBM while the sums below wait for what the value kernel left (a wave's k-step: the
+    // same place in every slab)
+    const int sh = a.w.pair ? h >> 1 : h, nb0 = a.w.pair ? 4 * (h & 1) : 4;
+    const uint8_t* wsrc = a.w.stream + (long long)sh * a.w.head_bytes + lane * 16;
+    uint4 wf[FO_MAX_SLABS][4];
+#pragma unroll
+    for (int sl = 0; sl < FO_MAX_SLABS; ++sl)
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) {
+            int pos = (slab0 + min(sl, ns - 1)) * 8 + wave + (DENSE ? 0 : COL_BLOCK_LAG_MAX - (nb0 + nb));
+            if (pos >= a.w.n16) pos -= a.w.n16;
+            wf[sl][nb] = *reinterpret_cast<const uint4*>(wsrc + (long long)pos * 8192 + (nb0 + nb) * 1024);
+        }
     auto row_of = [&](int col, int& b) -> int {
         b = col / gq;
         return h * gq + (col - b * gq);
     };
+    __shared__ float zl[32 * FO_MAX_GROUPS];
     __shared__ int crow[32], cused[32];                              // per column: row of y, splits (and 256: the window's)
     if (tid < 32) {
         int b = 0, used = 0, row = 0;
@@ -1767,40 +1787,71 @@ __global__ __launch_bounds__(512) void fold_output_kernel(const FoldOutArgs a)
         cused[tid] = used + (window ? 256 : 0);
     }
     __syncthreads();
-    for (int idx = tid; idx < 32 * ns * 32; idx += 512) {            // 16-byte pieces: [column][channel / 4]
-        const int col = idx / (ns * 32), c4 = idx - col * (ns * 32), used = cused[col] & 255, n = used + (cused[col] >> 8);
-        float4 v2[2] = {};                                           // even and odd splits: a shorter chain of roundings
-        const int ch = slab0 * 128 + 4 * c4;
-        for (int k = 0; k < n; ++k) {
-            float4& v = v2[k & 1];
-            const long long rk = (k < used ? k : s.splits - 1) * split_stride + crow[col];
-            const float4 t = *reinterpret_cast<const float4*>(a.y + rk * d + ch);
-            v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
-            if (!DENSE && a.ng) {
-                // (8-bit caches: a code's zero-point multiplies its weight row once, that of the low nibble)
-                const float z = a.yz[rk * a.ng + ch / a.group], zo = a.w.nibbles ? 0.0f : z;
-                v.x += z; v.y += zo; v.z += z; v.w += zo;
-            }
-        }
-        *reinterpret_cast<float4*>(yl + col * FO_STRIDE + 4 * c4) = make_float4(v2[0].x + v2[1].x, v2[0].y + v2[1].y, v2[0].z + v2[1].z, v2[0].w + v2[1].w);
+    // the groups' offsets: [column][group of the workgroup]
+    const bool offsets = !DENSE && a.ng;
+    const int cg = offsets ? ns * 128 / a.group : 1;
+    if (offsets && tid < 32 * cg) {
+        const int col = tid / cg, g = slab0 * 128 / a.group + tid - col * cg, used = cused[col] & 255, n = used + (cused[col] >> 8);
+        float z[4] = {};                                             // (short chains of roundings, here and below)
+        for (int k = 0; k < n; k += 4)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (k + j < n) z[j] += a.yz[((k + j < used ? k + j : s.splits - 1) * split_stride + crow[col]) * a.ng + g];
+        zl[col * FO_MAX_GROUPS + tid - col * cg] = (z[0] + z[1]) + (z[2] + z[3]);
     }
     __syncthreads();
-    const int sh = a.w.pair ? h >> 1 : h, nb0 = a.w.pair ? 4 * (h & 1) : 4;
-    const uint8_t* wsrc = a.w.stream + (long long)sh * a.w.head_bytes + lane * 16;
+    // 16-byte pieces [column][channel / 4], two of them and four splits at a time: one latency for eight loads.  (Columns that
+    // hold no query stay as they are: nothing of theirs is stored.)
+    const int pieces = min(32, ncol - cb * 32) * ns * 32;
+    for (int p0 = tid; p0 < pieces; p0 += 2 * 512) {
+        const float* src[2];
+        int col[2], c4[2], n[2], last[2];
+        float4 v[4][2] = {};
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int idx = min(p0 + i * 512, pieces - 1);
+            col[i] = idx / (ns * 32);
+            c4[i] = idx - col[i] * (ns * 32);
+            const int used = cused[col[i]] & 255;
+            n[i] = used + (cused[col[i]] >> 8);
+            last[i] = n[i] > used ? s.splits - 1 : used - 1;         // where the last of them lies
+            src[i] = a.y + (long long)crow[col[i]] * d + slab0 * 128 + 4 * c4[i];
+        }
+        for (int k = 0; k < max(n[0], n[1]); k += 4) {
+            float4 t[4][2];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    t[j][i] = *reinterpret_cast<const float4*>(src[i] + (k + j < n[i] - 1 ? k + j : last[i]) * split_stride * d);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    if (k + j < n[i]) { v[j][i].x += t[j][i].x; v[j][i].y += t[j][i].y; v[j][i].z += t[j][i].z; v[j][i].w += t[j][i].w; }
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            float4 w = make_float4((v[0][i].x + v[1][i].x) + (v[2][i].x + v[3][i].x), (v[0][i].y + v[1][i].y) + (v[2][i].y + v[3][i].y),
+                                   (v[0][i].z + v[1][i].z) + (v[2][i].z + v[3][i].z), (v[0][i].w + v[1][i].w) + (v[2][i].w + v[3][i].w));
+            if (offsets) {
+                // (8-bit caches: a code's zero-point multiplies its weight row once, that of the low nibble)
+                const float z = zl[col[i] * FO_MAX_GROUPS + 4 * c4[i] / a.group], zo = a.w.nibbles ? 0.0f : z;
+                w.x += z; w.y += zo; w.z += z; w.w += zo;
+            }
+            *reinterpret_cast<float4*>(yl + col[i] * FO_STRIDE + 4 * c4[i]) = w;         // (behind the last piece it is written again)
+        }
+    }
+    __syncthreads();
     f32x16 acc[4];
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[nb][i] = 0.0f;
-    for (int k = wave; k < ns * 8; k += 8) {                         // a wave's k-step: the same place in every slab
-        const int sl = k >> 3, ks = k & 7;
-        uint4 wf[4];
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb) {
-            int pos = (slab0 + sl) * 8 + ks + (DENSE ? 0 : COL_BLOCK_LAG_MAX - (nb0 + nb));
-            if (pos >= a.w.n16) pos -= a.w.n16;
-            wf[nb] = *reinterpret_cast<const uint4*>(wsrc + (long long)pos * 8192 + (nb0 + nb) * 1024);
-        }
+    for (int sl = 0; sl < FO_MAX_SLABS; ++sl) {
+        if (sl >= ns) break;
+        const int ks = wave;
         uint32_t yp[3][4];
         {
             float v[8];
@@ -1827,7 +1878,7 @@ __global__ __launch_bounds__(512) void fold_output_kernel(const FoldOutArgs a)
         }
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb) {
-            uint4 wb = wf[nb];
+            uint4 wb = wf[sl][nb];
             if constexpr (!DENSE) {                                  // fp16 -> bf16: at most 8 significant bits, exact
                 const uint32_t w4[4] = {wb.x, wb.y, wb.z, wb.w};
                 uint32_t d4[4];
