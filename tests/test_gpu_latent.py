@@ -50,6 +50,12 @@ def test_projection_matches_oracle(xq, M, d, n_lat):
     _check_projection(torch_to_bits(out), xo.project_rows(x, ut), x, ut)
 
 
+@pytest.mark.parametrize("M,d,n_lat", [(17, 128, 32), (33, 4224, 64), (16, 5120, 96), (256, 1024, 512), (257, 1024, 512)])
+def test_projection_tiles(xq, M, d, n_lat):
+    """Ragged 16-row tiles, fewer steps than waves, steps beyond one round of loads, either side of the larger tiles."""
+    test_projection_matches_oracle(xq, M, d, n_lat)
+
+
 def test_projection_exact_case_and_noop(xq):
     rng = np.random.default_rng(5)
     x = rng.integers(-1, 2, size=(40, 256)).astype(np.float32)
