@@ -139,6 +139,14 @@ def test_steps_of_a_value_workgroup(xq, bits, G):
     _run(xq, w, bits, G, lens, pairs=[(b, (5 * b + 3) % 32) for b in range(9)])
 
 
+@pytest.mark.parametrize("B", [15, 16, 17, 29])
+def test_sequences_dealt_over_the_chip(xq, B):
+    """From 16 sequences on they are taken in another order than they come in; lengths of every kind, several the same."""
+    w = xi.C2.scaled(B=B, L=700, d=1024, Hq=16, Hkv=16, n_outlier=10)
+    lens = [1 + (b * b * 97 + 41 * b) % 700 if b % 3 else 700 - b for b in range(B)]
+    _run(xq, w, 3, 128, lens, pairs=[(b, (3 * b + 1) % 16) for b in range(B)])
+
+
 @pytest.mark.parametrize("bits", [3, 16])
 def test_smaller_workspaces(xq, bits):
     """Between the smallest workspace that is accepted and the one that is asked for, the launch goes in groups of sequences,
