@@ -331,9 +331,10 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
 // registers; the rests of the zero-points enter through one more matrix instruction per slab and row tile.  At the end
 // the slab ways' partial scores meet in LDS, and the softmax weights against the tile's maximum are stored as the value
 // kernel reads them.
-// Bound by issue and by the latency of the loads (with runs of adjacent slabs 1024 tiles of 2 bits took 114 us: 89 without the
-// codes' loads, 75 with nothing loaded); codes read in operand order straight into registers (64 cache lines touched by every
-// load) took 173 us.
+// Bound by issue: matrix and vector instructions of a SIMD's two waves overlap little (a 16 x 16 x 32 product alone 19 cycles, with
+// three vector instructions 23, with six 39), and with nothing loaded the kernel takes 0.65 of its time.  Rests cut to bf16 parts
+// where they are read, four times over, cost 2 to 3 us of 100 (1024 tiles of 2 bits); codes read in operand order straight into
+// registers (64 cache lines touched by every load) two thirds more time.
 // =====================================================================================================================
 struct FoldScoreArgs {
     FoldSource x;
@@ -449,9 +450,10 @@ __device__ __forceinline__ void fold_scores_finish(const FoldShape& s, const flo
 
 template <int RT>
 constexpr int FOLD_SCORE_RED = 8 * RT * 8 * 1024 + 8 * 8 * 16 * RT * 4;
-// a wave's codes of one slab, and its records (8 bytes per token and group, 16 for nibble streams)
+// a wave's codes of one slab, its records (4 bytes per token and group, 8 for nibble streams), and the tokens' rests as operands
+// (8 bytes per group)
 template <int BITS, int G, bool NIB>
-constexpr int FOLD_SCORE_WAVE = FOLD_TILE * 16 * BITS + (128 / G) * FOLD_TILE * (NIB ? 16 : 8);
+constexpr int FOLD_SCORE_WAVE = FOLD_TILE * 16 * BITS + (128 / G) * FOLD_TILE * (NIB ? 8 : 4) + (128 / G) * FOLD_TILE * 8;
 template <int BITS, int G, int RT, bool NIB>
 constexpr int FOLD_SCORE_LDS = 8 * FOLD_SCORE_WAVE<BITS, G, NIB> > FOLD_SCORE_RED<RT> ? 8 * FOLD_SCORE_WAVE<BITS, G, NIB> : FOLD_SCORE_RED<RT>;
 
@@ -476,6 +478,7 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
     const int slab0 = o.slab0, slab1 = o.slab1;
     uint8_t* image = lds + wave * FOLD_SCORE_WAVE<BITS, G, NIB>;     // [token 128][ROWB]
     uint32_t* records = reinterpret_cast<uint32_t*>(image + FOLD_TILE * ROWB);
+    uint2* rests = reinterpret_cast<uint2*>(image + FOLD_TILE * ROWB + GPS * FOLD_TILE * (NIB ? 8 : 4));     // [token][group]
 
     // Codes go through the wave's LDS image: loaded row by row (a load then touches 64 / BITS rows once; in operand order
     // every row would be touched by four quarter waves, and L1 look-ups bound the kernel), written once the slab before has
@@ -501,7 +504,8 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
             }
         }
     };
-    // -> records: -zi (fp16) | scale (bf16), rest of the zero-point (fp32); nibble streams: -zi of either nibble, scale, rest
+    // -> records: -zi (fp16) | scale (bf16); nibble streams: -zi of either nibble, scale (fp32)
+    float rs[2][GPS];                                                // what is left of the zero-points
     auto write_meta = [&]() XQ_INLINE_LAMBDA {
 #pragma unroll
         for (int t = 0; t < 2; ++t)
@@ -509,19 +513,32 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
             for (int g = 0; g < GPS; ++g) {
                 const float z = g ? bf16_hi_to_f32(zs[t][0]) : bf16_lo_to_f32(zs[t][0]);
                 const float sc = g ? bf16_hi_to_f32(zs[t][1]) : bf16_lo_to_f32(zs[t][1]);
-                float rest;
-                const float zi = fold_integer_zero(sc, z, NIB ? 255.0f : (float)((1 << BITS) - 1), rest);
+                const float zi = fold_integer_zero(sc, z, NIB ? 255.0f : (float)((1 << BITS) - 1), rs[t][g]);
                 const int at = g * FOLD_TILE + t * 64 + lane;
                 if constexpr (NIB) {
                     const float zh = floorf(zi * (1.0f / 16.0f));
-                    reinterpret_cast<uint4*>(records)[at] =
-                        make_uint4(f16_bits((zi - 16.0f * zh) * (-1.0f / FOLD_CODE_UNIT)) | (f16_bits(zh * (-1.0f / FOLD_CODE_UNIT)) << 16),
-                                   __float_as_uint(sc), __float_as_uint(rest), 0u);
-                } else {
                     reinterpret_cast<uint2*>(records)[at] =
-                        make_uint2(f16_bits(zi * (-1.0f / FOLD_CODE_UNIT)) | (__float_as_uint(sc) & 0xFFFF0000u), __float_as_uint(rest));
+                        make_uint2(f16_bits((zi - 16.0f * zh) * (-1.0f / FOLD_CODE_UNIT)) | (f16_bits(zh * (-1.0f / FOLD_CODE_UNIT)) << 16),
+                                   __float_as_uint(sc));
+                } else {
+                    records[at] = f16_bits(zi * (-1.0f / FOLD_CODE_UNIT)) | (__float_as_uint(sc) & 0xFFFF0000u);
                 }
             }
+    };
+    // -> rests: three bf16 parts each, cut here, once per token (every quarter wave of the products needs them)
+    auto write_rests = [&]() XQ_INLINE_LAMBDA {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            uint2 v[GPS];
+#pragma unroll
+            for (int g = 0; g < GPS; ++g) {
+                uint32_t h, m, l;
+                split_bf16x3(rs[t][g], h, m, l);
+                v[g] = make_uint2(pack_hi16(h, m), l >> 16);
+            }
+            if constexpr (GPS == 2) reinterpret_cast<uint4*>(rests)[t * 64 + lane] = make_uint4(v[0].x, v[0].y, v[GPS - 1].x, v[GPS - 1].y);
+            else rests[t * 64 + lane] = v[0];
+        }
     };
 
     f32x4 S[RT][8];
@@ -535,8 +552,7 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
     // (scheduling fences keep it there).
     if (slab0 < slab1) {
         uint4 u[2][RT][2][2], uz[RT];                                // folded queries of the two halves: [rt][tick][hi, lo]
-        uint32_t rec[4][3];                                          // records of units t - 1 .. t + 2: -zi, scale, rest
-        float rest0[4];                                              // (groups of 64: the first group's rest, for the second half's units)
+        uint32_t rec[4][2];                                          // records of units t - 1 .. t + 2: -zi, scale
         uint32_t cw[4][2];                                           // code dwords of units t .. t + 2
         uint32_t F[2][8];                                            // token operands of units t, t + 1
         f32x4 P[2][RT];
@@ -548,12 +564,11 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
             constexpr int t = decltype(T)::value, h = (t >> 3) & 1, i = t & 7, n = t & 3;
             const int at = (GPS == 2 ? h : 0) * FOLD_TILE + i * 16 + c16;
             if constexpr (NIB) {
-                const uint4 r = reinterpret_cast<const uint4*>(records)[at];
-                rec[n][0] = r.x; rec[n][1] = r.y; rec[n][2] = r.z;
-            } else {
                 const uint2 r = reinterpret_cast<const uint2*>(records)[at];
-                rec[n][0] = r.x; rec[n][1] = r.x & 0xFFFF0000u; rec[n][2] = r.y;
-                if constexpr (GPS == 2 && h == 1) rest0[n] = __uint_as_float(records[(i * 16 + c16) * 2 + 1]);
+                rec[n][0] = r.x; rec[n][1] = r.y;
+            } else {
+                const uint32_t r = records[at];
+                rec[n][0] = r; rec[n][1] = r & 0xFFFF0000u;
             }
             const uint32_t* src = reinterpret_cast<const uint32_t*>(image + (i * 16 + c16) * ROWB);
             if constexpr (G == 128) {                                // dwords of the lane's unit of 32 codes: those of half h
@@ -607,6 +622,7 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
         static_for<0, NL>([&](auto K) XQ_INLINE_LAMBDA { load_codes(slab0, K); });
         static_for<0, 4 * RT>([&](auto I) XQ_INLINE_LAMBDA { load_u(slab0, std::integral_constant<int, 0>{}, I); });
         write_meta();
+        write_rests();
         write_codes();
         read_unit(std::integral_constant<int, 0>{});
         read_unit(std::integral_constant<int, 1>{});
@@ -624,6 +640,9 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
                 // (units 14 and 15 of this slab have been read: the next slab's records and codes may take their place)
                 if constexpr (t == 14) { write_meta(); write_codes(); }
                 read_unit(std::integral_constant<int, t + 2>{});
+                uint4 mz = make_uint4(0u, 0u, 0u, 0u);
+                if constexpr (h == 1 && GPS == 2) mz = reinterpret_cast<const uint4*>(rests)[i * 16 + c16];
+                if constexpr (h == 1 && GPS == 1) { const uint2 r = rests[i * 16 + c16]; mz.x = r.x; mz.y = r.y; }
                 // the next half's folded queries, ahead of the codes in the first half: loads return in order, and the queries
                 // come out of L2, the codes from farther away
                 if constexpr (i == 0)
@@ -647,19 +666,11 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
                     __builtin_amdgcn_sched_barrier(0);
                 });
                 if constexpr (h == 1) {
-                    uint32_t a3[3], b3[3];
-                    uint4 mz;
-                    split_bf16x3(__uint_as_float(rec[t & 3][2]), a3[0], a3[1], a3[2]);
-                    if constexpr (GPS == 2) {
-                        split_bf16x3(rest0[t & 3], b3[0], b3[1], b3[2]);
-                        mz = make_uint4(pack_hi16(b3[0], b3[1]), b3[2] >> 16, pack_hi16(a3[0], a3[1]), a3[2] >> 16);
-                    } else {
-                        mz = make_uint4(pack_hi16(a3[0], a3[1]), a3[2] >> 16, 0u, 0u);
-                    }
 #pragma unroll
                     for (int rt = 0; rt < RT; ++rt)
                         S[rt][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, uz[rt]), __builtin_bit_cast(bf16x8, mz), S[rt][i], 0, 0, 0);
                 }
+                if constexpr (t == 15) write_rests();                // (the next slab's: unit 15's have been read)
                 __builtin_amdgcn_sched_barrier(0);
             });
         }
