@@ -24,9 +24,10 @@ struct FoldShape {
     int mhalf;                           // softmax weights and maxima per 128 tokens (0) or 64 (1: per-channel blocks of 64)
     BatchI32 len;                        // of the call's sequences
     int dealt;                           // score and value workgroups take the launch's sequences in the order below (else as they come)
-    BatchI32 order;
+    uint8_t order[XQ_MAX_BATCH];
 };
-__device__ __forceinline__ int fold_sequence(const FoldShape& s, int k) { return s.dealt ? s.order.v[k] : k; }
+static_assert(XQ_MAX_BATCH <= 256, "a sequence's number in a byte");
+__device__ __forceinline__ int fold_sequence(const FoldShape& s, int k) { return s.dealt ? __builtin_amdgcn_readfirstlane((int)s.order[k]) : k; }
 
 // The tokens a workgroup may take and where their tiles lie.  A per-channel cache's complete blocks come first, its window
 // has the tiles behind them (from an even one on) and the last split; it is the work of the first workgroups of a launch.
@@ -110,6 +111,22 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
         place[wave][c32] = cb * 32 + c32 < ncol ? (b * s.nrb + rb) * rpb + (row - rb * rpb) : -1;
     }
 
+    // the 32 query rows as an operand: lane = column, k-slots in the order the accumulator rows below come in
+    uint4 qa[4][2];
+    float l1 = 0.0f;
+    {
+        int b;
+        const int row = row_of(min(cb * 32 + c32, ncol - 1), b);
+        const uint16_t* qv = a.q + ((long long)(s.b0 + b) * s.R + row) * 128 + 4 * half;
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const uint2 x = *reinterpret_cast<const uint2*>(qv + 32 * nb + 16 * k);
+                const uint2 y = *reinterpret_cast<const uint2*>(qv + 32 * nb + 16 * k + 8);
+                qa[nb][k] = make_uint4(x.x, x.y, y.x, y.y);
+            }
+    }
     // Every weight fragment of the wave's slab is asked for before anything is waited for (2 waves in flight on a SIMD at most,
     // 32 loads each): with eight at a time a wave met the memory's latency four times, 15 us for 16 to 34 MB.
     const int sh = a.w.pair ? h >> 1 : h, nb0 = a.w.pair ? 4 * (h & 1) : 0;
@@ -126,27 +143,15 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
                 if (pos >= a.w.n16) pos -= a.w.n16;
                 wf[pr][nb][k] = *reinterpret_cast<const uint4*>(wsrc + (long long)pos * 8192 + (nb0 + nb) * 1024);
             }
-
-    // the 32 query rows as an operand: lane = column, k-slots in the order the accumulator rows below come in
-    uint4 qa[4][2];
-    float l1 = 0.0f;
-    {
-        int b;
-        const int row = row_of(min(cb * 32 + c32, ncol - 1), b);
-        const uint16_t* qv = a.q + ((long long)(s.b0 + b) * s.R + row) * 128 + 4 * half;
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb)
+    for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const uint2 x = *reinterpret_cast<const uint2*>(qv + 32 * nb + 16 * k);
-                const uint2 y = *reinterpret_cast<const uint2*>(qv + 32 * nb + 16 * k + 8);
-                qa[nb][k] = make_uint4(x.x, x.y, y.x, y.y);
-                const uint32_t w4[4] = {x.x, x.y, y.x, y.y};
+        for (int k = 0; k < 2; ++k) {
+            const uint32_t w4[4] = {qa[nb][k].x, qa[nb][k].y, qa[nb][k].z, qa[nb][k].w};
 #pragma unroll
-                for (int i = 0; i < 4; ++i) l1 += fabsf(bf16_lo_to_f32(w4[i])) + fabsf(bf16_hi_to_f32(w4[i]));
-            }
-        l1 += __shfl_xor(l1, 32);
-    }
+            for (int i = 0; i < 4; ++i) l1 += fabsf(bf16_lo_to_f32(w4[i])) + fabsf(bf16_hi_to_f32(w4[i]));
+        }
+    l1 += __shfl_xor(l1, 32);
     // A coded stream's weights are at most 2^12 (times the slot's factor): |u| <= 2^12 |q|_1, which a power of two brings
     // below 2^15 for the fp16 parts of u.  The score kernel takes it (and the stream's own factor) out again.
     int e = 0;
@@ -1761,7 +1766,7 @@ constexpr int FO_LDS = 32 * FO_STRIDE * 4;               // 66 KiB, reused for t
 constexpr int FO_MAX_GROUPS = FO_MAX_SLABS * 2;
 
 template <bool DENSE>
-__global__ __launch_bounds__(512) void fold_output_kernel(const FoldOutArgs a)
+__global__ __launch_bounds__(512, 4) void fold_output_kernel(const FoldOutArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     float* yl = reinterpret_cast<float*>(lds);
@@ -1777,15 +1782,17 @@ __global__ __launch_bounds__(512) void fold_output_kernel(const FoldOutArgs a)
     // same place in every slab)
     const int sh = a.w.pair ? h >> 1 : h, nb0 = a.w.pair ? 4 * (h & 1) : 4;
     const uint8_t* wsrc = a.w.stream + (long long)sh * a.w.head_bytes + lane * 16;
-    uint4 wf[FO_MAX_SLABS][4];
-#pragma unroll
-    for (int sl = 0; sl < FO_MAX_SLABS; ++sl)
+    uint4 wf[2][4];                                                  // (two slabs ahead: with all four two workgroups do not fit a CU)
+    auto load_weights = [&](int sl, uint4 (&f)[4]) XQ_INLINE_LAMBDA {
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb) {
             int pos = (slab0 + min(sl, ns - 1)) * 8 + wave + (DENSE ? 0 : COL_BLOCK_LAG_MAX - (nb0 + nb));
             if (pos >= a.w.n16) pos -= a.w.n16;
-            wf[sl][nb] = *reinterpret_cast<const uint4*>(wsrc + (long long)pos * 8192 + (nb0 + nb) * 1024);
+            f[nb] = *reinterpret_cast<const uint4*>(wsrc + (long long)pos * 8192 + (nb0 + nb) * 1024);
         }
+    };
+    load_weights(0, wf[0]);
+    load_weights(1, wf[1]);
     auto row_of = [&](int col, int& b) -> int {
         b = col / gq;
         return h * gq + (col - b * gq);
@@ -1894,7 +1901,7 @@ __global__ __launch_bounds__(512) void fold_output_kernel(const FoldOutArgs a)
         }
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb) {
-            uint4 wb = wf[sl][nb];
+            uint4 wb = wf[sl & 1][nb];
             if constexpr (!DENSE) {                                  // fp16 -> bf16: at most 8 significant bits, exact
                 const uint32_t w4[4] = {wb.x, wb.y, wb.z, wb.w};
                 uint32_t d4[4];
@@ -1911,6 +1918,7 @@ __global__ __launch_bounds__(512) void fold_output_kernel(const FoldOutArgs a)
                                                                   __builtin_bit_cast(bf16x8, make_uint4(yp[p][0], yp[p][1], yp[p][2], yp[p][3])),
                                                                   acc[nb], 0, 0, 0);
         }
+        if (sl + 2 < FO_MAX_SLABS) load_weights(sl + 2, wf[sl & 1]);
     }
     // the waves' sums, two column blocks at a time: [wave][block][register quad][lane] x 4
     const float f = DENSE ? 1.0f : ldexpf(1.0f, -a.w.shift[sh]);
@@ -2086,7 +2094,7 @@ static void fold_order(FoldShape& s)
         place[first[best] + n_of[best]++] = by_len[i];
         load[best] += s.len.v[s.b0 + by_len[i]];
     }
-    for (int i = 0; i < s.nb; ++i) s.order.v[i] = place[i];
+    for (int i = 0; i < s.nb; ++i) s.order[i] = (uint8_t)place[i];
 }
 
 template <int BITS, int G, int RT>
