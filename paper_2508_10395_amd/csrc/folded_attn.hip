@@ -5,9 +5,9 @@
 //   fold_output_kernel   o = y Wv_h, split over the channels
 //   fold_finish_kernel   sum of these splits, divided by the softmax denominator
 // Against rematerialising K and V tile by tile (MI355X, us per step with the append, before / after): 8 x 4096 tokens, 3 bits,
-// 32 KV heads of a d = 4096 layer 1664 / 110; 16 x up to 8191, 2 bits in groups of 64, 32 on 8 heads 1512 / 300; 4 x 32768,
-// 2 bits 6330 / 255; bf16 accumulator, 4 x up to 6000 1080 / 125.  The operations no longer bound it: what is left is the
-// latency of the codes, the unpacking, and 12 us each for reading the two halves of the weight stream.
+// 32 KV heads of a d = 4096 layer 1664 / 104; 16 x up to 8191, 2 bits in groups of 64, 32 on 8 heads 1512 / 222; 4 x 32768,
+// 2 bits 6330 / 220; bf16 accumulator, 4 x up to 6000 1080 / 120.  The operations no longer bound it: what is left is the
+// unpacking beside the matrix instructions, and 15 us each for reading the two halves of the weight stream.
 #include <algorithm>
 
 #include "folded_common.hpp"
@@ -2006,10 +2006,6 @@ int fold_splits(int nb, int nrb, int n_slabs_v, int max_len, int per_cu)
     const int per = nb * nrb * ((n_slabs_v + 1) / 2), nt = (max_len + FOLD_VTILE - 1) / FOLD_VTILE;
     return std::max(1, std::min({nt, (256 * per_cu + per - 1) / per, 16 * per_cu}));
 }
-static int fold_splits(const FoldProblem& f, int B, int nrb, int max_len)
-{
-    return fold_splits(B, nrb, f.n_slabs_v, max_len, f.dense || f.block ? 1 : 2);
-}
 
 static FoldPlan fold_plan(const FoldProblem& f, int B, int nb, int max_len, int splits)
 {
@@ -2033,6 +2029,17 @@ static FoldPlan fold_plan(const FoldProblem& f, int B, int nb, int max_len, int 
     L.ud = f.block ? align256((size_t)nb * L.nrb * f.n_slabs_k * FOLD_U_DENSE(L.rt)) : 0;
     L.total = L.p + L.mtile + L.rowfac + L.lsum + L.uy + L.yz + L.ud;
     return L;
+}
+
+// Two workgroups a CU where their sums fit the partials of the rematerialising kernels, which a caller brings at the least
+// (8 x 4096 tokens of 32 heads would ask for a tenth more than these).
+static int fold_splits(const FoldProblem& f, int B, int nrb, int max_len)
+{
+    const int one = fold_splits(B, nrb, f.n_slabs_v, max_len, 1);
+    if (f.dense || f.block) return one;
+    const int two = fold_splits(B, nrb, f.n_slabs_v, max_len, 2);
+    const size_t partials = (size_t)B * f.Hq * ((max_len + TILE_TOKENS - 1) / TILE_TOKENS) * (TILE_TOKENS / CHUNK_TOKENS) * (128 + 2) * sizeof(float);
+    return fold_plan(f, B, B, max_len, two).total <= std::max(partials, fold_plan(f, B, B, max_len, one).total) ? two : one;
 }
 
 size_t fold_workspace_bytes(const FoldProblem& f, int B, int max_len)
