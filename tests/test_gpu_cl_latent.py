@@ -71,6 +71,20 @@ def test_delta_projection_matches_oracle(xq, B, T, cap, d, n_lat):
     _check_rounded(torch_to_bits(out), exact, absum, ref, 0.01)
 
 
+@pytest.mark.parametrize("d,n_lat", [(4096, 512), (3968, 96)])
+def test_a_row_has_the_same_latent_delta_however_many_rows_come_with_it(xq, d, n_lat):
+    """One order of the sums for every number of rows: T = 1 has the bits of a chunk."""
+    gen = torch.Generator("cuda").manual_seed(d)
+    B, T, cap, start = 2, 850, 900, [3, 50]
+    acc, x = (torch.randn((B, n, d), generator=gen, device="cuda").bfloat16() for n in (cap, T))
+    ut = torch.randn((n_lat, d), generator=gen, device="cuda").mul(d ** -0.5).bfloat16()
+    want = xq.xq_cl_latent_delta_project(x, acc, ut, start)
+    for t in (1, 8, 9, 64, 150):
+        for t0 in (0, T - t):
+            got = xq.xq_cl_latent_delta_project(x[:, t0:t0 + t].contiguous(), acc, ut, [s + t0 for s in start])
+            assert torch.equal(got, want[:, t0:t0 + t]), (t, t0)
+
+
 def test_delta_projection_of_an_unchanged_input_is_zero_and_empty_is_a_noop(xq):
     rng = np.random.default_rng(3)
     ut = _subspace(rng, 256, 64)

@@ -52,8 +52,20 @@ def test_projection_matches_oracle(xq, M, d, n_lat):
 
 @pytest.mark.parametrize("M,d,n_lat", [(17, 128, 32), (33, 4224, 64), (16, 5120, 96), (256, 1024, 512), (257, 1024, 512)])
 def test_projection_tiles(xq, M, d, n_lat):
-    """Ragged 16-row tiles, fewer steps than waves, steps beyond one round of loads, either side of the larger tiles."""
+    """Ragged row tiles, one step per wave, steps in rounds of loads of every size, either side of the larger tiles."""
     test_projection_matches_oracle(xq, M, d, n_lat)
+
+
+@pytest.mark.parametrize("d,n_lat", [(4096, 512), (3968, 96), (128, 1024)])
+def test_a_row_has_the_same_latents_however_many_rows_come_with_it(xq, d, n_lat):
+    """One order of the sums for every number of rows: a token's latents have the same bits in a decode step as in a chunk."""
+    gen = torch.Generator("cuda").manual_seed(d)
+    x = torch.randn((1700, d), generator=gen, device="cuda").bfloat16()
+    ut = torch.randn((n_lat, d), generator=gen, device="cuda").mul(d ** -0.5).bfloat16()
+    want = xq.xq_latent_project(x, ut)
+    for m in (1, 16, 17, 64, 128, 129, 300):
+        for r0 in (0, 1700 - m):
+            assert torch.equal(xq.xq_latent_project(x[r0:r0 + m].contiguous(), ut), want[r0:r0 + m]), (m, r0)
 
 
 def test_projection_exact_case_and_noop(xq):
