@@ -1298,7 +1298,7 @@ __global__ __launch_bounds__(FOLD_VALUE_THREADS, 2) void fold_values_kernel(cons
     auto write_stage = [&](int buf) XQ_INLINE_LAMBDA {
 #pragma unroll
         for (int hf = 0; hf < VT / FOLD_TILE; ++hf) {
-            const float f = fm[hf] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(fm[hf] - M + P_EXP);
+            const float f = fm[hf] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(fm[hf] - M) * (float)(1 << P_EXP);
 #pragma unroll
             for (int k = 0; k < PH; ++k) {
                 const int e = hf * PH + k;

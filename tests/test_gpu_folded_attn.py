@@ -225,6 +225,37 @@ def test_rows_of_zeros(xq, bits, G, rows, nats):
 
 
 @pytest.mark.parametrize("bits,G", CODED)
+@pytest.mark.parametrize("Hq,Hkv", [(16, 16), (32, 8)])
+def test_weights_of_tiles_whose_maxima_nearly_agree(xq, bits, G, Hq, Hkv):
+    """Two tokens in different tiles, one 1.5 to 2 times 2^-22 (log2) above the other, hold all the weight and opposite values: the
+    output is half the difference of their weights, 4 to 6 times 2^-24.  The weights and their two sums are rounded to 2^-24
+    or 2^-25 (and exp2 by one such step): within 0.6 of it.  With the tiles' factor formed from steps of 2^-20 it is 0."""
+    d, L = 4096, 256
+    x = torch.zeros((1, L, d // G, G))
+    x[0, :, :, 3], x[0, :, :, 4] = -1.0, 2.0 ** bits - 2.0                # every group: scale 1, zero-point -1
+    x[0, :, 0, 0] = -1.0                                                  # key channels 0 and 2, value channel 1
+    x[0, [3, 140], 0, 0] = 0.0
+    x[0, 140, 0, 2] = 1.0
+    x[0, 140, 0, 1], x[0, 3, 0, 1] = 1.0, -1.0
+    wk, wv = torch.zeros((d, Hkv, 128)), torch.zeros((d, Hkv, 128))
+    wk[0, :, 0] = wk[2, :, 1] = 1.0
+    wv[1] = 1.0
+    step = (1.5 + torch.arange(Hq) % 16 / 32) * 2.0 ** -22
+    q = torch.zeros((1, Hq, 128))
+    q[0, :, 0], q[0, :, 1] = 64.0, step
+    gpu = lambda t: t.to("cuda", torch.bfloat16).contiguous()
+    attn = xq.XQAttn(Hq, Hkv, 128, float(np.log(2.0)))
+    cache = xq.alloc_cache(1, L, d, G, bits)
+    xq.xq_quantize_append(cache, gpu(x.reshape(1, L, d)), [0])
+    wprep = xq.xq_prepare_weights(attn, d, G, bits, gpu(wk.reshape(d, -1)), gpu(wv.reshape(d, -1)))
+    call = lambda: xq.xq_remat_attn_decode(attn, gpu(q), wprep, [L], xcache=cache)
+    out = call().cpu().double()[0]
+    assert _folds(call)
+    ref = torch.tanh(step.double() * np.log(2.0) / 2)[:, None]
+    assert float((out / ref - 1).abs().max()) <= 0.6, (out[:, 0] / ref[:, 0]).tolist()
+
+
+@pytest.mark.parametrize("bits,G", CODED)
 def test_scales_of_either_sign(xq, bits, G):
     """x^ = code scale + zero holds for a negative scale too."""
     w = xi.C2.scaled(B=1, L=600, d=2304, Hq=16, Hkv=16, n_outlier=0)
