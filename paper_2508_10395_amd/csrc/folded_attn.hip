@@ -1257,13 +1257,14 @@ __global__ __launch_bounds__(FOLD_VALUE_THREADS, 2) void fold_values_kernel(cons
     }
 
     // ---- staging: thread -> softmax weights (always of the same row) and (token, group) pairs
-    constexpr int NP = 2 * RT, PH = 512 * RT / NT;                  // 16-byte pieces per thread and VT (128) tokens
+    static_assert(VT == FOLD_TILE, "a step has one stored maximum per row");
+    constexpr int NP = 512 * RT / NT;                               // 16-byte pieces per thread and step
     const int prow = RT == 2 ? ((wave >> 1) & 1) * 16 + c16 : c16;
     const float M = mrow[prow];
     const float* psrc = a.p + (((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) * 4 * FOLD_P_TILE32<RT>;
     const float* msrc = a.mtile + (((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0) * 16 * RT + prow;
     float4 pv[NP];
-    float fm[VT / FOLD_TILE];
+    float fm;
     constexpr int NE = VT * NG / NT;                       // (token, group) pairs per thread: 1 or 2
     const int eg = tid % NG, et = tid / NG;                         // group and first token of this thread's pairs
     uint32_t sv[NE], zv[NE];
@@ -1271,15 +1272,9 @@ __global__ __launch_bounds__(FOLD_VALUE_THREADS, 2) void fold_values_kernel(cons
     const uint16_t* zgrp = zbase + (min(g0 + eg, x.ng - 1) >> x.meta_shift);
     const float my_ginv = ginv[eg];
     auto load_stage = [&](int t) XQ_INLINE_LAMBDA {
+        fm = msrc[(long long)t * 16 * RT];
 #pragma unroll
-        for (int hf = 0; hf < VT / FOLD_TILE; ++hf) {
-            fm[hf] = msrc[(long long)(VT / FOLD_TILE * t + hf) * 16 * RT];
-#pragma unroll
-            for (int k = 0; k < PH; ++k) {
-                const int e = hf * PH + k;
-                pv[e] = *reinterpret_cast<const float4*>(psrc + (long long)t * (VT / 32) * FOLD_P_TILE32<RT> + (e * NT + tid) * 4);
-            }
-        }
+        for (int e = 0; e < NP; ++e) pv[e] = *reinterpret_cast<const float4*>(psrc + (long long)t * (VT / 32) * FOLD_P_TILE32<RT> + (e * NT + tid) * 4);
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
             const uint32_t at = (uint32_t)min(t * VT + et + e * (NT / NG), o.len - 1) * (uint32_t)x.ng_row;
@@ -1296,28 +1291,24 @@ __global__ __launch_bounds__(FOLD_VALUE_THREADS, 2) void fold_values_kernel(cons
 #pragma unroll
     for (int g = 0; g < NG; ++g) az[g] = 0.0f;
     auto write_stage = [&](int buf) XQ_INLINE_LAMBDA {
+        const float f = fm == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(fm - M) * (float)(1 << P_EXP);
 #pragma unroll
-        for (int hf = 0; hf < VT / FOLD_TILE; ++hf) {
-            const float f = fm[hf] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(fm[hf] - M) * (float)(1 << P_EXP);
-#pragma unroll
-            for (int k = 0; k < PH; ++k) {
-                const int e = hf * PH + k;
-                float4& v = pv[e];
-                v.x *= f; v.y *= f; v.z *= f; v.w *= f;
-                if (o.cblk == 0) lacc += (v.x + v.y) + (v.z + v.w);
-                if constexpr (SCALED) {
-                    int t32, rt, part;
-                    piece(e, t32, rt, part);
-                    const xq_f32x2 a2 = {v.x, v.y}, b2 = {v.z, v.w};
-                    const xq_f16x2 ah = __builtin_convertvector(a2, xq_f16x2), bh = __builtin_convertvector(b2, xq_f16x2);
-                    const xq_f32x2 ar = {v.x - (float)ah.x, v.y - (float)ah.y}, br = {v.z - (float)bh.x, v.w - (float)bh.y};
-                    const xq_f16x2 al = __builtin_convertvector(ar, xq_f16x2), bl = __builtin_convertvector(br, xq_f16x2);
-                    uint8_t* dst = lds + L::P_OFF + buf * L::P_BYTES + (t32 * RT + rt) * 2048 + lane * 16 + part * 8;
-                    *reinterpret_cast<uint2*>(dst) = make_uint2(__builtin_bit_cast(uint32_t, ah), __builtin_bit_cast(uint32_t, bh));
-                    *reinterpret_cast<uint2*>(dst + 1024) = make_uint2(__builtin_bit_cast(uint32_t, al), __builtin_bit_cast(uint32_t, bl));
-                } else {
-                    *reinterpret_cast<float4*>(lds + L::P_OFF + buf * L::P_BYTES + (e * NT + tid) * 16) = v;
-                }
+        for (int e = 0; e < NP; ++e) {
+            float4& v = pv[e];
+            v.x *= f; v.y *= f; v.z *= f; v.w *= f;
+            if (o.cblk == 0) lacc += (v.x + v.y) + (v.z + v.w);
+            if constexpr (SCALED) {
+                int t32, rt, part;
+                piece(e, t32, rt, part);
+                const xq_f32x2 a2 = {v.x, v.y}, b2 = {v.z, v.w};
+                const xq_f16x2 ah = __builtin_convertvector(a2, xq_f16x2), bh = __builtin_convertvector(b2, xq_f16x2);
+                const xq_f32x2 ar = {v.x - (float)ah.x, v.y - (float)ah.y}, br = {v.z - (float)bh.x, v.w - (float)bh.y};
+                const xq_f16x2 al = __builtin_convertvector(ar, xq_f16x2), bl = __builtin_convertvector(br, xq_f16x2);
+                uint8_t* dst = lds + L::P_OFF + buf * L::P_BYTES + (t32 * RT + rt) * 2048 + lane * 16 + part * 8;
+                *reinterpret_cast<uint2*>(dst) = make_uint2(__builtin_bit_cast(uint32_t, ah), __builtin_bit_cast(uint32_t, bh));
+                *reinterpret_cast<uint2*>(dst + 1024) = make_uint2(__builtin_bit_cast(uint32_t, al), __builtin_bit_cast(uint32_t, bl));
+            } else {
+                *reinterpret_cast<float4*>(lds + L::P_OFF + buf * L::P_BYTES + (e * NT + tid) * 16) = v;
             }
         }
 #pragma unroll
@@ -1385,19 +1376,10 @@ __global__ __launch_bounds__(FOLD_VALUE_THREADS, 2) void fold_values_kernel(cons
             else if constexpr (BITS == 3) { m0[j] = perm_bytes(r[2 * j + 1], r[2 * j], sel0); m1[j] = perm_bytes(r[2 * j + 1], r[2 * j], sel1); }
             else { m0[j] = perm_bytes(r[2 * j + 1], r[2 * j], 0x05040100u); m1[j] = perm_bytes(r[2 * j + 1], r[2 * j], 0x07060302u); }
             if constexpr (PPT == 2) {
-                // lanes n and n + 8 exchange half octets: codes 0-3 then belong to the first group, 4-7 to the second
-                if constexpr (BITS == 2) {
-                    const uint32_t ot = dpp_u32<0x128 /* row_ror:8 */>(m0[j]);
-                    m0[j] = perm_bytes(ot, m0[j], lower ? 0x06020400u : 0x03070105u);
-                } else {
-                    uint32_t lo, hi;
-                    if constexpr (BITS == 3) { lo = m0[j] & 0x0FFF0FFFu; hi = (m1[j] >> 4) & 0x0FFF0FFFu; }
-                    else { lo = m0[j]; hi = m1[j]; }
-                    const uint32_t keep = lower ? lo : hi, got = dpp_u32<0x128>(lower ? hi : lo);
-                    const uint32_t n0 = lower ? keep : got, n1 = lower ? got : keep;
-                    if constexpr (BITS == 3) { m0[j] = n0 | (n1 << 12 & 0xF000F000u); m1[j] = (n0 >> 8 & 0x000F000Fu) | (n1 << 4); }
-                    else { m0[j] = n0; m1[j] = n1; }
-                }
+                // (4 bits) lanes n and n + 8 exchange half octets: codes 0-3 then belong to the first group, 4-7 to the second
+                const uint32_t keep = lower ? m0[j] : m1[j], got = dpp_u32<0x128 /* row_ror:8 */>(lower ? m1[j] : m0[j]);
+                m0[j] = lower ? keep : got;
+                m1[j] = lower ? got : keep;
             }
         }
     };
