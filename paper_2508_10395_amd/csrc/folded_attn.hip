@@ -354,9 +354,10 @@ struct FoldScoreArgs {
     int n_window;
 };
 
-// the tile of a score workgroup and the slabs of a wave: every SW-th one, SW the waves of the workgroup (4 or 8)
-struct FoldScorePlace { int b, rb, tile, tile0, len, SW, slab0, slab1, nw; };           // nw = waves that hold any slab
-__device__ __forceinline__ bool fold_score_place(const FoldShape& s, bool window, int waves, int n_slabs, int wg, int wave, FoldScorePlace& o)
+// the tile of a score workgroup of SW waves (4 or 8) and the slabs of a wave: every SW-th one of coded rows (step = SW), a run of
+// adjacent ones of bf16 rows (step = 1)
+struct FoldScorePlace { int b, rb, tile, tile0, len, SW, slab0, slab1, step, nw; };     // nw = waves that hold any slab
+__device__ __forceinline__ bool fold_score_place(const FoldShape& s, bool window, bool runs, int waves, int n_slabs, int wg, int wave, FoldScorePlace& o)
 {
     const int tiles = window ? 1 : s.tiles, n = s.nb * s.nrb * tiles;
     const int item = xcd_contiguous(n, wg);
@@ -368,9 +369,11 @@ __device__ __forceinline__ bool fold_score_place(const FoldShape& s, bool window
     o.len = span.len;
     o.tile0 = span.tile0;
     o.SW = waves;
-    o.slab0 = wave;
-    o.slab1 = max(wave, n_slabs);
-    o.nw = min(waves, n_slabs);
+    const int per = runs ? (n_slabs + waves - 1) / waves : 1;
+    o.slab0 = wave * per;
+    o.slab1 = max(o.slab0, runs ? min(o.slab0 + per, n_slabs) : n_slabs);
+    o.step = runs ? 1 : waves;
+    o.nw = min(waves, (n_slabs + per - 1) / per);
     return o.tile * FOLD_TILE < o.len;
 }
 
@@ -472,7 +475,7 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
     const FoldSource& x = a.x;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     FoldScorePlace o;
-    if (!fold_score_place(s, false, a.waves, x.n_slabs, blockIdx.x, wave, o)) return;
+    if (!fold_score_place(s, false, false, a.waves, x.n_slabs, blockIdx.x, wave, o)) return;
     const int b = o.b, rb = o.rb, len = o.len, tok0 = o.tile * FOLD_TILE;
     const int c16 = lane & 15, q = lane >> 4;
     const uint8_t* cbase = x.codes + (long long)(s.b0 + b) * x.cap * x.row_bytes;
@@ -635,8 +638,8 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) P[1][rt] = zero4;
         rec[3][1] = 0u;                                              // (unit -1 adds nothing)
-        for (int slab = slab0; slab < slab1; slab += o.SW) {
-            const int snext = slab + o.SW < slab1 ? slab + o.SW : slab;    // (the last iteration prepares itself again)
+        for (int slab = slab0; slab < slab1; slab += o.step) {
+            const int snext = slab + o.step < slab1 ? slab + o.step : slab;    // (the last iteration prepares itself again)
             __builtin_amdgcn_sched_barrier(0);
             static_for<0, 16>([&](auto T) XQ_INLINE_LAMBDA {
                 constexpr int t = decltype(T)::value, h = t >> 3, i = t & 7;
@@ -690,6 +693,10 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
 // the same over bf16 rows (the cross-layer accumulator, a residual window): no codes and no groups, u in three bf16 parts.
 // The rows of a half slab (128 bytes each) go through the wave's LDS image as the codes do, 16 token rows at a time; their
 // 16-byte pieces are swizzled by the row, so that neither the row-wise write nor the fragment read meets bank conflicts.
+// A wave has a run of adjacent slabs: its pieces are whole cache lines, so there is nothing to share with the other waves, and
+// side by side these read one 2 KiB stretch of 128 rows at a time.  Whole steps, slabs dealt out as above / runs: 8 x 8192 rows of
+// d = 4096 259 / 238 us, 16 x 8192 of d = 2048 and 16 heads 242 / 216, 8 x 4096 of d = 4096 148 / 142; 6 x 8192, where the XCDs
+// are at different places of their sequences, 225 either way.
 template <int RT>
 __device__ __forceinline__ void fold_scores_dense(const FoldScoreArgs& a, const FoldSource& x, const uint8_t* u_all, bool window, int waves, uint8_t* lds)
 {
@@ -698,7 +705,7 @@ __device__ __forceinline__ void fold_scores_dense(const FoldScoreArgs& a, const 
     const FoldShape& s = a.s;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     FoldScorePlace o;
-    if (!fold_score_place(s, window, waves, x.n_slabs, blockIdx.x, wave, o)) return;
+    if (!fold_score_place(s, window, true, waves, x.n_slabs, blockIdx.x, wave, o)) return;
     const int b = o.b, rb = o.rb, len = o.len, tok0 = o.tile * FOLD_TILE;
     const int c16 = lane & 15, q = lane >> 4;
     const uint8_t* xbase = reinterpret_cast<const uint8_t*>(x.rows) + (long long)(s.b0 + b) * x.cap * x.row_bytes;
@@ -737,8 +744,8 @@ __device__ __forceinline__ void fold_scores_dense(const FoldScoreArgs& a, const 
         };
         load_u(2 * o.slab0, std::integral_constant<int, 0>{});
         static_for<0, 8>([&](auto I) XQ_INLINE_LAMBDA { load_x(2 * o.slab0, I); });
-        for (int slab = o.slab0; slab < o.slab1; slab += o.SW) {
-            const int snext = slab + o.SW < o.slab1 ? slab + o.SW : slab;
+        for (int slab = o.slab0; slab < o.slab1; slab += o.step) {
+            const int snext = slab + o.step < o.slab1 ? slab + o.step : slab;
             static_for<0, 2>([&](auto HF) XQ_INLINE_LAMBDA {
                 constexpr int h = decltype(HF)::value;
                 const int hn = h == 0 ? 2 * slab + 1 : 2 * snext;
@@ -2194,7 +2201,12 @@ hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSo
             // ways then run beside the other's products, and fewer ways meet.  Whole steps, eight waves / four: 1024 tiles of 2
             // bits 233 / 215 us (group 128), 273 / 263 (group 64), latent 136 / 127, 16 heads of 4 bits 124 / 111; 512 tiles of
             // 3 bits 143 / 138; 384 tiles 166 / 161; 256 tiles 94.4 / 94.1.
-            const int waves = B * sh.nrb * sh.tiles >= 3 * 128 && !f.block ? 4 : 8;
+            // Over bf16 rows of 17 query heads and more four waves only where their rounds of 512 workgroups are no emptier than those
+            // of 256 of eight waves: eight / four, d = 4096: 512 tiles 245 / 238, 1024 tiles 443 / 426, but 768 tiles 372 / 390; with 16
+            // heads 768 tiles of d = 2048 202 / 202, 520 tiles 148 / 140, and with 2 slabs, on which eight waves idle, 640 tiles 63 / 59.
+            const int n = B * sh.nrb * sh.tiles;
+            const bool four = !f.block && n >= 3 * 128 && (!f.dense || L.rt == 1 || f.n_slabs_k <= 4 || 2 * ((n + 511) / 512) <= (n + 255) / 256);
+            const int waves = four ? 4 : 8;
             FoldScoreArgs a{kx, sh, u, rowfac, p, mtile, L.u_slab, waves, FoldSource{}, u_dense, 0};
             if (any_window) { a.window = *window; a.n_window = xcd_grid(sh.nb * sh.nrb); }
             const int grid = a.n_window + xcd_grid(sh.nb * sh.nrb * sh.tiles);

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(512) void fold_scores_pc_kernel(const FoldScoreArgs
         return;
     }
     FoldScorePlace o;
-    if (!fold_score_place(s, false, 8, x.n_slabs, (int)blockIdx.x - a.n_window, wave, o)) return;
+    if (!fold_score_place(s, false, false, 8, x.n_slabs, (int)blockIdx.x - a.n_window, wave, o)) return;
     const int b = o.b, rb = o.rb, len = o.len, tok0 = o.tile * FOLD_TILE;
     const int c16 = lane & 15, q = lane >> 4, d = x.n_slabs * 128;
     const int nblk = len / s.block, blk0 = tok0 / s.block;
@@ -205,8 +205,8 @@ __global__ __launch_bounds__(512) void fold_scores_pc_kernel(const FoldScoreArgs
         read_unit(std::integral_constant<int, 0>{});
         read_unit(std::integral_constant<int, 1>{});
         static_for<0, 8>([&](auto K) XQ_INLINE_LAMBDA { unpack(std::integral_constant<int, 0>{}, K); });
-        for (int slab = slab0; slab < slab1; slab += o.SW) {
-            const int snext = slab + o.SW < slab1 ? slab + o.SW : slab;
+        for (int slab = slab0; slab < slab1; slab += o.step) {
+            const int snext = slab + o.step < slab1 ? slab + o.step : slab;
             __builtin_amdgcn_sched_barrier(0);
             static_for<0, 16>([&](auto T) XQ_INLINE_LAMBDA {
                 constexpr int t = decltype(T)::value, h = t >> 3, i = t & 7;

@@ -123,10 +123,11 @@ def test_formats_rows_and_tile_edges(xq, bits, G, Hq, Hkv, d, lens):
     _run(xq, w, bits, G, lens)
 
 
-@pytest.mark.parametrize("bits,G", [(2, 64), (3, 128), (16, 128)])
-def test_token_ways_of_a_score_workgroup(xq, bits, G):
-    """Enough tiles for score workgroups of four waves, two of them without a slab on this narrow layer, and tiles past the length."""
-    w = xi.C2.scaled(B=16, L=4000, d=256, Hq=64, Hkv=8, n_outlier=2)
+@pytest.mark.parametrize("bits,G,d", [(2, 64, 256), (3, 128, 256), (16, 128, 256), (3, 128, 640), (16, 128, 640)])
+def test_token_ways_of_a_score_workgroup(xq, bits, G, d):
+    """Enough tiles for score workgroups of four waves, two of them without a slab on the narrow layer (one of them, or a wave with
+    fewer than the others, on the wider one), and tiles past the length."""
+    w = xi.C2.scaled(B=16, L=4000, d=d, Hq=64, Hkv=8, n_outlier=2)
     lens = [4000, 3969, 129, 128, 1, 2049] + [100] * 10
     _run(xq, w, bits, G, lens, pairs=[(0, 0), (0, 63), (1, 17), (2, 5), (3, 40), (4, 33), (5, 62), (15, 8)])
 
