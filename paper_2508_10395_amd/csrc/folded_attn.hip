@@ -1736,8 +1736,10 @@ __global__ __launch_bounds__(512) void fold_values_dense_kernel(const FoldValueA
 // =====================================================================================================================
 // Output projection.  A workgroup takes one KV head, 32 query columns and a few slabs: it sums y over the token splits,
 // adds the offsets of the groups, and multiplies by the slabs' share of Wv_h, the prepared stream's fragments as they
-// are (fp16 ones are cut to bf16, exactly) against y in three bf16 parts.  Bound by reading the value half of the
-// stream once.
+// are (fp16 ones are cut to bf16, exactly) against y in three bf16 parts.  Bound by the latency of three rounds of loads (the
+// splits in use, y, the third slab's weights) and by reading the value half of the stream once.  No load of the sums stands
+// under a condition, which would make it a wait of its own: 32 splits of 3 x 13012 tokens, d = 1024, 18.3 / 12.0 us so (and
+// fold_finish_kernel 9.0 / 5.2), 4 splits of 4 x 4096 tokens, d = 4096, 16.1 / 13.8.
 // =====================================================================================================================
 struct FoldOutArgs {
     FoldWeights w;
@@ -1771,6 +1773,7 @@ __global__ __launch_bounds__(512, 4) void fold_output_kernel(const FoldOutArgs a
     // same place in every slab)
     const int sh = a.w.pair ? h >> 1 : h, nb0 = a.w.pair ? 4 * (h & 1) : 4;
     const uint8_t* wsrc = a.w.stream + (long long)sh * a.w.head_bytes + lane * 16;
+    const int shift = DENSE ? 0 : a.w.shift[sh];
     uint4 wf[2][4];                                                  // (two slabs ahead: with all four two workgroups do not fit a CU)
     auto load_weights = [&](int sl, uint4 (&f)[4]) XQ_INLINE_LAMBDA {
 #pragma unroll
@@ -1788,7 +1791,9 @@ __global__ __launch_bounds__(512, 4) void fold_output_kernel(const FoldOutArgs a
     };
     __shared__ float zl[32 * FO_MAX_GROUPS];
     __shared__ int crow[32], cused[32];                              // per column: row of y, splits (and 256: the window's)
+    __shared__ __attribute__((aligned(16))) float unit[32];          // coded streams: what a code's weight row is divided by
     if (tid < 32) {
+        if constexpr (!DENSE) unit[tid] = __uint_as_float((uint32_t)(127 - a.tab.wexp_of_code[tid]) << 23);
         int b = 0, used = 0, row = 0;
         bool window = false;
         if (cb * 32 + tid < ncol) {
@@ -1805,55 +1810,72 @@ __global__ __launch_bounds__(512, 4) void fold_output_kernel(const FoldOutArgs a
     if (offsets && tid < 32 * cg) {
         const int col = tid / cg, g = slab0 * 128 / a.group + tid - col * cg, used = cused[col] & 255, n = used + (cused[col] >> 8);
         float z[4] = {};                                             // (short chains of roundings, here and below)
-        for (int k = 0; k < n; k += 4)
+        for (int k = 0; k < n; k += 8) {
+            float t[8];
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (k + j < n) z[j] += a.yz[((k + j < used ? k + j : s.splits - 1) * split_stride + crow[col]) * a.ng + g];
+            for (int j = 0; j < 8; ++j) t[j] = a.yz[((k + j < used ? k + j : n > used ? s.splits - 1 : used - 1) * split_stride + crow[col]) * a.ng + g];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) z[j & 3] += k + j < n ? t[j] : 0.0f;
+        }
         zl[col * FO_MAX_GROUPS + tid - col * cg] = (z[0] + z[1]) + (z[2] + z[3]);
     }
     __syncthreads();
-    // 16-byte pieces [column][channel / 4], two of them and four splits at a time: one latency for eight loads.  (Columns that
-    // hold no query stay as they are: nothing of theirs is stored.)
+    // 16-byte pieces [column][channel / 4], eight loads of a thread at a time: two pieces and four splits, or one piece and eight
+    // splits where every thread has one at most.  (Columns that hold no query stay as they are: nothing of theirs is stored.)
     const int pieces = min(32, ncol - cb * 32) * ns * 32;
-    for (int p0 = tid; p0 < pieces; p0 += 2 * 512) {
-        const float* src[2];
-        int col[2], c4[2], n[2], last[2];
-        float4 v[4][2] = {};
+    auto sum_pieces = [&](auto PIECES) XQ_INLINE_LAMBDA {
+        constexpr int P = decltype(PIECES)::value, K = 8 / P;
+        for (int p0 = tid; p0 < pieces; p0 += P * 512) {
+            const float* src[P];
+            int col[P], c4[P], n[P], last[P], most = 0;
+            float4 v[4][P] = {};
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int idx = min(p0 + i * 512, pieces - 1);
-            col[i] = idx / (ns * 32);
-            c4[i] = idx - col[i] * (ns * 32);
-            const int used = cused[col[i]] & 255;
-            n[i] = used + (cused[col[i]] >> 8);
-            last[i] = n[i] > used ? s.splits - 1 : used - 1;         // where the last of them lies
-            src[i] = a.y + (long long)crow[col[i]] * d + slab0 * 128 + 4 * c4[i];
-        }
-        for (int k = 0; k < max(n[0], n[1]); k += 4) {
-            float4 t[4][2];
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    t[j][i] = *reinterpret_cast<const float4*>(src[i] + (k + j < n[i] - 1 ? k + j : last[i]) * split_stride * d);
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    if (k + j < n[i]) { v[j][i].x += t[j][i].x; v[j][i].y += t[j][i].y; v[j][i].z += t[j][i].z; v[j][i].w += t[j][i].w; }
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            float4 w = make_float4((v[0][i].x + v[1][i].x) + (v[2][i].x + v[3][i].x), (v[0][i].y + v[1][i].y) + (v[2][i].y + v[3][i].y),
-                                   (v[0][i].z + v[1][i].z) + (v[2][i].z + v[3][i].z), (v[0][i].w + v[1][i].w) + (v[2][i].w + v[3][i].w));
-            if (offsets) {
-                // (8-bit caches: a code's zero-point multiplies its weight row once, that of the low nibble)
-                const float z = zl[col[i] * FO_MAX_GROUPS + 4 * c4[i] / a.group], zo = a.w.nibbles ? 0.0f : z;
-                w.x += z; w.y += zo; w.z += z; w.w += zo;
+            for (int i = 0; i < P; ++i) {
+                const int idx = min(p0 + i * 512, pieces - 1);
+                col[i] = idx / (ns * 32);
+                c4[i] = idx - col[i] * (ns * 32);
+                const int used = cused[col[i]] & 255;
+                n[i] = used + (cused[col[i]] >> 8);
+                most = max(most, n[i]);
+                last[i] = n[i] > used ? s.splits - 1 : used - 1;     // where the last of them lies
+                src[i] = a.y + (long long)crow[col[i]] * d + slab0 * 128 + 4 * c4[i];
             }
-            *reinterpret_cast<float4*>(yl + col[i] * FO_STRIDE + 4 * c4[i]) = w;         // (behind the last piece it is written again)
+            for (int k = 0; k < most; k += K) {
+                float4 t[K][P];
+#pragma unroll
+                for (int j = 0; j < K; ++j)
+#pragma unroll
+                    for (int i = 0; i < P; ++i)
+                        t[j][i] = *reinterpret_cast<const float4*>(src[i] + (k + j < n[i] - 1 ? k + j : last[i]) * split_stride * d);
+#pragma unroll
+                for (int j = 0; j < K; ++j)
+#pragma unroll
+                    for (int i = 0; i < P; ++i)
+                    {
+                        const bool ok = k + j < n[i];
+                        float4& w = v[j & 3][i];
+                        w.x += ok ? t[j][i].x : 0.0f; w.y += ok ? t[j][i].y : 0.0f; w.z += ok ? t[j][i].z : 0.0f; w.w += ok ? t[j][i].w : 0.0f;
+                    }
+            }
+#pragma unroll
+            for (int i = 0; i < P; ++i) {
+                float4 w = make_float4((v[0][i].x + v[1][i].x) + (v[2][i].x + v[3][i].x), (v[0][i].y + v[1][i].y) + (v[2][i].y + v[3][i].y),
+                                       (v[0][i].z + v[1][i].z) + (v[2][i].z + v[3][i].z), (v[0][i].w + v[1][i].w) + (v[2][i].w + v[3][i].w));
+                if (offsets) {
+                    // (8-bit caches: a code's zero-point multiplies its weight row once, that of the low nibble)
+                    const float z = zl[col[i] * FO_MAX_GROUPS + 4 * c4[i] / a.group], zo = a.w.nibbles ? 0.0f : z;
+                    w.x += z; w.y += zo; w.z += z; w.w += zo;
+                }
+                if constexpr (!DENSE) {
+                    const float4 f = *reinterpret_cast<const float4*>(unit + (4 * c4[i] & 31));
+                    w.x *= f.x; w.y *= f.y; w.z *= f.z; w.w *= f.w;
+                }
+                *reinterpret_cast<float4*>(yl + col[i] * FO_STRIDE + 4 * c4[i]) = w;     // (behind the last piece it is written again)
+            }
         }
-    }
+    };
+    if (pieces > 512) sum_pieces(std::integral_constant<int, 2>{});
+    else sum_pieces(std::integral_constant<int, 1>{});
     __syncthreads();
     f32x16 acc[4];
 #pragma unroll
@@ -1869,16 +1891,9 @@ __global__ __launch_bounds__(512, 4) void fold_output_kernel(const FoldOutArgs a
             float v[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                int ch;
-                float f = 1.0f;
-                if constexpr (DENSE) {
-                    ch = ks * 16 + half * 8 + i;
-                } else {
-                    int p;
-                    ch = stream_channel(a.tab, a.w.group, ks, half, i, &p);
-                    f = __uint_as_float((uint32_t)(127 - a.tab.wexp_of_code[p]) << 23);
-                }
-                v[i] = yl[c32 * FO_STRIDE + sl * 128 + ch] * f;
+                int p;
+                const int ch = DENSE ? ks * 16 + half * 8 + i : stream_channel(a.tab, a.w.group, ks, half, i, &p);
+                v[i] = yl[c32 * FO_STRIDE + sl * 128 + ch];
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -1907,10 +1922,13 @@ __global__ __launch_bounds__(512, 4) void fold_output_kernel(const FoldOutArgs a
                                                                   __builtin_bit_cast(bf16x8, make_uint4(yp[p][0], yp[p][1], yp[p][2], yp[p][3])),
                                                                   acc[nb], 0, 0, 0);
         }
-        if (sl + 2 < FO_MAX_SLABS) load_weights(sl + 2, wf[sl & 1]);
+        if (sl + 2 < FO_MAX_SLABS) {
+            load_weights(sl + 2, wf[sl & 1]);
+            asm volatile("" ::: "memory");                           // (the compiler would move them behind the next slab's products)
+        }
     }
     // the waves' sums, two column blocks at a time: [wave][block][register quad][lane] x 4
-    const float f = DENSE ? 1.0f : ldexpf(1.0f, -a.w.shift[sh]);
+    const float f = DENSE ? 1.0f : ldexpf(1.0f, -shift);
     float4* red = reinterpret_cast<float4*>(lds);
     int b = 0, row = 0;
     const bool ok = cb * 32 + c32 < ncol;
@@ -1949,10 +1967,13 @@ __global__ __launch_bounds__(256) void fold_finish_kernel(const float* __restric
     bool window;
     fold_used_splits(s, b, used, window);
     float L4[4] = {};
-    for (int k = 0; k < used; k += 4)
+    for (int k = 0; k < used; k += 8) {                              // (eight loads at a time, the last split's again)
+        float t[8];
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (k + j < used) L4[j] += lsum[((long long)(k + j) * s.nb + b) * s.nrb * 16 * rt + row];
+        for (int j = 0; j < 8; ++j) t[j] = lsum[((long long)min(k + j, used - 1) * s.nb + b) * s.nrb * 16 * rt + row];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) L4[j & 3] += k + j < used ? t[j] : 0.0f;
+    }
     float L = (L4[0] + L4[1]) + (L4[2] + L4[3]);
     if (window) L += lsum[((long long)(s.splits - 1) * s.nb + b) * s.nrb * 16 * rt + row];
     float4 t = make_float4(0.0f, 0.0f, 0.0f, 0.0f);

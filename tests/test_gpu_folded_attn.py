@@ -140,6 +140,14 @@ def test_steps_of_a_value_workgroup(xq, bits, G):
     _run(xq, w, bits, G, lens, pairs=[(b, (5 * b + 3) % 32) for b in range(9)])
 
 
+@pytest.mark.parametrize("bits,G", [(2, 64), (3, 128), (8, 128), (16, 128)])
+@pytest.mark.parametrize("Hq,Hkv,lens", [(16, 16, [4608, 2300, 300, 1]), (16, 4, [4600] + [260 * b + 7 for b in range(10)])])
+def test_sums_over_many_token_splits(xq, bits, G, Hq, Hkv, lens):
+    """Columns of up to 18 token splits beside such of one, in output workgroups with a piece per thread and with several."""
+    w = xi.C2.scaled(B=len(lens), L=max(lens), d=640, Hq=Hq, Hkv=Hkv, n_outlier=6)
+    _run(xq, w, bits, G, lens, pairs=[(b, (3 * b + 1) % Hq) for b in range(len(lens))])
+
+
 @pytest.mark.parametrize("B", [15, 16, 17, 29])
 def test_sequences_dealt_over_the_chip(xq, B):
     """From 16 sequences on they are taken in another order than they come in; lengths of every kind, several the same."""
