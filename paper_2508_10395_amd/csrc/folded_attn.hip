@@ -74,13 +74,11 @@ struct FoldQueryArgs {
     uint8_t* u_dense;                    // per-channel caches: the same u for the window's bf16 rows, or null
 };
 
-// channel inside its slab of slot (half, i) of k-step ks of the slab, in the first prepared stream
-__device__ __forceinline__ int stream_channel(const UnpackTable& tab, int group, int ks, int half, int i, int* code)
+// channel inside its slab of slot (half, i) of k-step ks of the slab, in the first prepared stream; code: tab.code_of_slot[ks & 3][i]
+__device__ __forceinline__ int stream_channel(int group, int ks, int half, int code)
 {
     const int ksg_n = group >> 4, gi = ks / ksg_n, ksg = ks % ksg_n;
-    const int p = tab.code_of_slot[ksg & 3][i];
-    *code = p;
-    return gi * group + half * (group >> 1) + (ksg >> 2) * 32 + p;
+    return gi * group + half * (group >> 1) + (ksg >> 2) * 32 + code;
 }
 
 constexpr int FQ_STRIDE = 132;           // floats per query column in LDS: 16-byte pieces of different columns on different banks
@@ -90,6 +88,7 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
 {
     __shared__ __attribute__((aligned(16))) float ul[2][32 * FQ_STRIDE];
     __shared__ float nrm[2][32];
+    __shared__ __attribute__((aligned(4))) int8_t table[2][64];      // coded streams: code_of_slot, then wexp_of_code
     __shared__ int place[2][32];             // row block of the launch 16 RT + row inside it, per column (-1: none)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int half = lane >> 5, c32 = lane & 31;
@@ -111,6 +110,7 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
         place[wave][c32] = cb * 32 + c32 < ncol ? (b * s.nrb + rb) * rpb + (row - rb * rpb) : -1;
     }
 
+    const int sh = a.w.pair ? h >> 1 : h, nb0 = a.w.pair ? 4 * (h & 1) : 0, shift = DENSE ? 0 : a.w.shift[sh];
     // the 32 query rows as an operand: lane = column, k-slots in the order the accumulator rows below come in
     uint4 qa[4][2];
     float l1 = 0.0f;
@@ -128,8 +128,8 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
             }
     }
     // Every weight fragment of the wave's slab is asked for before anything is waited for (2 waves in flight on a SIMD at most,
-    // 32 loads each): with eight at a time a wave met the memory's latency four times, 15 us for 16 to 34 MB.
-    const int sh = a.w.pair ? h >> 1 : h, nb0 = a.w.pair ? 4 * (h & 1) : 0;
+    // 32 loads each), and no load comes behind them: 34 MB of 8 x 4096 tokens, d = 4096, 16.2 us with eight at a time, 15.8 with byte
+    // loads of the tables behind them, 13.6 now (weights already in the Infinity Cache: 12.0, 13.3, 12.3).
     const uint8_t* wsrc = a.w.stream + (long long)sh * a.w.head_bytes + lane * 16;
     uint4 wf[4][4][2];
 #pragma unroll
@@ -152,6 +152,23 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
             for (int i = 0; i < 4; ++i) l1 += fabsf(bf16_lo_to_f32(w4[i])) + fabsf(bf16_hi_to_f32(w4[i]));
         }
     l1 += __shfl_xor(l1, 32);
+    // Coded streams: code index and exponent of the lane's slot, of even and odd pairs of k-steps.  The tables come by scalar loads
+    // and are looked up in LDS: a vector load behind the weights would wait for all of them.
+    int slot_code[2] = {}, slot_exp[2] = {};
+    if constexpr (!DENSE) {
+        uint32_t w[16], mine_w = 0u;
+        __builtin_memcpy(w, &a.tab, 64);
+#pragma unroll
+        for (int k = 0; k < 16; ++k) mine_w = (lane & 15) == k ? w[k] : mine_w;
+        reinterpret_cast<uint32_t*>(table[wave])[lane & 15] = mine_w;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            slot_code[k] = table[wave][(2 * k + (c32 >> 4)) * 8 + (c32 & 7)];
+            slot_exp[k] = table[wave][32 + slot_code[k]];
+        }
+    }
     // A coded stream's weights are at most 2^12 (times the slot's factor): |u| <= 2^12 |q|_1, which a power of two brings
     // below 2^15 for the fp16 parts of u.  The score kernel takes it (and the stream's own factor) out again.
     int e = 0;
@@ -163,7 +180,7 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
     if (slab == 0 && half == 0 && cb * 32 + c32 < ncol) {
         int b;
         const int row = row_of(cb * 32 + c32, b);
-        const float f = DENSE ? a.scale_log2e : ldexpf(a.scale_log2e * FOLD_CODE_UNIT, -e - a.w.shift[sh]);
+        const float f = DENSE ? a.scale_log2e : ldexpf(a.scale_log2e * FOLD_CODE_UNIT, -e - shift);
         a.rowfac[(long long)b * s.nrb * 16 * a.rt + row] = f;
     }
 
@@ -213,9 +230,8 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
             if constexpr (DENSE) {
                 ch = ks * 16 + hs * 8 + i;
             } else {
-                int p;
-                ch = stream_channel(a.tab, a.w.group, ks, hs, i, &p);
-                f = ldexpf(1.0f, -a.tab.wexp_of_code[p]);
+                ch = stream_channel(G, ks, hs, slot_code[pr & 1]);
+                f = ldexpf(1.0f, -slot_exp[pr & 1]);
             }
         }
 #pragma unroll
@@ -1891,8 +1907,7 @@ __global__ __launch_bounds__(512, 4) void fold_output_kernel(const FoldOutArgs a
             float v[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                int p;
-                const int ch = DENSE ? ks * 16 + half * 8 + i : stream_channel(a.tab, a.w.group, ks, half, i, &p);
+                const int ch = DENSE ? ks * 16 + half * 8 + i : stream_channel(a.w.group, ks, half, a.tab.code_of_slot[ks & 3][i]);
                 v[i] = yl[c32 * FO_STRIDE + sl * 128 + ch];
             }
 #pragma unroll
