@@ -799,8 +799,8 @@ __global__ __launch_bounds__(512) void fold_scores_dense_kernel(const FoldScoreA
 
 // =====================================================================================================================
 // Values.  A workgroup owns two slabs (256 channels) of a sequence, one row block and a range of tokens; its four waves are
-// two slab ways and two token ways, and two workgroups share a CU, so that one's set-up, barriers and sums run beside the
-// other's products.  Per 128 tokens all waves bring the stored softmax weights to the sequence's maximum and stage them in LDS
+// two slab ways and two token ways, and two workgroups share a CU where there are enough of them (fold_splits), so that one's
+// set-up, barriers and sums run beside the other's products.  Per 128 tokens all waves bring the stored softmax weights to the sequence's maximum and stage them in LDS
 // with the tokens' scales, integer zero-points and rests; a wave then takes 32 tokens at a time.  The contraction runs over
 // tokens, so an operand dword pairs the codes of two tokens: a lane takes octet n = lane % 16 of the slab (8 channels) for
 // eight tokens, merges token pairs, and column tile k of the product is code k of every lane's octet -- no transposition.
@@ -815,12 +815,13 @@ __global__ __launch_bounds__(512) void fold_scores_dense_kernel(const FoldScoreA
 // scales and maxima before the loop eight at a time 10, 3, 2, 0.5.
 //
 // Range of the fp16 parts.  Weights are taken against the range's own maximum of the row and scales against the range's
-// largest scale of the group, so the parts end 2^-40 below their product (or below the weight alone): a token is cut by at most
-// 2^-41 of the largest scale, whatever its weight.  Every row has a token of weight 1 in its tiles, so with scales within a factor 2^13 (12
-// exponents) that is 2^-28 of what the row sums up, and 2^12 such cuts in random directions reach the 2^-22 that
+// largest scale of the group.  The low parts end at 2^-24, so they are off by up to 2^-25.  Weights are cut times 2^15: a token is cut by at
+// most 2^-40 of the largest scale, whatever its weight.  Weights times scales have the largest scale in [2^14, 2^15): at most 2^-39 of it.
+// Every row has a token of weight 1 in its tiles, so with scales within a factor 2^13 (12 exponents) that is 2^-27 (2^-26) of what the
+// row sums up, and 2^12 such cuts in random directions, 0.6 times as large in the mean, reach 2^-22 (2^-21), about what
 // the parts carry.  A range with a wider group, a negative scale or a non-finite one is summed in plain
-// fp32 instead (fold_values_plain), and one with zero scales among others where their tokens may hold all the weight.  Measured, one token of 300 larger by 2^20 / 2^28 that no row attends to: error
-// 1.1e-5 / 1.7e-3 with one factor per group and no such limit, 5e-7 now.
+// fp32 instead (fold_values_plain), and one with zero scales among others where their tokens may hold all the weight.  Measured, one
+// token of 300 larger by 2^20 / 2^28 that no row attends to: error 1.1e-5 / 1.7e-3 with one factor per group and no such limit, 5e-7 now.
 // =====================================================================================================================
 struct FoldValueArgs {
     FoldSource x;
@@ -2056,8 +2057,10 @@ static FoldPlan fold_plan(const FoldProblem& f, int B, int nb, int max_len, int 
     return L;
 }
 
-// Two workgroups a CU where their sums fit the partials of the rematerialising kernels, which a caller brings at the least
-// (8 x 4096 tokens of 32 heads would ask for a tenth more than these).
+// Two workgroups a CU where their sums fit the partials of the rematerialising kernels, which a caller brings at the least, so that
+// the query stays what it is and such a step never goes in groups.  (8 x 4096 tokens of 32 heads would ask for a tenth more than
+// these: two splits there, a workgroup of four waves on every CU, 38 us where four splits take 34; with three the step is the same.
+// Counts between the two took it to 0.89 to 1.11 times its time on 44 other shapes.)
 static int fold_splits(const FoldProblem& f, int B, int nrb, int max_len)
 {
     const int one = fold_splits(B, nrb, f.n_slabs_v, max_len, 1);
@@ -2103,8 +2106,8 @@ bool fold_fits(const FoldProblem& f, int B, int max_len, size_t bytes)
 
 // Order of a launch's sequences.  Every XCD gets a contiguous eighth of the work items (xcd_contiguous), so with sequences of
 // different lengths the XCD with the longest ones is the last to finish.  From two sequences per XCD on they are dealt out,
-// longest first, each to the XCD with the fewest tokens that still has a place.  16 sequences of 4177 to 8191 tokens, us: value kernel 113 -> 103, scores 110.5 -> 109,
-// whole step 237 -> 225.
+// longest first, each to the XCD with the fewest tokens that still has a place.  16 sequences of 4177 to 8191 tokens, us: value
+// kernel 113 -> 103, scores 110.5 -> 109, whole step 237 -> 225.
 static void fold_order(FoldShape& s)
 {
     int by_len[XQ_MAX_BATCH], place[XQ_MAX_BATCH], n_of[8] = {}, first[9] = {};

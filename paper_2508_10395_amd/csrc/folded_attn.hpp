@@ -16,7 +16,7 @@ struct FoldProblem {
 hipError_t allow_large_lds(const void* kernel, int lds_bytes);
 bool unpack_table_for(int bits, UnpackTable* t);
 
-int fold_splits(int nb, int nrb, int n_slabs_v, int max_len, int per_cu = 1);          // token splits of the weighted sums
+int fold_splits(int nb, int nrb, int n_slabs_v, int max_len, int per_cu);               // token splits of the weighted sums
 size_t fold_workspace_bytes(const FoldProblem& f, int B, int max_len);
 bool fold_fits(const FoldProblem& f, int B, int max_len, size_t bytes);
 hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSource& kx, const FoldSource& vx, const FoldWeights& kw,

@@ -161,7 +161,7 @@ static bool folding_pays(const StepCost& c, const xq_attn_t* a, int B, int max_l
     const long long nt = (max_len + TILE_TOKENS - 1) / TILE_TOKENS, waves = (nt * a->n_kv_heads * B + 255) / 256;
     if (!folding_may_pay(a, B, max_len, d)) return false;
     const int Hq = a->n_q_heads, Hkv = a->n_kv_heads, rt = Hq <= 16 ? 1 : 2, slabs = d / 128;
-    const long long nbt = (long long)B * ((Hq + 16 * rt - 1) / (16 * rt)), splits = fold_splits(B, (int)(nbt / B), slabs, max_len);
+    const long long nbt = (long long)B * ((Hq + 16 * rt - 1) / (16 * rt)), splits = fold_splits(B, (int)(nbt / B), slabs, max_len, 1);
     const float kd = (float)d / 256, len = (float)max_len / 8192, gb = 2e-9f * B * max_len * d;
     const float remat = c.base + waves * (c.wave_d * kd + c.wave + (Hq / Hkv >= 4 ? c.wave_gqa : 0.0f)) + 1e-6f * c.rows * B * Hq * max_len +
                         c.len * len + (c.bytes + c.head_bytes * Hkv) * gb + extra;

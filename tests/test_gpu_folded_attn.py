@@ -156,6 +156,20 @@ def test_sequences_dealt_over_the_chip(xq, B):
     _run(xq, w, 3, 128, lens, pairs=[(b, (3 * b + 1) % 16) for b in range(B)])
 
 
+@pytest.mark.parametrize("B", [16, 29])
+@pytest.mark.parametrize("source,G", [("acc", 128), ("per_channel", 64), ("per_channel", 128)])
+def test_sequences_of_other_sources_dealt_over_the_chip(xq, source, G, B):
+    """The same over bf16 rows, and over blocks with a window, some of them windows alone."""
+    w = xi.C2.scaled(B=B, L=700, d=1024, Hq=16, Hkv=16, n_outlier=10)
+    lens = [1 + (b * b * 97 + 41 * b) % 700 if b % 3 else 700 - b for b in range(B)]
+    pairs = [(b, (3 * b + 1) % 16) for b in range(B)]
+    if source == "acc":
+        return _run(xq, w, 16, G, lens, pairs=pairs)
+    err = []
+    assert _folds(lambda: err.append(_attend(xq, w, 3, G, lens, pairs=pairs)))
+    assert err[0] <= TOL
+
+
 @pytest.mark.parametrize("bits", [3, 16])
 def test_smaller_workspaces(xq, bits):
     """Between the smallest workspace that is accepted and the one that is asked for, the launch goes in groups of sequences,
@@ -419,6 +433,18 @@ def test_same_bits_again_in_any_order_on_any_workspace(xq, kind):
         got = call(q, lens, [0, 1, 2], torch.full((n,), fill, dtype=torch.uint8, device="cuda"))
         assert torch.equal(got, want), fill
     assert torch.equal(call(q, lens, [2, 0, 1]), want[[2, 0, 1]])
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_same_bits_in_any_order_of_many_sequences(xq, kind):
+    """The same where the launch takes its sequences in an order of its own."""
+    q, call, _ = _cases(xq, kind, B=17, L=400)
+    lens = [1 + (b * b * 97 + 41 * b) % 399 for b in range(16)] + [400]
+    as_they_are = list(range(17))
+    assert _folds(lambda: call(q, lens, as_they_are))
+    want = call(q, lens, as_they_are)
+    for order in (as_they_are[::-1], [(5 * b + 3) % 17 for b in range(17)]):
+        assert torch.equal(call(q, lens, order), want[order]), order
 
 
 @pytest.mark.parametrize("kind", KINDS)
