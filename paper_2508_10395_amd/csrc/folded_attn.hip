@@ -993,9 +993,10 @@ __device__ __forceinline__ void fold_meet(const f32x4 (&acc)[RT][8], uint8_t* ld
 }
 
 // The sums of a range whose scales lie too far apart for fp16 parts: x^ and the sums in fp32, a thread per channel of
-// either slab and quarter of the rows.  Rare, and bound by the vector ALU and the LDS reads of the weights: with every
-// range on it a step over 8 x 4096 tokens of 3 bits (32 heads, d = 4096) takes 330 us (105 on the fp16 parts, 1650 when K and V
-// are rematerialised), 16 x 8191 of 2 bits in groups of 64 1160 us (300; 1790).
+// either slab and half of the rows.  Rare, and bound by the vector ALU and the LDS reads of the weights, the latter uncovered where
+// one workgroup of four waves has a CU: with every range on it a decode call over 8 x 4096 tokens of 3 bits (32 heads, d = 4096)
+// takes 330 us (95 on the fp16 parts; 374 when the codes were waited for 8 tokens at a time; 1650 when K and V are
+// rematerialised), 16 x 8191 of 2 bits in groups of 64 687 us (206; 778; 1790).
 template <int BITS, int G, int RT, bool NIB>
 __device__ __forceinline__ void fold_values_plain(const FoldValueArgs& a, const FoldValuePlace& o, const float* mrow, uint8_t* lds, float* lp)
 {
@@ -1021,17 +1022,21 @@ __device__ __forceinline__ void fold_values_plain(const FoldValueArgs& a, const 
     for (int r = 0; r < ROWS; ++r) y[0][r] = y[1][r] = 0.0f;
     for (int t = o.t0; t < o.t1; ++t) {
         __syncthreads();
+#pragma unroll 1
+        for (int hf = 0; hf < 2; ++hf) {                             // (past the length: the last tile again, which counts for nothing)
+            const long long t128 = min(2 * t + hf, (o.len - 1) / FOLD_TILE);
+            const float m = msrc[t128 * 16 * RT];
+            float4 v[PH];
 #pragma unroll
-        for (int e = 0; e < 2 * PH; ++e) {
-            const int t128 = 2 * t + e / PH;
-            float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (t128 * FOLD_TILE < o.len) {
-                const float m = msrc[(long long)t128 * 16 * RT], f = m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - M);
-                v = *reinterpret_cast<const float4*>(psrc + (long long)t * 8 * FOLD_P_TILE32<RT> + (e * NT + tid) * 4);
-                v.x *= f; v.y *= f; v.z *= f; v.w *= f;
-                lacc += (v.x + v.y) + (v.z + v.w);
+            for (int e = 0; e < PH; ++e) v[e] = *reinterpret_cast<const float4*>(psrc + t128 * 4 * FOLD_P_TILE32<RT> + (e * NT + tid) * 4);
+            const bool live = (2 * t + hf) * FOLD_TILE < o.len;
+            const float f = m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - M);
+#pragma unroll
+            for (int e = 0; e < PH; ++e) {
+                v[e].x = live ? v[e].x * f : 0.0f; v[e].y = live ? v[e].y * f : 0.0f; v[e].z = live ? v[e].z * f : 0.0f; v[e].w = live ? v[e].w * f : 0.0f;
+                lacc += (v[e].x + v[e].y) + (v[e].z + v[e].w);
+                p[(hf * PH + e) * NT + tid] = v[e];
             }
-            p[e * NT + tid] = v;
         }
 #pragma unroll
         for (int e = 0; e < GROUPS * 256 / NT; ++e) {
@@ -1042,25 +1047,40 @@ __device__ __forceinline__ void fold_values_plain(const FoldValueArgs& a, const 
         __syncthreads();
         const int ntok = min(o.len - t * FOLD_VTILE, FOLD_VTILE);
         const float2* szg = sz + ch / G * 256;
-        for (int k = 0; k < (ntok + 31) / 32 * 4; ++k) {             // [tokens / 32][half of the slots][pair of quarters]: 8 tokens at a time
+        // [tokens / 32][half of the slots][pair of quarters]: 8 tokens at a time, the next ones' codes on their way
+        auto token_at = [](int k, int q, int i) XQ_INLINE_LAMBDA { return (k >> 2) * 32 + 4 * (4 * ((k >> 1) & 1) + i) + (k & 1) * 2 + q; };
+        uint16_t next[2][2][4];
+        auto load_codes = [&](int k) XQ_INLINE_LAMBDA {
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint8_t* c = code + (long long)min(t * FOLD_VTILE + token_at(k, q, i), o.len - 1) * x.row_bytes;
+#pragma unroll
+                    for (int n = 0; n < 2; ++n) {
+                        if constexpr (BITS == 3) __builtin_memcpy(&next[n][q][i], c + n * step, 2);
+                        else next[n][q][i] = c[n * step];
+                    }
+                }
+        };
+        load_codes(0);
+        for (int k = 0; k < (ntok + 31) / 32 * 4; ++k) {
             const int k32 = k >> 2, h = (k >> 1) & 1, q0 = (k & 1) * 2;
             float xv[2][2][4];
 #pragma unroll
             for (int q = 0; q < 2; ++q)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int at = k32 * 32 + 4 * (4 * h + i) + q0 + q;
-                    const uint8_t* c = code + (long long)min(t * FOLD_VTILE + at, o.len - 1) * x.row_bytes;
+                    const int at = token_at(k, q, i);
 #pragma unroll
                     for (int n = 0; n < 2; ++n) {
-                        uint16_t v;
-                        if constexpr (BITS == 3) __builtin_memcpy(&v, c + n * step, 2);
-                        else v = c[n * step];
-                        const float num = (float)((v >> shift) & ((1u << BITS) - 1u));
+                        const float num = (float)((next[n][q][i] >> shift) & ((1u << BITS) - 1u));
                         const float2 m = szg[n * (128 / G) * 256 + at];
                         xv[n][q][i] = NIB && (ch & 1) ? num * m.x : __builtin_fmaf(num, m.x, m.y);   // (8-bit caches: the zero-point goes with the low nibble)
                     }
                 }
+            load_codes(k + 1);
+            asm volatile("" ::: "memory");                           // (the compiler would load them where they are used)
 #pragma unroll
             for (int q = 0; q < 2; ++q)
 #pragma unroll
@@ -1096,8 +1116,8 @@ __device__ __forceinline__ void fold_values_plain(const FoldValueArgs& a, const 
 // Scales of zero (constant rows: padding, a row not yet written) add nothing to the products, so only the others' spread counts,
 // and how far below its row's maximum the weights of their tokens lie.  Tiles without such a scale show that: true if in
 // every row they reach to within what the spread leaves of the 12 exponents.  ginv < 0 marks the groups in question.
-// Read once more, and only by ranges that hold one: a step whose last row is zero takes 107 us instead of 104 (8 x 4096, 3 bits), 322
-// instead of 296 (16 x 8191, 2 bits in groups of 64); in plain fp32 the first took 340.
+// Read once more, and only by ranges that hold one: a decode call whose last rows are zero takes 99 us instead of 95 (8 x 4096, 3
+// bits), 219 instead of 206 (16 x 8191, 2 bits in groups of 64); in plain fp32 it would be 330 and 700.
 template <int NG, int RT>
 __device__ __forceinline__ bool fold_zero_scales_harmless(const FoldValueArgs& a, const FoldValuePlace& o, const float* mrow, const float* ginv, int g0, uint8_t* lds)
 {
