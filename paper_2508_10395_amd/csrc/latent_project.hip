@@ -61,7 +61,9 @@ __device__ __forceinline__ void wave_lds_order()
 }
 
 // One round of a wave: STEPS times 16 channels from channel k on, all of them asked for before the first product (the fence keeps
-// the loads in front of it).  With one step's loads at a time, 512 rows of d = 4096 to 512 latent channels took 21 us, 18 so.
+// the loads in front of it).  Four steps (two of deltas) leave three or four workgroups to a CU, which hide more than longer rounds
+// do.  One step at a time / these / 16: 512 rows of d = 4096 to 512 latent channels 19.9 / 16.3 / 16.5 us, 2048 rows of d = 256
+// to 2048 18.3 / 17.2 / 27.9, of d = 5120 333 / 282 / 303; deltas 29.5 / 24.9 / 27.3, 25.8 / 26.5 / 40.9, 502 / 433 / 490.
 template <int STEPS, bool DELTA>
 __device__ __forceinline__ void project_round(const uint16_t* ap, const uint16_t* bp, const uint16_t* sp, int k, f32x16& acc)
 {
@@ -114,12 +116,11 @@ __global__ __launch_bounds__(512) void latent_project_kernel(const uint16_t* __r
     f32x16 acc;
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+    constexpr int MOST = DELTA ? 2 : 4;
     int i = 0;
-    for (; i + 16 <= steps; i += 16) project_round<16, DELTA>(ap, bp, sp, i * 16, acc);
-    if (steps & 8) { project_round<8, DELTA>(ap, bp, sp, i * 16, acc); i += 8; }
-    if (steps & 4) { project_round<4, DELTA>(ap, bp, sp, i * 16, acc); i += 4; }
-    if (steps & 2) { project_round<2, DELTA>(ap, bp, sp, i * 16, acc); i += 2; }
-    if (steps & 1) project_round<1, DELTA>(ap, bp, sp, i * 16, acc);
+    for (; i + MOST <= steps; i += MOST) project_round<MOST, DELTA>(ap, bp, sp, i * 16, acc);
+    if (MOST > 2 && steps - i >= 2) { project_round<2, DELTA>(ap, bp, sp, i * 16, acc); i += 2; }
+    if (steps - i >= 1) project_round<1, DELTA>(ap, bp, sp, i * 16, acc);
     // accumulator element i of lane (r, kb) is D[m][n] with n = r, m = 8 (i/4) + 4 kb + i%4
 #pragma unroll
     for (int e = 0; e < 16; ++e) red[wave][8 * (e >> 2) + 4 * kb + (e & 3)][r] = acc[e];
@@ -135,7 +136,7 @@ __global__ __launch_bounds__(512) void latent_project_kernel(const uint16_t* __r
 
 // The same for few rows, to the bit: 16 x 16 output tiles, in a corner of the same products, whose other rows and columns repeat
 // them.  An operand load of the kernel above touches 32 cache lines for 32 bytes each, which bounds it once its loads are in
-// flight (16 rows of d = 4096 to 2048 latent channels 15 us); here rows are read by whole lines, eight of them a load, and go
+// flight (16 rows of d = 4096 to 2048 latent channels 13 us); here rows are read by whole lines, eight of them a load, and go
 // through LDS into operand order, 512 channels (256 of deltas) asked for before the first is used.  Pieces of 16 bytes are
 // swizzled by the row against bank conflicts.  16 rows to 2048 latent channels 8.6 us (19.2 in 32 x 32 tiles with one step's
 // loads at a time), of deltas 12.7 (24.8); the 16.8 MB of Ut take 3.
@@ -235,7 +236,7 @@ static hipError_t launch_project(const uint16_t* x, const uint16_t* ut, uint16_t
                                  const BatchI32& start, hipStream_t s)
 {
     // As long as two workgroups a CU hold all 16 x 16 tiles.  us a call in 32 x 32 / 16 x 16 tiles, d = 4096, 2048 latent channels:
-    // 16 rows 15.2 / 9.9, 64 rows 18.4 / 13.0, 128 rows 18.4 / 22.6; 512 latent channels: 256 rows 16.8 / 11.8, 512 rows 17.2 / 21.5.
+    // 16 rows 13.4 / 10.3, 64 rows 16.0 / 11.4, 128 rows 16.0 / 20.7; 512 latent channels: 256 rows 15.8 / 11.1, 512 rows 16.3 / 20.7.
     if ((long long)(n_lat / 16) * ((M + 15) / 16) <= 512)
         latent_project_rows16_kernel<DELTA><<<dim3(n_lat / 16, (M + 15) / 16), dim3(512), 0, s>>>(x, ut, out, M, d, n_lat, a, T, cap, start);
     else
