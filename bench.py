@@ -24,8 +24,8 @@ PEAK_HBM_GBS = 8000.0         # MI355X HBM3E, published
 # HBM-side bytes of one xq_remat_attn_decode on this workload, its five kernels together: rocprofv3 FETCH_SIZE + WRITE_SIZE,
 # each scaled by the factor that makes the counter read 256 MiB for a plain 256 MiB device copy
 # (profiles/remat_attn_hbm_traffic.txt; counters cannot be read from inside this process, so this is a recorded constant)
-DECODE_HBM_BYTES = 2.328e8
-DECODE_HBM_BYTES_MEASURED_AT = "b78502c"
+DECODE_HBM_BYTES = 2.164e8
+DECODE_HBM_BYTES_MEASURED_AT = "2ca48a8"
 
 
 def parse():

@@ -5,9 +5,9 @@
 //   fold_output_kernel   o = y Wv_h, split over the channels
 //   fold_finish_kernel   sum of these splits, divided by the softmax denominator
 // Against rematerialising K and V tile by tile (MI355X, us per step with the append, before / after): 8 x 4096 tokens, 3 bits,
-// 32 KV heads of a d = 4096 layer 1664 / 104; 16 x up to 8191, 2 bits in groups of 64, 32 on 8 heads 1512 / 222; 4 x 32768,
-// 2 bits 6330 / 220; bf16 accumulator, 4 x up to 6000 1080 / 120.  The operations no longer bound it: what is left is the
-// unpacking beside the matrix instructions, and 15 us each for reading the two halves of the weight stream.
+// 32 KV heads of a d = 4096 layer 1664 / 102; 16 x up to 8191, 2 bits in groups of 64, 32 on 8 heads 1512 / 222; 4 x 32768,
+// 2 bits 6330 / 211; bf16 accumulator, 4 x up to 6000 1080 / 118.  The operations no longer bound it: what is left is the
+// unpacking beside the matrix instructions, and 14 us each for reading the two halves of the weight stream.
 #include <algorithm>
 
 #include "folded_common.hpp"
@@ -810,9 +810,9 @@ __global__ __launch_bounds__(512) void fold_scores_dense_kernel(const FoldScoreA
 // 2 and 3 bits: (code - zi) times the scale has at most 3 + 8 bits, so it is exact in fp16 and goes into the codes' operand (one
 // packed product per dword), and the weights are cut into fp16 hi + lo once, when they are staged.  Other codes have a bit too
 // many: there weight times scale is cut per group.  Bound by issue: the vector ALU takes about 1.5 times as long as the matrix
-// instructions.  Measured, us, waves of weight times scale in workgroups of eight / this: 4 x 32768 tokens of 2 bits 118 / 106,
-// 16 x 8191 of 2 bits in groups of 64 154 / 115, half the width 43 / 37, 8 x 4096 of 3 bits 36 / 34; of these the loads of
-// scales and maxima before the loop eight at a time 10, 3, 2, 0.5.
+// instructions.  Measured, us, weight times scale in workgroups of eight waves / this: 4 x 32768 tokens of 2 bits 118 / 102,
+// 16 x 8191 of 2 bits in groups of 64 149 / 104, half the width 44 / 37 (of these the loads of scales and maxima before the loop eight
+// at a time 10, 3, 2); 8 x 4096 of 3 bits, where the workspace leaves a CU one workgroup, 35 / 38, and 34 with two.
 //
 // Range of the fp16 parts.  Weights are taken against the range's own maximum of the row and scales against the range's
 // largest scale of the group.  The low parts end at 2^-24, so they are off by up to 2^-25.  Weights are cut times 2^15: a token is cut by at

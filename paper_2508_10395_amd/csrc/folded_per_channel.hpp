@@ -12,10 +12,10 @@
 // a block cuts the weights as they are stored, against the maximum of their own block (128 or 64 tokens, FoldShape::mhalf),
 // and multiplies the rest of the factor in with the scales, in fp32.  So a block's largest weight is cut to 2^-25 of itself or
 // better (a block 2^30 larger at weights of 2^-30 was off by 2e-4 without).  Both loops take as
-// long (a step of 8 x 4077 tokens 114 us either way); one loop that always does the latter, unrolled alone, ran 3 us slower.
+// long (measured on a step of 8 x 4077 tokens); one loop that always does the latter, unrolled alone, ran 3 us slower.
 // Bound by issue and by the latency of the loads, as the per-token kernels.  8 sequences of up to 4077 tokens, 3 bits, 32 KV
-// heads, d = 4096: scores 39 us, values 43 us with the windows (36 + 32 and 34 + 11 in launches of their own); the step 1432 us
-// when K and V were rematerialised, 126 now.
+// heads, d = 4096, six layers in turn: scores 47 us, values 43 us with the windows (one layer again and again 36 and 42); the step
+// 1432 us when K and V were rematerialised, 116 now.
 #pragma once
 
 template <int BITS>

@@ -138,6 +138,12 @@ static FoldProblem fold_problem(const xq_attn_t* a, int d, int group, int bits, 
 // 1 to 16 query heads, all formats, nearest where the two are within a factor of two of each other; the median step is 5 % off.
 // Of the steps that folding made slower by 3 % or more, 62 of 4120 coded ones (up to 1.35 times), 86 of 809 over bf16 rows (1.71) and
 // 56 of 1288 per-channel ones (1.58), 22 (1.12), 12 (1.20) and 24 (1.21) still fold, and 33 that folding makes faster no longer do.
+//
+// The fits are older than the score and value kernels as they are (which are up to a quarter faster over coded rows, with other slab ways
+// and up to twice the token splits that are counted here), so they now keep too many steps from folding.  Of drawn steps above the
+// line before, slower folded by 3 % and folded all the same: coded 0 of 10039, bf16 rows 32 of 2951 (up to 1.18 times), per channel 0 of 3021;
+// faster folded by 3 % and not folded: 287 (up to 1.68), 51 (1.38) and 86 (2.48).  Below it folding is faster for 2840 of 11085
+// coded steps and slower for 7592, over bf16 rows 331 and 3570 of 4056, per channel 3107 and 670 of 3906.
 struct StepCost {
     float base, wave_d, wave, wave_gqa, rows, len, bytes, head_bytes;                       // rematerialising
     float f_base, f_ways, f_scores, f_values, f_len, f_sums, f_tiles, f_bytes, f_row_bytes, f_weights;
@@ -188,7 +194,8 @@ static bool pc_folding_pays(const xq_attn_t* a, int B, int max_len, int d, int b
 }
 
 // The same for a latent cache, whose two rematerialising passes are five launches too.  Measured (us with projection and
-// append, remat / folded), one wave: r = 256 46 / 41 to 51 / 59, r = 512 57 / 44, r = 1024 81 / 57.
+// append, remat / folded), one wave: r = 256 46 / 41 to 51 / 59, r = 512 57 / 44, r = 1024 81 / 57.  (With the kernels as they are
+// now 1543 of 1712 drawn steps below the line are faster folded, by up to 1.88 times, 50 slower.)
 static bool latent_folding_pays(const xq_attn_t* a, int B, int max_len, int r)
 {
     const long long tiles = (max_len + TILE_TOKENS - 1) / TILE_TOKENS, waves = (tiles * (a->n_kv_heads / 2) * B + 255) / 256;
