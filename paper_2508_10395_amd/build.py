@@ -10,7 +10,7 @@ LIB = os.path.join(HERE, "libxquant.so")
 SOURCES = ["api.hip", "quantize.hip", "cl_accumulate.hip", "prepare_weights.hip", "remat_attn.hip",
            "remat_attn16.hip", "latent_project.hip", "folded_attn.hip"]
 HEADERS = ["common.hpp", "remat_layout.hpp", "unpack.hpp", "remat_common.hpp", "remat_epilogues.hpp", "remat_launch.hpp",
-           "folded_common.hpp", "folded_attn.hpp", "folded_per_channel.hpp"]
+           "folded_common.hpp", "folded_attn.hpp", "folded_digits.hpp", "folded_per_channel.hpp"]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

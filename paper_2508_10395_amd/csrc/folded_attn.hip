@@ -1,12 +1,13 @@
 // Decode attention without rematerialised keys and values (see folded_common.hpp for the algebra and the precision):
 //   fold_query_kernel    u = q Wk_h^T for every query row, split and laid out as operand fragments of the score kernel
 //   fold_scores_kernel   S = u X^T for 128 tokens a workgroup; softmax weights against the tile's maximum
+//                        (fold_scores_digits_kernel, folded_digits.hpp: 2-bit codes on the f8f6f4 products, 256 tokens)
 //   fold_values_kernel   y = sum over tokens of softmax weight times cached row, for a slab range and a token range
 //   fold_output_kernel   o = y Wv_h, split over the channels
 //   fold_finish_kernel   sum of these splits, divided by the softmax denominator
 // Against rematerialising K and V tile by tile (MI355X, us per step with the append, before / after): 8 x 4096 tokens, 3 bits,
-// 32 KV heads of a d = 4096 layer 1664 / 102; 16 x up to 8191, 2 bits in groups of 64, 32 on 8 heads 1512 / 222; 4 x 32768,
-// 2 bits 6330 / 211; bf16 accumulator, 4 x up to 6000 1080 / 118.  The operations no longer bound it: what is left is the
+// 32 KV heads of a d = 4096 layer 1664 / 102; 16 x up to 8191, 2 bits in groups of 64, 32 on 8 heads 1512 / 192; 4 x 32768,
+// 2 bits 6330 / 195; bf16 accumulator, 4 x up to 6000 1080 / 118.  The operations no longer bound it: what is left is the
 // unpacking beside the matrix instructions, and 14 us each for reading the two halves of the weight stream.
 #include <algorithm>
 
@@ -83,13 +84,19 @@ __device__ __forceinline__ int stream_channel(int group, int ks, int half, int c
 
 constexpr int FQ_STRIDE = 132;           // floats per query column in LDS: 16-byte pieces of different columns on different banks
 
-template <bool DENSE, int G>
+// u of a slab in base-32 digits (folded_digits.hpp)
+constexpr float FOLD_WIDE_ROWS = 8.0f;
+template <int G>
+__device__ __forceinline__ void fold_store_digits(const FoldQueryArgs& a, const float* mine, const int* place, int lane, int slab, bool wide_rows);
+
+template <bool DENSE, int G, bool DIGITS = false>
 __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
 {
     __shared__ __attribute__((aligned(16))) float ul[2][32 * FQ_STRIDE];
     __shared__ float nrm[2][32];
     __shared__ __attribute__((aligned(4))) int8_t table[2][64];      // coded streams: code_of_slot, then wexp_of_code
     __shared__ int place[2][32];             // row block of the launch 16 RT + row inside it, per column (-1: none)
+    __shared__ float row_tops[2][DIGITS ? 128 : 1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int half = lane >> 5, c32 = lane & 31;
     const int slab = blockIdx.x * 2 + wave, h = blockIdx.y, cb = blockIdx.z;
@@ -180,7 +187,7 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
     if (slab == 0 && half == 0 && cb * 32 + c32 < ncol) {
         int b;
         const int row = row_of(cb * 32 + c32, b);
-        const float f = DENSE ? a.scale_log2e : ldexpf(a.scale_log2e * FOLD_CODE_UNIT, -e - shift);
+        const float f = DENSE ? a.scale_log2e : ldexpf(a.scale_log2e * (DIGITS ? 1.0f : FOLD_CODE_UNIT), -e - shift);
         a.rowfac[(long long)b * s.nrb * 16 * a.rt + row] = f;
     }
 
@@ -203,6 +210,7 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
 #pragma unroll
     for (int pr = 0; pr < 4; ++pr) {
         f32x16 uacc = zero16;
+        [[maybe_unused]] float row_top = 0.0f;                       // digits: largest weight of the lane's channel
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb) {
             f32x16 t;
@@ -215,6 +223,9 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
             }
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
+                if constexpr (DIGITS)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) row_top = fmaxf(row_top, fabsf(t[8 * k + i]));
                 uint32_t d[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) d[i] = pack_hi16(__float_as_uint(t[8 * k + 2 * i]), __float_as_uint(t[8 * k + 2 * i + 1]));
@@ -234,6 +245,10 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
                 f = ldexpf(1.0f, -slot_exp[pr & 1]);
             }
         }
+        if constexpr (DIGITS) {
+            row_top = fmaxf(row_top, __shfl_xor(row_top, 32)) * f;
+            if (half == 0) row_tops[wave][ch] = row_top;
+        }
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int col = 8 * (i >> 2) + 4 * half + (i & 3);
@@ -243,6 +258,23 @@ __global__ __launch_bounds__(128) void fold_query_kernel(const FoldQueryArgs a)
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_wave_barrier();
 
+    if constexpr (DIGITS) {
+        // 32 channels that share a power of two: do their weight rows (those not zero) differ too much?
+        bool wide = false;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const float v = row_tops[wave][64 * k + lane];
+            float top = v, low = v > 0.0f ? v : INFINITY;
+#pragma unroll
+            for (int off = 16; off > 0; off >>= 1) {
+                top = fmaxf(top, __shfl_xor(top, off));
+                low = fminf(low, __shfl_xor(low, off));
+            }
+            wide |= top > FOLD_WIDE_ROWS * low;
+        }
+        fold_store_digits<G>(a, mine, place[wave], lane, slab, __any(wide));
+        return;
+    }
     // out: 16-byte pieces (column, tick, quarter); a fragment is read lane by lane, lane = 16 quarter + row
     const int rt_log2 = a.rt - 1 + 4;
     if (!DENSE && a.u_dense) {                                       // (a code's unit is part of the row factor)
@@ -705,6 +737,8 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
     }
     fold_scores_finish<RT>(s, a.rowfac, a.p, a.mtile, S, reinterpret_cast<float*>(lds), o, lane, wave);
 }
+
+#include "folded_digits.hpp"
 
 // the same over bf16 rows (the cross-layer accumulator, a residual window): no codes and no groups, u in three bf16 parts.
 // The rows of a half slab (128 bytes each) go through the wave's LDS image as the codes do, 16 token rows at a time; their
@@ -2041,6 +2075,7 @@ static size_t align256(size_t n) { return (n + 255) / 256 * 256; }
 // workgroup, slab ways) follows from B, so that a sequence's result does not depend on the group it is launched in.
 struct FoldPlan {
     int rt, nrb, tiles, splits, chunks, chunk_slabs, u_slab;
+    int digits;                                            // queries in base-32 digits
     size_t p, mtile, rowfac, lsum, uy, yz, ud, total;      // bytes; u and y share a region (u is dead when y is written),
                                                            // the output splits lie over p (dead by then)
 };
@@ -2061,8 +2096,9 @@ static FoldPlan fold_plan(const FoldProblem& f, int B, int nb, int max_len, int 
     const int rpb = 16 * L.rt;
     L.nrb = (R + rpb - 1) / rpb;
     L.tiles = (max_len + FOLD_VTILE - 1) / FOLD_VTILE * 2 + (f.block ? 2 : 0);
+    L.digits = f.digits;
     L.splits = splits = splits + (f.block ? 1 : 0);
-    L.u_slab = f.dense ? FOLD_U_DENSE(L.rt) : FOLD_U_CODED(L.rt);
+    L.u_slab = f.dense ? FOLD_U_DENSE(L.rt) : f.digits ? FOLD_UD_SLAB : FOLD_U_CODED(L.rt);
     const int colblocks = (B * (f.Hq / f.Hkv) + 31) / 32;
     L.chunk_slabs = std::max(1, std::min(FO_MAX_SLABS, f.n_slabs_v * f.Hkv * colblocks / 256));
     L.chunks = (f.n_slabs_v + L.chunk_slabs - 1) / L.chunk_slabs;
@@ -2070,7 +2106,8 @@ static FoldPlan fold_plan(const FoldProblem& f, int B, int nb, int max_len, int 
     L.mtile = align256(((size_t)nb * L.nrb * L.tiles * rpb * 4) << (f.block == 64));
     L.rowfac = align256((size_t)nb * L.nrb * rpb * 4);
     L.lsum = align256((size_t)splits * nb * L.nrb * rpb * 4);
-    L.uy = align256(std::max((size_t)nb * L.nrb * f.n_slabs_k * L.u_slab, (size_t)splits * nb * R * f.n_slabs_v * 512));
+    const size_t u_block = f.digits ? (size_t)fold_ud_block(f.n_slabs_k, f.n_slabs_k * (128 / f.group)) : (size_t)f.n_slabs_k * L.u_slab;
+    L.uy = align256(std::max((size_t)nb * L.nrb * u_block, (size_t)splits * nb * R * f.n_slabs_v * 512));
     L.yz = f.dense || f.block ? 0 : align256((size_t)splits * nb * R * f.ng_v * 4);
     L.ud = f.block ? align256((size_t)nb * L.nrb * f.n_slabs_k * FOLD_U_DENSE(L.rt)) : 0;
     L.total = L.p + L.mtile + L.rowfac + L.lsum + L.uy + L.yz + L.ud;
@@ -2096,11 +2133,25 @@ size_t fold_workspace_bytes(const FoldProblem& f, int B, int max_len)
     return fold_plan(f, B, B, max_len, fold_splits(f, B, nrb, max_len)).total;
 }
 
+// Queries in base-32 digits for 2-bit codes with the scales along the channels and more than 16 query rows, where the tiles of 128 tokens fill
+// rounds of 512 workgroups of 256 tokens no less than rounds of 512 of 128: a round takes 76 us over 32 slabs of groups of 128, one of the
+// fp16 kernel 48 (1024 tiles 76 / 97, 1536 would be 152 / 144) - and where their buffers, larger by half, are no more than
+// what a caller brings.
+static int fold_digits(FoldProblem f, int B, int max_len)
+{
+    if (f.dense || f.nibbles || f.block || f.bits != 2 || f.Hq <= 16) return 0;
+    const int nrb = (f.Hq + 31) / 32, n = B * nrb * ((max_len + FOLD_VTILE - 1) / FOLD_VTILE * 2);
+    if (n < 1024 || 2 * ((n + 1023) / 1024) > (n + 511) / 512) return 0;
+    f.digits = 1;
+    return fold_workspace_bytes(f, B, max_len) <= f.query_bytes;
+}
+
 // The largest launch group that fits the workspace, for B sequences; where not even one does, one with fewer splits; false if
 // that does not either.  `bytes` is cut to what the query asks for, so that results do not depend on how much more a caller
 // brings; they depend on less only where splits are given up.
-static bool fold_fit(const FoldProblem& f, int B, int max_len, size_t bytes, int* nb, FoldPlan* plan)
+static bool fold_fit(FoldProblem f, int B, int max_len, size_t bytes, int* nb, FoldPlan* plan)
 {
+    f.digits = fold_digits(f, B, max_len);
     const int R = f.Hq, nrb = (R + (R <= 16 ? 15 : 31)) / (R <= 16 ? 16 : 32);
     bytes = std::min(bytes, std::max(f.query_bytes, fold_workspace_bytes(f, B, max_len)));
     const int splits = fold_splits(f, B, nrb, max_len);
@@ -2249,6 +2300,8 @@ hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSo
             FoldQueryArgs a{kw, sh, q, u, rowfac, softmax_scale * 1.44269504088896340736f, L.u_slab, f.n_slabs_k, L.rt, tab, u_dense};
             const dim3 grid((f.n_slabs_k + 1) / 2, f.Hkv, colblocks);
             if (f.dense) fold_query_kernel<true, 128><<<grid, dim3(128), 0, s>>>(a);
+            else if (L.digits && f.group == 64) fold_query_kernel<false, 64, true><<<grid, dim3(128), 0, s>>>(a);
+            else if (L.digits) fold_query_kernel<false, 128, true><<<grid, dim3(128), 0, s>>>(a);
             else if (f.group == 64) fold_query_kernel<false, 64><<<grid, dim3(128), 0, s>>>(a);
             else fold_query_kernel<false, 128><<<grid, dim3(128), 0, s>>>(a);
         }
@@ -2268,8 +2321,10 @@ hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSo
             const int waves = four ? 4 : 8;
             FoldScoreArgs a{kx, sh, u, rowfac, p, mtile, L.u_slab, waves, FoldSource{}, u_dense, 0};
             if (any_window) { a.window = *window; a.n_window = xcd_grid(sh.nb * sh.nrb); }
-            const int grid = a.n_window + xcd_grid(sh.nb * sh.nrb * sh.tiles);
-            e = f.block ? (L.rt == 1 ? scores_pc_for<1>(bits, a, grid, s) : scores_pc_for<2>(bits, a, grid, s))
+            const int grid = a.n_window + xcd_grid(sh.nb * sh.nrb * sh.tiles / (L.digits ? 2 : 1));
+            e = L.digits ? (f.group == 64 ? launch(fold_scores_digits_kernel<64>, grid, FoldDigitLds::TOTAL, a, s, 4)
+                                          : launch(fold_scores_digits_kernel<128>, grid, FoldDigitLds::TOTAL, a, s, 4))
+              : f.block ? (L.rt == 1 ? scores_pc_for<1>(bits, a, grid, s) : scores_pc_for<2>(bits, a, grid, s))
                         : (L.rt == 1 ? scores_for<1>(bits, f.group, f.nibbles, a, grid, s) : scores_for<2>(bits, f.group, f.nibbles, a, grid, s));
             if (e != hipSuccess) return e;
         }

@@ -10,6 +10,7 @@ struct FoldProblem {
     int bits, group, nibbles;            // of the walk (8-bit caches: 4, 128, 1)
     int n_slabs_k, n_slabs_v, ng_v;      // slabs of 128 walked channels on either side, groups of the values' side
     int block;                           // per-channel cache: tokens per block (else 0); its walk has groups of 128
+    int digits;                          // queries in base-32 digits (set by the plan)
     size_t query_bytes;                  // what the entry point's workspace query says for this call
 };
 

@@ -132,6 +132,34 @@ def test_token_ways_of_a_score_workgroup(xq, bits, G, d):
     _run(xq, w, bits, G, lens, pairs=[(0, 0), (0, 63), (1, 17), (2, 5), (3, 40), (4, 33), (5, 62), (15, 8)])
 
 
+@pytest.mark.parametrize("step", [dict(L=2048), dict(L=2048, Hq=48), dict(L=1792, taken=False), dict(L=2304, taken=False), dict(L=2048, bits=3, taken=False),
+                                  dict(L=4096, Hq=16, taken=False)])
+def test_which_steps_take_queries_in_digits(xq, step):
+    step = dict(dict(B=32, d=640, Hq=64, bits=2, taken=True), **step)
+    taken = step.pop("taken")
+    call = _step(xq, Hkv=step["Hq"], **step)
+    call()
+    assert any("digits" in n for n in _kernels(call)) == taken
+
+
+# (groups of 10 bytes a row; a last row block of 16 rows; 52 groups, which come in two runs; whole runs)
+@pytest.mark.parametrize("d,G,Hq,Hkv,B", [(640, 128, 64, 64, 32), (384, 64, 48, 48, 32), (3328, 64, 128, 32, 16), (1024, 64, 64, 64, 32)])
+@pytest.mark.parametrize("small_rows", [False, True])
+def test_queries_in_digits(xq, d, G, Hq, Hkv, B, small_rows):
+    """Enough tiles for queries in base-32 digits, with lengths at the edges of tiles and products.  Weight rows 2^-10 of the others
+    against channels 2^10 as large take further digits."""
+    w = xi.C2.scaled(B=B, L=2048, d=d, Hq=Hq, Hkv=Hkv, n_outlier=d // 100)
+    lens = [2048, 2047, 1025, 257, 256, 129, 65, 33, 1] + [40] * (B - 9)
+    x, wk = xi.gen_x(w), xi.gen_weights(w)[0]
+    if small_rows:
+        rows = [3, 70, 71, 200]
+        x, wk = xi.from_bf16_bits(x).copy(), xi.from_bf16_bits(wk).copy()
+        x[:, :, rows] *= 2.0 ** 10
+        wk[rows] *= 2.0 ** -10
+        x, wk = xi.to_bf16_bits(x), xi.to_bf16_bits(wk)
+    _run(xq, w, 2, G, lens, x_bits=x, wk=wk, pairs=[(b, (11 * b + 5) % Hq) for b in range(10)] + [(0, Hq - 1), (1, 0)])
+
+
 @pytest.mark.parametrize("bits,G", [(2, 64), (2, 128), (3, 64), (3, 128), (4, 64), (4, 128), (8, 128)])
 def test_steps_of_a_value_workgroup(xq, bits, G):
     """Ranges of one to four steps of 128 tokens, with a last step that is full, holds one token, or is missing."""
