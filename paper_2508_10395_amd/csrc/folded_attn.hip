@@ -2149,9 +2149,8 @@ static int fold_digits(FoldProblem f, int B, int max_len)
 // The largest launch group that fits the workspace, for B sequences; where not even one does, one with fewer splits; false if
 // that does not either.  `bytes` is cut to what the query asks for, so that results do not depend on how much more a caller
 // brings; they depend on less only where splits are given up.
-static bool fold_fit(FoldProblem f, int B, int max_len, size_t bytes, int* nb, FoldPlan* plan)
+static bool fold_fit_plan(const FoldProblem& f, int B, int max_len, size_t bytes, bool fewer_splits, int* nb, FoldPlan* plan)
 {
-    f.digits = fold_digits(f, B, max_len);
     const int R = f.Hq, nrb = (R + (R <= 16 ? 15 : 31)) / (R <= 16 ? 16 : 32);
     bytes = std::min(bytes, std::max(f.query_bytes, fold_workspace_bytes(f, B, max_len)));
     const int splits = fold_splits(f, B, nrb, max_len);
@@ -2161,11 +2160,19 @@ static bool fold_fit(FoldProblem f, int B, int max_len, size_t bytes, int* nb, F
         if (p.total <= bytes) { *nb = n; *plan = p; return true; }
         if (n == 1) break;
     }
-    for (int sp = splits - 1; sp >= 1; --sp) {
+    for (int sp = splits - 1; fewer_splits && sp >= 1; --sp) {
         const FoldPlan p = fold_plan(f, B, 1, max_len, sp);
         if (p.total <= bytes) { *nb = 1; *plan = p; return true; }
     }
     return false;
+}
+// (digits, whose buffers are larger, only where they fit)
+static bool fold_fit(FoldProblem f, int B, int max_len, size_t bytes, int* nb, FoldPlan* plan)
+{
+    f.digits = fold_digits(f, B, max_len);
+    if (f.digits && fold_fit_plan(f, B, max_len, bytes, false, nb, plan)) return true;
+    f.digits = 0;
+    return fold_fit_plan(f, B, max_len, bytes, true, nb, plan);
 }
 
 bool fold_fits(const FoldProblem& f, int B, int max_len, size_t bytes)

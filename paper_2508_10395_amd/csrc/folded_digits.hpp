@@ -201,8 +201,9 @@ __global__ __launch_bounds__(256, 2) void fold_scores_digits_kernel(const FoldSc
     };
 
     // Scores, and (T) what has been added to them since the last FLUSH slabs: rounded at their full size once per half slab the result was off
-    // by 9.5e-7 (16 sequences of up to 8191 tokens, groups of 64), 5.9e-7 so, as on the fp16 form
-    constexpr int FLUSH = 2;
+    // by 9.5e-7 (16 sequences of up to 8191 tokens, groups of 64), 5.9e-7 so, against 6.0e-7 on the fp16 form; 5.4e-7 against 5.4e-7 over eight
+    // slabs, where 8 instead of 4 gave 6.3e-7
+    constexpr int FLUSH = 4;
     float S[NT][16], T[NT][16];
 #pragma unroll
     for (int tt = 0; tt < NT; ++tt)
