@@ -397,6 +397,7 @@ struct FoldScoreArgs {
     float* p;                            // [nb][nrb][tiles][4][FOLD_P_TILE32]
     float* mtile;                        // [nb][nrb][tiles << mhalf][16 RT]
     int u_slab, waves;                   // waves of a workgroup
+    int row_split;                       // bf16 rows: a workgroup has one row tile of the row block's two
     FoldSource window;                   // per-channel caches: the window's rows, its folded queries and workgroups
     const uint8_t* u_window;
     int n_window;
@@ -404,12 +405,15 @@ struct FoldScoreArgs {
 
 // the tile of a score workgroup of SW waves (4 or 8) and the slabs of a wave: every SW-th one of coded rows (step = SW), a run of
 // adjacent ones of bf16 rows (step = 1)
-struct FoldScorePlace { int b, rb, tile, tile0, len, SW, slab0, slab1, step, nw; };     // nw = waves that hold any slab
-__device__ __forceinline__ bool fold_score_place(const FoldShape& s, bool window, bool runs, int waves, int n_slabs, int wg, int wave, FoldScorePlace& o)
+// (nw: waves that hold any slab; rt0: first row tile of a workgroup that has one of the row block's `parts`)
+struct FoldScorePlace { int b, rb, tile, tile0, len, SW, slab0, slab1, step, nw, rt0; };
+__device__ __forceinline__ bool fold_score_place(const FoldShape& s, bool window, bool runs, int waves, int n_slabs, int wg, int wave, FoldScorePlace& o, int parts = 1)
 {
-    const int tiles = window ? 1 : s.tiles, n = s.nb * s.nrb * tiles;
-    const int item = xcd_contiguous(n, wg);
+    const int tiles = window ? 1 : s.tiles, n = s.nb * s.nrb * tiles * parts;
+    int item = xcd_contiguous(n, wg);
     if (item >= n) return false;
+    o.rt0 = item % parts;
+    item /= parts;
     o.tile = item % tiles;
     o.rb = (item / tiles) % s.nrb;
     o.b = fold_sequence(s, item / (tiles * s.nrb));
@@ -425,8 +429,8 @@ __device__ __forceinline__ bool fold_score_place(const FoldShape& s, bool window
     return o.tile * FOLD_TILE < o.len;
 }
 
-// what happens to the waves' partial scores: the end of every score kernel
-template <int RT>
+// what happens to the waves' partial scores: the end of every score kernel (BRT: row tiles of the row block)
+template <int RT, int BRT = RT>
 __device__ __forceinline__ void fold_scores_finish(const FoldShape& s, const float* rowfac_all, float* p_all, float* mtile_all,
                                                    f32x4 (&S)[RT][8], float* lds, const FoldScorePlace& o, int lane, int wave)
 {
@@ -441,7 +445,7 @@ __device__ __forceinline__ void fold_scores_finish(const FoldShape& s, const flo
                 part[((wave * RT + rt) * 8 + i) * 64 + lane] = make_float4(S[rt][i][0], S[rt][i][1], S[rt][i][2], S[rt][i][3]);
     __syncthreads();
     const int c16 = lane & 15, q = lane >> 4, share = 8 / o.SW;      // tile16s a wave sums up
-    const float* rowfac = rowfac_all + ((long long)o.b * s.nrb + o.rb) * 16 * RT;
+    const float* rowfac = rowfac_all + ((long long)o.b * s.nrb + o.rb) * 16 * BRT + 16 * o.rt0;
     float* mx = lds + o.SW * RT * 8 * 256;                           // [tile16][16 RT], behind the partial scores
     // (the sums replace the first wave's partial scores: what a wave reads there it has itself replaced)
     for (int j = 0; j < share; ++j) {
@@ -488,11 +492,11 @@ __device__ __forceinline__ void fold_scores_finish(const FoldShape& s, const flo
             }
             const float M = s.mhalf ? (i0 & 4 ? h1 : h0) : fmaxf(h0, h1);
             Mu[rt][r] = M == -INFINITY ? 0.0f : M;                  // nothing visible: all weights 0
-            if (stores) mtile_all[((((long long)o.b * s.nrb + o.rb) * s.tiles << s.mhalf) + mrow0) * 16 * RT + row] = M;
+            if (stores) mtile_all[((((long long)o.b * s.nrb + o.rb) * s.tiles << s.mhalf) + mrow0) * 16 * BRT + 16 * o.rt0 + row] = M;
         }
     for (int j = 0; j < share; ++j) {
         const int i16 = wave * share + j, t32 = (i16 & 1) * 16 + c16, slot = t32 >> 2, qd = t32 & 3;
-        float* pt = p_all + ((((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0 + o.tile) * 4 + (i16 >> 1)) * FOLD_P_TILE32<RT>;
+        float* pt = p_all + ((((long long)o.b * s.nrb + o.rb) * s.tiles + o.tile0 + o.tile) * 4 + (i16 >> 1)) * FOLD_P_TILE32<BRT> + o.rt0 * 512;
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             const float4 t = part[(rt * 8 + i16) * 64 + lane];
@@ -747,19 +751,19 @@ __global__ __launch_bounds__(512) void fold_scores_kernel(const FoldScoreArgs a)
 // side by side these read one 2 KiB stretch of 128 rows at a time.  Whole steps, slabs dealt out as above / runs: 8 x 8192 rows of
 // d = 4096 259 / 238 us, 16 x 8192 of d = 2048 and 16 heads 242 / 216, 8 x 4096 of d = 4096 148 / 142; 6 x 8192, where the XCDs
 // are at different places of their sequences, 225 either way.
-template <int RT>
+template <int RT, int BRT = RT>
 __device__ __forceinline__ void fold_scores_dense(const FoldScoreArgs& a, const FoldSource& x, const uint8_t* u_all, bool window, int waves, uint8_t* lds)
 {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    constexpr int u_slab = FOLD_U_DENSE(RT);
+    constexpr int u_slab = FOLD_U_DENSE(BRT);
     const FoldShape& s = a.s;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     FoldScorePlace o;
-    if (!fold_score_place(s, window, true, waves, x.n_slabs, blockIdx.x, wave, o)) return;
+    if (!fold_score_place(s, window, true, waves, x.n_slabs, blockIdx.x, wave, o, BRT / RT)) return;
     const int b = o.b, rb = o.rb, len = o.len, tok0 = o.tile * FOLD_TILE;
     const int c16 = lane & 15, q = lane >> 4;
     const uint8_t* xbase = reinterpret_cast<const uint8_t*>(x.rows) + (long long)(s.b0 + b) * x.cap * x.row_bytes;
-    const uint8_t* ubase = u_all + ((long long)b * s.nrb + rb) * x.n_slabs * u_slab;
+    const uint8_t* ubase = u_all + ((long long)b * s.nrb + rb) * x.n_slabs * u_slab + o.rt0 * 4 * 3072;
     const uint32_t uoff = lane * 16;
     uint8_t* image = lds + wave * 2 * 2048;                          // two images of 16 rows x 128 bytes
     f32x4 S[RT][8];
@@ -821,14 +825,14 @@ __device__ __forceinline__ void fold_scores_dense(const FoldScoreArgs& a, const 
             });
         }
     }
-    fold_scores_finish<RT>(s, a.rowfac, a.p, a.mtile, S, reinterpret_cast<float*>(lds), o, lane, wave);
+    fold_scores_finish<RT, BRT>(s, a.rowfac, a.p, a.mtile, S, reinterpret_cast<float*>(lds), o, lane, wave);
 }
 
-template <int RT>
+template <int RT, int BRT = RT>
 __global__ __launch_bounds__(512) void fold_scores_dense_kernel(const FoldScoreArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    fold_scores_dense<RT>(a, a.x, a.u, false, a.waves, lds);
+    fold_scores_dense<RT, BRT>(a, a.x, a.u, false, a.waves, lds);
 }
 
 // =====================================================================================================================
@@ -2237,6 +2241,8 @@ static hipError_t scores_for(int bits, int G, bool nibbles, const FoldScoreArgs&
         case 4064: return run_scores<4, 64, RT>(a, nibbles, grid, s);
         case 4128: return run_scores<4, 128, RT>(a, nibbles, grid, s);
     }
+    if constexpr (RT == 2)
+        if (a.row_split) return launch(fold_scores_dense_kernel<1, 2>, grid, FOLD_SCORE_RED<1> / 8 * a.waves, a, s, a.waves);
     return launch(fold_scores_dense_kernel<RT>, grid, FOLD_SCORE_RED<RT> / 8 * a.waves, a, s, a.waves);
 }
 template <int RT>
@@ -2326,9 +2332,14 @@ hipError_t run_folded_attn(const FoldProblem& f, const uint16_t* q, const FoldSo
             const int n = B * sh.nrb * sh.tiles;
             const bool four = !f.block && n >= 3 * 128 && (!f.dense || L.rt == 1 || f.n_slabs_k <= 4 || 2 * ((n + 511) / 512) <= (n + 255) / 256);
             const int waves = four ? 4 : 8;
-            FoldScoreArgs a{kx, sh, u, rowfac, p, mtile, L.u_slab, waves, FoldSource{}, u_dense, 0};
+            // Over bf16 rows a tile's two row tiles go to workgroups of their own where half of the CUs or more would be left without one: half
+            // of the products and queries each, and the rows come out of L2 for the second (neighbours on one XCD).  The sums are the same.
+            // This kernel, both row tiles / one: 128 tiles of d = 4096 36.1 / 29.2 us, 126 35.9 / 28.2, 63 (half of a round) 32.8 / 24.0,
+            // 16 31.4 / 21.7, 64 of d = 1024 23.4 / 19.2.  From 129 tiles on the second ones would wait for a second round.
+            const int row_split = f.dense && !f.block && L.rt == 2 && n <= 128;
+            FoldScoreArgs a{kx, sh, u, rowfac, p, mtile, L.u_slab, waves, row_split, FoldSource{}, u_dense, 0};
             if (any_window) { a.window = *window; a.n_window = xcd_grid(sh.nb * sh.nrb); }
-            const int grid = a.n_window + xcd_grid(sh.nb * sh.nrb * sh.tiles / (L.digits ? 2 : 1));
+            const int grid = a.n_window + xcd_grid(sh.nb * sh.nrb * sh.tiles * (row_split ? 2 : 1) / (L.digits ? 2 : 1));
             e = L.digits ? (f.group == 64 ? launch(fold_scores_digits_kernel<64>, grid, FoldDigitLds::TOTAL, a, s, 4)
                                           : launch(fold_scores_digits_kernel<128>, grid, FoldDigitLds::TOTAL, a, s, 4))
               : f.block ? (L.rt == 1 ? scores_pc_for<1>(bits, a, grid, s) : scores_pc_for<2>(bits, a, grid, s))

@@ -132,6 +132,21 @@ def test_token_ways_of_a_score_workgroup(xq, bits, G, d):
     _run(xq, w, bits, G, lens, pairs=[(0, 0), (0, 63), (1, 17), (2, 5), (3, 40), (4, 33), (5, 62), (15, 8)])
 
 
+@pytest.mark.parametrize("Hq,Hkv,d,lens,split", [(32, 32, 640, [4096, 3969, 129, 1], True), (32, 32, 640, [4100, 257, 128, 1], False),
+                                                 (40, 40, 4096, [511, 33], True), (32, 8, 4224, [700, 33, 1], True), (16, 16, 4096, [300, 1, 129], False)])
+def test_row_tiles_of_a_score_workgroup(xq, Hq, Hkv, d, lens, split):
+    """Over bf16 rows a workgroup has one row tile of a row block up to 128 tiles, both of them beyond (16 rows have only one): rows of
+    padding in the last row block, waves without a slab, tiles past the length."""
+    w = xi.C2.scaled(B=len(lens), L=max(lens), d=d, Hq=Hq, Hkv=Hkv, n_outlier=d // 100)
+    x = bits_to_torch(xi.gen_x(w))
+    wk, wv = xi.gen_weights(w)
+    attn = xq.XQAttn(Hq, Hkv, 128, 128 ** -0.5)
+    wprep = xq.xq_prepare_weights(attn, d, 128, 16, bits_to_torch(wk), bits_to_torch(wv))
+    names = _kernels(lambda: xq.xq_remat_attn_decode(attn, bits_to_torch(xi.gen_q(w)), wprep, lens, acc_bf16=x))
+    assert any("fold_scores_dense_kernel<1, 2>" in n for n in names) == split, names
+    _run(xq, w, 16, 128, lens, pairs=[(b, h) for b in range(w.B) for h in (0, 15, Hq - 16, Hq - 1)])
+
+
 @pytest.mark.parametrize("step", [dict(L=2048), dict(L=2048, Hq=48), dict(L=1792, taken=False), dict(L=2304, taken=False), dict(L=2048, bits=3, taken=False),
                                   dict(L=4096, Hq=16, taken=False)])
 def test_which_steps_take_queries_in_digits(xq, step):
